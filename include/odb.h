@@ -455,9 +455,12 @@ size_t odb_stream_workspace_size(const odb_window_t* w, int32_t depth, int64_t s
  *   d_left_views     [M] out: un-emitted views, per rank in increasing view index
  *   d_left_off       [W+1] out
  *   h_trace          [max_rounds] host out, or NULL: one record per round
- * Rounds are enqueued in chunks, each as long as a lower bound on the rounds left (from
- * the sampler cursors, the rates and, non-join, the quota; at least 8 after the first);
- * the call synchronises `stream` once per chunk and at the end.  Returns ODB_E_CAPACITY if
+ * Rounds up to the first one that overflows (G_r > T for some rank) are run together; the
+ * call synchronises `stream` once for them (twice in non-join mode).  From a round that
+ * overflows on, and from the start when a positive slot_capacity is smaller than a rank's
+ * largest buffer, rounds are enqueued in chunks, each as long as a lower bound on the rounds
+ * left (from the sampler cursors, the rates and, non-join, the quota; at least 8 after the
+ * first), with one synchronisation per chunk and at the end.  Returns ODB_E_CAPACITY if
  * slot_capacity < W * S (required_slot_capacity tells the size) or the iteration needs
  * more than max_rounds rounds, ODB_E_INVALID_DATA for a perm entry outside [0, N) or a
  * sample length < 1 met among the views the iteration fetches.

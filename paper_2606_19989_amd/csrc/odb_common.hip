@@ -158,7 +158,7 @@ __global__ void store_values_kernel(Values64 vals, int64_t* dst, int count, DevS
     }
 }
 
-static int store_values(const int64_t* src, int64_t count, int64_t* dst, DevStatus* st, hipStream_t s) {
+int store_values(const int64_t* src, int64_t count, int64_t* dst, DevStatus* st, hipStream_t s) {
     int64_t a = 0;
     do {
         Values64 v{};

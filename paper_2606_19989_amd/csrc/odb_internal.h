@@ -142,6 +142,10 @@ int check_workspace(const odb_window_t* w, void* d_ws, size_t ws_bytes, Layout* 
 int upload_small(const odb_window_t* w, const Layout& L, void* d_ws, const int64_t* cap,
                  hipStream_t s);
 
+// Stores `count` host values at dst through kernel arguments; with `st`, also resets the
+// status word.
+int store_values(const int64_t* src, int64_t count, int64_t* dst, DevStatus* st, hipStream_t s);
+
 // Host copy of the status word, round state, summary and per-rank state, read with one
 // device-to-host copy (the workspace keeps them next to each other) and one
 // synchronisation of the stream.

@@ -1,6 +1,10 @@
 // The unified streaming loop (Sec. 2.3 "Unified loop and termination"; App. C, App. E):
 // one logical sampler iteration of W ranks, round by round, on the device.
 //
+// Iterations start with their rounds formed together for as long as no round overflows (see
+// "rounds without overflow" below); what follows describes the rounds after that, which run
+// one after the other.
+//
 // Per-rank state (App. C): sampler-pending views R_r (a cursor into the rank's view
 // sequence), the collate buffer B_r (the worker queue is folded into it: a fetched view
 // lands in the buffer in the same round) and the emitted views E_r (the rank's emit
@@ -641,11 +645,13 @@ __device__ __forceinline__ unsigned long long staged_key(int32_t code, int64_t m
 }
 
 // Launch j: books round j-2, emits round j-1, forms round j (see the top of this file).
+// The first launch is j0: round j0's form, from the committed state before that round
+// (empty buffers, and rec[j0 - 1] holding the steps and views emitted so far).
 // Global loads are issued in two batches ahead of the work that needs them (the
 // control state, then the rank's group starts, sorted keys and the next fetch's length
 // codes), so that a round costs few memory round trips beside a running collate.
 template <int KPT>
-__global__ void __launch_bounds__(kST) stream_round_kernel(StreamArgs a, int64_t j) {
+__global__ void __launch_bounds__(kST) stream_round_kernel(StreamArgs a, int64_t j, int64_t j0) {
     constexpr int P = KPT * kST;
     extern __shared__ unsigned long long s_dyn[];
     unsigned char* lds = reinterpret_cast<unsigned char*>(s_dyn);
@@ -653,13 +659,13 @@ __global__ void __launch_bounds__(kST) stream_round_kernel(StreamArgs a, int64_t
     const int tid = threadIdx.x;
     // ---- first batch: control state and the fetch records published for round j-1
     const int32_t done = a.g->done;   // written by an earlier launch
-    const int64_t kb = j >= 2 ? j - 2 : 0;
+    const int64_t kb = j >= j0 + 2 ? j - 2 : j0;
     const StreamRec rk = a.rec[kb];
     const StreamRec rp = a.rec[kb > 0 ? kb - 1 : 0];
     const RankForm* Fe = a.form + ((j + 1) & 1) * a.W;   // round j-1
     RankForm ft{}, fr{};
     int64_t cap_t = 0;
-    if (j >= 1) {
+    if (j > j0) {
         if (tid < a.W) {
             ft = Fe[tid];
             cap_t = a.cap ? a.cap[tid] : 0;
@@ -667,6 +673,7 @@ __global__ void __launch_bounds__(kST) stream_round_kernel(StreamArgs a, int64_t
         fr = Fe[r];
     }
     const int64_t ebase = a.ranks[r].emitted;
+    const int64_t start = a.ranks[r].cursor;
     const int64_t rate = a.rate[r];
     if (done) return;
     // the first batch is complete here (one wait), so the second one below is not drained
@@ -675,7 +682,7 @@ __global__ void __launch_bounds__(kST) stream_round_kernel(StreamArgs a, int64_t
     // ---- second batch, before the booking and the round decision are known: this rank's
     // group starts and sorted keys (used if round j-1 emits) and the length codes of the
     // views round j can fetch
-    const bool may_emit = j >= 1 && fr.status > 0;
+    const bool may_emit = j > j0 && fr.status > 0;
     const int64_t G = may_emit ? fr.status : 0;
     const int64_t n = may_emit ? fr.n : 0;
     const int32_t* gsg = a.gs + (int64_t)r * (a.D + 1);
@@ -692,7 +699,7 @@ __global__ void __launch_bounds__(kST) stream_round_kernel(StreamArgs a, int64_t
         const int64_t i = tid + c * kST;
         kv[c] = i < n ? skey[i] : 0ull;
     }
-    const int64_t cursor = j >= 1 ? fr.cursor : 0;   // committed by the emit phase below
+    const int64_t cursor = j > j0 ? fr.cursor : start;   // committed by the emit phase below
     int64_t fmax = a.q - cursor;
     fmax = fmax < rate ? fmax : rate;
     fmax = fmax < a.D ? fmax : a.D;
@@ -703,8 +710,8 @@ __global__ void __launch_bounds__(kST) stream_round_kernel(StreamArgs a, int64_t
         const int64_t i = tid + c * kST;
         code[c] = i < fmax ? vlen_r[cursor + i] : 1;
     }
-    int64_t base = 0;
-    if (j >= 2) {
+    int64_t base = j0 > 0 ? rp.cum_steps : 0;   // launches j0, j0 + 1: before round j0
+    if (j >= j0 + 2) {
         const Booked b = book_round(a, j - 2, rk, rp, r == 0);
         if (b.done) return;
         base = b.steps;
@@ -723,7 +730,7 @@ __global__ void __launch_bounds__(kST) stream_round_kernel(StreamArgs a, int64_t
     // in an emit round the rank's groups
     int64_t n0 = 0;          // the rank's buffer after round j-1
     bool in_lds = false;     // its keys are in L.kl[0..n0)
-    if (j >= 1) {
+    if (j > j0) {
         const RoundView v = decide_round(a, j - 1, ft, cap_t);
         if (r == 0 && tid == 0) {
             a.rec[j - 1].kind = v.kind;
@@ -922,6 +929,659 @@ __global__ void __launch_bounds__(kST) stream_book_kernel(StreamArgs a, int64_t 
     if (threadIdx.x == 0) a.rec[k].booked = 1;
 }
 
+// ------------------------------------------------------------------ rounds without overflow
+// A round in which no rank holds more than T groups returns nothing: every buffer is empty
+// after it.  While that holds, what a rank fetches in a round does not depend on the
+// lengths, so every emitting round's buffers are known before the first is formed:
+//
+//   k0 = ceil(buffer_size / min rate) rounds fill the slowest rank's buffer (its last buffer
+//   may take fewer), the ranks then hold n_r = min(D, k0 * rate_r) views each, or what is left
+//   of their q, and emitting round e takes rank r's views [e * n_r, (e + 1) * n_r) below q.
+//
+// All rounds are then formed at once (one block per rank and round), the targets T_e and the
+// running step count follow from the group counts in one launch, and the slots of all
+// rounds are written at once.  T_e is the largest group count unless a rank holds fewer
+// views (Eq. 3's S+_min) or has a smaller output-slot capacity; the first such round e
+// is reported (fail) and the protocol goes on from there round by round, from the state
+// the rounds before it left.  One round at a time costs a launch of one block per rank, a
+// chain of latencies that leaves three quarters of the chip idle: 64 ranks x 262,144 views
+// in 257 rounds took 5.45 ms of round launches (21 us each) and 0.65 ms for the view table;
+// formed together they take 0.39 ms (the form, bound by its 16.7 M random reads of the CSR
+// offsets) and 0.06 ms (the slots).
+//
+// A rank's emitted views of a round are its whole buffer, shortest first: the reverse of
+// formation order, whatever the split.  So the form writes identities, views and row
+// records at their place in the rank's stream (position e * n_r + n - 1 - p), which in join
+// mode is their final place.
+constexpr int64_t kBulkBlocks = int64_t(1) << 22;   // rank-rounds of one launch (2^32 threads at most)
+
+struct BulkState {
+    int64_t steps;        // S: aligned steps, after a quota cut
+    int64_t emitted;      // views emitted in the last round, after a quota cut
+    int64_t splits;
+    int64_t changed;      // rounds in which some rank had G_r != T
+    int64_t fail;         // first round with an overflow (rounds formed if none)
+    int64_t cut;          // steps kept of the last round
+    unsigned long long max_step;
+    unsigned long long real_tokens;
+    unsigned long long bad_views;
+    int64_t padded;
+    int32_t err;
+    int32_t pad;
+};
+
+struct BulkArgs {
+    int W;
+    int64_t N, q, D, budget, scap;
+    int64_t E;                  // emitting rounds
+    int64_t n_all, rate_all;    // every rank's n_r and rate, or read from `sched`
+    const int64_t* sched;       // [W] rate << 32 | n_r where ranks differ, or null
+    int64_t bufsize;
+    int stop_round;             // join 0; 1: the round after the last emitting one fetches, too
+    const int64_t* tok_off;
+    const int32_t* perm;
+    BulkState* st;
+    int32_t* T;                 // [E] largest group count of the round, then its target
+    uint32_t* sum;              // [E] groups of the round over the ranks
+    int64_t* base;              // [E] steps before the round
+    int32_t* G;                 // [W * E] group counts, rank-major
+    int32_t* gs;                // [W * q] group starts, rank r's round e from r * q + e * n_r on
+    int64_t* tile;              // [W * E] padded elements of the rank's slots of the round
+    int64_t* stepsum;           // [D] samples per step of the round the quota cuts
+    // per view, rank r's stream from r * q on
+    int32_t* views;
+    int32_t* ids;
+    int64_t* ts;
+    int32_t* len;
+};
+
+__device__ __forceinline__ int64_t bulk_n(const BulkArgs& b, int r) {
+    return b.sched ? (b.sched[r] & 0xFFFFFFFFll) : b.n_all;
+}
+
+// Rank r's cursor before emitting round e and the views it then holds.
+__device__ __forceinline__ void bulk_range(const BulkArgs& b, int r, int64_t e, int64_t* c, int64_t* n) {
+    const int64_t n0 = bulk_n(b, r);
+    const int64_t at = e * n0;
+    *c = at < b.q ? at : b.q;
+    const int64_t left = b.q - *c;
+    *n = left < n0 ? left : n0;
+}
+
+// Round and rank of a block.  Workgroups are dealt to the 8 XCDs round robin; with many
+// rounds, a round's W blocks go to one XCD, whose L2 then holds the round's W * n entries
+// of perm (each rank reads every W-th of them).
+__device__ __forceinline__ bool bulk_block(const BulkArgs& b, int64_t rounds, int64_t* e, int* r) {
+    const int64_t x = blockIdx.x;
+    if (rounds >= 64) {
+        const int64_t g = x >> 3;
+        *e = (g / b.W) * 8 + (x & 7);
+        *r = (int)(g % b.W);
+    } else {
+        *e = x / b.W;
+        *r = (int)(x % b.W);
+    }
+    return *e < rounds;
+}
+
+inline int64_t bulk_grid(int64_t W, int64_t rounds) { return rounds >= 64 ? (rounds + 7) / 8 * 8 * W : rounds * W; }
+
+__global__ void bulk_init_kernel(BulkArgs b, DevStatus* st) {
+    const int t = threadIdx.x;
+    if (t == 0) {
+        *b.st = BulkState{};
+        st->err = 0;
+        st->first_bad = 0x7FFFFFFFFFFFFFFFll;
+        st->first_bad_len = 0x7FFFFFFFFFFFFFFFll;
+        st->min_len = 0xFFFFFFFFu;
+        st->max_len = 0;
+    }
+    for (int64_t i = t; i < b.D; i += blockDim.x) b.stepsum[i] = 0;
+    for (int64_t i = t; i < b.E; i += blockDim.x) {
+        b.T[i] = 0;
+        b.sum[i] = 0;
+    }
+}
+
+// Fetch and grouping of rank r's buffer of round e: the buffer's views sorted to (length
+// desc, view asc), written out shortest first, and the group starts of Sec. 2.2.
+//
+// The sort is a stable LSD radix sort on the length, digits of up to 8 bits: a wave takes
+// KPT consecutive groups of 64 positions in order, keeping its running count of each digit
+// in LDS, so an item's rank among equal digits is the wave's count so far plus the lower
+// lanes holding the digit, and one scan over (digit, wave) gives every wave's first slot.
+// LDS: counts, sorted lengths and their indices in the buffer, token starts and identities.
+typedef int64_t Offsets __attribute__((ext_vector_type(2), aligned(8)));   // a sample's two CSR offsets in one load
+
+template <int NT, int KPT>
+__global__ void __launch_bounds__(NT) bulk_form_kernel(BulkArgs b) {
+    constexpr int kWaves = NT / kWave, P = NT * KPT;
+    constexpr int kBins = 256, kPer = kBins * kWaves / NT;
+    static_assert(kPer * NT == kBins * kWaves, "counters per thread");
+    __shared__ int32_t s_cnt[kBins * kWaves];
+    __shared__ uint32_t s_len[P];
+    __shared__ int64_t s_ts[P];
+    __shared__ int32_t s_id[P];
+    __shared__ uint16_t s_idx[P], s_nxt[P], s_gs[P];
+    __shared__ uint32_t s_seen[P / 32];
+    __shared__ int32_t s_G, s_err, s_rep;
+    int64_t e;
+    int r;
+    if (!bulk_block(b, b.E + b.stop_round, &e, &r)) return;
+    const int tid = threadIdx.x, w = tid / kWave;
+    int64_t c0, n64;
+    bool check_only = false;
+    if (e < b.E) {
+        bulk_range(b, r, e, &c0, &n64);
+    } else {
+        // the round that stops the iteration: a rank that is ready then has formed its
+        // buffer, so its views' data is checked
+        int64_t n0, rate = b.sched ? b.sched[r] >> 32 : b.rate_all;
+        bulk_range(b, r, e, &c0, &n0);
+        n64 = b.q - c0;
+        n64 = n64 < rate ? n64 : rate;
+        n64 = n64 < b.D ? n64 : b.D;
+        if (n64 < b.bufsize && c0 + n64 < b.q) n64 = 0;
+        check_only = true;
+    }
+    const int n = (int)n64;
+    if (n == 0) {   // a finished rank (or one that does not form in the stop round)
+        if (tid == 0 && !check_only) b.G[(int64_t)r * b.E + e] = 0;
+        return;
+    }
+    if (tid == 0) {
+        s_err = 0;
+        s_rep = 0;
+    }
+    for (int i = tid; i < P / 32; i += NT) s_seen[i] = 0;
+    __syncthreads();
+    // positions of wave w: [w * KPT * 64, (w + 1) * KPT * 64), item c at + c * 64 + lane
+    const int p0 = w * KPT * kWave + (tid & (kWave - 1));
+    uint32_t len[KPT];
+    int32_t err = 0;
+    uint32_t mx = 0;
+    {
+        int32_t id[KPT];
+#pragma unroll
+        for (int c = 0; c < KPT; ++c) {
+            const int i = p0 + c * kWave;
+            const int64_t m = (c0 + (i < n ? i : n - 1)) * b.W + r;
+            id[c] = b.perm[m < b.N ? m : m % b.N];
+        }
+        int64_t t0[KPT], t1[KPT];
+#pragma unroll
+        for (int c = 0; c < KPT; ++c) {
+            const bool ok = id[c] >= 0 && id[c] < b.N;
+            const int64_t s = ok ? id[c] : 0;
+            const Offsets o = *reinterpret_cast<const Offsets*>(b.tok_off + s);
+            t0[c] = o[0];
+            t1[c] = o[1];
+            if (!ok) err |= kSErrIdentity;
+        }
+#pragma unroll
+        for (int c = 0; c < KPT; ++c) {
+            const int i = p0 + c * kWave;
+            int64_t l = t1[c] - t0[c];
+            if (l < 1 || l > 0x7FFFFFFF) {
+                err |= kSErrLength;
+                l = 1;
+            }
+            len[c] = (uint32_t)l;
+            if (i < n) {
+                s_ts[i] = t0[c];
+                s_id[i] = id[c];
+                mx = len[c] > mx ? len[c] : mx;
+            }
+        }
+    }
+    if (err) atomicOr(&s_err, err);
+    const uint32_t maxlen = (uint32_t)sblock_reduce<NT, OpMax>((int32_t)mx);
+    if (s_err) {   // uniform (the reduction's barriers order it): the caller goes round by round
+        if (tid == 0) {
+            atomicOr(&b.st->err, s_err);
+            if (!check_only) b.G[(int64_t)r * b.E + e] = 0;
+        }
+        return;
+    }
+    if (check_only) return;
+    // ---- sort
+    uint32_t idx[KPT];
+#pragma unroll
+    for (int c = 0; c < KPT; ++c) idx[c] = (uint32_t)(p0 + c * kWave);
+    const int bits = 32 - __clz((int)maxlen);
+    const int passes = (bits + 7) / 8;
+    const int dbits = (bits + passes - 1) / passes;
+    const uint32_t mask = (1u << dbits) - 1;
+    for (int sh = 0, k = 0; k < passes; ++k, sh += dbits) {
+        for (int i = tid; i < kBins * kWaves; i += NT) s_cnt[i] = 0;
+        __syncthreads();
+        int at[KPT];
+        uint32_t dg[KPT];
+#pragma unroll
+        for (int c = 0; c < KPT; ++c) {
+            const bool valid = p0 + c * kWave < n;
+            const uint32_t d = mask - ((len[c] >> sh) & mask);
+            uint64_t m = __ballot(valid);
+            for (int bt = 0; bt < dbits; ++bt) {
+                const bool on = (d >> bt) & 1;
+                const uint64_t bb = __ballot(on);
+                m &= on ? bb : ~bb;
+            }
+            const int below = lanes_below(m);
+            dg[c] = d;
+            // every lane of the wave reads the count before the digit's first lane adds to it:
+            // LDS operations of one wave complete in order (the fences keep the compiler to it)
+            at[c] = valid ? s_cnt[d * kWaves + w] + below : 0;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (valid && below == 0) s_cnt[d * kWaves + w] += __popcll(m);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+        __syncthreads();
+        {
+            int v[kPer], sum = 0;
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) {
+                v[i] = s_cnt[tid * kPer + i];
+                sum += v[i];
+            }
+            int tot;
+            int ex = sblock_excl<NT>(sum, &tot);
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) {
+                s_cnt[tid * kPer + i] = ex;
+                ex += v[i];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < KPT; ++c)
+            if (p0 + c * kWave < n) {
+                const int to = s_cnt[dg[c] * kWaves + w] + at[c];
+                s_len[to] = len[c];
+                s_idx[to] = (uint16_t)idx[c];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < KPT; ++c) {
+            const int p = p0 + c * kWave;
+            len[c] = p < n ? s_len[p] : 1u;
+            idx[c] = p < n ? s_idx[p] : 0u;
+        }
+    }
+    // ---- emitted rows, shortest first, and the self-check that they are the buffer's views,
+    // each once; the links to the next group start
+    const int64_t out = (int64_t)r * b.q + c0;
+    bool rep = false;
+#pragma unroll
+    for (int c = 0; c < KPT; ++c) {
+        const int p = p0 + c * kWave;
+        if (p >= n) continue;
+        const uint32_t i = idx[c], bit = 1u << (i & 31);
+        rep |= (atomicOr(&s_seen[i >> 5], bit) & bit) != 0;
+        const int64_t x = out + (n - 1 - p);
+        b.views[x] = (int32_t)((c0 + i) * b.W + r);
+        b.ids[x] = s_id[i];
+        b.ts[x] = s_ts[i];
+        b.len[x] = (int32_t)len[c];
+        const int64_t nx = p == 0 ? 1 : p + batch_size(b.budget, (int32_t)s_len[p - 1]);
+        s_nxt[p] = (uint16_t)(nx < n ? nx : n);
+    }
+    if (rep) atomicOr(&s_rep, 1);
+    __syncthreads();
+    if (tid == 0) {
+        int p = 0, g = 0;
+        while (p < n) {
+            s_gs[g++] = (uint16_t)p;
+            p = s_nxt[p];
+        }
+        s_G = g;
+        b.G[(int64_t)r * b.E + e] = g;
+        atomicMax(&b.T[e], g);
+        atomicAdd(&b.sum[e], (uint32_t)g);
+        if (s_rep) atomicAdd(&b.st->bad_views, 1ull);
+    }
+    __syncthreads();
+    const int G = s_G;
+    for (int g = tid; g < G; g += NT) b.gs[out + g] = s_gs[g];
+}
+
+// Targets and running step counts of all rounds, and the first round that would overflow.
+// One block, one thread per round.
+__global__ void __launch_bounds__(1024) bulk_targets_kernel(BulkArgs b) {
+    __shared__ int32_t s_fail;
+    int64_t steps = 0, splits = 0, changed = 0;
+    for (int64_t e0 = 0; e0 < b.E; e0 += 1024) {
+        if (threadIdx.x == 0) s_fail = 1024;
+        __syncthreads();
+        const int64_t e = e0 + threadIdx.x;
+        int64_t T = 0, more = 0;   // target, and the splits it takes
+        if (e < b.E) {
+            const int64_t mx = b.T[e];
+            int64_t c, held, ready = b.W;   // fewest views held by a rank that is not finished
+            bulk_range(b, 0, e, &c, &held);
+            if (b.sched) {
+                held = LLONG_MAX;
+                ready = 0;
+                for (int r = 0; r < b.W; ++r) {
+                    int64_t n;
+                    bulk_range(b, r, e, &c, &n);
+                    ready += n > 0;
+                    held = n > 0 && n < held ? n : held;
+                }
+            }
+            T = mx > 1 ? mx : 1;
+            more = T * ready - (int64_t)b.sum[e];
+            if (mx > held) atomicMin(&s_fail, (int32_t)threadIdx.x);
+        }
+        __syncthreads();
+        const int32_t fail = s_fail;
+        const bool live = e < b.E && (int32_t)threadIdx.x < fail;
+        if (!live) T = more = 0;
+        int64_t tot;
+        const int64_t ex = sblock_excl<1024>(T, &tot);
+        if (live) {
+            b.T[e] = (int32_t)T;
+            b.base[e] = steps + ex;
+        }
+        steps += tot;
+        splits += sblock_sum<1024>(more);
+        changed += sblock_sum<1024>((int64_t)(more != 0));
+        if (fail < 1024 || e0 + 1024 >= b.E) {
+            if (threadIdx.x == 0) {
+                b.st->steps = steps;
+                b.st->splits = splits;
+                b.st->changed = changed;
+                b.st->fail = fail < 1024 ? e0 + fail : b.E;
+            }
+            return;
+        }
+    }
+}
+
+// Where the slots go: the staging (rank r's step x at r * scap + x) or, with `fin` set, the
+// window plan layout (r * S + x) with row offsets and, within the rank-round, tile offsets.
+struct BulkSlots {
+    int32_t* rows;
+    int32_t* maxlen;
+    int64_t* tokens;
+    double* approx;       // may be null
+    int64_t* row_off;     // fin
+    int64_t* tile_off;    // fin
+    int fin;
+    int64_t cut_round;    // the round whose step sizes are wanted (a quota cut), or -1
+};
+
+// Slots of rank r in round e: the groups are split (Algorithm 1) to T_e; a group's tokens
+// are the difference of two prefix sums over the buffer's lengths.  A finished rank gets
+// IDLE slots.
+template <int NT, int KPT>
+__global__ void __launch_bounds__(NT) bulk_slots_kernel(BulkArgs b, BulkSlots o) {
+#pragma clang fp contract(off)
+    constexpr int P = NT * KPT;
+    __shared__ int64_t s_tok[P + 1];   // tokens of the first i rows of the emission order
+    __shared__ int32_t s_gs[P + 1];
+    __shared__ int64_t s_X, s_js;
+    __shared__ int s_go;
+    int64_t e;
+    int r;
+    if (!bulk_block(b, b.E, &e, &r)) return;
+    const int tid = threadIdx.x;
+    const int64_t S = b.st->steps;
+    // the error word may change while this launch runs: one thread decides for the block
+    if (tid == 0)
+        s_go = b.st->err == 0 && e < b.st->fail && !(o.fin && (b.st->fail < b.E || S > b.scap));
+    __syncthreads();
+    if (!s_go) return;
+    int64_t c0, n64;
+    bulk_range(b, r, e, &c0, &n64);
+    const int n = (int)n64;
+    const int T = b.T[e], G = b.G[(int64_t)r * b.E + e];
+    const int64_t base = b.base[e];
+    const int64_t in = (int64_t)r * b.q + c0;
+    const int64_t dst = o.fin ? (int64_t)r * S + base : (int64_t)r * b.scap + base;
+    const int64_t room = o.fin ? T : b.scap - base;   // staged steps: those below the capacity
+    if (n == 0) {
+        for (int j = tid; j < T && j < room; j += NT) {
+            o.rows[dst + j] = 0;
+            o.maxlen[dst + j] = 0;
+            o.tokens[dst + j] = 0;
+            if (o.approx) o.approx[dst + j] = 0.0;
+            if (o.fin) {
+                o.row_off[dst + j] = in;
+                o.tile_off[dst + j] = 0;
+            }
+        }
+        if (tid == 0) b.tile[(int64_t)r * b.E + e] = 0;
+        return;
+    }
+    if (tid == 0) {
+        s_X = 0;
+        s_js = -1;
+    }
+    // prefix sums of the rows' lengths; a thread takes KPT consecutive rows
+    {
+        int64_t v[KPT], sum = 0;
+#pragma unroll
+        for (int c = 0; c < KPT; ++c) {
+            const int y = tid * KPT + c;
+            v[c] = y < n ? b.len[in + y] : 0;
+            sum += v[c];
+        }
+        for (int g = tid; g <= G; g += NT) s_gs[g] = g < G ? b.gs[in + g] : n;
+        int64_t tot;
+        int64_t ex = sblock_excl<NT>(sum, &tot);
+#pragma unroll
+        for (int c = 0; c < KPT; ++c) {
+            s_tok[tid * KPT + c] = ex;
+            ex += v[c];
+        }
+        if (tid == 0) s_tok[P] = tot;
+    }
+    __syncthreads();
+    int64_t X = 0, js = 0;
+    if (G < T) {
+        // positions [0, X) become singletons, [X, end of group j*) stays one group, later
+        // groups are unchanged; j* is the first group whose cumulative surplus reaches T - G
+        const int64_t need = T - G;
+        int64_t carry = 0;
+        for (int b0 = 0; b0 < G; b0 += NT) {
+            const int g = b0 + tid;
+            const int64_t v = g < G ? (int64_t)(s_gs[g + 1] - s_gs[g]) - 1 : 0;
+            int64_t tot;
+            const int64_t ex = carry + sblock_excl<NT>(v, &tot);
+            if (g < G && ex < need && ex + v >= need) {
+                s_js = g;
+                s_X = s_gs[g] + (need - ex);
+            }
+            carry += tot;
+        }
+        __syncthreads();
+        X = s_X;
+        js = s_js;
+        if (js < 0 || X + 1 + (G - 1 - js) != T) {   // the group sizes do not add up to the buffer
+            if (tid == 0) atomicOr(&b.st->err, kSErrInternal);
+            return;
+        }
+    }
+    const double mean = (double)s_tok[P] / (double)n;
+    int64_t carry = 0;
+    for (int j0 = 0; j0 < T; j0 += NT) {
+        const int j = j0 + tid;   // step of the round; adjusted group t = T - 1 - j
+        int64_t cells = 0;
+        int a0 = 0, a1 = 0, mlen = 0;
+        if (j < T) {
+            const int t = T - 1 - j;
+            if (t < X) {
+                a0 = t;
+                a1 = t + 1;
+            } else {
+                const int g = (int)(js + (t - X));
+                a0 = t == X ? (int)X : s_gs[g];
+                a1 = s_gs[g + 1];
+            }
+            mlen = b.len[in + (n - 1 - a0)];
+            cells = (int64_t)(a1 - a0) * mlen;
+        }
+        int64_t tot = 0, ex = 0;
+        if (o.fin) ex = carry + sblock_excl<NT>(cells, &tot);
+        carry += tot;
+        if (j < T && j < room) {
+            o.rows[dst + j] = a1 - a0;
+            o.maxlen[dst + j] = mlen;
+            o.tokens[dst + j] = s_tok[n - a0] - s_tok[n - a1];
+            if (o.approx) o.approx[dst + j] = (double)(a1 - a0) * mean;
+            if (o.fin) {
+                o.row_off[dst + j] = in + (n - a1);
+                o.tile_off[dst + j] = ex;
+            }
+        }
+        if (j < T && e == o.cut_round)
+            atomicAdd((unsigned long long*)&b.stepsum[j], (unsigned long long)(a1 - a0));
+    }
+    if (o.fin && tid == 0) b.tile[(int64_t)r * b.E + e] = carry;
+}
+
+// A sample quota reached in the last round: the steps up to the one that reaches it are kept.
+__global__ void __launch_bounds__(kST) bulk_cut_kernel(BulkArgs b, int64_t before, int64_t quota) {
+    if (b.st->fail < b.E) return;
+    const int64_t e = b.E - 1, T = b.T[e];
+    __shared__ int64_t s_cut;
+    if (threadIdx.x == 0) s_cut = T;
+    __syncthreads();
+    int64_t carry = 0;
+    for (int64_t j0 = 0; j0 < T; j0 += kST) {
+        const int64_t j = j0 + threadIdx.x;
+        const int64_t v = j < T ? b.stepsum[j] : 0;
+        int64_t tot;
+        const int64_t ex = before + carry + sblock_excl<kST>(v, &tot);
+        if (j < T && ex < quota && ex + v >= quota) s_cut = j + 1;
+        carry += tot;
+    }
+    __syncthreads();
+    const int64_t cut = s_cut;
+    int64_t kept = 0;
+    for (int64_t j = threadIdx.x; j < cut; j += kST) kept += b.stepsum[j];
+    kept = sblock_sum<kST>(kept);
+    if (threadIdx.x == 0) {
+        b.st->cut = cut;
+        b.st->emitted = kept;
+        b.st->steps = b.base[e] + cut;
+    }
+}
+
+// Samples of every step over the ranks (rank stride `stride`): the largest, and the slots'
+// real tokens.  One thread per step; blocks of one wave, so that a thousand steps already
+// spread over the chip.
+__global__ void __launch_bounds__(kWave) bulk_steps_kernel(BulkArgs b, const int32_t* __restrict__ rows,
+                                                           const int64_t* __restrict__ tokens, int64_t stride,
+                                                           int64_t most) {
+    if (b.st->err) return;
+    int64_t S = b.st->steps;
+    if (stride == 0) {   // the plan layout
+        if (b.st->fail < b.E || S > b.scap) return;
+        stride = S;
+    }
+    S = S < most ? S : most;
+    unsigned long long mx = 0, real = 0;
+    for (int64_t j = (int64_t)blockIdx.x * kWave + threadIdx.x; j < S; j += (int64_t)gridDim.x * kWave) {
+        unsigned long long n = 0;
+#pragma unroll 8
+        for (int r = 0; r < b.W; ++r) {
+            n += (unsigned long long)rows[r * stride + j];
+            real += (unsigned long long)tokens[r * stride + j];
+        }
+        mx = n > mx ? n : mx;
+    }
+    mx = wave_last(wave_scan_dpp<OpMax>(mx));
+    real = wave_last(wave_scan_dpp<OpAdd>(real));
+    if (threadIdx.x == 0 && mx) {
+        atomicMax(&b.st->max_step, mx);
+        atomicAdd(&b.st->real_tokens, real);
+    }
+}
+
+struct BulkTileLoad {
+    const int64_t* v;
+    int64_t n;   // the scan runs over n + 1 entries: entry n receives the total
+    __device__ int64_t operator()(int64_t i) const { return i < n ? v[i] : 0; }
+};
+
+// Tile offsets of rank r's slots of round e: the rank-round's first tile added to the offsets
+// within it.  Block 0 also closes the offset arrays.
+__global__ void __launch_bounds__(kWave) bulk_tiles_kernel(BulkArgs b, int64_t* __restrict__ tile_off,
+                                                           int64_t* __restrict__ row_off,
+                                                           int64_t* __restrict__ left_off) {
+    const int64_t S = b.st->steps;
+    if (b.st->err || b.st->fail < b.E || S > b.scap) return;
+    int64_t e;
+    int r;
+    if (blockIdx.x == 0) {
+        const int64_t K = (int64_t)b.W * S, total = b.tile[(int64_t)b.W * b.E];
+        for (int64_t i = threadIdx.x; i <= b.W; i += kWave) left_off[i] = 0;
+        if (threadIdx.x == 0) {
+            tile_off[K] = total;
+            row_off[K] = (int64_t)b.W * b.q;
+            b.st->padded = total;
+        }
+    }
+    if (!bulk_block(b, b.E, &e, &r)) return;
+    const int64_t add = b.tile[(int64_t)r * b.E + e], at = (int64_t)r * S + b.base[e];
+    const int T = b.T[e];
+    for (int j = threadIdx.x; j < T; j += kWave) tile_off[at + j] += add;
+}
+
+// Rank r's emitted views moved to their place among the ranks' (a quota cut or a stop leaves
+// gaps between the ranks' streams): blockIdx.x is the rank, blockIdx.y a slice of its stream.
+__global__ void __launch_bounds__(256) bulk_emit_out_kernel(BulkArgs b, int64_t S, const int64_t* row_off,
+                                                            int32_t* emit_views, int32_t* emit_order, int64_t* row_ts,
+                                                            int32_t* row_len) {
+    const int r = blockIdx.x;
+    const int64_t lo = row_off[(int64_t)r * S], hi = row_off[(int64_t)(r + 1) * S];
+    const int64_t in = (int64_t)r * b.q;
+    const int64_t stride = (int64_t)gridDim.y * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.y * blockDim.x + threadIdx.x; i < hi - lo; i += stride) {
+        emit_views[lo + i] = b.views[in + i];
+        emit_order[lo + i] = b.ids[in + i];
+        if (row_ts) {
+            row_ts[lo + i] = b.ts[in + i];
+            row_len[lo + i] = b.len[in + i];
+        }
+    }
+}
+
+__global__ void __launch_bounds__(256) copy_i32_kernel(const int32_t* __restrict__ src, int32_t* __restrict__ dst,
+                                                       int64_t n) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) dst[i] = src[i];
+}
+
+// The committed state before round j0, after the first `fail` emitting rounds: the sequential
+// rounds go on from it (stream_init_kernel has cleared everything else).
+__global__ void bulk_resume_kernel(BulkArgs b, StreamArgs a, int64_t fail, int64_t j0, int64_t emitted) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i0 == 0) {
+        a.g->steps = b.st->steps;
+        a.g->emitted = emitted;
+        a.g->rounds = j0;
+        a.g->emit_rounds = fail;
+        a.g->skip_rounds = j0 - fail;
+        a.g->splits = b.st->splits;
+        a.g->second_gather = b.st->changed;
+        a.g->max_step = (int64_t)b.st->max_step;
+        a.rec[j0 - 1].cum_steps = b.st->steps;
+        a.rec[j0 - 1].cum_emitted = emitted;
+    }
+    for (int64_t r = i0; r < a.W; r += stride) {
+        int64_t c, n;
+        bulk_range(b, (int)r, fail, &c, &n);
+        a.ranks[r].cursor = c;
+        a.ranks[r].emitted = c;
+        bulk_range(b, (int)r, 0, &c, &n);
+        atomicMax(&a.g->max_outstanding, (unsigned long long)n);
+    }
+}
+
 // ------------------------------------------------------------------ final plan
 __global__ void stream_slots_kernel(StreamArgs a, int64_t S, int32_t* rows, int32_t* maxlen, int64_t* tokens,
                                     double* approx) {
@@ -1104,7 +1764,7 @@ __global__ void clear_totals_kernel(StreamTotals* t) {
 
 struct StreamLayout {
     size_t g, ranks, form, rec, stepsum, bufv, skey, gs, srows, smax, stok, sadj, evw, vbits, vid, vts, vlen,
-        totals, partials, rate, cap, total;
+        totals, partials, rate, cap, bulk_st, bulk_T, bulk_sum, bulk_base, bulk_G, total;
 };
 
 // Workspace layout of a streaming iteration after the window workspace (`at` bytes).
@@ -1146,6 +1806,14 @@ bool stream_layout(size_t at, int64_t W, int64_t N, int64_t D, int64_t scap, int
     L->partials = take(8 * (scan_n / kScanTile + 4));
     L->rate = take(4 * W);
     L->cap = take(8 * W);
+    // rounds formed together: at most one per view of a rank, per protocol round and, over
+    // the ranks, kBulkBlocks rank-rounds
+    const int64_t E = std::max<int64_t>(1, std::min(std::min(q, rounds), kBulkBlocks / W + 1));
+    L->bulk_st = take(sizeof(BulkState));
+    L->bulk_T = take(4 * E);
+    L->bulk_sum = take(4 * E);
+    L->bulk_base = take(8 * E);
+    L->bulk_G = take(4 * W * E);
     L->total = o;
     return o - at <= (size_t)kMaxStreamBytes;
 }
@@ -1169,6 +1837,75 @@ int64_t stream_rounds_left(const StreamArgs& a, const int32_t* rate, const std::
         b = std::min(b, std::max<int64_t>(1, (a.quota - hg.emitted + per - 1) / per));
     }
     return std::max(b, at_least);
+}
+
+// The emitting rounds of an iteration in which no round overflows.
+struct BulkSchedule {
+    bool use = false;
+    int64_t E = 0;            // emitting rounds
+    int64_t k0 = 1;           // protocol rounds per emitting round, the last one's excepted
+    int64_t last_round = 0;   // protocol round of the last emitting round
+    int64_t rounds = 0;       // protocol rounds, with the one that sees the stop
+    int32_t stop = ODB_STOP_DRAINED;
+    int stop_round = 0;       // the stop round fetches (non-join, some ranks not finished)
+    std::vector<int64_t> n0;  // n_r
+    bool uniform = true;
+    int64_t q = 0;
+
+    int64_t round_of(int64_t e) const { return e + 1 == E ? last_round : (e + 1) * k0 - 1; }
+    int64_t emitted_before(int64_t e) const {
+        int64_t s = 0;
+        for (int64_t n : n0) s += std::min(q, e * n);
+        return s;
+    }
+};
+
+BulkSchedule bulk_schedule(const StreamArgs& a, const odb_stream_params_t* p) {
+    BulkSchedule b;
+    b.q = a.q;
+    if (a.q == 0) return b;
+    int64_t min_rate = p->rate[0];
+    for (int r = 1; r < a.W; ++r) min_rate = std::min<int64_t>(min_rate, p->rate[r]);
+    b.k0 = (a.bufsize + min_rate - 1) / min_rate;
+    int64_t n_max = 0;
+    b.n0.resize(a.W);
+    for (int r = 0; r < a.W; ++r) {
+        b.n0[r] = std::min<int64_t>(a.D, b.k0 * p->rate[r]);
+        n_max = std::max(n_max, b.n0[r]);
+        b.uniform = b.uniform && p->rate[r] == p->rate[0];
+    }
+    // a capacity that could bind makes overflow likely: round by round from the start
+    if (p->slot_capacity)
+        for (int r = 0; r < a.W; ++r)
+            if (p->slot_capacity[r] > 0 && p->slot_capacity[r] < std::min(n_max, a.q)) return b;
+    const int64_t n_slow = std::min<int64_t>(a.D, b.k0 * min_rate);   // the slowest rank finishes last
+    const int64_t all = (a.q + n_slow - 1) / n_slow;
+    b.E = all;
+    bool quota = false;
+    if (a.mode == ODB_MODE_NONJOIN_QUOTA) {
+        b.E = (a.q + n_max - 1) / n_max;   // the first rank finishes
+        if (b.emitted_before(b.E) >= a.quota) {
+            int64_t lo = 0, hi = b.E;   // emitted_before(lo) < quota <= emitted_before(hi)
+            while (hi - lo > 1) {
+                const int64_t mid = lo + (hi - lo) / 2;
+                if (b.emitted_before(mid) >= a.quota) hi = mid; else lo = mid;
+            }
+            b.E = hi;
+            quota = true;
+        }
+    }
+    const int64_t left = a.q - (b.E - 1) * n_slow;   // the slowest rank's views before the last round
+    const int64_t k_last = (std::min(a.bufsize, left) + min_rate - 1) / min_rate;
+    b.last_round = (b.E - 1) * b.k0 + k_last - 1;
+    b.rounds = b.last_round + (quota ? 1 : 2);
+    if (quota) {
+        b.stop = ODB_STOP_QUOTA;
+    } else if (b.emitted_before(b.E) < a.q * a.W) {
+        b.stop = ODB_STOP_RANK_FINISHED;
+        b.stop_round = 1;
+    }
+    b.use = b.rounds <= a.max_rounds && b.E <= kBulkBlocks / a.W;
+    return b;
 }
 
 int check_stream_params(const odb_window_t* w, const odb_stream_params_t* p, int64_t slot_capacity) {
@@ -1247,9 +1984,6 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
         return set_error(ODB_E_WORKSPACE, "workspace has %zu bytes, %zu needed", ws_bytes, SL.total);
     memset(h_info, 0, sizeof(*h_info));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // the window part of the workspace: rank offsets and a cleared status word, as after
-    // odb_align_groups, so odb_collate / odb_collate_status work on this workspace
-    ODB_TRY(upload_small(w, L, d_ws, nullptr, s));
 
     StreamArgs a{};
     a.W = W;
@@ -1282,51 +2016,199 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
     a.vid = ws_at<int32_t>(d_ws, SL.vid);
     a.vts = ws_at<int64_t>(d_ws, SL.vts);
     a.vlen = ws_at<int32_t>(d_ws, SL.vlen);
-    ODB_TRY_HIP(hipMemcpyAsync(const_cast<int32_t*>(a.rate), params->rate, 4 * W, hipMemcpyHostToDevice, s));
-    if (a.cap)
-        ODB_TRY_HIP(hipMemcpyAsync(const_cast<int64_t*>(a.cap), params->slot_capacity, 8 * W, hipMemcpyHostToDevice, s));
-    if (M > 0) {
-        hipLaunchKernelGGL(stream_views_kernel, dim3(grid_for(M, 256, (int64_t)num_cus() * kPlanBlocksPerCU)),
-                           dim3(256), 0, s, a, const_cast<int32_t*>(a.vid), const_cast<int64_t*>(a.vts),
-                           const_cast<int32_t*>(a.vlen));
-        ODB_LAUNCHED();
-    }
-    hipLaunchKernelGGL(stream_init_kernel, dim3(grid_for(std::max<int64_t>(params->max_rounds, W), 256, 1024)),
-                       dim3(256), 0, s, a, params->max_rounds);
-    ODB_LAUNCHED();
-
-    // rounds, in chunks, until the done flag is up
-    const int kpt = sort_kpt(a.D);
-    const size_t lds = round_lds_bytes(a.D);
-    auto launch_round = [&](int64_t j) {
-        switch (kpt) {
-            case 1: hipLaunchKernelGGL(stream_round_kernel<1>, dim3(W), dim3(kST), lds, s, a, j); break;
-            case 2: hipLaunchKernelGGL(stream_round_kernel<2>, dim3(W), dim3(kST), lds, s, a, j); break;
-            case 4: hipLaunchKernelGGL(stream_round_kernel<4>, dim3(W), dim3(kST), lds, s, a, j); break;
-            default: hipLaunchKernelGGL(stream_round_kernel<8>, dim3(W), dim3(kST), lds, s, a, j); break;
-        }
-    };
-    static_assert(kMaxDepth <= 8 * kST, "sort slots per thread");
+    const int64_t gcap = (int64_t)num_cus() * kPlanBlocksPerCU;
     StreamGlobal hg{};
     std::vector<RankStream> hr(W);   // committed state after the last booked round
-    launch_round(0);                  // round 0's form
-    ODB_LAUNCHED();
-    for (int64_t k0 = 0; k0 < a.max_rounds;) {
-        // rounds k0 .. k0+cnt-1: launch k+1 emits round k; the chunk's last round is then
-        // booked on its own
-        const int64_t cnt = std::min<int64_t>(a.max_rounds - k0, stream_rounds_left(a, params->rate, hr, hg,
-                                                                                    k0 == 0 ? 1 : kMinChunk));
-        for (int64_t k = k0; k < k0 + cnt; ++k) {
-            launch_round(k + 1);
+    int64_t fetched = 0;             // views fetched by the end
+    int64_t j0 = 0;                  // first round that runs on its own
+    std::vector<int32_t> targets;    // T of the rounds formed together, before round j0
+
+    // ---- the rounds formed together
+    const BulkSchedule bs = bulk_schedule(a, params);
+    const bool join = a.mode == ODB_MODE_JOIN;
+    BulkArgs b{};
+    BulkState hb{};
+    bool bulk_done = false;
+    if (bs.use) {
+        b.W = W;
+        b.N = N;
+        b.q = q;
+        b.D = a.D;
+        b.budget = budget;
+        b.scap = scap;
+        b.E = bs.E;
+        b.n_all = bs.n0[0];
+        b.rate_all = params->rate[0];
+        b.bufsize = a.bufsize;
+        b.stop_round = bs.stop_round;
+        b.tok_off = a.tok_off;
+        b.perm = d_perm;
+        b.st = ws_at<BulkState>(d_ws, SL.bulk_st);
+        b.T = ws_at<int32_t>(d_ws, SL.bulk_T);
+        b.base = ws_at<int64_t>(d_ws, SL.bulk_base);
+        b.G = ws_at<int32_t>(d_ws, SL.bulk_G);
+        b.sum = ws_at<uint32_t>(d_ws, SL.bulk_sum);
+        // the window workspace's gathered row records (n + 1 + W entries, at least M + 1) are
+        // free here: only a collate without row records writes them
+        b.gs = ws_at<int32_t>(d_ws, L.row_len);
+        b.tile = ws_at<int64_t>(d_ws, L.row_ts);
+        b.stepsum = a.stepsum;
+        b.views = join ? d_emit_views : a.evw;
+        b.ids = join ? d_emit_order : const_cast<int32_t*>(a.vid);
+        b.ts = join && d_row_token_start ? d_row_token_start : const_cast<int64_t*>(a.vts);
+        b.len = join && d_row_len ? d_row_len : const_cast<int32_t*>(a.vlen);
+        if (!bs.uniform) {
+            int64_t* sched = ws_at<int64_t>(d_ws, SL.cap);   // the capacities are not read on this path
+            std::vector<int64_t> packed(W);
+            for (int r = 0; r < W; ++r) packed[r] = ((int64_t)params->rate[r] << 32) | bs.n0[r];
+            ODB_TRY(store_values(packed.data(), W, sched, nullptr, s));
+            b.sched = sched;
+        }
+        hipLaunchKernelGGL(bulk_init_kernel, dim3(1), dim3(256), 0, s, b, ws_at<DevStatus>(d_ws, L.status));
+        ODB_LAUNCHED();
+        const dim3 form_grid((unsigned)bulk_grid(W, bs.E + bs.stop_round)), grid((unsigned)bulk_grid(W, bs.E));
+        const BulkSlots staged{ws_at<int32_t>(d_ws, SL.srows), ws_at<int32_t>(d_ws, SL.smax), ws_at<int64_t>(d_ws, SL.stok),
+                               ws_at<double>(d_ws, SL.sadj), nullptr, nullptr, 0,
+                               bs.stop == ODB_STOP_QUOTA ? bs.E - 1 : -1};
+        const BulkSlots final_slots{d_slot_rows, d_slot_maxlen, d_slot_tokens, d_slot_tokens_approx, d_slot_row_off,
+                                    d_slot_tile_off, 1, -1};
+        const int64_t n_max = std::min(q, *std::max_element(bs.n0.begin(), bs.n0.end()));
+        auto slots = [&](const BulkSlots& o) {
+            if (n_max <= 256) hipLaunchKernelGGL((bulk_slots_kernel<256, 1>), grid, dim3(256), 0, s, b, o);
+            else if (n_max <= 512) hipLaunchKernelGGL((bulk_slots_kernel<256, 2>), grid, dim3(256), 0, s, b, o);
+            else if (n_max <= 1024) hipLaunchKernelGGL((bulk_slots_kernel<256, 4>), grid, dim3(256), 0, s, b, o);
+            else hipLaunchKernelGGL((bulk_slots_kernel<512, 8>), grid, dim3(512), 0, s, b, o);
+        };
+        // a buffer of n views takes the smallest block and slots per thread that hold it
+        if (n_max <= 256) hipLaunchKernelGGL((bulk_form_kernel<256, 1>), form_grid, dim3(256), 0, s, b);
+        else if (n_max <= 512) hipLaunchKernelGGL((bulk_form_kernel<256, 2>), form_grid, dim3(256), 0, s, b);
+        else if (n_max <= 1024) hipLaunchKernelGGL((bulk_form_kernel<256, 4>), form_grid, dim3(256), 0, s, b);
+        else hipLaunchKernelGGL((bulk_form_kernel<512, 8>), form_grid, dim3(512), 0, s, b);
+        static_assert(kMaxDepth <= 512 * 8, "views per rank-round");
+        ODB_LAUNCHED();
+        hipLaunchKernelGGL(bulk_targets_kernel, dim3(1), dim3(1024), 0, s, b);
+        ODB_LAUNCHED();
+        slots(join ? final_slots : staged);
+        ODB_LAUNCHED();
+        const unsigned step_grid = grid_for(std::max<int64_t>(1, std::min(scap, bs.E * n_max)), kWave, gcap * 4);
+        if (join) {
+            ODB_TRY((device_excl_scan<int64_t>(BulkTileLoad{b.tile, (int64_t)W * bs.E}, StoreS{b.tile}, (int64_t)W * bs.E + 1,
+                                               ws_at<int64_t>(d_ws, SL.partials), s)));
+            hipLaunchKernelGGL(bulk_tiles_kernel, grid, dim3(kWave), 0, s, b, d_slot_tile_off, d_slot_row_off, d_left_off);
+            ODB_LAUNCHED();
+            hipLaunchKernelGGL(bulk_steps_kernel, dim3(step_grid), dim3(kWave), 0, s, b, (const int32_t*)d_slot_rows,
+                               (const int64_t*)d_slot_tokens, (int64_t)0, scap);
+        } else {
+            if (bs.stop == ODB_STOP_QUOTA) {
+                hipLaunchKernelGGL(bulk_cut_kernel, dim3(1), dim3(kST), 0, s, b, bs.emitted_before(bs.E - 1), a.quota);
+                ODB_LAUNCHED();
+            }
+            hipLaunchKernelGGL(bulk_steps_kernel, dim3(step_grid), dim3(kWave), 0, s, b, (const int32_t*)staged.rows,
+                               (const int64_t*)staged.tokens, scap, scap);
+        }
+        ODB_LAUNCHED();
+        // the state and, next to it, the targets
+        const size_t bytes = SL.bulk_T - SL.bulk_st + 4 * (h_trace ? bs.E : 0);
+        std::vector<char> back(bytes);
+        ODB_TRY_HIP(hipMemcpyAsync(back.data(), b.st, bytes, hipMemcpyDeviceToHost, s));
+        ODB_TRY_HIP(hipStreamSynchronize(s));
+        memcpy(&hb, back.data(), sizeof(hb));
+        if (hb.err & kSErrInternal) return set_error(ODB_E_INTERNAL, "streaming round state inconsistent");
+        // bad data: the sequential rounds report what the iteration meets
+        const int64_t fail = hb.err ? 0 : hb.fail;
+        if (h_trace && fail > 0) {
+            targets.resize(fail);
+            memcpy(targets.data(), back.data() + (SL.bulk_T - SL.bulk_st), 4 * fail);
+        }
+        if (fail == bs.E) {
+            bulk_done = true;
+            hg.steps = hb.steps;
+            hg.emitted = bs.stop == ODB_STOP_QUOTA ? bs.emitted_before(bs.E - 1) + hb.emitted : bs.emitted_before(bs.E);
+            hg.rounds = bs.rounds;
+            hg.emit_rounds = bs.E;
+            hg.skip_rounds = bs.last_round + 1 - bs.E;
+            hg.splits = hb.splits;
+            hg.second_gather = hb.changed;
+            hg.max_step = (int64_t)hb.max_step;
+            hg.max_outstanding = (unsigned long long)n_max;
+            hg.stop = bs.stop;
+            hg.done = 1;
+            fetched = bs.emitted_before(bs.E);
+            if (bs.stop_round)
+                for (int r = 0; r < W; ++r)
+                    fetched += std::min<int64_t>(q - std::min(q, bs.E * bs.n0[r]), std::min<int64_t>(params->rate[r], a.D));
+        } else if (fail > 0) {
+            // go on from the first round that overflows: its protocol rounds start after the
+            // last emitting round before it
+            j0 = bs.round_of(fail - 1) + 1;
+            if (join) {
+                hipLaunchKernelGGL(copy_i32_kernel, dim3(grid_for(M, 256, gcap)), dim3(256), 0, s,
+                                   (const int32_t*)d_emit_views, a.evw, M);
+                ODB_LAUNCHED();
+                slots(staged);
+                ODB_LAUNCHED();
+                hipLaunchKernelGGL(bulk_steps_kernel, dim3(step_grid), dim3(kWave), 0, s, b, (const int32_t*)staged.rows,
+                                   (const int64_t*)staged.tokens, scap, scap);
+                ODB_LAUNCHED();
+            }
+        }
+    }
+
+    // ---- the rounds one after the other
+    if (!bulk_done) {
+        // the window part of the workspace: rank offsets and a cleared status word, as after
+        // odb_align_groups
+        ODB_TRY(upload_small(w, L, d_ws, nullptr, s));
+        hipLaunchKernelGGL(stream_init_kernel, dim3(grid_for(std::max<int64_t>(params->max_rounds, W), 256, 1024)),
+                           dim3(256), 0, s, a, params->max_rounds);
+        ODB_LAUNCHED();
+        if (j0 > 0) {
+            const int64_t fail = hb.fail;
+            hg.emitted = bs.emitted_before(fail);
+            for (int r = 0; r < W; ++r) hr[r].cursor = std::min(q, fail * bs.n0[r]);
+            hipLaunchKernelGGL(bulk_resume_kernel, dim3(grid_for(W, 256)), dim3(256), 0, s, b, a, fail, j0, hg.emitted);
             ODB_LAUNCHED();
         }
-        hipLaunchKernelGGL(stream_book_kernel, dim3(1), dim3(kST), 0, s, a, k0 + cnt - 1);
+        ODB_TRY_HIP(hipMemcpyAsync(const_cast<int32_t*>(a.rate), params->rate, 4 * W, hipMemcpyHostToDevice, s));
+        if (a.cap)
+            ODB_TRY_HIP(hipMemcpyAsync(const_cast<int64_t*>(a.cap), params->slot_capacity, 8 * W, hipMemcpyHostToDevice, s));
+        if (M > 0) {
+            hipLaunchKernelGGL(stream_views_kernel, dim3(grid_for(M, 256, gcap)), dim3(256), 0, s, a,
+                               const_cast<int32_t*>(a.vid), const_cast<int64_t*>(a.vts), const_cast<int32_t*>(a.vlen));
+            ODB_LAUNCHED();
+        }
+
+        // rounds, in chunks, until the done flag is up
+        const int kpt = sort_kpt(a.D);
+        const size_t lds = round_lds_bytes(a.D);
+        auto launch_round = [&](int64_t j) {
+            switch (kpt) {
+                case 1: hipLaunchKernelGGL(stream_round_kernel<1>, dim3(W), dim3(kST), lds, s, a, j, j0); break;
+                case 2: hipLaunchKernelGGL(stream_round_kernel<2>, dim3(W), dim3(kST), lds, s, a, j, j0); break;
+                case 4: hipLaunchKernelGGL(stream_round_kernel<4>, dim3(W), dim3(kST), lds, s, a, j, j0); break;
+                default: hipLaunchKernelGGL(stream_round_kernel<8>, dim3(W), dim3(kST), lds, s, a, j, j0); break;
+            }
+        };
+        static_assert(kMaxDepth <= 8 * kST, "sort slots per thread");
+        launch_round(j0);                  // round j0's form
         ODB_LAUNCHED();
-        ODB_TRY_HIP(hipMemcpyAsync(&hg, a.g, sizeof(hg), hipMemcpyDeviceToHost, s));
-        ODB_TRY_HIP(hipMemcpyAsync(hr.data(), a.ranks, sizeof(RankStream) * W, hipMemcpyDeviceToHost, s));
-        ODB_TRY_HIP(hipStreamSynchronize(s));
-        if (hg.done) break;
-        k0 += cnt;
+        for (int64_t k0 = j0; k0 < a.max_rounds;) {
+            // rounds k0 .. k0+cnt-1: launch k+1 emits round k; the chunk's last round is then
+            // booked on its own
+            const int64_t cnt = std::min<int64_t>(a.max_rounds - k0, stream_rounds_left(a, params->rate, hr, hg,
+                                                                                        k0 == j0 ? 1 : kMinChunk));
+            for (int64_t k = k0; k < k0 + cnt; ++k) {
+                launch_round(k + 1);
+                ODB_LAUNCHED();
+            }
+            hipLaunchKernelGGL(stream_book_kernel, dim3(1), dim3(kST), 0, s, a, k0 + cnt - 1);
+            ODB_LAUNCHED();
+            ODB_TRY_HIP(hipMemcpyAsync(&hg, a.g, sizeof(hg), hipMemcpyDeviceToHost, s));
+            ODB_TRY_HIP(hipMemcpyAsync(hr.data(), a.ranks, sizeof(RankStream) * W, hipMemcpyDeviceToHost, s));
+            ODB_TRY_HIP(hipStreamSynchronize(s));
+            if (hg.done) break;
+            k0 += cnt;
+        }
     }
     if (hg.err & kSErrIdentity) return set_error(ODB_E_INVALID_DATA, "perm holds a value outside [0, N)");
     if (hg.err & kSErrLength) return set_error(ODB_E_INVALID_DATA, "a sample has length < 1 or >= 2^31");
@@ -1355,8 +2237,45 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
         return set_error(ODB_E_CAPACITY, "plan needs %lld slots, capacity is %lld", (long long)K,
                          (long long)slot_capacity);
 
+    // the host trace: rounds formed together by the schedule, then the recorded ones
+    std::vector<StreamRec> hrec;
+    auto fill_trace = [&]() {
+        if (!h_trace) return;
+        int64_t phi = M;
+        for (int64_t i = 0; i < hg.rounds; ++i) h_trace[i] = odb_stream_round_t{1, 0, 0, 0, 0};
+        const int64_t together = (int64_t)targets.size();
+        for (int64_t e = 0; e < together; ++e) {
+            odb_stream_round_t& t = h_trace[bs.round_of(e)];
+            t.kind = 0;
+            t.target = targets[e];
+            t.emitted = (e + 1 < bs.E ? bs.emitted_before(e + 1) : bulk_done ? hg.emitted : bs.emitted_before(e + 1)) -
+                        bs.emitted_before(e);
+        }
+        if (bulk_done && bs.rounds > bs.last_round + 1) h_trace[bs.rounds - 1].kind = 2;
+        for (int64_t i = bulk_done ? hg.rounds : j0; i < hg.rounds; ++i) {
+            h_trace[i].kind = hrec[i].kind;
+            h_trace[i].target = hrec[i].kind == 0 ? hrec[i].target : 0;
+            h_trace[i].emitted = hrec[i].kind == 0 ? hrec[i].emitted : 0;
+        }
+        for (int64_t i = 0; i < hg.rounds; ++i) {
+            phi -= h_trace[i].emitted;
+            h_trace[i].phi = phi;
+        }
+    };
+    if (bulk_done && join) {
+        // everything is in place: every view emitted once, each identity by its M / N views
+        h_info->real_tokens = (int64_t)hb.real_tokens;
+        h_info->padded_elems = hb.padded;
+        h_info->pad_fraction = hb.padded > 0 ? 1.0 - (double)hb.real_tokens / (double)hb.padded : 0.0;
+        h_info->bad_views = (int64_t)hb.bad_views;
+        h_info->duplicate_ids = M - N;
+        fill_trace();
+        if (hb.bad_views != 0)
+            return set_error(ODB_E_INTERNAL, "streaming plan does not account for every view exactly once");
+        return ODB_OK;
+    }
+
     // plan arrays in the window layout
-    const int64_t gcap = (int64_t)num_cus() * kPlanBlocksPerCU;
     int64_t* partials = ws_at<int64_t>(d_ws, SL.partials);
     if (K > 0) {
         hipLaunchKernelGGL(stream_slots_kernel, dim3(grid_for(K, 256, gcap)), dim3(256), 0, s, a, S, d_slot_rows,
@@ -1377,7 +2296,11 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
     }
     hipLaunchKernelGGL(clear_totals_kernel, dim3(1), dim3(64), 0, s, tot);
     ODB_LAUNCHED();
-    if (K > 0) {
+    if (K > 0 && bulk_done) {
+        hipLaunchKernelGGL(bulk_emit_out_kernel, dim3(W, 64), dim3(256), 0, s, b, S, (const int64_t*)d_slot_row_off,
+                           d_emit_views, d_emit_order, d_row_token_start, d_row_len);
+        ODB_LAUNCHED();
+    } else if (K > 0) {
         hipLaunchKernelGGL(stream_emit_out_kernel, dim3(W, 64), dim3(256), 0, s, a, S, (const int64_t*)d_slot_row_off,
                            d_emit_views, d_emit_order, d_row_token_start, d_row_len);
         ODB_LAUNCHED();
@@ -1402,18 +2325,20 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
     int64_t padded = 0, nleft = 0;
     ODB_TRY_HIP(hipMemcpyAsync(&ht, tot, sizeof(ht), hipMemcpyDeviceToHost, s));
     ODB_TRY_HIP(hipMemcpyAsync(&padded, d_slot_tile_off + K, 8, hipMemcpyDeviceToHost, s));
-    ODB_TRY_HIP(hipMemcpyAsync(hr.data(), a.ranks, sizeof(RankStream) * W, hipMemcpyDeviceToHost, s));
+    if (!bulk_done)
+        ODB_TRY_HIP(hipMemcpyAsync(hr.data(), a.ranks, sizeof(RankStream) * W, hipMemcpyDeviceToHost, s));
     if (M > 0) ODB_TRY_HIP(hipMemcpyAsync(&nleft, partials + (M + kScanTile - 1) / kScanTile, 8,
                                           hipMemcpyDeviceToHost, s));
-    std::vector<StreamRec> hrec(h_trace ? hg.rounds : 0);
-    if (h_trace && hg.rounds > 0)
+    if (h_trace && !bulk_done && hg.rounds > 0) {
+        hrec.resize(hg.rounds);
         ODB_TRY_HIP(hipMemcpyAsync(hrec.data(), a.rec, sizeof(StreamRec) * hg.rounds, hipMemcpyDeviceToHost, s));
+    }
     ODB_TRY_HIP(hipStreamSynchronize(s));
     // the left-over offsets end with the total; the scan left off[W] unset
     ODB_TRY_HIP(hipMemcpyAsync(d_left_off + W, &nleft, 8, hipMemcpyHostToDevice, s));
     ODB_TRY_HIP(hipStreamSynchronize(s));
-    int64_t fetched = 0;
-    for (int r = 0; r < W; ++r) fetched += hr[r].cursor;
+    if (!bulk_done)
+        for (int r = 0; r < W; ++r) fetched += hr[r].cursor;
     h_info->real_tokens = (int64_t)ht.real_tokens;
     h_info->padded_elems = padded;
     h_info->pad_fraction = padded > 0 ? 1.0 - (double)ht.real_tokens / (double)padded : 0.0;
@@ -1422,17 +2347,7 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
     h_info->bad_views = (int64_t)ht.bad_views;
     h_info->missing_ids = (int64_t)ht.missing_ids;
     h_info->duplicate_ids = (int64_t)ht.duplicate_ids;
-    if (h_trace) {
-        int64_t phi = M;
-        for (int64_t i = 0; i < hg.rounds; ++i) {
-            phi -= hrec[i].kind == 0 ? hrec[i].emitted : 0;
-            h_trace[i].kind = hrec[i].kind;
-            h_trace[i].reserved0 = 0;
-            h_trace[i].target = hrec[i].kind == 0 ? hrec[i].target : 0;
-            h_trace[i].emitted = hrec[i].kind == 0 ? hrec[i].emitted : 0;
-            h_trace[i].phi = phi;
-        }
-    }
+    fill_trace();
     if (nleft != M - hg.emitted || ht.bad_views != 0)
         return set_error(ODB_E_INTERNAL, "streaming plan does not account for every view exactly once");
     return ODB_OK;

@@ -362,3 +362,46 @@ def test_stream_budget_int64_max():
     lens = rng.integers(1, 3000, 2500)
     perm = rng.permutation(len(lens)).astype(np.int32)
     run_case("budget_int64_max", lens, perm, 3, (1 << 63) - 1, 128, 200, [128, 50, 128])
+
+
+def together_cases():
+    """Rounds formed together: buffer sizes at the edges of the block variants (256, 512, 1024
+    and 4096 views), 64 rounds and more (dealt to the XCDs), a capacity that never binds, and
+    the ways such a run ends: drained, in a round that overflows (the rest goes round by
+    round), at a quota inside and at the end of a round, and at the first finished rank."""
+    rng = np.random.default_rng(83)
+    out = []
+    for buf in (1, 255, 256, 257, 512, 513, 1024, 1025, 4096):
+        out.append((f"buffer_{buf}", rng.integers(1, 5000, 3 * 2 * buf + 5), 2, 16384, buf, buf, [buf, buf], {}))
+    out.append(("rounds_64", rng.integers(1, 700, 64 * 3 * 40), 3, 4000, 40, 40, [40] * 3, {}))
+    out.append(("rounds_65_long", rng.integers(1, 2 ** 31 - 1, 65 * 40 - 3), 1, 2 ** 40, 40, 64, [64], {}))
+    out.append(("wide_digits", rng.integers(2 ** 16, 2 ** 24, 2000), 2, 2 ** 25, 300, 300, [300] * 2, {}))
+    out.append(("free_capacity", rng.integers(1, 900, 3000), 3, 6000, 128, 128, [128] * 3,
+                dict(cap=np.array([128, 0, 500]))))
+    # uneven rates: the fast rank's last buffer is small, so a late round overflows
+    out.append(("resume", rng.integers(1, 900, 3 * 1003), 3, 3000, 100, 300, [100, 129, 250], {}))
+    out.append(("resume_skips", rng.integers(1, 900, 3 * 905), 3, 3000, 100, 300, [13, 17, 40], {}))
+    for quota in (1950, 3000):
+        out.append((f"resume_quota_{quota}", rng.integers(1, 900, 3 * 1003), 3, 3000, 100, 300, [100, 129, 250],
+                    dict(mode="nonjoin", quota=quota)))
+    for quota in (1, 600, 601, 1799, 1800, 3000):
+        out.append((f"quota_{quota}", rng.integers(1, 2000, 3000), 3, 6000, 200, 200, [200] * 3,
+                    dict(mode="nonjoin", quota=quota)))
+    # the stop round still fetches: one rank ready (its views count as fetched), one not
+    out.append(("finished", rng.integers(900, 1000, 3 * 400), 3, 1000, 50, 200, [50, 100, 200],
+                dict(mode="nonjoin", quota=10 ** 6)))
+    return out
+
+
+@pytest.mark.parametrize("idx", range(len(together_cases())))
+def test_stream_rounds_together(idx):
+    name, lens, W, budget, buf, depth, rate, kw = together_cases()[idx]
+    perm = np.random.default_rng(100 + idx).permutation(len(lens)).astype(np.int32)
+    small = int(lens.sum()) < 1 << 24
+    run_case(name, lens, perm, W, budget, buf, depth, np.asarray(rate, dtype=np.int32), full_collate=small,
+             tokens=None if small else _one_token(), **kw)
+
+
+def _one_token():
+    import torch
+    return torch.zeros(1, dtype=torch.int32, device="cuda")
