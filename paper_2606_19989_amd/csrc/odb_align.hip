@@ -839,6 +839,31 @@ __global__ void __launch_bounds__(kBlock) popcount_kernel(const uint32_t* __rest
     if (threadIdx.x == 0 && c) atomicAdd((unsigned long long*)&info->distinct_views, (unsigned long long)c);
 }
 
+// Missing and duplicate identities of an identity map over the listed views.
+int count_identities(const odb_window_t* w, const Layout& L, void* ws, const int32_t* emit, int64_t ne,
+                     const int32_t* left, int64_t nl, hipStream_t s) {
+    int32_t* cover = ws_at<int32_t>(ws, L.cover);
+    DevStatus* st = ws_at<DevStatus>(ws, L.status);
+    const int64_t n = w->num_samples, nid = w->num_identities;
+    const int64_t cap = (int64_t)num_cus() * kPlanBlocksPerCU;
+    hipLaunchKernelGGL(fill_i32_kernel, dim3(grid_for(nid, kBlock, cap)), dim3(kBlock), 0, s, cover, nid, 0);
+    ODB_LAUNCHED();
+    if (ne > 0) {
+        hipLaunchKernelGGL(count_kernel, dim3(grid_for(ne, kBlock, cap)), dim3(kBlock), 0, s, emit, ne, n,
+                           w->d_identity, nid, cover, st);
+        ODB_LAUNCHED();
+    }
+    if (nl > 0) {
+        hipLaunchKernelGGL(count_kernel, dim3(grid_for(nl, kBlock, cap)), dim3(kBlock), 0, s, left, nl, n,
+                           w->d_identity, nid, cover, st);
+        ODB_LAUNCHED();
+    }
+    hipLaunchKernelGGL(coverage_reduce_kernel, dim3(grid_for(nid, kBlock, cap)), dim3(kBlock), 0, s,
+                       (const int32_t*)cover, nid, 0, 1, ws_at<DevInfo>(ws, L.info));
+    ODB_LAUNCHED();
+    return ODB_OK;
+}
+
 // Coverage (App. C): a bitset over the sampler views proves "every view exactly once"
 // when it holds n distinct views and n ids were listed; the exact per-view counters run
 // only when it does not (run_coverage_exact).  Identities of an identity map are always
@@ -869,25 +894,8 @@ int run_coverage(const odb_window_t* w, const Layout& L, void* ws, const int32_t
                            (const uint32_t*)bits, words, info);
         ODB_LAUNCHED();
     }
-    if (w->d_identity && n > 0) {
-        // the identity counters reuse the bitset's memory: the popcount above has consumed it
-        const int64_t nid = w->num_identities;
-        hipLaunchKernelGGL(fill_i32_kernel, dim3(grid_for(nid, kBlock, cap)), dim3(kBlock), 0, s, cover, nid, 0);
-        ODB_LAUNCHED();
-        if (ne > 0) {
-            hipLaunchKernelGGL(count_kernel, dim3(grid_for(ne, kBlock, cap)), dim3(kBlock), 0, s, emitted, ne, n,
-                               w->d_identity, nid, cover, st);
-            ODB_LAUNCHED();
-        }
-        if (nl > 0) {
-            hipLaunchKernelGGL(count_kernel, dim3(grid_for(nl, kBlock, cap)), dim3(kBlock), 0, s, left, nl, n,
-                               w->d_identity, nid, cover, st);
-            ODB_LAUNCHED();
-        }
-        hipLaunchKernelGGL(coverage_reduce_kernel, dim3(grid_for(nid, kBlock, cap)), dim3(kBlock), 0, s,
-                           (const int32_t*)cover, nid, 0, 1, info);
-        ODB_LAUNCHED();
-    }
+    // the identity counters reuse the bitset's memory: the popcount above has consumed it
+    if (w->d_identity && n > 0) ODB_TRY(count_identities(w, L, ws, emitted, ne, left, nl, s));
     return ODB_OK;
 }
 
@@ -1089,27 +1097,7 @@ int run_plan_coverage(const odb_window_t* w, const Layout& L, void* ws, const in
                        (const int64_t*)chunk_first, C, emit, row_off, S, left, loff, w->d_identity ? 0 : 1,
                        ws_at<DevInfo>(ws, L.info), ws_at<DevStatus>(ws, L.status));
     ODB_LAUNCHED();
-    if (w->d_identity) {
-        int32_t* cover = ws_at<int32_t>(ws, L.cover);
-        DevStatus* st = ws_at<DevStatus>(ws, L.status);
-        const int64_t nid = w->num_identities;
-        const int64_t cap = (int64_t)num_cus() * kPlanBlocksPerCU;
-        hipLaunchKernelGGL(fill_i32_kernel, dim3(grid_for(nid, kBlock, cap)), dim3(kBlock), 0, s, cover, nid, 0);
-        ODB_LAUNCHED();
-        if (ne > 0) {
-            hipLaunchKernelGGL(count_kernel, dim3(grid_for(ne, kBlock, cap)), dim3(kBlock), 0, s, emit, ne, n,
-                               w->d_identity, nid, cover, st);
-            ODB_LAUNCHED();
-        }
-        if (nl > 0) {
-            hipLaunchKernelGGL(count_kernel, dim3(grid_for(nl, kBlock, cap)), dim3(kBlock), 0, s, left, nl, n,
-                               w->d_identity, nid, cover, st);
-            ODB_LAUNCHED();
-        }
-        hipLaunchKernelGGL(coverage_reduce_kernel, dim3(grid_for(nid, kBlock, cap)), dim3(kBlock), 0, s,
-                           (const int32_t*)cover, nid, 0, 1, ws_at<DevInfo>(ws, L.info));
-        ODB_LAUNCHED();
-    }
+    if (w->d_identity) ODB_TRY(count_identities(w, L, ws, emit, ne, left, nl, s));
     return ODB_OK;
 }
 
@@ -1133,6 +1121,561 @@ int finish_coverage(const odb_window_t* w, const Layout& L, void* ws, const int3
     ODB_TRY_HIP(hipMemcpyAsync(hi, info, sizeof(*hi), hipMemcpyDeviceToHost, s));
     ODB_TRY_HIP(hipStreamSynchronize(s));
     return ODB_OK;
+}
+
+// ---------------------------------------------------------------- windows aligned in one round
+// Without overflow (T = the largest group count: no active rank buffers fewer samples and
+// no smaller positive capacity) the first round empties every buffer.  A rank's emitted rows
+// are then its formation order reversed, whatever the split, and everything else has a
+// closed form: the singletons of a split end at X = k + j*, where j* is the first group with
+// start(j* + 1) - (j* + 1) >= k = T - G (the surplus of groups 0 .. j* is their samples less
+// their number).  Five launches in place of a round's nine and the final plan's seven:
+//
+//   rows_kernel       checks the stage-1 arrays, records the group starts and writes every
+//                     rank's reversed order with its row records
+//   rank_tiles_kernel tokens before every tile of a rank
+//   cut_steps_kernel, cut_kernel (sample quota only)
+//                     step sizes, the first step that reaches the quota, each rank's share
+//   slots_kernel      T, and rows, longest length, tokens and row offset of every slot
+//   tiles_kernel      tile offsets, the largest step, the totals
+//   share_kernel      (sample quota only) rows and left-overs moved to their final place
+//
+// S is known on the device only, so slots_kernel and tiles_kernel run a grid that does not
+// depend on it: block b takes the b-th of gridDim.x equal ranges of slots, and the ranges'
+// sums are scanned by every block of the second launch.
+//
+// The stage-1 check also proves coverage: a rank's order holds ids of the rank only, strictly
+// ordered by (length desc, id asc) under lengths that equal each id's CSR length, so no id
+// comes twice, and it has as many places as the rank has ids.
+struct OneArgs {
+    int W;
+    int64_t n;
+    int nonjoin;
+    int64_t quota;
+    int64_t slot_capacity;
+    const int64_t* tok_off;
+    const int64_t* off;        // [W + 1] rank offsets
+    const int32_t* order;
+    const int32_t* slen;
+    const int32_t* gidx;
+    const int32_t* groups;     // [W] G_r
+    int32_t* gs;               // [n] rank-local start of group g of rank r at off[r] + g
+    int64_t* gpre;             // [n] tokens before that start within its tile of the rank
+    int64_t* tpre;             // [W * per_rank] tokens of the rank before each of its tiles
+    int per_rank;              // tiles (kRowTile positions) of the largest rank
+    int64_t* lo;               // [W + 1] first row of every rank (the rank offsets in join mode)
+    int64_t* steps;            // [max n_r] samples per step (sample quota only)
+    I64Pair* part;             // [gridDim.x] (padded elements, real tokens) per range of slots
+    RoundState* rs;
+    DevInfo* info;
+    DevStatus* st;
+    // rows: the final arrays in join mode, else staged at the rank's own positions
+    int32_t* emit;
+    int32_t* len;
+    int64_t* ts;               // may be null
+};
+
+constexpr int kRowItems = 4;                       // consecutive positions per thread
+constexpr int64_t kRowTile = kBlock * kRowItems;   // positions of one rank per block
+constexpr int kMaxRanges = 1024;                   // blocks of slots_kernel / tiles_kernel
+typedef int32_t I4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef int64_t L2 __attribute__((ext_vector_type(2), aligned(8)));
+
+// Group counts a rank may have: 0 exactly for an empty rank, at most its samples.
+__device__ __forceinline__ bool groups_ok(int64_t G, int64_t cnt) {
+    return G >= 0 && G <= cnt && ((cnt == 0) == (G == 0));
+}
+
+// Blocks `per_rank` tiles of every rank.  With xcd set, rank r's blocks run on XCD r mod 8
+// (blocks are dealt to the XCDs round robin), whose L2 then holds the rank's CSR offsets for
+// the random reads: 16.7 M rows of 64 ranks gather from 134 MB of offsets.
+//
+// Bound by those reads (one 16-byte load per row, each in its own cache line) and, beside
+// them, 12 B read and 16 B written per row in 16-byte accesses.  64 x 262,144 rows: 0.58 ms as
+// five kernels (check, length prefix, emit, row records, coverage), 0.2x ms here.
+__global__ void __launch_bounds__(kBlock) rows_kernel(OneArgs a, int xcd) {
+    const int64_t b = blockIdx.x;
+    int r;
+    int64_t tile;
+    if (xcd) {
+        const int64_t g = b / kXcds;
+        r = (int)(g / a.per_rank) * kXcds + (int)(b % kXcds);
+        tile = g % a.per_rank;
+    } else {
+        r = (int)(b / a.per_rank);
+        tile = b % a.per_rank;
+    }
+    if (b == 0) {   // ranks without samples have no block of their own
+        for (int k = threadIdx.x; k < a.W; k += kBlock)
+            if (!groups_ok(a.groups[k], a.off[k + 1] - a.off[k])) atomicOr(&a.st->err, kErrGroupIndex);
+    }
+    if (r >= a.W) return;
+    const int64_t base = a.off[r], nr = a.off[r + 1] - base;
+    if (tile * kRowTile >= nr) return;
+    const int64_t q0 = tile * kRowTile + (int64_t)threadIdx.x * kRowItems;
+    const int64_t G = groups_ok(a.groups[r], nr) ? a.groups[r] : 0;
+    const int64_t p0 = base + q0;
+    const int m = nr - q0 < kRowItems ? (int)(nr - q0) : kRowItems;   // live positions, <= 0 past the rank
+    int32_t id[kRowItems], l[kRowItems], g[kRowItems];
+    if (m == kRowItems) {
+        // streamed past the caches, which hold the offsets
+        const I4 x = __builtin_nontemporal_load(reinterpret_cast<const I4*>(a.order + p0));
+        const I4 y = __builtin_nontemporal_load(reinterpret_cast<const I4*>(a.slen + p0));
+        const I4 z = __builtin_nontemporal_load(reinterpret_cast<const I4*>(a.gidx + p0));
+#pragma unroll
+        for (int i = 0; i < kRowItems; ++i) {
+            id[i] = x[i];
+            l[i] = y[i];
+            g[i] = z[i];
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < kRowItems; ++i) {
+            const int64_t p = i < m ? p0 + i : base;
+            id[i] = a.order[p];
+            l[i] = a.slen[p];
+            g[i] = a.gidx[p];
+        }
+    }
+    const int64_t pp = q0 > 0 && m > 0 ? p0 - 1 : base;   // the position before, if the rank has one
+    int32_t pid = a.order[pp], pl = a.slen[pp], pg = a.gidx[pp];
+    int64_t t0[kRowItems], t1[kRowItems];
+#pragma unroll
+    for (int i = 0; i < kRowItems; ++i) {
+        const bool in = id[i] >= base && id[i] < base + nr;
+        const L2 o = *reinterpret_cast<const L2*>(a.tok_off + (in ? (int64_t)id[i] : base));
+        t0[i] = o[0];
+        t1[i] = o[1];
+    }
+    // tokens of the tile before each position
+    int64_t pre;
+    {
+        int64_t sum = 0, tot;
+#pragma unroll
+        for (int i = 0; i < kRowItems; ++i) sum += i < m ? l[i] : 0;
+        const int64_t inc = wave_scan_dpp<OpAdd>(sum);
+        __shared__ int64_t s_w[kBlock / kWave];
+        const int w = threadIdx.x / kWave;
+        if ((threadIdx.x & (kWave - 1)) == kWave - 1) s_w[w] = inc;
+        __syncthreads();
+        pre = inc - sum;
+        tot = 0;
+#pragma unroll
+        for (int i = 0; i < kBlock / kWave; ++i) {
+            pre += i < w ? s_w[i] : 0;
+            tot += s_w[i];
+        }
+        if (threadIdx.x == 0) a.tpre[(int64_t)r * a.per_rank + tile] = tot;   // rank_tiles_kernel: prefix
+    }
+    if (m <= 0) return;
+    bool bad_order = false, bad_group = false;
+    int64_t first = LLONG_MAX;
+#pragma unroll
+    for (int i = 0; i < kRowItems; ++i) {
+        if (i < m) {
+            const int64_t q = q0 + i;
+            const bool in = id[i] >= base && id[i] < base + nr;
+            bool ok = in && l[i] >= 1;
+            bool gok = g[i] >= 0 && g[i] < G;
+            if (q == 0) {
+                gok = gok && g[i] == 0;
+            } else {
+                ok = ok && (pl > l[i] || (pl == l[i] && pid < id[i]));
+                const int32_t d = g[i] - pg;
+                gok = gok && (d == 0 || d == 1);
+            }
+            if (q == nr - 1) gok = gok && g[i] == G - 1;
+            if (gok && (q == 0 || g[i] != pg)) {
+                a.gs[base + g[i]] = (int32_t)q;
+                a.gpre[base + g[i]] = pre;
+            }
+            if (!ok || !gok) {
+                bad_order |= !ok;
+                bad_group |= !gok;
+                first = first < base + q ? first : base + q;
+            }
+            if (in) {
+                const int64_t w = t1[i] - t0[i];
+                if (w < 1 || w > INT_MAX || t0[i] < 0) {
+                    atomicOr(&a.st->err, kErrLength);
+                    atomicMin((unsigned long long*)&a.st->first_bad_len, (unsigned long long)id[i]);
+                } else if (w != (int64_t)l[i]) {
+                    atomicOr(&a.st->err, kErrSortedLen);
+                    atomicMin((unsigned long long*)&a.st->first_bad_csr, (unsigned long long)id[i]);
+                }
+            }
+        }
+        pre += l[i];
+        pid = id[i];
+        pl = l[i];
+        pg = g[i];
+    }
+    if (bad_order || bad_group) {
+        atomicOr(&a.st->err, (bad_order ? kErrOrder : 0) | (bad_group ? kErrGroupIndex : 0));
+        atomicMin((unsigned long long*)&a.st->first_bad, (unsigned long long)first);
+    }
+    // position q goes to row nr - 1 - q of the rank
+    const int64_t o = base + nr - q0 - m;
+    if (m == kRowItems) {
+        __builtin_nontemporal_store(I4{id[3], id[2], id[1], id[0]}, reinterpret_cast<I4*>(a.emit + o));
+        __builtin_nontemporal_store(I4{l[3], l[2], l[1], l[0]}, reinterpret_cast<I4*>(a.len + o));
+        if (a.ts) {
+            __builtin_nontemporal_store(L2{t0[3], t0[2]}, reinterpret_cast<L2*>(a.ts + o));
+            __builtin_nontemporal_store(L2{t0[1], t0[0]}, reinterpret_cast<L2*>(a.ts + o + 2));
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < kRowItems; ++i) {
+            if (i >= m) break;
+            a.emit[o + m - 1 - i] = id[i];
+            a.len[o + m - 1 - i] = l[i];
+            if (a.ts) a.ts[o + m - 1 - i] = t0[i];
+        }
+    }
+}
+
+// One block per rank: the tokens of the rank's tiles become the tokens before each tile.
+__global__ void __launch_bounds__(kBlock) rank_tiles_kernel(OneArgs a) {
+    const int r = blockIdx.x;
+    const int64_t tiles = (a.off[r + 1] - a.off[r] + kRowTile - 1) / kRowTile;
+    int64_t* t = a.tpre + (int64_t)r * a.per_rank;
+    int64_t carry = 0;
+    for (int64_t b = 0; b < tiles; b += kBlock) {
+        const int64_t i = b + threadIdx.x;
+        const int64_t v = i < tiles ? t[i] : 0;
+        int64_t tot;
+        const int64_t ex = block_excl_sum(v, &tot);
+        if (i < tiles) t[i] = carry + ex;
+        carry += tot;
+    }
+}
+
+// The target over the active ranks, and whether a rank would overflow (Eq. 3's S+_min below
+// the largest group count).  One wave's worth of work; block-uniform.
+struct OneTarget {
+    int64_t T;
+    bool overflow;
+};
+
+__device__ __forceinline__ OneTarget one_target(const OneArgs& a) {
+    int64_t mx = 0, small = 0;   // small: LLONG_MAX - the fewest samples of an active rank
+    for (int r = threadIdx.x; r < a.W; r += blockDim.x) {
+        const int64_t G = a.groups[r];
+        if (G <= 0) continue;
+        const int64_t s = LLONG_MAX - (a.off[r + 1] - a.off[r]);
+        mx = G > mx ? G : mx;
+        small = s > small ? s : small;
+    }
+    __shared__ int64_t s_mx[kBlock / kWave], s_small[kBlock / kWave];
+    mx = wave_last(wave_scan_dpp<OpMax>(mx));
+    small = wave_last(wave_scan_dpp<OpMax>(small));
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        s_mx[threadIdx.x / kWave] = mx;
+        s_small[threadIdx.x / kWave] = small;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kBlock / kWave; ++i) {
+        mx = s_mx[i] > mx ? s_mx[i] : mx;
+        small = s_small[i] > small ? s_small[i] : small;
+    }
+    __syncthreads();
+    return OneTarget{mx > 1 ? mx : 1, mx > LLONG_MAX - small};
+}
+
+// Positions [*a0, *a1) of adjusted group t of a rank with cnt > 0 samples in G groups (starts
+// gs[0 .. G)), aligned to T >= G.  Returns the formation group they are, or -1 for a piece of
+// one (a split's singletons and what is left of group j*).
+__device__ __forceinline__ int64_t one_group(const int32_t* __restrict__ gs, int64_t G, int64_t cnt, int64_t T,
+                                             int64_t t, int64_t* a0, int64_t* a1) {
+    const int64_t k = T - G;
+    int64_t js = 0, X = -1;
+    if (k > 0) {
+        int64_t lo = -1, hi = G - 1;   // surplus(lo) < k <= surplus(hi) = cnt - G
+        while (hi - lo > 1) {
+            const int64_t mid = (lo + hi) >> 1;
+            if ((int64_t)gs[mid + 1] - (mid + 1) >= k) hi = mid; else lo = mid;
+        }
+        js = hi;
+        X = k + js;
+        if (t < X) {
+            *a0 = t;
+            *a1 = t + 1;
+            return -1;
+        }
+    }
+    const int64_t g = k > 0 ? js + (t - X) : t;
+    *a0 = t == X ? X : (int64_t)gs[g];
+    *a1 = g + 1 < G ? (int64_t)gs[g + 1] : cnt;
+    return t == X ? -1 : g;
+}
+
+// Samples per step over the ranks, for the sample quota: a block takes 64 steps, its waves
+// every fourth rank.
+__global__ void __launch_bounds__(kBlock) cut_steps_kernel(OneArgs a) {
+    if (stage1_bad(a.st)) return;
+    const OneTarget tg = one_target(a);
+    if (tg.overflow) return;
+    __shared__ int64_t s_n[kBlock / kWave][kWave];
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    for (int64_t j0 = (int64_t)blockIdx.x * kWave; j0 < tg.T; j0 += (int64_t)gridDim.x * kWave) {
+        const int64_t j = j0 + lane;
+        int64_t n = 0;
+        if (j < tg.T) {
+            for (int r = w; r < a.W; r += kBlock / kWave) {
+                const int64_t cnt = a.off[r + 1] - a.off[r];
+                if (cnt == 0) continue;
+                int64_t a0, a1;
+                one_group(a.gs + a.off[r], a.groups[r], cnt, tg.T, tg.T - 1 - j, &a0, &a1);
+                n += a1 - a0;
+            }
+        }
+        s_n[w][lane] = n;
+        __syncthreads();
+        if (w == 0 && j < tg.T) {
+#pragma unroll
+            for (int i = 1; i < kBlock / kWave; ++i) n += s_n[i][lane];
+            a.steps[j] = n;
+        }
+        __syncthreads();
+    }
+}
+
+// The first step at which the emitted samples reach the quota, every rank's emitted rows
+// (lo: running sum over the ranks) and left-overs.  One block.
+__global__ void __launch_bounds__(kBlock) cut_kernel(OneArgs a, int64_t* __restrict__ left_off) {
+    if (stage1_bad(a.st)) return;
+    const OneTarget tg = one_target(a);
+    if (tg.overflow) return;
+    __shared__ int64_t s_cut;
+    if (threadIdx.x == 0) s_cut = tg.T;
+    __syncthreads();
+    int64_t carry = 0;
+    for (int64_t b = 0; b < tg.T; b += kBlock) {
+        const int64_t j = b + threadIdx.x;
+        const int64_t v = j < tg.T ? a.steps[j] : 0;
+        int64_t tot;
+        const int64_t ex = carry + block_excl_sum(v, &tot);
+        if (j < tg.T && ex < a.quota && ex + v >= a.quota) s_cut = j + 1;
+        carry += tot;
+        if (carry >= a.quota) break;   // uniform
+    }
+    __syncthreads();
+    const int64_t cut = s_cut;
+    I64Pair at{0, 0};
+    for (int b = 0; b < a.W; b += kBlock) {
+        const int r = b + threadIdx.x;
+        I64Pair v{0, 0};
+        if (r < a.W) {
+            const int64_t cnt = a.off[r + 1] - a.off[r];
+            int64_t q = 0, e;   // formation positions that stay
+            if (cut < tg.T && cnt > 0) one_group(a.gs + a.off[r], a.groups[r], cnt, tg.T, tg.T - cut, &q, &e);
+            v = I64Pair{cnt - q, q};
+        }
+        I64Pair tot;
+        const I64Pair ex = block_excl_sum(v, &tot);
+        if (r < a.W) {
+            a.lo[r] = at.a + ex.a;
+            left_off[r] = at.b + ex.b;
+        }
+        at += tot;
+    }
+    if (threadIdx.x == 0) {
+        a.lo[a.W] = at.a;
+        left_off[a.W] = at.b;
+        a.rs->cut = cut;
+        a.rs->quota_hit = at.a >= a.quota ? 1 : 0;
+    }
+}
+
+// Rows, longest length, tokens and row offset of every slot, one thread each.  A slot that is
+// a whole group takes its tokens from the prefixes at its start and at the next group's; a
+// piece of a split group longer than one row (one slot of a split rank) is summed by its
+// wave.  (Summing every slot's lengths, 64 lanes a slot, took 229 us on 64 x 262,144 samples:
+// the first slots of a rank hold thousands of its shortest samples, so a few waves read
+// half the lengths.)
+__global__ void __launch_bounds__(kBlock) slots_kernel(OneArgs a, int32_t* __restrict__ rows,
+                                                       int32_t* __restrict__ maxlen, int64_t* __restrict__ row_off,
+                                                       int64_t* __restrict__ tokens, double* __restrict__ approx) {
+#pragma clang fp contract(off)
+    if (stage1_bad(a.st)) return;
+    const OneTarget tg = one_target(a);
+    const int64_t S = a.nonjoin && !tg.overflow ? a.rs->cut : tg.T;
+    const int64_t K = (int64_t)a.W * S;
+    if (blockIdx.x == 0) {
+        int64_t splits = 0, changed = 0;
+        for (int r = threadIdx.x; r < a.W; r += kBlock) {
+            const int64_t G = a.groups[r];
+            if (G <= 0) continue;
+            splits += tg.T - G;
+            changed += G != tg.T;
+        }
+        splits = block_sum(splits);
+        changed = block_sum(changed);
+        if (threadIdx.x == 0) {
+            a.rs->T = tg.T;
+            a.rs->overflowed = tg.overflow ? 1 : 0;   // the host goes round by round
+            a.rs->splits = splits;
+            a.rs->second_gather = changed > 0 ? 1 : 0;
+            if (!a.nonjoin) a.rs->cut = S;
+        }
+    }
+    if (tg.overflow || K > a.slot_capacity) return;
+    const int64_t per = (K + gridDim.x - 1) / gridDim.x;
+    const int64_t k0 = (int64_t)blockIdx.x * per, k1 = k0 + per < K ? k0 + per : K;
+    const int lane = threadIdx.x & (kWave - 1);
+    int64_t cells = 0, real = 0;
+    for (int64_t b = k0; b < k1; b += kBlock) {   // uniform
+        const int64_t k = b + threadIdx.x;
+        const bool on = k < k1;
+        int64_t a0 = 0, a1 = 0, base = 0, cnt = 0, sum = 0;
+        int32_t ml = 0;
+        int r = 0;
+        bool piece = false;
+        if (on) {
+            r = (int)(k / S);
+            const int64_t j = k - (int64_t)r * S;
+            base = a.off[r];
+            cnt = a.off[r + 1] - base;
+        }
+        if (on && cnt > 0) {
+            const int64_t G = a.groups[r];
+            const int64_t g = one_group(a.gs + base, G, cnt, tg.T, tg.T - 1 - (k - (int64_t)r * S), &a0, &a1);
+            ml = a.slen[base + a0];
+            const int64_t* tp = a.tpre + (int64_t)r * a.per_rank;
+            if (g >= 0) {
+                const int64_t end = a1 < cnt ? tp[a1 / kRowTile] + a.gpre[base + g + 1]
+                                             : a.tok_off[base + cnt] - a.tok_off[base];
+                sum = end - (tp[a0 / kRowTile] + a.gpre[base + g]);
+            } else if (a1 - a0 == 1) {
+                sum = ml;
+            } else {
+                piece = true;
+            }
+        }
+        uint64_t need = __ballot(piece);
+        while (need) {   // uniform in the wave
+            const int src = __builtin_ctzll(need);
+            need &= need - 1;
+            const int64_t from = ::__shfl(base + a0, src, kWave), to = ::__shfl(base + a1, src, kWave);
+            int64_t part = 0;
+            for (int64_t q = from + lane; q < to; q += kWave) part += a.slen[q];
+            part = wave_last(wave_scan_dpp<OpAdd>(part));
+            if (lane == src) sum = part;
+        }
+        if (on) {
+            rows[k] = (int32_t)(a1 - a0);
+            maxlen[k] = ml;
+            tokens[k] = sum;
+            row_off[k] = a.lo[r] + (cnt - a1);
+            if (approx) {
+                double v = 0.0;
+                if (cnt > 0) {
+                    const double mean = (double)(a.tok_off[base + cnt] - a.tok_off[base]) / (double)cnt;
+                    v = (double)(a1 - a0) * mean;
+                }
+                approx[k] = v;
+            }
+            cells += (a1 - a0) * ml;
+            real += sum;
+        }
+    }
+    cells = block_sum(cells);
+    real = block_sum(real);
+    if (threadIdx.x == 0) a.part[blockIdx.x] = I64Pair{cells, real};
+}
+
+// Tile offsets of a range of slots after the ranges before it; the largest step; the totals
+// and, in join mode, the (empty) left-over offsets.
+__global__ void __launch_bounds__(kBlock) tiles_kernel(OneArgs a, const int32_t* __restrict__ rows,
+                                                       const int32_t* __restrict__ maxlen,
+                                                       int64_t* __restrict__ row_off, int64_t* __restrict__ tile_off,
+                                                       int64_t* __restrict__ left_off) {
+    if (stage1_bad(a.st) || a.rs->overflowed) return;
+    const int64_t S = a.rs->cut, K = (int64_t)a.W * S;
+    if (K > a.slot_capacity) return;
+    const int64_t per = (K + gridDim.x - 1) / gridDim.x;
+    const int64_t k0 = (int64_t)blockIdx.x * per, k1 = k0 + per < K ? k0 + per : K;
+    // the ranges before this block's, and all of them
+    I64Pair before{0, 0}, all{0, 0};
+    for (unsigned i = threadIdx.x; i < gridDim.x; i += kBlock) {
+        const I64Pair p = a.part[i];
+        all += p;
+        if (i < blockIdx.x) before += p;
+    }
+    before.a = block_sum(before.a);
+    all.a = block_sum(all.a);
+    all.b = block_sum(all.b);
+    int64_t carry = before.a;
+    for (int64_t b = k0; b < k1; b += kBlock) {
+        const int64_t k = b + threadIdx.x;
+        const int64_t v = k < k1 ? (int64_t)rows[k] * maxlen[k] : 0;
+        int64_t tot;
+        const int64_t ex = block_excl_sum(v, &tot);
+        if (k < k1) tile_off[k] = carry + ex;
+        carry += tot;
+    }
+    if (blockIdx.x == 0) {
+        const int64_t emitted = a.lo[a.W];
+        if (!a.nonjoin)
+            for (int r = threadIdx.x; r <= a.W; r += kBlock) left_off[r] = 0;
+        if (threadIdx.x == 0) {
+            tile_off[K] = all.a;
+            row_off[K] = emitted;
+            a.rs->emitted_total = emitted;
+            a.info->emitted = emitted;
+            a.info->padded_elems = all.a;
+            a.info->real_tokens = all.b;
+            a.info->pad_fraction = all.a > 0 ? 1.0 - (double)all.b / (double)all.a : 0.0;
+        }
+    }
+    // 64 steps at a time, a wave taking every fourth rank
+    __shared__ int64_t s_n[kBlock / kWave][kWave];
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    int64_t mx = 0;
+    for (int64_t j0 = (int64_t)blockIdx.x * kWave; j0 < S; j0 += (int64_t)gridDim.x * kWave) {
+        const int64_t j = j0 + lane;
+        int64_t n = 0;
+        if (j < S) {
+#pragma unroll 8
+            for (int r = w; r < a.W; r += kBlock / kWave) n += rows[(int64_t)r * S + j];
+        }
+        s_n[w][lane] = n;
+        __syncthreads();
+        if (w == 0) {
+#pragma unroll
+            for (int i = 1; i < kBlock / kWave; ++i) n += s_n[i][lane];
+            mx = n > mx ? n : mx;
+        }
+        __syncthreads();
+    }
+    if (w == 0) {
+        mx = wave_last(wave_scan_dpp<OpMax>(mx));
+        if (lane == 0 && mx) atomicMax((unsigned long long*)&a.rs->step_max, (unsigned long long)mx);
+    }
+}
+
+// Sample quota: the staged rows of rank r up to its share go to lo[r] on, its first formation
+// positions (the rows past the share) to the left-overs.  Blocks as in rows_kernel.
+__global__ void __launch_bounds__(kBlock) share_kernel(OneArgs a, const int64_t* __restrict__ left_off,
+                                                       int32_t* __restrict__ emit, int32_t* __restrict__ len,
+                                                       int64_t* __restrict__ ts, int32_t* __restrict__ left) {
+    if (stage1_bad(a.st) || a.rs->overflowed) return;
+    const int r = (int)(blockIdx.x / a.per_rank);
+    const int64_t base = a.off[r], nr = a.off[r + 1] - base;
+    const int64_t lo = a.lo[r], share = a.lo[r + 1] - lo, l0 = left_off[r];
+    const int64_t i0 = (int64_t)(blockIdx.x % a.per_rank) * kRowTile;
+#pragma unroll
+    for (int c = 0; c < kRowItems; ++c) {
+        const int64_t i = i0 + c * kBlock + threadIdx.x;
+        if (i < share) {
+            emit[lo + i] = a.emit[base + i];
+            len[lo + i] = a.len[base + i];
+            if (ts) ts[lo + i] = a.ts[base + i];
+        } else if (i < nr) {
+            left[l0 + (nr - 1 - i)] = a.emit[base + i];   // row i is formation position nr - 1 - i
+        }
+    }
 }
 
 struct RoundBuffers {
@@ -1182,7 +1725,7 @@ extern "C" int odb_align_groups(const odb_window_t* w, int64_t budget, const odb
     memset(h_info, 0, sizeof(*h_info));
 
     hipStream_t s = static_cast<hipStream_t>(stream);
-    ODB_TRY(upload_small(w, L, d_ws, cap, s));
+    ODB_TRY(upload_small(w, L, d_ws, cap, s, true));
     const int64_t* d_off = ws_at<int64_t>(d_ws, L.rank_off);
     const int64_t* d_cap = ws_at<int64_t>(d_ws, L.cap);
     RankState* d_ranks = ws_at<RankState>(d_ws, L.ranks);
@@ -1211,6 +1754,117 @@ extern "C" int odb_align_groups(const odb_window_t* w, int64_t budget, const odb
     int32_t* dst_len = nonjoin ? ws_at<int32_t>(d_ws, L.stage_len) : row_len;
     const int64_t gcap = (int64_t)num_cus() * kPlanBlocksPerCU;
     const unsigned gridn = grid_for(n, kBlock, gcap);
+
+    // ---- a window that aligns in one round
+    int64_t max_nr = 0, empty_ranks = 0, min_cap = LLONG_MAX;
+    for (int r = 0; r < W; ++r) {
+        const int64_t nr = w->rank_offsets[r + 1] - w->rank_offsets[r];
+        max_nr = std::max(max_nr, nr);
+        empty_ranks += nr == 0;
+        if (cap && cap[r] > 0) min_cap = std::min(min_cap, cap[r]);
+    }
+    const int64_t per_rank = (max_nr + kRowTile - 1) / kRowTile;
+    // XCD-affine random reads pay off when every XCD has a rank and a rank's offsets fit in its
+    // L2 with room to spare
+    const int xcd = W >= kXcds && max_nr * 8 <= (int64_t)2 << 20;
+    const int64_t row_blocks = (xcd ? (W + kXcds - 1) / kXcds * kXcds : W) * per_rank;
+    // a positive capacity below a rank's samples makes overflow likely, a sample-quota window
+    // with an empty rank stops before its first round, and ranks of very unequal sizes would
+    // leave most of the per-rank blocks without work (tpre has room for n of them): these go
+    // round by round
+    if (n > 0 && min_cap >= max_nr && !(nonjoin && empty_ranks > 0) && W * per_rank <= n &&
+        row_blocks <= 32 * ((n + kRowTile - 1) / kRowTile + W) && row_blocks < (1 << 23)) {
+        OneArgs a{};
+        a.W = W;
+        a.n = n;
+        a.nonjoin = nonjoin ? 1 : 0;
+        a.quota = params->quota;
+        a.slot_capacity = slot_capacity;
+        a.tok_off = w->d_token_offsets;
+        a.off = d_off;
+        a.order = d_order;
+        a.slen = d_sorted_len;
+        a.gidx = d_group_index;
+        a.groups = d_groups_per_rank;
+        a.gs = gstart;
+        a.gpre = stok;
+        a.tpre = reinterpret_cast<int64_t*>(sadj);
+        a.per_rank = (int)per_rank;
+        a.lo = nonjoin ? d_gbase : const_cast<int64_t*>(d_off);
+        a.steps = steps;
+        a.part = ws_at<I64Pair>(d_ws, L.cs);
+        a.rs = d_rs;
+        a.info = d_info;
+        a.st = st;
+        a.emit = dst;
+        a.len = dst_len;
+        a.ts = nonjoin && d_row_token_start ? ws_at<int64_t>(d_ws, L.row_ts) : d_row_token_start;
+        // one wave of slots each, up to kMaxRanges blocks (part holds n + 1 words, two a block)
+        const unsigned ranges = grid_for(n, 64, kMaxRanges);
+        hipLaunchKernelGGL(rows_kernel, dim3((unsigned)row_blocks), dim3(kBlock), 0, s, a, xcd);
+        ODB_LAUNCHED();
+        hipLaunchKernelGGL(rank_tiles_kernel, dim3(W), dim3(kBlock), 0, s, a);
+        ODB_LAUNCHED();
+        if (nonjoin) {
+            hipLaunchKernelGGL(cut_steps_kernel, dim3(grid_for(max_nr, kWave, kMaxRanges)), dim3(kBlock), 0, s, a);
+            ODB_LAUNCHED();
+            hipLaunchKernelGGL(cut_kernel, dim3(1), dim3(kBlock), 0, s, a, d_leftover_off);
+            ODB_LAUNCHED();
+        }
+        hipLaunchKernelGGL(slots_kernel, dim3(ranges), dim3(kBlock), 0, s, a, d_slot_rows, d_slot_maxlen, d_slot_row_off,
+                           d_slot_tokens, d_slot_tokens_approx);
+        ODB_LAUNCHED();
+        hipLaunchKernelGGL(tiles_kernel, dim3(ranges), dim3(kBlock), 0, s, a, (const int32_t*)d_slot_rows,
+                           (const int32_t*)d_slot_maxlen, d_slot_row_off, d_slot_tile_off, d_leftover_off);
+        ODB_LAUNCHED();
+        if (nonjoin) {
+            hipLaunchKernelGGL(share_kernel, dim3((unsigned)(W * per_rank)), dim3(kBlock), 0, s, a,
+                               (const int64_t*)d_leftover_off, d_emit_order, row_len, d_row_token_start, d_leftover);
+            ODB_LAUNCHED();
+        }
+        // every view is emitted or left over once, so the identities count over all views
+        if (w->d_identity) ODB_TRY(count_identities(w, L, d_ws, d_order, n, nullptr, 0, s));
+        HostState h;
+        ODB_TRY(read_state(L, d_ws, 0, &h, s));
+        if (h.st.err & (kErrOrder | kErrGroupIndex))
+            return set_error(ODB_E_INVALID_DATA,
+                             "stage-1 arrays do not describe this window (first inconsistent position %lld)",
+                             (long long)h.st.first_bad);
+        if (!h.rs.overflowed) {
+            const int64_t S = h.rs.cut, K = (int64_t)W * S;
+            h_info->steps = S;
+            h_info->rounds = 1;
+            h_info->stop_reason = nonjoin && h.rs.quota_hit ? ODB_STOP_QUOTA : ODB_STOP_DRAINED;
+            h_info->splits = h.rs.splits;
+            h_info->second_gather_rounds = h.rs.second_gather;
+            h_info->required_slot_capacity = K;
+            if (K > slot_capacity)
+                return set_error(ODB_E_CAPACITY, "plan needs %lld slots, capacity is %lld", (long long)K,
+                                 (long long)slot_capacity);
+            h_info->max_step_samples = h.rs.step_max;
+            h_info->emitted_samples = h.info.emitted;
+            h_info->leftover_samples = n - h.info.emitted;
+            h_info->real_tokens = h.info.real_tokens;
+            h_info->padded_elems = h.info.padded_elems;
+            h_info->missing_ids = h.info.missing_ids;
+            h_info->duplicate_ids = h.info.duplicate_ids;
+            h_info->pad_fraction = h.info.pad_fraction;
+            if (h.st.err & kErrLength)
+                return set_error(ODB_E_INVALID_DATA,
+                                 "sample %lld has a length outside [1, 2^31) or a negative token offset",
+                                 (long long)h.st.first_bad_len);
+            if (h.st.err & kErrSortedLen)
+                return set_error(ODB_E_INVALID_DATA,
+                                 "stage-1 arrays do not describe this window (sorted length of sample %lld is not its "
+                                 "CSR length)", (long long)h.st.first_bad_csr);
+            if (h.st.err & kErrIdentity)
+                return set_error(ODB_E_INVALID_DATA, "identity map holds a value outside [0, num_identities)");
+            if (h.st.err & kErrInternal) return set_error(ODB_E_INTERNAL, "internal inconsistency in the aligned plan");
+            return ODB_OK;
+        }
+        // some rank overflows: start over, round by round
+        ODB_TRY(upload_small(w, L, d_ws, cap, s));
+    }
 
     hipLaunchKernelGGL(round0_ranks_kernel, dim3(1), dim3(kBlock), 0, s, d_off, d_groups_per_rank, W, d_ranks,
                        d_gbase, st, d_rs, d_info);
@@ -1343,11 +1997,6 @@ extern "C" int odb_align_groups(const odb_window_t* w, int64_t budget, const odb
     }
     const int64_t nemit = hrs.emitted_total;
     if (nemit > 0 && K > 0) {
-        // rank-per-XCD gathers pay off when every XCD has a rank and a rank's offsets fit
-        // in its L2 with room to spare
-        int64_t max_nr = 0;
-        for (int r = 0; r < W; ++r) max_nr = std::max(max_nr, w->rank_offsets[r + 1] - w->rank_offsets[r]);
-        const int xcd = W >= kXcds && max_nr * 8 <= (int64_t)2 << 20;
         const unsigned grid = xcd ? (unsigned)(kXcds * std::max<int64_t>(1, std::min<int64_t>(
                                         (int64_t)num_cus() * 2 / kXcds, (max_nr + kBlock - 1) / kBlock)))
                                   : grid_for(nemit, kBlock, gcap);

@@ -134,8 +134,8 @@ int check_workspace(const odb_window_t* w, void* d_ws, size_t ws_bytes, Layout* 
 // Small host arrays reach the device as kernel arguments, kValuesPerLaunch values per
 // launch: no host-to-device copy (which, from pageable memory, may wait for the stream)
 // and nothing a graph capture could not record.
-constexpr int kValuesPerLaunch = 64;
-struct Values64 {
+constexpr int kValuesPerLaunch = 128;
+struct Values {
     int64_t v[kValuesPerLaunch];
 };
 
@@ -143,7 +143,8 @@ struct Values64 {
 // resets the status word.  The collate's error word is left alone: odb_collate clears it
 // when it starts and odb_collate_status when it has read it, so a plan call made on the
 // same workspace in between does not erase a collate error.
-__global__ void store_values_kernel(Values64 vals, int64_t* dst, int count, DevStatus* st) {
+__global__ void store_values_kernel(Values vals, int64_t* dst, int count, DevStatus* st, RoundState* rs,
+                                    DevInfo* info) {
     const int t = threadIdx.x;
     if (t < count) dst[t] = vals.v[t];
     if (st) {
@@ -151,31 +152,38 @@ __global__ void store_values_kernel(Values64 vals, int64_t* dst, int count, DevS
             st->err = 0;
             st->first_bad = 0x7FFFFFFFFFFFFFFFll;
             st->first_bad_len = 0x7FFFFFFFFFFFFFFFll;
+            st->first_bad_csr = 0x7FFFFFFFFFFFFFFFll;
             st->min_len = 0xFFFFFFFFu;
             st->max_len = 0;
         }
         if (t < kMaxJumpRounds) st->jump_changed[t] = 0;
     }
+    if (t == 0 && rs) *rs = RoundState{};
+    if (t == 0 && info) *info = DevInfo{};
 }
 
-int store_values(const int64_t* src, int64_t count, int64_t* dst, DevStatus* st, hipStream_t s) {
+int store_values(const int64_t* src, int64_t count, int64_t* dst, DevStatus* st, hipStream_t s, RoundState* rs,
+                 DevInfo* info) {
     int64_t a = 0;
     do {
-        Values64 v{};
+        Values v{};
         const int64_t left = count - a;
         const int c = (int)(left < kValuesPerLaunch ? (left > 0 ? left : 0) : kValuesPerLaunch);
         for (int i = 0; i < c; ++i) v.v[i] = src[a + i];
         hipLaunchKernelGGL(store_values_kernel, dim3(1), dim3(kValuesPerLaunch), 0, s, v, dst + a, c,
-                           a == 0 ? st : (DevStatus*)nullptr);
+                           a == 0 ? st : (DevStatus*)nullptr, a == 0 ? rs : (RoundState*)nullptr,
+                           a == 0 ? info : (DevInfo*)nullptr);
         ODB_LAUNCHED();
         a += kValuesPerLaunch;
     } while (a < count);
     return ODB_OK;
 }
 
-int upload_small(const odb_window_t* w, const Layout& L, void* ws, const int64_t* cap, hipStream_t s) {
+int upload_small(const odb_window_t* w, const Layout& L, void* ws, const int64_t* cap, hipStream_t s, bool rounds) {
     const int W = w->num_ranks;
-    ODB_TRY(store_values(w->rank_offsets, W + 1, ws_at<int64_t>(ws, L.rank_off), ws_at<DevStatus>(ws, L.status), s));
+    ODB_TRY(store_values(w->rank_offsets, W + 1, ws_at<int64_t>(ws, L.rank_off), ws_at<DevStatus>(ws, L.status), s,
+                         rounds ? ws_at<RoundState>(ws, L.round) : nullptr,
+                         rounds ? ws_at<DevInfo>(ws, L.info) : nullptr));
     if (cap) ODB_TRY(store_values(cap, W, ws_at<int64_t>(ws, L.cap), nullptr, s));
     return ODB_OK;
 }

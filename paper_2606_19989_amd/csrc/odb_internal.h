@@ -61,6 +61,7 @@ struct DevStatus {
     int32_t collate_err;
     int64_t first_bad;            // smallest offending sample index (atomicMin)
     int64_t first_bad_len;        // smallest sample with an invalid CSR length found by alignment
+    int64_t first_bad_csr;        // smallest sample whose stage-1 length is not its CSR length
     uint32_t min_len;
     uint32_t max_len;
     int32_t jump_changed[kMaxJumpRounds];
@@ -98,6 +99,7 @@ struct RoundState {
     int64_t total_groups;    // groups over all ranks this round
     int64_t leftover_total;  // samples back in buffers after this round
     int64_t second_gather;   // rounds in which some active rank had G_r != T (all rounds)
+    int64_t overflowed;      // a one-round alignment met a rank that overflows
 };
 
 // Final summary assembled on the device (mirrors odb_plan_info_t's counters).
@@ -138,13 +140,15 @@ inline T* ws_at(void* ws, size_t off) {
 int check_window(const odb_window_t* w);
 int check_workspace(const odb_window_t* w, void* d_ws, size_t ws_bytes, Layout* L);
 
-// Uploads rank offsets (and optionally capacities) and clears the status word.
+// Uploads rank offsets (and optionally capacities) and clears the status word and, with
+// `rounds`, the round state and the summary.
 int upload_small(const odb_window_t* w, const Layout& L, void* d_ws, const int64_t* cap,
-                 hipStream_t s);
+                 hipStream_t s, bool rounds = false);
 
-// Stores `count` host values at dst through kernel arguments; with `st`, also resets the
-// status word.
-int store_values(const int64_t* src, int64_t count, int64_t* dst, DevStatus* st, hipStream_t s);
+// Stores `count` host values at dst through kernel arguments; also resets the status word,
+// the round state and the summary where they are given.
+int store_values(const int64_t* src, int64_t count, int64_t* dst, DevStatus* st, hipStream_t s,
+                 RoundState* rs = nullptr, DevInfo* info = nullptr);
 
 // Host copy of the status word, round state, summary and per-rank state, read with one
 // device-to-host copy (the workspace keeps them next to each other) and one

@@ -1033,6 +1033,7 @@ __global__ void bulk_init_kernel(BulkArgs b, DevStatus* st) {
         st->err = 0;
         st->first_bad = 0x7FFFFFFFFFFFFFFFll;
         st->first_bad_len = 0x7FFFFFFFFFFFFFFFll;
+        st->first_bad_csr = 0x7FFFFFFFFFFFFFFFll;
         st->min_len = 0xFFFFFFFFu;
         st->max_len = 0;
     }

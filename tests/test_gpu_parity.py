@@ -590,3 +590,52 @@ def test_two_stream_schedule():
     compare_collate_sampled(w, outs, ref)
     collate_properties(outs, ref)
     compare_collate_by_rank(w, outs, ref, toks)
+
+
+def one_round_windows():
+    """Windows aligned in one round, and the edges of that path: ranks at the edges of a
+    block's tile (1,024 positions, 4 per thread), ranks dealt to the XCDs (8 and more) or not,
+    empty ranks, one slot per sample and one slot per rank (lanes per slot 1 to 64), more
+    slot ranges than blocks, splits with X = 0 and at the last group, quotas inside and at a
+    step's end, an identity map, and windows that turn out to overflow and start over."""
+    rng = np.random.default_rng(91)
+    U = lambda lo, hi, n: rng.integers(lo, hi, size=n)
+    win = synth.window_from_ranks
+    out = []
+    for n in (1, 3, 4, 5, 1023, 1024, 1025, 2049):
+        out.append(win(f"tile_{n}", [U(50, 60, n), U(50, 60, max(n - 1, 1))], 240))
+    out.append(win("xcd_ranks", [U(20, 900, 1500 + 7 * r) for r in range(11)], 8192))
+    out.append(win("empty_ranks", [U(5, 50, 400), U(1, 2, 0), U(5, 50, 399), U(1, 2, 0)], 300))
+    out.append(win("singletons", [U(100, 900, 3000) for _ in range(9)], 100))
+    out.append(win("one_group", [U(1, 9, 5000), U(1, 9, 4000)], 1 << 20))
+    out.append(win("few_rows", [U(30, 60, 70000)], 130))
+    out.append(win("deep_split", [U(1000, 1001, 900), U(1, 3, 900)], 1000))
+    out.append(win("split_last", [U(10, 11, 40), np.concatenate([U(90, 91, 3), U(1, 2, 37)])], 100))
+    out.append(win("overflow_restart", [U(500, 900, 300), U(10, 20, 7)], 1000))
+    out.append(win("very_ragged", [U(10, 400, 60000)] + [U(10, 400, 200 + r) for r in range(70)], 2000))
+    for q in (1, 2, 700, 2999, 3000, 5000):
+        out.append(win(f"quota_{q}", [U(10, 700, 1000 + 13 * r) for r in range(3)], 4096, mode="nonjoin", quota=q))
+    # equal lengths: every step but the first holds the same samples, so the quota can fall on
+    # a step's end
+    for q in (2, 3 * 16 + 2, 3 * 16 + 3):
+        out.append(win(f"quota_even_{q}", [np.full(333, 100), np.full(333, 100)], 800, mode="nonjoin", quota=q))
+    out.append(win("quota_overflow", [U(500, 900, 300), U(10, 20, 7)], 1000, mode="nonjoin", quota=250))
+    out.append(win("quota_empty_rank", [U(10, 20, 100), U(1, 2, 0)], 100, mode="nonjoin", quota=50))
+    for mode, q in (("join", 0), ("nonjoin", 900)):
+        ident = rng.permutation(1990)
+        ident = np.concatenate([ident, ident[:10]]).astype(np.int64)
+        out.append(win(f"identities_{mode}", [U(10, 400, 500) for _ in range(4)], 2048, mode=mode, quota=q,
+                       identity=ident, num_identities=1990))
+    out.append(win("capacity_free", [U(10, 300, 400), U(10, 300, 500)], 2000, capacity=np.array([500, 0])))
+    return out
+
+
+@pytest.mark.parametrize("idx", range(len(one_round_windows())))
+def test_one_round_windows(idx):
+    w = one_round_windows()[idx]
+    log(f"one round: {w.name}")
+    ref = oracle.plan_window(w)
+    pipe, outs = run_gpu(w, pad_id=idx)
+    compare_plan(w, pipe, ref)
+    compare_loss_weights(pipe, ref)
+    compare_collate_full(w, outs, ref, pad_id=idx)
