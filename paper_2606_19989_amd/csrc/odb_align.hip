@@ -1237,8 +1237,14 @@ __global__ void __launch_bounds__(kBlock) rows_kernel(OneArgs a, int xcd) {
             g[i] = a.gidx[p];
         }
     }
-    const int64_t pp = q0 > 0 && m > 0 ? p0 - 1 : base;   // the position before, if the rank has one
-    int32_t pid = a.order[pp], pl = a.slen[pp], pg = a.gidx[pp];
+    // the position before the thread's first: the lane below's last (full by then), or a load
+    int32_t pid = ::__shfl_up(id[kRowItems - 1], 1, kWave), pl = ::__shfl_up(l[kRowItems - 1], 1, kWave),
+            pg = ::__shfl_up(g[kRowItems - 1], 1, kWave);
+    if ((threadIdx.x & (kWave - 1)) == 0 && q0 > 0 && m > 0) {
+        pid = a.order[p0 - 1];
+        pl = a.slen[p0 - 1];
+        pg = a.gidx[p0 - 1];
+    }
     int64_t t0[kRowItems], t1[kRowItems];
 #pragma unroll
     for (int i = 0; i < kRowItems; ++i) {

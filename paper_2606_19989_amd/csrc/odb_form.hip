@@ -48,6 +48,12 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid, int dbit
     return peers;
 }
 
+// Lengths, their validity and the window's shortest and longest.  Every block ends with two
+// atomics on the same two words, ~10 ns each one after the other: 2,048 blocks spent 50 us on
+// them whatever the window's size (8 x 65,536 samples: 50 us, now XX; 64 x 262,144: 67, now YY).
+constexpr int kLengthsDeep = 8;
+constexpr int kLengthsBlocksPerCU = 2;
+
 __global__ void __launch_bounds__(kBlock) lengths_kernel(const int64_t* __restrict__ tok_off, int64_t n,
                                                          int32_t* __restrict__ len, DevStatus* st) {
     uint32_t lmin = 0xFFFFFFFFu, lmax = 0;
@@ -63,18 +69,18 @@ __global__ void __launch_bounds__(kBlock) lengths_kernel(const int64_t* __restri
         lmin = (uint32_t)l < lmin ? (uint32_t)l : lmin;
         lmax = (uint32_t)l > lmax ? (uint32_t)l : lmax;
     };
-    // four grid-stride iterations at a time, their loads issued together: with the grid at
-    // full occupancy, one load in flight per lane leaves the kernel latency bound
+    // kLengthsDeep grid-stride iterations at a time, their loads issued together: the grid is
+    // two blocks per compute unit, so the loads in flight come from depth
     int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (; p + 3 * stride < n; p += 4 * stride) {
-        int64_t a[4], b[4];
+    for (; p + (kLengthsDeep - 1) * stride < n; p += kLengthsDeep * stride) {
+        int64_t a[kLengthsDeep], b[kLengthsDeep];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < kLengthsDeep; ++k) {
             a[k] = tok_off[p + k * stride];
             b[k] = tok_off[p + k * stride + 1];
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) one(p + k * stride, a[k], b[k]);
+        for (int k = 0; k < kLengthsDeep; ++k) one(p + k * stride, a[k], b[k]);
     }
     for (; p < n; p += stride) one(p, tok_off[p], tok_off[p + 1]);
     // one pair of atomics per block: lanes -> waves (shuffles) -> block (LDS)
@@ -374,174 +380,39 @@ __global__ void __launch_bounds__(kBlock) jump_kernel(const int32_t* __restrict_
     if (__ballot(changed) && (threadIdx.x & (kWave - 1)) == 0) st->jump_changed[round] = 1;
 }
 
-// ---- run-table chain walk
-// Positions q >= 1 of a rank (q < cnt_r) fall into runs of equal step: q starts a run when
-// q = 1 or its step B(l[q - 1]) differs from the step of q - 1.  The chain's group starts
-// are q = 0 and, in run k, the positions c_k, c_k + b_k, ... of the run, where b_k is the
-// run's step and c_k its first chain position (none if the chain jumps over the run).  The
-// group index of a position is the number of group starts at or before it, minus one.
-// Rank r's run table (run k: start, step, first chain position, group starts before the
-// run) sits at positions off[r] + k of four position-indexed arrays (a rank has fewer runs
-// than positions).  Work is split into the sort's tiles (at most kSortTile positions of
-// one rank).
-constexpr int kRunCap = 4096;   // runs per rank held in LDS by run_chase_kernel
+// ---- chain walk over runs of equal step
+// Positions q >= 1 of a rank (q < cnt_r) fall into runs of equal step b = B(l[q - 1]); the
+// lengths are sorted, so the step never decreases along the rank.  The chain's group starts
+// are q = 0 and, in run k, the positions c_k, c_k + b_k, ... of the run, where c_k is the
+// chain's first position in it (none if the chain jumps over the run).  The group index of a
+// position is the number of group starts at or before it, minus one: g_k group starts before
+// run k (position 0 not counted), plus (q - c_k) / b_k + 1 once q >= c_k.
+//
+// One block of kChainThreads per rank:
+//   runs    the distinct steps are known without looking at the samples: the values
+//           b = B(longest) .. sqrt(budget), and for each length l below budget / sqrt(budget)
+//           the step budget / l, at most 2 sqrt(budget) + 2 or the length range; a run starts
+//           at the first length at or below a threshold, found by one binary search per
+//           candidate (a sample of 1,024 lengths in LDS, then the samples between two of them).
+//           Where a rank has fewer samples than there may be steps, its samples are looked at
+//           instead
+//   chase   one thread follows the chain from run to run: the only serial part, a
+//           multiplication by the step's reciprocal per run (computed by all threads before)
+//   counts  group starts per run and their prefix, by all threads
+// The group index of every position follows in closed form: in the same block for ranks of at
+// most kRankBlockMax samples, else by chain_index_kernel over all tiles.
+//
+// Bound by the chase: ~30 ns per run.  64 ranks x 262,144 samples, ~700 runs per rank: the
+// run table from a count, a scan and a write pass over all samples took 105 us and a chase that
+// divides 83 us; XX us here, and the group indices YY instead of 71 us (nothing is read per
+// sample any more).
+constexpr int kChainThreads = 1024;
+constexpr int kChainWaves = kChainThreads / kWave;
+constexpr int kRunCap = 4096;   // runs per rank
 
-// Whether rank-local position q (global p) starts a run.
-__device__ __forceinline__ bool run_start_at(const int32_t* __restrict__ slen, int64_t p, int64_t q, int64_t cnt,
-                                             int64_t budget) {
-    if (q < 1 || q >= cnt) return false;
-    return q == 1 || batch_size(budget, slen[p - 1]) != batch_size(budget, slen[p - 2]);
-}
-
-struct RunTile {
-    int r;
-    int64_t base;    // off[r]
-    int64_t start;   // first position of the tile
-    int32_t count;   // positions of the tile
-    int64_t cnt;     // live positions of the rank
-};
-
-__device__ __forceinline__ RunTile run_tile(const int64_t* __restrict__ off, const int64_t* __restrict__ tile_first,
-                                            int W, const RankState* __restrict__ ranks, int64_t b) {
-    RunTile t;
-    t.r = rank_of(tile_first, W, b);
-    t.base = off[t.r];
-    t.start = t.base + (b - tile_first[t.r]) * kSortTile;
-    const int64_t left = off[t.r + 1] - t.start;
-    t.count = (int32_t)(left < kSortTile ? left : kSortTile);
-    t.cnt = ranks[t.r].cnt;
-    return t;
-}
-
-// Run starts per tile.
-__global__ void __launch_bounds__(kBlock) run_count_kernel(const int64_t* __restrict__ off,
-                                                           const int64_t* __restrict__ tile_first, int W,
-                                                           const RankState* __restrict__ ranks,
-                                                           const int32_t* __restrict__ slen, int64_t budget,
-                                                           uint32_t* __restrict__ tile_runs) {
-    const RunTile t = run_tile(off, tile_first, W, ranks, blockIdx.x);
-    uint32_t c = 0;
-    for (int i = threadIdx.x; i < t.count; i += kBlock)
-        c += run_start_at(slen, t.start + i, t.start + i - t.base, t.cnt, budget);
-    c = block_sum(c);
-    if (threadIdx.x == 0) tile_runs[blockIdx.x] = c;
-}
-
-// One block per rank: the rank's tile counts become the index of each tile's first run
-// (in place), and rank_runs[r] the rank's number of runs.
-__global__ void __launch_bounds__(kBlock) run_tile_scan_kernel(const int64_t* __restrict__ tile_first,
-                                                               uint32_t* __restrict__ tile_runs,
-                                                               uint32_t* __restrict__ rank_runs) {
-    const int r = blockIdx.x;
-    const int64_t t0 = tile_first[r], t1 = tile_first[r + 1];
-    uint32_t carry = 0;
-    for (int64_t b = t0; b < t1; b += kBlock) {
-        const int64_t t = b + threadIdx.x;
-        const uint32_t v = t < t1 ? tile_runs[t] : 0u;
-        uint32_t tot;
-        const uint32_t ex = block_excl_sum(v, &tot);
-        if (t < t1) tile_runs[t] = carry + ex;
-        carry += tot;
-    }
-    if (threadIdx.x == 0) rank_runs[r] = carry;
-}
-
-// The run table's starts and steps, written by the tile holding each run start.  A tile's
-// positions are taken in rounds of kBlock consecutive positions, so a block scan of the
-// round's flags numbers its run starts in position order.
-__global__ void __launch_bounds__(kBlock) run_write_kernel(const int64_t* __restrict__ off,
-                                                           const int64_t* __restrict__ tile_first, int W,
-                                                           const RankState* __restrict__ ranks,
-                                                           const int32_t* __restrict__ slen, int64_t budget,
-                                                           const uint32_t* __restrict__ tile_runs,
-                                                           int32_t* __restrict__ run_start,
-                                                           int32_t* __restrict__ run_b) {
-    const RunTile t = run_tile(off, tile_first, W, ranks, blockIdx.x);
-    uint32_t k0 = tile_runs[blockIdx.x];
-    for (int i0 = 0; i0 < t.count; i0 += kBlock) {
-        const int i = i0 + threadIdx.x;
-        const int64_t p = t.start + i;
-        const bool f = i < t.count && run_start_at(slen, p, p - t.base, t.cnt, budget);
-        uint32_t tot;
-        const uint32_t ex = block_excl_sum((uint32_t)f, &tot);
-        if (f) {
-            const int64_t k = t.base + k0 + ex;
-            const int64_t b = batch_size(budget, slen[p - 1]);
-            run_start[k] = (int32_t)(p - t.base);
-            run_b[k] = (int32_t)(b < INT32_MAX ? b : INT32_MAX);   // any step >= 2^31 leaves the rank
-        }
-        k0 += tot;
-    }
-}
-
-// One block per rank: thread 0 walks the chain run by run and records for every run the
-// first chain position (INT32_MAX if the chain skips the run) and the group starts before
-// the run; G_r is the rank's number of group starts.  Positions and steps stay below 2^31
-// (larger steps are stored as INT32_MAX), so the walk runs in 32-bit integers; the table
-// and its results sit in LDS when they fit.
-__global__ void __launch_bounds__(kBlock) run_chase_kernel(const int64_t* __restrict__ off, RankState* ranks,
-                                                           const uint32_t* __restrict__ rank_runs,
-                                                           const int32_t* __restrict__ run_start,
-                                                           const int32_t* __restrict__ run_b,
-                                                           int32_t* __restrict__ run_c, int32_t* __restrict__ run_g) {
-    __shared__ uint32_t ls[kRunCap + 1], lb[kRunCap], lc[kRunCap], lg[kRunCap];
-    const int r = blockIdx.x;
-    const int64_t base = off[r];
-    const int64_t c = ranks[r].cnt;
-    if (c < 2) {   // no position >= 1, no run: position 0 (if any) is the only group start
-        if (threadIdx.x == 0) ranks[r].G = c;
-        return;
-    }
-    const int64_t R = rank_runs[r];
-    if (R <= kRunCap) {
-        for (int64_t i = threadIdx.x; i < R; i += blockDim.x) {
-            ls[i] = (uint32_t)run_start[base + i];
-            lb[i] = (uint32_t)run_b[base + i];
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            ls[R] = (uint32_t)c;
-            uint32_t cur = 1;     // next(0) = 1: the second group starts at position 1
-            uint32_t marks = 1;   // position 0
-#pragma unroll 4
-            for (int i = 0; i < (int)R; ++i) {
-                const uint32_t e = ls[i + 1], b = lb[i];
-                const bool hit = cur < e;
-                lc[i] = hit ? cur : (uint32_t)INT32_MAX;
-                lg[i] = marks;
-                // chain positions cur, cur + b, ... below e; the next one is >= e
-                const uint32_t k = hit ? (e - cur + b - 1) / b : 0u;
-                cur += k * b;
-                marks += k;
-            }
-            ranks[r].G = marks;
-        }
-        __syncthreads();
-        for (int64_t i = threadIdx.x; i < R; i += blockDim.x) {
-            run_c[base + i] = (int32_t)lc[i];
-            run_g[base + i] = (int32_t)lg[i];
-        }
-        return;
-    }
-    if (threadIdx.x != 0) return;
-    uint32_t cur = 1, marks = 1;
-    for (int64_t i = 0; i < R; ++i) {
-        const uint32_t e = (uint32_t)(i + 1 < R ? run_start[base + i + 1] : c);
-        const uint32_t b = (uint32_t)run_b[base + i];
-        const bool hit = cur < e;
-        run_c[base + i] = hit ? (int32_t)cur : INT32_MAX;
-        run_g[base + i] = (int32_t)marks;
-        const uint32_t k = hit ? (e - cur + b - 1) / b : 0u;
-        cur += k * b;
-        marks += k;
-    }
-    ranks[r].G = marks;
-}
-
-// One block: every rank's first global group id (exclusive sum of G_r), the group count
-// per rank for the caller, and the total in gbase[W].
-__global__ void __launch_bounds__(kBlock) rank_groups_kernel(RankState* ranks, int W, int64_t* __restrict__ gbase,
-                                                             int32_t* __restrict__ groups_out) {
+// One block: every rank's first global group id (exclusive sum of G_r) and the total in
+// gbase[W].
+__global__ void __launch_bounds__(kBlock) rank_groups_kernel(RankState* ranks, int W, int64_t* __restrict__ gbase) {
     int64_t carry = 0;
     for (int b = 0; b < W; b += kBlock) {
         const int r = b + threadIdx.x;
@@ -551,60 +422,10 @@ __global__ void __launch_bounds__(kBlock) rank_groups_kernel(RankState* ranks, i
         if (r < W) {
             ranks[r].gbase = carry + ex;
             gbase[r] = carry + ex;
-            if (groups_out) groups_out[r] = (int32_t)G;
         }
         carry += tot;
     }
     if (threadIdx.x == 0) gbase[W] = carry;
-}
-
-// Group index of every live position and the global position of every group start, from
-// the run table: position q of run k is in the group that starts at the last chain
-// position of the run at or before q, or, before c_k, in the last group started before
-// the run.
-__global__ void __launch_bounds__(kBlock) run_gidx_kernel(const int64_t* __restrict__ off,
-                                                          const int64_t* __restrict__ tile_first, int W,
-                                                          const RankState* __restrict__ ranks,
-                                                          const int32_t* __restrict__ slen, int64_t budget,
-                                                          const uint32_t* __restrict__ tile_runs,
-                                                          const int32_t* __restrict__ run_b,
-                                                          const int32_t* __restrict__ run_c,
-                                                          const int32_t* __restrict__ run_g,
-                                                          int32_t* __restrict__ gidx, int32_t* __restrict__ gstart) {
-    const RunTile t = run_tile(off, tile_first, W, ranks, blockIdx.x);
-    const int64_t gb = ranks[t.r].gbase;
-    // run starts before the current position in this rank, the current position included
-    uint32_t k0 = tile_runs[blockIdx.x];
-    for (int i0 = 0; i0 < t.count; i0 += kBlock) {
-        const int i = i0 + threadIdx.x;
-        const int64_t p = t.start + i;
-        const int64_t q = p - t.base;
-        const bool live = i < t.count && q < t.cnt;
-        const bool f = live && run_start_at(slen, p, q, t.cnt, budget);
-        uint32_t tot;
-        const uint32_t ex = block_excl_sum((uint32_t)f, &tot);
-        if (live) {
-            int64_t g = 0;
-            bool mark = true;
-            if (q > 0) {
-                const int64_t k = t.base + k0 + ex + (f ? 1 : 0) - 1;   // q's run
-                const uint32_t c = (uint32_t)run_c[k], b = (uint32_t)run_b[k];
-                const int64_t G = run_g[k];
-                if ((uint32_t)q >= c) {
-                    const uint32_t d = (uint32_t)q - c;
-                    const uint32_t m = d / b;
-                    g = G + m;
-                    mark = d - m * b == 0;
-                } else {
-                    g = G - 1;
-                    mark = false;
-                }
-            }
-            gidx[p] = (int32_t)g;
-            if (mark) gstart[gb + g] = (int32_t)p;
-        }
-        k0 += tot;
-    }
 }
 
 __global__ void init_jump_flags(DevStatus* st) {
@@ -667,13 +488,12 @@ __global__ void groups_kernel(const int32_t* __restrict__ incl, const int64_t* _
 // ---- one block per rank
 // When every rank holds at most kRankBlockMax samples, each rank is grouped by one
 // 1024-thread block in two launches, with no host synchronisation: rank_sort_kernel (lengths, validity, stable LSD
-// radix sort on byte digits of the length) and rank_walk_kernel (the group chain over the
+// radix sort on byte digits of the length) and chain_kernel (the group chain over the
 // runs of equal batch size, and the group index of every position in closed form).
 constexpr int kRankThreads = 1024;
 constexpr int kRankWaves = kRankThreads / kWave;
 constexpr int kRankItems = 4;                     // lengths a thread loads at once in the first pass
 constexpr int kRankGroup = 4;                     // rounds of a pass whose items are loaded together
-constexpr int kRankRunCap = 3840;                 // runs of equal batch size a rank may have
 // Samples of the largest rank grouped this way.  A block's pass over its rank is bound by
 // the issue rate of its one compute unit (every round of 1024 items costs each of its 16
 // waves a few hundred instructions: ~2.7 us per round on MI355X), so larger ranks go to the
@@ -982,137 +802,337 @@ __device__ __forceinline__ void chunk_run_starts(const int32_t* __restrict__ sle
     }
 }
 
-// Group chain of rank r from its sorted lengths.  Positions q >= 1 fall into runs of equal
-// step B(l[q-1]) (the lengths are sorted, so the step never decreases along the rank).
-// Inside a run of step b the chain advances by b, so one thread walks the runs and records
-// each run's first chain position c; then every position's group index follows in closed
-// form: the chain positions before its run, plus those of its run up to it.
-__global__ void __launch_bounds__(kRankThreads) rank_walk_kernel(const int64_t* __restrict__ off,
-                                                                 const int32_t* __restrict__ slen, int64_t budget,
-                                                                 int32_t* __restrict__ gidx,
-                                                                 int32_t* __restrict__ groups_out, DevStatus* st) {
-    __shared__ uint32_t s_start[kRankRunCap + 1], s_b[kRankRunCap], s_c[kRankRunCap], s_gb[kRankRunCap];
-    const int r = blockIdx.x;
-    const int64_t base = off[r];
-    const int cnt = (int)(off[r + 1] - base);
+// Exclusive scan of v over the block (kChainThreads threads); *total receives the sum.
+__device__ __forceinline__ uint32_t chain_scan(uint32_t v, uint32_t* total) {
+    __shared__ uint32_t s_w[kChainWaves];
     const int t = threadIdx.x;
-    if (cnt <= 1) {
-        if (t == 0) {
-            if (cnt == 1) gidx[base] = 0;
-            groups_out[r] = cnt;
-        }
-        return;
-    }
-    // run starts: every thread checks a chunk of positions [1, cnt); the step is monotone, so
-    // a chunk whose first position and last position have the step of the position before
-    // it holds no run start
-    const int span = cnt - 1;
-    const int per = (span + kRankThreads - 1) / kRankThreads;
-    const int lo = 1 + t * per;
-    const int hi = lo + per < cnt ? lo + per : cnt;
-    const bool busy = lo < hi && (lo == 1 || step_of(slen[base + lo - 2], budget) !=
-                                                 step_of(slen[base + hi - 2], budget));
-    uint32_t mine = 0;
-    if (busy) chunk_run_starts(slen, base, lo, hi, budget, [&](int, uint32_t) { ++mine; });
-    // exclusive scan of the per-thread counts over the block
-    __shared__ uint32_t s_wsum[kRankWaves];
-    __shared__ uint32_t s_total;
-    uint32_t inc = wave_scan_dpp<OpAdd>(mine);
-    if ((t & (kWave - 1)) == kWave - 1) s_wsum[t / kWave] = inc;
+    const uint32_t inc = wave_scan_dpp<OpAdd>(v);
+    if ((t & (kWave - 1)) == kWave - 1) s_w[t / kWave] = inc;
     __syncthreads();
     uint32_t pre = 0, tot = 0;
 #pragma unroll
-    for (int i = 0; i < kRankWaves; ++i) {
-        pre += i < t / kWave ? s_wsum[i] : 0u;
-        tot += s_wsum[i];
+    for (int i = 0; i < kChainWaves; ++i) {
+        const uint32_t x = s_w[i];
+        pre += i < t / kWave ? x : 0u;
+        tot += x;
     }
-    const uint32_t at0 = pre + inc - mine;
-    if (tot > (uint32_t)kRankRunCap) {
-        // more runs than the table holds (the host picks this path only when that cannot
-        // happen): report, and leave the rank without groups
+    __syncthreads();
+    *total = tot;
+    return pre + inc - v;
+}
+
+// The run table of a rank longer than one block's share, for chain_index_kernel: rank r's run
+// k at position off[r] + k of four position-indexed arrays, and the run that holds the first
+// position of every sort tile.
+struct RunTable {
+    int32_t* start;
+    int32_t* step;
+    int32_t* first;    // c_k (INT32_MAX if the chain jumps over the run)
+    int32_t* before;   // g_k
+    uint32_t* tile;    // [sort tiles]
+    uint32_t* runs;    // [W]
+};
+
+// kIndex: write the group indices here (short ranks); otherwise leave the run table.
+// sq = floor(sqrt(budget)); by_step: at most kRunCap - 2 steps are possible for this budget
+// and length range (otherwise the rank holds at most kRunCap samples).
+template <bool kIndex>
+__global__ void __launch_bounds__(kChainThreads) chain_kernel(const int64_t* __restrict__ off, RankState* ranks,
+                                                              const int32_t* __restrict__ slen, int64_t budget,
+                                                              int64_t sq, int by_step, int32_t* __restrict__ gidx,
+                                                              int32_t* __restrict__ groups_out, RunTable tbl,
+                                                              const int64_t* __restrict__ tile_first, DevStatus* st) {
+    __shared__ uint32_t s_start[kRunCap + 1], s_b[kRunCap], s_c[kRunCap], s_m[kRunCap];
+    __shared__ int32_t s_len[kChainThreads];
+    const int r = blockIdx.x;
+    const int64_t base = off[r];
+    const int cnt = (int)(ranks ? ranks[r].cnt : off[r + 1] - base);
+    const int t = threadIdx.x;
+    if (cnt <= 1) {   // no position >= 1, no run: position 0 (if any) is the only group start
         if (t == 0) {
-            atomicOr(&st->err, kErrInternal);
-            groups_out[r] = 0;
+            if (kIndex && cnt == 1) gidx[base] = 0;
+            if (ranks) ranks[r].G = cnt;
+            if (groups_out) groups_out[r] = cnt;
         }
         return;
     }
-    if (mine) {
-        uint32_t at = at0;
-        chunk_run_starts(slen, base, lo, hi, budget, [&](int q, uint32_t b) {
-            s_start[at] = (uint32_t)q;
-            s_b[at] = b;
-            ++at;
-        });
+    const int32_t* len = slen + base;
+    const int last = cnt - 1;   // lengths [0, last) are the steps of positions [1, cnt)
+    int R = 0;
+    if (by_step) {
+        // the longest of every `stride` lengths
+        const int stride = (last + kChainThreads - 1) / kChainThreads;
+        s_len[t] = t * (int64_t)stride < last ? len[t * stride] : 0;
+        __syncthreads();
+        const int64_t lmax = len[0], lmin = len[last - 1];
+        const int64_t blo = batch_size(budget, (int32_t)lmax), bhi = batch_size(budget, (int32_t)lmin);
+        const int64_t na = blo <= sq ? (bhi < sq ? bhi : sq) - blo + 1 : 0;
+        const int64_t lhi = lmax < budget / (sq + 1) ? lmax : budget / (sq + 1);
+        const int64_t nb = lhi >= lmin ? lhi - lmin + 1 : 0;
+        const int64_t nc = na + nb;
+        if (nc > kRunCap) {   // cannot happen (the host's bound): report, and leave the rank without groups
+            if (t == 0) {
+                atomicOr(&st->err, kErrInternal);
+                if (ranks) ranks[r].G = 0;
+                if (groups_out) groups_out[r] = 0;
+            }
+            return;
+        }
+        // first position of every candidate step (s_c), then the runs that hold a position
+        for (int i = t; i < (int)nc; i += kChainThreads) {
+            const int64_t b = i < na ? blo + i : (int64_t)step_of((int32_t)(lhi - (i - na)), budget);
+            const int64_t at = i < na ? budget / b : lhi - (i - na);   // step b: lengths at most `at`
+            int p = 0;
+            if (i > 0) {
+                int lo = 0, hi = kChainThreads;   // first sample at or below the threshold
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (s_len[mid] <= at) hi = mid; else lo = mid + 1;
+                }
+                // between sample lo - 1 (above) and sample lo
+                int a = lo > 0 ? (lo - 1) * stride + 1 : 0;
+                int z = (int64_t)lo * stride < last ? lo * stride : last;
+                while (a < z) {
+                    const int mid = (a + z) >> 1;
+                    if (len[mid] <= at) z = mid; else a = mid + 1;
+                }
+                p = a;
+            }
+            s_c[i] = (uint32_t)p;
+            s_m[i] = (uint32_t)b;
+        }
+        __syncthreads();
+        for (int i0 = 0; i0 < (int)nc; i0 += kChainThreads) {
+            const int i = i0 + t;
+            bool live = false;
+            if (i < (int)nc) live = s_c[i] < (i + 1 < (int)nc ? s_c[i + 1] : (uint32_t)last);
+            uint32_t tot;
+            const uint32_t ex = chain_scan(live ? 1u : 0u, &tot);
+            if (live) {
+                s_start[R + ex] = s_c[i] + 1;
+                s_b[R + ex] = s_m[i];
+            }
+            R += (int)tot;
+        }
+    } else {
+        const int per = (last + kChainThreads - 1) / kChainThreads;
+        const int lo = 1 + t * per;
+        const int hi = lo + per < cnt ? lo + per : cnt;
+        // the step never decreases, so a chunk whose first and last positions have the step of
+        // the position before it holds no run start
+        const bool busy = lo < hi && (lo == 1 || step_of(len[lo - 2], budget) != step_of(len[hi - 2], budget));
+        uint32_t mine = 0, tot;
+        if (busy) chunk_run_starts(slen, base, lo, hi, budget, [&](int, uint32_t) { ++mine; });
+        uint32_t at = chain_scan(mine, &tot);
+        if (tot > (uint32_t)kRunCap) {   // cannot happen (at most kRunCap samples)
+            if (t == 0) {
+                atomicOr(&st->err, kErrInternal);
+                if (ranks) ranks[r].G = 0;
+                if (groups_out) groups_out[r] = 0;
+            }
+            return;
+        }
+        if (mine)
+            chunk_run_starts(slen, base, lo, hi, budget, [&](int q, uint32_t b) {
+                s_start[at] = (uint32_t)q;
+                s_b[at] = b;
+                ++at;
+            });
+        R = (int)tot;
     }
-    const int R = (int)tot;
     if (t == 0) s_start[R] = (uint32_t)cnt;
     __syncthreads();
+    // reciprocals: with m = ceil(2^32 / b), (x * m) >> 32 is x / b or one more for x < 2^32
+    // (b = 1 has no 32-bit m)
+    for (int i = t; i < R; i += kChainThreads) s_m[i] = 0xFFFFFFFFu / s_b[i] + 1u;
+    __syncthreads();
     if (t == 0) {
-        // positions, steps and their sums stay below 2^32 (positions < 2^31, steps <= 2^31 - 1),
-        // so the walk runs on 32-bit division
+        // positions, steps and their sums stay below 2^32 (positions < 2^31, steps <= 2^31 - 1)
         uint32_t cur = 1;   // next(0) = 1: the second group starts at position 1
+#pragma unroll 8
         for (int i = 0; i < R; ++i) {
-            const uint32_t e = s_start[i + 1], b = s_b[i];
+            const uint32_t e = s_start[i + 1], b = s_b[i], m = s_m[i];
             const bool hit = cur < e;
-            s_c[i] = hit ? cur : 0xFFFFFFFFu;
-            const uint32_t k = hit ? (e - cur + b - 1) / b : 0u;
-            cur += k * b;
+            s_c[i] = hit ? cur : 0x7FFFFFFFu;
+            // x = (e - cur) + (b - 1) = k b + rem, k the positions cur, cur + b, ... below e; the
+            // next one is cur + k b = e + b - 1 - rem
+            const uint32_t eb = e + b - 1;
+            const uint32_t x = eb - cur;
+            uint32_t k = __umulhi(x, m);
+            k = b == 1 ? x : k;
+            uint32_t rem = x - k * b;
+            rem = rem >= b ? rem + b : rem;   // k was one too many: rem wrapped below 0
+            cur = hit ? eb - rem : cur;
         }
     }
     __syncthreads();
-    // chain positions per run and their exclusive prefix (runs dealt round robin over threads)
-    {
-        uint32_t carry = 0;
-        for (int i0 = 0; i0 < R; i0 += kRankThreads) {
-            const int i = i0 + t;
-            uint32_t ng = 0;
-            if (i < R) {
-                const uint32_t c = s_c[i], e = s_start[i + 1], b = s_b[i];
-                ng = c < e ? (e - c + b - 1) / b : 0u;
+    // group starts per run and their exclusive prefix (into s_m)
+    uint32_t carry = 0;
+    for (int i0 = 0; i0 < R; i0 += kChainThreads) {
+        const int i = i0 + t;
+        uint32_t ng = 0, tot;
+        if (i < R) {
+            const uint32_t c = s_c[i], e = s_start[i + 1], b = s_b[i];
+            ng = c < e ? (e - c + b - 1) / b : 0u;
+        }
+        const uint32_t ex = chain_scan(ng, &tot);
+        if (i < R) s_m[i] = carry + ex;
+        carry += tot;
+    }
+    if (t == 0) {
+        if (ranks) ranks[r].G = 1 + (int64_t)carry;
+        if (groups_out) groups_out[r] = (int32_t)(1 + carry);
+    }
+    __syncthreads();
+    auto run_of = [&](uint32_t q) {   // last run with start <= q
+        int a = 0, z = R;
+        while (z - a > 1) {
+            const int m = (a + z) >> 1;
+            if (s_start[m] <= q) a = m; else z = m;
+        }
+        return a;
+    };
+    if (kIndex) {
+        for (int q = t; q < cnt; q += kChainThreads) {
+            int32_t g = 0;
+            if (q > 0) {
+                const int a = run_of((uint32_t)q);
+                const uint32_t c = s_c[a];
+                g = (int32_t)(s_m[a] + ((uint32_t)q >= c ? ((uint32_t)q - c) / s_b[a] + 1u : 0u));
             }
-            const uint32_t inc2 = wave_scan_dpp<OpAdd>(ng);
-            __syncthreads();
-            if ((t & (kWave - 1)) == kWave - 1) s_wsum[t / kWave] = inc2;
-            __syncthreads();
-            uint32_t pre2 = 0, tot2 = 0;
+            gidx[base + q] = g;
+        }
+    } else {
+        for (int i = t; i < R; i += kChainThreads) {
+            tbl.start[base + i] = (int32_t)s_start[i];
+            tbl.step[base + i] = (int32_t)s_b[i];
+            tbl.first[base + i] = (int32_t)s_c[i];
+            tbl.before[base + i] = (int32_t)s_m[i];
+        }
+        const int64_t t0 = tile_first[r], t1 = tile_first[r + 1];
+        for (int64_t j = t0 + t; j < t1; j += kChainThreads) {
+            const int64_t q = (j - t0) * kSortTile;
+            if (q < cnt) tbl.tile[j] = (uint32_t)(q > 0 ? run_of((uint32_t)q) : 0);
+        }
+        if (t == 0) {
+            tbl.start[base + R] = cnt;   // R < cnt: a rank has fewer runs than positions
+            tbl.runs[r] = (uint32_t)R;
+        }
+    }
+}
+
+typedef int32_t I4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// Group index of every live position, and with `gstart` the global position of every group
+// start at its global group id, from the run table.  One block per sort tile, eight
+// consecutive positions per thread: one search (between the runs of the tile's first
+// positions) and one division, then a step along the run.
+__global__ void __launch_bounds__(kBlock) chain_index_kernel(const int64_t* __restrict__ off,
+                                                             const int64_t* __restrict__ tile_first, int W,
+                                                             const RankState* __restrict__ ranks, RunTable tbl,
+                                                             int32_t* __restrict__ gidx, int32_t* __restrict__ gstart) {
+    static_assert(kSortTile == kBlock * 8, "eight positions per thread");
+    const int64_t b = blockIdx.x;
+    const int r = rank_of(tile_first, W, b);
+    const int64_t base = off[r];
+    const int64_t cnt = ranks ? ranks[r].cnt : off[r + 1] - base;
+    const int64_t tile0 = (b - tile_first[r]) * kSortTile;
+    const int64_t q0 = tile0 + (int64_t)threadIdx.x * 8;
+    if (q0 >= cnt) return;
+    const int m = cnt - q0 < 8 ? (int)(cnt - q0) : 8;
+    // the run of position max(q0, 1), between the runs of this tile's and the next tile's first
+    // positions
+    const int32_t* start = tbl.start + base;
+    uint32_t q = q0 > 0 ? (uint32_t)q0 : 1u;
+    int a = 0;
+    uint32_t end = 0, nxt = 0, step = 1;   // the run's end, the next group start, the step
+    int32_t g = 0;                         // group of the current position
+    bool head = true;                      // the current position starts its group
+    auto enter = [&](uint32_t x) {
+        end = (uint32_t)start[a + 1];
+        step = (uint32_t)tbl.step[base + a];
+        const uint32_t c = (uint32_t)tbl.first[base + a];
+        g = tbl.before[base + a];
+        nxt = c;
+        head = false;
+        if (x >= c) {
+            const uint32_t k = (x - c) / step;
+            g += (int32_t)k + 1;
+            nxt = c + (k + 1) * step;
+            head = nxt - step == x;
+        }
+    };
+    if (cnt > 1) {
+        a = (int)tbl.tile[b];
+        int z = tile0 + kSortTile < cnt ? (int)tbl.tile[b + 1] + 1 : (int)tbl.runs[r];
+        while (z - a > 1) {
+            const int mid = (a + z) >> 1;
+            if ((uint32_t)start[mid] <= q) a = mid; else z = mid;
+        }
+        enter(q);
+    }
+    int32_t out[8];
+    uint32_t heads = 0;
 #pragma unroll
-            for (int w2 = 0; w2 < kRankWaves; ++w2) {
-                pre2 += w2 < t / kWave ? s_wsum[w2] : 0u;
-                tot2 += s_wsum[w2];
-            }
-            if (i < R) s_gb[i] = carry + pre2 + inc2 - ng;
-            carry += tot2;
+    for (int i = 0; i < 8; ++i) {
+        const uint32_t x = (uint32_t)q0 + i;
+        if (x == 0) {   // position 0: the first group, of one
+            out[i] = 0;
+            heads |= 1u;
+            continue;
         }
-        if (t == 0) s_total = carry;
-    }
-    __syncthreads();
-    // group index of every position: chain positions up to it, minus one
-    for (int q = t; q < cnt; q += kRankThreads) {
-        int32_t g = 0;
-        if (q > 0) {
-            int a = 0, z = R;   // last run with start <= q: s_start[a] <= q < s_start[z]
-            while (z - a > 1) {
-                const int m = (a + z) >> 1;
-                if (s_start[m] <= (uint32_t)q) a = m; else z = m;
+        if (i < m && x > q) {
+            if (x >= end) {   // a run holds at least one position
+                a += 1;
+                enter(x);
+            } else if (x == nxt) {
+                g += 1;
+                nxt += step;
+                head = true;
+            } else {
+                head = false;
             }
-            const uint32_t c = s_c[a];
-            g = (int32_t)(s_gb[a] + ((uint32_t)q >= c ? ((uint32_t)q - c) / s_b[a] + 1u : 0u));
+            q = x;
         }
-        gidx[base + q] = g;
+        out[i] = g;
+        heads |= head && i < m ? 1u << i : 0u;
     }
-    if (t == 0) groups_out[r] = (int32_t)(1 + s_total);
+    int32_t* o = gidx + base + q0;
+    if (m == 8) {
+        *reinterpret_cast<I4*>(o) = I4{out[0], out[1], out[2], out[3]};
+        *reinterpret_cast<I4*>(o + 4) = I4{out[4], out[5], out[6], out[7]};
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (i < m) o[i] = out[i];
+    }
+    if (gstart) {
+        const int64_t gb = ranks[r].gbase;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if ((heads >> i) & 1) gstart[gb + out[i]] = (int32_t)(base + q0 + i);
+    }
 }
 
 }  // namespace
 
-// Distinct steps a rank's sorted sequence can hold: at most the distinct values of
-// floor(budget / l), i.e. at most 2 sqrt(budget) + 1, at most the number of distinct
-// lengths (len_range, if known, else 0) and at most the rank's positions.
-static int64_t runs_bound(int64_t budget, int64_t max_cnt, int64_t len_range) {
-    int64_t b = 2 * ((int64_t)std::sqrt((double)budget) + 1) + 1;
-    if (len_range > 0 && len_range < b) b = len_range;
-    if (max_cnt < b) b = max_cnt;
-    return b;
+// floor(sqrt(v)).
+static int64_t isqrt(int64_t v) {
+    uint64_t s = (uint64_t)std::sqrt((double)v);
+    while (s * s > (uint64_t)v) --s;
+    while ((s + 1) * (s + 1) <= (uint64_t)v) ++s;
+    return (int64_t)s;
+}
+
+// Whether chain_kernel can list the steps of a rank from the budget and the range of its
+// lengths (0: unknown), or has to look at its samples, or (kChainJump) neither fits its table:
+// floor(budget / l) takes at most 2 sqrt(budget) values, and one per length plus the few
+// that the listing adds.
+enum ChainBy { kChainByStep, kChainBySample, kChainJump };
+
+static ChainBy chain_by(int64_t budget, int64_t max_cnt, int64_t len_range) {
+    if (2 * (isqrt(budget) + 1) <= kRunCap || (len_range > 0 && len_range + 4 <= kRunCap)) return kChainByStep;
+    return max_cnt <= kRunCap ? kChainBySample : kChainJump;
 }
 
 // Mark scan, group index of every position, global group starts, G_r.
@@ -1142,47 +1162,36 @@ int group_sequences(const Layout& L, void* ws, int W, int64_t n, int64_t budget,
     int32_t* incl = ws_at<int32_t>(ws, L.incl);
     DevStatus* st = ws_at<DevStatus>(ws, L.status);
     const unsigned grid = grid_for(n + 1, kBlock, (int64_t)num_cus() * kPlanBlocksPerCU);
-    if (runs_bound(budget, max_cnt, len_range) <= kRunCap && n < INT32_MAX) {
-        // run-table walk over the sort's tiles
+    const ChainBy by = chain_by(budget, max_cnt, len_range);
+    if (by != kChainJump) {
         int64_t* d_tile_first = ws_at<int64_t>(ws, L.tile_first);
         if (!tiles_ready) {
             hipLaunchKernelGGL(sort_tiles_kernel, dim3(1), dim3(kBlock), 0, s, d_off, W, d_tile_first);
             ODB_LAUNCHED();
         }
+        const RunTable tbl{j0, j1, ws_at<int32_t>(ws, L.gsize), incl, ws_at<uint32_t>(ws, L.counts),
+                           ws_at<uint32_t>(ws, L.rank_runs)};
+        hipLaunchKernelGGL(chain_kernel<false>, dim3(W), dim3(kChainThreads), 0, s, d_off, d_ranks, d_slen, budget,
+                           isqrt(budget), by == kChainByStep ? 1 : 0, (int32_t*)nullptr, d_groups_out, tbl,
+                           (const int64_t*)d_tile_first, st);
+        ODB_LAUNCHED();
+        if (d_ranks) {   // the next round of an alignment numbers its groups over all ranks
+            hipLaunchKernelGGL(rank_groups_kernel, dim3(1), dim3(kBlock), 0, s, d_ranks, W, ws_at<int64_t>(ws, L.gbase));
+            ODB_LAUNCHED();
+        }
         const unsigned tiles = (unsigned)L.num_sort_blocks;
-        uint32_t* tile_runs = ws_at<uint32_t>(ws, L.counts);
-        uint32_t* rank_runs = ws_at<uint32_t>(ws, L.rank_runs);
-        int32_t* run_start = j0;
-        int32_t* run_b = j1;
-        int32_t* run_c = ws_at<int32_t>(ws, L.gsize);
-        int32_t* run_g = incl;
-        const RankState* cr = d_ranks;
         if (tiles > 0) {
-            hipLaunchKernelGGL(run_count_kernel, dim3(tiles), dim3(kBlock), 0, s, d_off, (const int64_t*)d_tile_first,
-                               W, cr, d_slen, budget, tile_runs);
-            ODB_LAUNCHED();
-        }
-        hipLaunchKernelGGL(run_tile_scan_kernel, dim3(W), dim3(kBlock), 0, s, (const int64_t*)d_tile_first, tile_runs,
-                           rank_runs);
-        ODB_LAUNCHED();
-        if (tiles > 0) {
-            hipLaunchKernelGGL(run_write_kernel, dim3(tiles), dim3(kBlock), 0, s, d_off, (const int64_t*)d_tile_first,
-                               W, cr, d_slen, budget, (const uint32_t*)tile_runs, run_start, run_b);
-            ODB_LAUNCHED();
-        }
-        hipLaunchKernelGGL(run_chase_kernel, dim3(W), dim3(kBlock), 0, s, d_off, d_ranks, (const uint32_t*)rank_runs,
-                           (const int32_t*)run_start, (const int32_t*)run_b, run_c, run_g);
-        ODB_LAUNCHED();
-        hipLaunchKernelGGL(rank_groups_kernel, dim3(1), dim3(kBlock), 0, s, d_ranks, W, ws_at<int64_t>(ws, L.gbase),
-                           d_groups_out);
-        ODB_LAUNCHED();
-        if (tiles > 0) {
-            hipLaunchKernelGGL(run_gidx_kernel, dim3(tiles), dim3(kBlock), 0, s, d_off, (const int64_t*)d_tile_first,
-                               W, cr, d_slen, budget, (const uint32_t*)tile_runs, (const int32_t*)run_b,
-                               (const int32_t*)run_c, (const int32_t*)run_g, d_gidx, ws_at<int32_t>(ws, L.gstart));
+            hipLaunchKernelGGL(chain_index_kernel, dim3(tiles), dim3(kBlock), 0, s, d_off, (const int64_t*)d_tile_first,
+                               W, (const RankState*)d_ranks, tbl, d_gidx,
+                               d_ranks ? ws_at<int32_t>(ws, L.gstart) : (int32_t*)nullptr);
             ODB_LAUNCHED();
         }
         return ODB_OK;
+    }
+    if (!d_ranks) {   // the jumping kernels read the counts from the rank states
+        d_ranks = ws_at<RankState>(ws, L.ranks);
+        hipLaunchKernelGGL(rank_counts_kernel, dim3(grid_for(W, kBlock)), dim3(kBlock), 0, s, d_off, W, d_ranks);
+        ODB_LAUNCHED();
     }
     hipLaunchKernelGGL(links_kernel, dim3(grid), dim3(kBlock), 0, s, d_slen, d_off,
                        (const RankState*)d_ranks, W, n, budget, j0, marks);
@@ -1220,7 +1229,6 @@ extern "C" int odb_form_groups(const odb_window_t* w, int64_t budget, int32_t* d
     hipStream_t s = static_cast<hipStream_t>(stream);
     ODB_TRY(upload_small(w, L, d_ws, nullptr, s));
     const int64_t* d_off = ws_at<int64_t>(d_ws, L.rank_off);
-    RankState* d_ranks = ws_at<RankState>(d_ws, L.ranks);
     DevStatus* st = ws_at<DevStatus>(d_ws, L.status);
     int32_t* len = ws_at<int32_t>(d_ws, L.len);
     int64_t max_cnt = 0;
@@ -1231,21 +1239,21 @@ extern "C" int odb_form_groups(const odb_window_t* w, int64_t budget, int32_t* d
 
     // one block per rank: two launches, no synchronisation (invalid lengths are grouped as
     // length 1 and reported by odb_align_groups)
-    if (max_cnt <= kRankBlockMax && runs_bound(budget, max_cnt, 0) <= kRankRunCap) {
+    const ChainBy by = chain_by(budget, max_cnt, 0);
+    if (max_cnt <= kRankBlockMax && by != kChainJump) {
         hipLaunchKernelGGL(rank_sort_kernel, dim3(W), dim3(kRankThreads), 0, s, w->d_token_offsets, d_off, len,
                            ws_at<int32_t>(d_ws, L.keys0), ws_at<int32_t>(d_ws, L.vals0), ws_at<int32_t>(d_ws, L.keys1),
                            ws_at<int32_t>(d_ws, L.vals1), d_order, d_sorted_len, st);
         ODB_LAUNCHED();
-        hipLaunchKernelGGL(rank_walk_kernel, dim3(W), dim3(kRankThreads), 0, s, d_off, (const int32_t*)d_sorted_len,
-                           budget, d_group_index, d_groups_per_rank, st);
+        hipLaunchKernelGGL(chain_kernel<true>, dim3(W), dim3(kChainThreads), 0, s, d_off, (RankState*)nullptr,
+                           (const int32_t*)d_sorted_len, budget, isqrt(budget), by == kChainByStep ? 1 : 0,
+                           d_group_index, d_groups_per_rank, RunTable{}, (const int64_t*)nullptr, st);
         ODB_LAUNCHED();
         return ODB_OK;
     }
-    hipLaunchKernelGGL(rank_counts_kernel, dim3(grid_for(W, kBlock)), dim3(kBlock), 0, s, d_off, W, d_ranks);
-    ODB_LAUNCHED();
 
     // (a1) lengths and their validity; the one synchronisation of this call
-    hipLaunchKernelGGL(lengths_kernel, dim3(grid_for(n, kBlock, (int64_t)num_cus() * kPlanBlocksPerCU)), dim3(kBlock), 0, s,
+    hipLaunchKernelGGL(lengths_kernel, dim3(grid_for(n, kBlock, (int64_t)num_cus() * kLengthsBlocksPerCU)), dim3(kBlock), 0, s,
                        w->d_token_offsets, n, len, st);
     ODB_LAUNCHED();
     DevStatus hs;
@@ -1255,13 +1263,6 @@ extern "C" int odb_form_groups(const odb_window_t* w, int64_t budget, int32_t* d
         return set_error(ODB_E_INVALID_DATA,
                          "sample %lld has a length outside [1, 2^31) or a negative token offset",
                          (long long)hs.first_bad);
-    if (n == 0) {
-        hipLaunchKernelGGL(groups_kernel, dim3(grid_for(W, kBlock)), dim3(kBlock), 0, s,
-                           (const int32_t*)len, d_off, W, d_ranks, ws_at<int64_t>(d_ws, L.gbase), d_groups_per_rank);
-        ODB_LAUNCHED();
-        return ODB_OK;
-    }
-
     // (a2) segmented stable radix sort on key = max_l - l
     const uint32_t maxl = hs.max_len, minl = hs.min_len;
     int bits = 0;
@@ -1311,10 +1312,7 @@ extern "C" int odb_form_groups(const odb_window_t* w, int64_t budget, int32_t* d
         }
     }
 
-    // (a3, a4) the group chain: the multi-kernel run walk or pointer jumping.  (A large
-    // rank's chain walked by one block per rank takes ~0.4 ms alone but tens of ms beside a
-    // running collate, which stalls the two-stream schedule; these grid-wide kernels
-    // share the GPU with it.)
-    return group_sequences(L, d_ws, W, n, budget, d_off, max_cnt, n > 0 ? (int64_t)hs.max_len - hs.min_len + 1 : 0,
-                           passes > 0, d_sorted_len, d_group_index, d_groups_per_rank, d_ranks, s);
+    // (a3, a4) the group chain
+    return group_sequences(L, d_ws, W, n, budget, d_off, max_cnt, (int64_t)maxl - minl + 1, passes > 0, d_sorted_len,
+                           d_group_index, d_groups_per_rank, nullptr, s);
 }
