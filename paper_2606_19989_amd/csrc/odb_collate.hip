@@ -62,6 +62,14 @@ constexpr int64_t kRunSteps = 64;      // 2^6
 constexpr int64_t kMinRunSteps = 8;    // 2^3
 constexpr int64_t kRunsPerBlock = 128;
 static_assert(kRunSteps == 64 && kMinRunSteps == 8, "the run length is 2^3 .. 2^6 steps");
+// Outputs of at most kDealtSteps steps per block (50 M elements on 256 compute units) are dealt
+// in runs of 4 steps, round robin by block index: so small an output ends before the blocks drift
+// apart, and the counter's same-address atomics (~12 ns each, one after the other) and the run
+// hand-over's barriers cost more than they even out.  us per call dealt / counted: 2 x 2,048
+// samples 16.6 / 19.5, 8 x 1,021 36.3 / 46.6, 8 x 4,096 59.1 / 67.3; 16 x 8,192 text (90,000
+// steps) 363 either way.  Runs of 2 and 8 steps: 17.1 and 17.3, 37.1 and 36.9, 61.4 and 60.9.
+constexpr int64_t kDealtSteps = 64;
+constexpr int kDealtShift = 2;
 // Three resident blocks (12 waves) per compute unit stream fastest (two, four, five or
 // six were slower), and they leave five of the eight wave slots and about half the
 // registers of every SIMD to kernels on other streams: the grouping and alignment of the next window can run
@@ -306,7 +314,8 @@ __device__ __forceinline__ v4i load_tokens(const Cursor& c, const RowRec& r, con
 }
 
 // Next step of this block's sequence, or -1 past its end: the next step of the run of
-// step s, else the first step of the block's next run.  A block's first run is its index;
+// step s, else the first step of the block's next run.  With `runs` null runs are dealt by block
+// index (small outputs); otherwise:  A block's first run is its index;
 // later runs are taken from a counter when a block needs one, so blocks that meet cheaper
 // runs take more of them (dealt statically, the blocks of one launch finished up to 15% of
 // the kernel's time apart).  Thread 0 keeps the block's next run index fetched one run
@@ -318,6 +327,10 @@ __device__ __forceinline__ int64_t next_step(int64_t s, int64_t nsteps, int64_t 
                                              unsigned long long* runs) {
     const int64_t r = s >> run_shift;
     if (s + 1 < ((r + 1) << run_shift) && s + 1 < nsteps) return s + 1;
+    if (!runs) {
+        const int64_t rd = r + gridDim.x;
+        return rd < nruns ? rd << run_shift : -1;
+    }
     __shared__ int64_t s_run;
     if (threadIdx.x == 0) {
         s_run = (int64_t)pf;
@@ -455,6 +468,10 @@ __global__ void __launch_bounds__(kCollateBlock) collate_kernel(Plan p, int32_t 
     // still gives every block kRunsPerBlock runs
     int run_shift = 3;
     while (run_shift < 6 && ((int64_t)gridDim.x * kRunsPerBlock << (run_shift + 1)) <= nsteps) ++run_shift;
+    if (nsteps <= (int64_t)gridDim.x * kDealtSteps) {
+        run_shift = kDealtShift;
+        p.runs = nullptr;
+    }
     const int64_t nruns = (nsteps + (1ll << run_shift) - 1) >> run_shift;
     if ((int64_t)blockIdx.x >= nruns) return;
     const int lane = threadIdx.x & (kWave - 1);
@@ -469,7 +486,7 @@ __global__ void __launch_bounds__(kCollateBlock) collate_kernel(Plan p, int32_t 
 
     // pipeline: step s0 is stored from stage a, s1's tokens load into b, s2's rows into c
     unsigned long long pf = 0;
-    if (threadIdx.x == 0) pf = atomicAdd(p.runs, 1ull) + gridDim.x;
+    if (p.runs && threadIdx.x == 0) pf = atomicAdd(p.runs, 1ull) + gridDim.x;
     int64_t s0 = (int64_t)blockIdx.x << run_shift;
     int64_t s1 = next_step(s0, nsteps, nruns, run_shift, pf, p.runs);
     int64_t s2 = s1 >= 0 ? next_step(s1, nsteps, nruns, run_shift, pf, p.runs) : -1;
