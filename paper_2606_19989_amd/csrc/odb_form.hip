@@ -50,7 +50,7 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid, int dbit
 
 // Lengths, their validity and the window's shortest and longest.  Every block ends with two
 // atomics on the same two words, ~10 ns each one after the other: 2,048 blocks spent 50 us on
-// them whatever the window's size (8 x 65,536 samples: 50 us, now XX; 64 x 262,144: 67, now YY).
+// them whatever the window's size (16 x 65,536 samples: 51 us, now 17; 64 x 262,144: 67, now 43).
 constexpr int kLengthsDeep = 8;
 constexpr int kLengthsBlocksPerCU = 2;
 
@@ -402,13 +402,14 @@ __global__ void __launch_bounds__(kBlock) jump_kernel(const int32_t* __restrict_
 // The group index of every position follows in closed form: in the same block for ranks of at
 // most kRankBlockMax samples, else by chain_index_kernel over all tiles.
 //
-// Bound by the chase: ~30 ns per run.  64 ranks x 262,144 samples, ~700 runs per rank: the
+// Bound by the chase: ~25 ns per run.  64 ranks x 262,144 samples, ~700 runs per rank: the
 // run table from a count, a scan and a write pass over all samples took 105 us and a chase that
-// divides 83 us; XX us here, and the group indices YY instead of 71 us (nothing is read per
+// divides 83 us; 38 us here, and the group indices 28 instead of 71 us (nothing is read per
 // sample any more).
 constexpr int kChainThreads = 1024;
 constexpr int kChainWaves = kChainThreads / kWave;
 constexpr int kRunCap = 4096;   // runs per rank
+constexpr int kChaseBatch = 8;  // runs the chase reads at once
 
 // One block: every rank's first global group id (exclusive sum of G_r) and the total in
 // gbase[W].
@@ -842,7 +843,8 @@ __global__ void __launch_bounds__(kChainThreads) chain_kernel(const int64_t* __r
                                                               int64_t sq, int by_step, int32_t* __restrict__ gidx,
                                                               int32_t* __restrict__ groups_out, RunTable tbl,
                                                               const int64_t* __restrict__ tile_first, DevStatus* st) {
-    __shared__ uint32_t s_start[kRunCap + 1], s_b[kRunCap], s_c[kRunCap], s_m[kRunCap];
+    __shared__ uint32_t s_start[kRunCap + 1], s_b[kRunCap + kChaseBatch], s_c[kRunCap + kChaseBatch],
+        s_m[kRunCap + kChaseBatch];
     __shared__ int32_t s_len[kChainThreads];
     const int r = blockIdx.x;
     const int64_t base = off[r];
@@ -942,28 +944,98 @@ __global__ void __launch_bounds__(kChainThreads) chain_kernel(const int64_t* __r
     }
     if (t == 0) s_start[R] = (uint32_t)cnt;
     __syncthreads();
-    // reciprocals: with m = ceil(2^32 / b), (x * m) >> 32 is x / b or one more for x < 2^32
-    // (b = 1 has no 32-bit m)
-    for (int i = t; i < R; i += kChainThreads) s_m[i] = 0xFFFFFFFFu / s_b[i] + 1u;
+    // The chase.  Let x = e + b - 1 - cur for the chain's position cur on entering a run that
+    // ends at e.  If cur < e the run holds k = x / b chain positions and the next one is
+    // e + b - 1 - x % b; if not, x < b, and the same expression gives cur again.  So the only
+    // chain is x' = x % b + (e' - e) + (b' - b).  A step larger than the rank leaves it like one
+    // of the rank's size.
+    //
+    // Ranks of up to 2^19 positions: x < 2^20 and the remainder runs in fp32, exact integers
+    // throughout.  inv is 1 / b less 2^-21 of it, so the quotient is at most x / b and less than
+    // one below it (b >= 2: x / b * 2^-20 < 1): the remainder comes out in [0, 2 b) and one
+    // subtraction brings it below b, taken if it does not turn the sign (the larger unsigned
+    // pattern).  Only the first run can have step 1, whose remainder is 0.
+    const bool fp = cnt <= (1 << 19);
+    for (int i = t; i < R; i += kChainThreads) {
+        const uint32_t b = s_b[i] < (uint32_t)cnt ? s_b[i] : (uint32_t)cnt;
+        const uint32_t bp = i > 0 ? (s_b[i - 1] < (uint32_t)cnt ? s_b[i - 1] : (uint32_t)cnt) : 0u;
+        // into run i: x_0 itself (cur = next(0) = 1, the second group starts at position 1), else
+        // what is added to the previous run's remainder
+        const uint32_t d = i > 0 ? s_start[i + 1] - s_start[i] + b - bp : s_start[1] + b - 2;
+        s_c[i] = fp ? __float_as_uint((float)d) : d;
+        // ceil(2^32 / b): (x * m) >> 32 is x / b or one more for x < 2^32
+        s_m[i] = fp ? __float_as_uint((1.0f / (float)b) * (1.0f - 0x1p-21f)) : 0xFFFFFFFFu / b + 1u;
+    }
     __syncthreads();
     if (t == 0) {
-        // positions, steps and their sums stay below 2^32 (positions < 2^31, steps <= 2^31 - 1)
-        uint32_t cur = 1;   // next(0) = 1: the second group starts at position 1
-#pragma unroll 8
-        for (int i = 0; i < R; ++i) {
-            const uint32_t e = s_start[i + 1], b = s_b[i], m = s_m[i];
-            const bool hit = cur < e;
-            s_c[i] = hit ? cur : 0x7FFFFFFFu;
-            // x = (e - cur) + (b - 1) = k b + rem, k the positions cur, cur + b, ... below e; the
-            // next one is cur + k b = e + b - 1 - rem
-            const uint32_t eb = e + b - 1;
-            const uint32_t x = eb - cur;
-            uint32_t k = __umulhi(x, m);
-            k = b == 1 ? x : k;
-            uint32_t rem = x - k * b;
-            rem = rem >= b ? rem + b : rem;   // k was one too many: rem wrapped below 0
-            cur = hit ? eb - rem : cur;
+        // s_c[i] becomes x of run i; runs come in batches read ahead of their use, so that the
+        // chain carries arithmetic only (reads past R return what is never used)
+        uint32_t d0[kChaseBatch], b0[kChaseBatch], m0[kChaseBatch], d1[kChaseBatch], b1[kChaseBatch], m1[kChaseBatch];
+        auto load = [&](int i0, uint32_t (&d)[kChaseBatch], uint32_t (&b)[kChaseBatch], uint32_t (&m)[kChaseBatch]) {
+#pragma unroll
+            for (int j = 0; j < kChaseBatch; ++j) {
+                d[j] = s_c[i0 + j];
+                b[j] = s_b[i0 + j];
+                m[j] = s_m[i0 + j];
+            }
+        };
+        auto walk = [&](auto run) {
+            load(0, d0, b0, m0);
+            for (int i0 = 0; i0 < R; i0 += 2 * kChaseBatch) {
+                if (i0 + kChaseBatch < R) load(i0 + kChaseBatch, d1, b1, m1);
+                run(i0, d0, b0, m0);
+                if (i0 + kChaseBatch >= R) break;
+                if (i0 + 2 * kChaseBatch < R) load(i0 + 2 * kChaseBatch, d0, b0, m0);
+                run(i0 + kChaseBatch, d1, b1, m1);
+            }
+        };
+        const uint32_t most = (uint32_t)cnt;
+        if (fp) {
+            float rem = 0.0f;
+            walk([&](int i0, const uint32_t (&d)[kChaseBatch], const uint32_t (&b)[kChaseBatch],
+                     const uint32_t (&m)[kChaseBatch]) {
+                float bf[kChaseBatch];
+                uint32_t xs[kChaseBatch];
+#pragma unroll
+                for (int j = 0; j < kChaseBatch; ++j) bf[j] = (float)(b[j] < most ? b[j] : most);
+#pragma unroll
+                for (int j = 0; j < kChaseBatch; ++j) {
+                    const float x = rem + __uint_as_float(d[j]);
+                    xs[j] = (uint32_t)x;
+                    const float q = __builtin_truncf(x * __uint_as_float(m[j]));
+                    const float ra = __builtin_fmaf(-q, bf[j], x);
+                    const uint32_t ua = __float_as_uint(ra), ub = __float_as_uint(ra - bf[j]);
+                    rem = __uint_as_float(ua < ub ? ua : ub);
+                    if (j == 0 && i0 == 0 && bf[0] == 1.0f) rem = 0.0f;
+                }
+#pragma unroll
+                for (int j = 0; j < kChaseBatch; ++j) s_c[i0 + j] = xs[j];
+            });
+        } else {
+            uint32_t rem = 0;
+            walk([&](int i0, const uint32_t (&d)[kChaseBatch], const uint32_t (&b)[kChaseBatch],
+                     const uint32_t (&m)[kChaseBatch]) {
+                uint32_t xs[kChaseBatch];
+#pragma unroll
+                for (int j = 0; j < kChaseBatch; ++j) {
+                    const uint32_t bj = b[j] < most ? b[j] : most;
+                    const uint32_t x = rem + d[j];
+                    xs[j] = x;
+                    const uint32_t ra = x - __umulhi(x, m[j]) * bj;
+                    rem = ra < ra + bj ? ra : ra + bj;   // wrapped below 0 if the quotient was one too many
+                    if (j == 0 && i0 == 0 && bj == 1) rem = 0;
+                }
+#pragma unroll
+                for (int j = 0; j < kChaseBatch; ++j) s_c[i0 + j] = xs[j];
+            });
         }
+    }
+    __syncthreads();
+    // the chain's first position in every run
+    for (int i = t; i < R; i += kChainThreads) {
+        const uint32_t b = s_b[i] < (uint32_t)cnt ? s_b[i] : (uint32_t)cnt;
+        const uint32_t cur = s_start[i + 1] + b - 1 - s_c[i];
+        s_c[i] = cur < s_start[i + 1] ? cur : 0x7FFFFFFFu;
     }
     __syncthreads();
     // group starts per run and their exclusive prefix (into s_m)
