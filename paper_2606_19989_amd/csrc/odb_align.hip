@@ -1685,6 +1685,347 @@ __global__ void __launch_bounds__(kBlock) share_kernel(OneArgs a, const int64_t*
     }
 }
 
+// ---------------------------------------------------------------- rounds of short ranks
+// Join-mode windows whose ranks hold at most kRankBlockMax samples and overflow (an
+// output-slot capacity, as a rule) run a round in two launches of one block per rank, with no
+// wait for the host between rounds: short_round_kernel aligns and emits, group_short_ranks
+// groups what it returned.  A round of the general path is twelve launches and one
+// synchronisation (~95 us on 8 x 4,096 samples; 20 us here).
+//
+// Overflow in closed form.  Along a rank the groups' sizes never decrease (the step B(l)
+// grows as the lengths fall), except for the last group, which the buffer's end clips.  The T
+// largest, ties to the later-formed, are therefore T consecutive groups: the last T, unless T
+// of the others are larger than the last group, then the T before it.  So what a round emits
+// is one range of positions, reversed, and what it returns the positions before it and after
+// it.  Stage-1 groups that are not sized like this (arrays that odb_form_groups did not
+// write) are left to the general path.
+struct ShortArgs {
+    int W;
+    int has_cap;
+    const int64_t* cap;
+    const int64_t* off;
+    RankState* ranks;
+    RoundState* rs;
+    DevStatus* st;
+    int32_t* dst;        // emitted ids and lengths, rank r from off[r] on
+    int32_t* dst_len;
+    // staged slot records, rank r's slots from off[r] on
+    int32_t* srows;
+    int32_t* smax;
+    int64_t* stok;
+    double* sadj;
+    int64_t* sroff;      // first row of the slot among the rank's
+};
+
+constexpr int kShortThreads = 1024;
+constexpr int kShortItems = (int)(kRankBlockMax / kShortThreads);   // positions per thread
+
+template <typename T, typename Op>
+__device__ __forceinline__ T short_reduce(T v, Op op) {
+    __shared__ T s_v[kShortThreads / kWave];
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) v = op(v, ::__shfl_xor(v, d, kWave));
+    if ((threadIdx.x & (kWave - 1)) == 0) s_v[threadIdx.x / kWave] = v;
+    __syncthreads();
+    T r = s_v[0];
+#pragma unroll
+    for (int i = 1; i < kShortThreads / kWave; ++i) r = op(r, s_v[i]);
+    __syncthreads();
+    return r;
+}
+
+__global__ void __launch_bounds__(kShortThreads) short_round_kernel(ShortArgs a, const int32_t* __restrict__ cur_ids,
+                                                                    const int32_t* __restrict__ cur_len,
+                                                                    const int32_t* __restrict__ gidx,
+                                                                    int32_t* __restrict__ next_ids,
+                                                                    int32_t* __restrict__ next_len) {
+#pragma clang fp contract(off)
+    __shared__ int32_t s_len[kRankBlockMax];
+    __shared__ uint16_t s_gs[kRankBlockMax + 2];
+    __shared__ int64_t s_pre[kShortThreads];   // tokens before position t * kShortItems
+    __shared__ int64_t s_w[kShortThreads / kWave];
+    if (stage1_bad(a.st)) return;
+    const int t = threadIdx.x, r = blockIdx.x;
+    // Eq. 3 over the active ranks
+    int64_t maxG = 0, minC = LLONG_MAX, minS = LLONG_MAX, total = 0, active = 0;
+    for (int q = t; q < a.W; q += kShortThreads) {
+        const int64_t Gq = a.ranks[q].G, Sq = a.ranks[q].cnt;
+        if (Gq <= 0) continue;
+        maxG = Gq > maxG ? Gq : maxG;
+        minS = Sq < minS ? Sq : minS;
+        if (a.has_cap && a.cap[q] > 0 && a.cap[q] < minC) minC = a.cap[q];
+        total += Gq;
+        active += 1;
+    }
+    maxG = short_reduce(maxG, MaxOp{});
+    minC = short_reduce(minC, MinOp{});
+    minS = short_reduce(minS, MinOp{});
+    RankState& R = a.ranks[r];
+    const int cnt = (int)R.cnt;
+    if (maxG == 0) {   // every buffer is empty
+        if (t == 0) R.next_cnt = 0;
+        return;
+    }
+    int64_t T64 = maxG;
+    T64 = minC < T64 ? minC : T64;
+    T64 = minS < T64 ? minS : T64;
+    const int T = (int)(T64 < 1 ? 1 : T64);
+    if (r == 0) {
+        int64_t splits = 0, over = 0, changed = 0;
+        for (int q = t; q < a.W; q += kShortThreads) {
+            const int64_t Gq = a.ranks[q].G;
+            if (Gq <= 0) continue;
+            splits += Gq < T ? T - Gq : 0;
+            over += Gq > T ? Gq - T : 0;
+            changed += Gq != T;
+        }
+        splits = short_reduce(splits, SumOp{});
+        over = short_reduce(over, SumOp{});
+        changed = short_reduce(changed, SumOp{});
+        if (t == 0) {
+            a.rs->T = T;
+            a.rs->splits += splits;
+            a.rs->overflow += over;
+            a.rs->second_gather += changed > 0 ? 1 : 0;
+            a.rs->rounds += 1;
+            a.rs->cut += T;   // steps so far
+        }
+    }
+    if (cnt == 0) {
+        if (t == 0) R.next_cnt = 0;
+        return;
+    }
+    const int64_t base = a.off[r];
+    const int G = (int)R.G;
+    for (int q = t; q < cnt; q += kShortThreads) {
+        s_len[q] = cur_len[base + q];
+        const int32_t g = gidx[base + q];
+        if (q == 0 || g != gidx[base + q - 1]) s_gs[g] = (uint16_t)q;
+    }
+    if (t == 0) s_gs[G] = (uint16_t)cnt;
+    __syncthreads();
+    // tokens before every kShortItems-th position
+    int64_t tok;
+    {
+        int64_t v = 0;
+#pragma unroll
+        for (int i = 0; i < kShortItems; ++i) v += t * kShortItems + i < cnt ? s_len[t * kShortItems + i] : 0;
+        const int64_t inc = wave_scan_dpp<OpAdd>(v);
+        if ((t & (kWave - 1)) == kWave - 1) s_w[t / kWave] = inc;
+        // sizes must not decrease up to the last group but one
+        bool odd = false;
+        for (int g = t; g + 2 < G; g += kShortThreads)
+            odd |= s_gs[g + 2] - s_gs[g + 1] < s_gs[g + 1] - s_gs[g] && g + 2 < G;
+        __syncthreads();
+        int64_t pre = inc - v;
+        tok = 0;
+#pragma unroll
+        for (int i = 0; i < kShortThreads / kWave; ++i) {
+            pre += i < t / kWave ? s_w[i] : 0;
+            tok += s_w[i];
+        }
+        s_pre[t] = pre;
+        if (G > T && odd) a.rs->irregular = 1;
+    }
+    __syncthreads();
+    auto tokens_before = [&](int p) {
+        const int c = p / kShortItems;
+        if (c >= kShortThreads) return tok;
+        int64_t v = s_pre[c];
+        for (int q = c * kShortItems; q < p; ++q) v += s_len[q];
+        return v;
+    };
+    // what is emitted: positions [A, B)
+    int A = 0, B = cnt, g0 = 0, js = 0, X = -1;
+    if (G < T) {
+        const int k = T - G;
+        int lo = -1, hi = G - 1;   // surplus(lo) < k <= surplus(hi)
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (s_gs[mid + 1] - (mid + 1) >= k) hi = mid; else lo = mid;
+        }
+        js = hi;
+        X = k + js;
+    } else if (G > T) {
+        // groups 0 .. G-2 larger than the last one: from index `lo` on
+        const int size_last = cnt - s_gs[G - 1];
+        int lo = 0, hi = G - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (s_gs[mid + 1] - s_gs[mid] > size_last) hi = mid; else lo = mid + 1;
+        }
+        g0 = G - 1 - lo < T ? G - T : G - 1 - T;
+        A = s_gs[g0];
+        B = s_gs[g0 + T];
+    }
+    const int64_t emitted = R.emitted, slots = R.slots;
+    const double mean = (double)tok / (double)cnt;
+    for (int j = t; j < T; j += kShortThreads) {
+        const int u = T - 1 - j;   // emission runs short to long
+        int a0, a1;
+        if (u < X) {
+            a0 = u;
+            a1 = u + 1;
+        } else {
+            const int g = X >= 0 ? js + (u - X) : g0 + u;
+            a0 = u == X ? X : s_gs[g];
+            a1 = s_gs[g + 1];
+        }
+        const int64_t o = base + slots + j;
+        a.srows[o] = a1 - a0;
+        a.smax[o] = s_len[a0];
+        a.stok[o] = tokens_before(a1) - tokens_before(a0);
+        a.sadj[o] = (double)(a1 - a0) * mean;
+        a.sroff[o] = emitted + (B - a1);
+    }
+    for (int q = t; q < cnt; q += kShortThreads) {
+        const int32_t id = cur_ids[base + q];
+        if (q >= A && q < B) {
+            const int64_t o = base + emitted + (B - 1 - q);
+            a.dst[o] = id;
+            a.dst_len[o] = s_len[q];
+        } else {
+            const int64_t o = base + (q < A ? q : A + q - B);
+            next_ids[o] = id;
+            next_len[o] = s_len[q];
+        }
+    }
+    __syncthreads();
+    if (t == 0) {
+        R.emitted = emitted + (B - A);
+        R.slots = slots + T;
+        R.next_cnt = A + (cnt - B);
+    }
+}
+
+// Whether the rounds have emptied every buffer; *S receives the steps.
+__device__ __forceinline__ bool short_done(const ShortArgs& a, int64_t* S) {
+    int64_t left = 0;
+    for (int q = threadIdx.x; q < a.W; q += blockDim.x) left += a.ranks[q].cnt;
+    *S = a.rs->cut;
+    return __syncthreads_or(left != 0) == 0 && !a.rs->irregular;
+}
+
+// The staged slots in the plan's layout, in equal ranges as tiles_kernel takes them.
+__global__ void __launch_bounds__(kBlock) short_slots_kernel(ShortArgs a, I64Pair* __restrict__ part,
+                                                             int64_t slot_capacity, int32_t* __restrict__ rows,
+                                                             int32_t* __restrict__ maxlen,
+                                                             int64_t* __restrict__ row_off,
+                                                             int64_t* __restrict__ tokens, double* __restrict__ approx) {
+    if (stage1_bad(a.st)) return;
+    int64_t S;
+    const bool done = short_done(a, &S);
+    const int64_t K = (int64_t)a.W * S;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.rs->overflowed = done ? 0 : 1;   // tiles_kernel: nothing to do yet
+    if (!done || K > slot_capacity) return;
+    const int64_t per = (K + gridDim.x - 1) / gridDim.x;
+    const int64_t k0 = (int64_t)blockIdx.x * per, k1 = k0 + per < K ? k0 + per : K;
+    int64_t cells = 0, real = 0;
+    for (int64_t k = k0 + threadIdx.x; k < k1; k += kBlock) {
+        const int r = (int)(k / S);
+        const int64_t j = k - (int64_t)r * S, base = a.off[r];
+        const bool live = j < a.ranks[r].slots;   // past them: IDLE
+        const int32_t n = live ? a.srows[base + j] : 0, m = live ? a.smax[base + j] : 0;
+        const int64_t tk = live ? a.stok[base + j] : 0;
+        rows[k] = n;
+        maxlen[k] = m;
+        tokens[k] = tk;
+        row_off[k] = live ? base + a.sroff[base + j] : a.off[r + 1];
+        if (approx) approx[k] = live ? a.sadj[base + j] : 0.0;
+        cells += (int64_t)n * m;
+        real += tk;
+    }
+    cells = block_sum(cells);
+    real = block_sum(real);
+    if (threadIdx.x == 0) part[blockIdx.x] = I64Pair{cells, real};
+}
+
+// Row records of rank r = blockIdx.x, the check of the carried lengths against the CSR
+// offsets, and coverage: the rank's rows are its ids, each once (one bit per id).
+__global__ void __launch_bounds__(kShortThreads) short_rows_kernel(ShortArgs a, const int64_t* __restrict__ tok_off,
+                                                                   int64_t* __restrict__ ts, int want_ids,
+                                                                   DevInfo* info) {
+    __shared__ uint32_t s_bit[kRankBlockMax / 32];
+    if (stage1_bad(a.st)) return;
+    int64_t S;
+    if (!short_done(a, &S)) return;
+    const int r = blockIdx.x, t = threadIdx.x;
+    const int64_t base = a.off[r];
+    const int nr = (int)(a.off[r + 1] - base);
+    for (int i = t; i < (int)(kRankBlockMax / 32); i += kShortThreads) s_bit[i] = 0;
+    __syncthreads();
+    int64_t fresh = 0;
+    for (int k = t; k < nr; k += kShortThreads) {
+        const int32_t id = a.dst[base + k];
+        const uint32_t v = (uint32_t)(id - (int32_t)base);
+        if (v >= (uint32_t)nr) {
+            atomicOr(&a.st->err, kErrInternal);
+            continue;
+        }
+        const uint32_t bit = 1u << (v & 31);
+        fresh += (atomicOr(&s_bit[v >> 5], bit) & bit) == 0;
+        const int64_t t0 = tok_off[id], w = tok_off[id + 1] - t0;
+        if (w < 1 || w > INT_MAX || t0 < 0) {
+            atomicOr(&a.st->err, kErrLength);
+            atomicMin((unsigned long long*)&a.st->first_bad_len, (unsigned long long)id);
+        } else if (w != (int64_t)a.dst_len[base + k]) {
+            atomicOr(&a.st->err, kErrSortedLen);
+            atomicMin((unsigned long long*)&a.st->first_bad_csr, (unsigned long long)id);
+        }
+        if (ts) ts[base + k] = t0;
+    }
+    fresh = short_reduce(fresh, SumOp{});
+    if (t == 0 && fresh != nr) {   // nr - fresh ids are missing, as many listings come again
+        atomicAdd((unsigned long long*)&info->bad_views, (unsigned long long)(nr - fresh));
+        if (want_ids) {
+            atomicAdd((unsigned long long*)&info->missing_ids, (unsigned long long)(nr - fresh));
+            atomicAdd((unsigned long long*)&info->duplicate_ids, (unsigned long long)(nr - fresh));
+        }
+    }
+}
+
+// Rounds enqueued before the host first looks (twice as many each further time): windows with
+// capacities take two to six rounds as a rule, and a launch past the last one returns at once.
+constexpr int64_t kShortChunk = 4;
+
+// The plan summary of a device-side alignment, and what it reports.
+int finish_short(const HostState& h, int W, int64_t n, int64_t slot_capacity, int stop, odb_plan_info_t* out) {
+    const int64_t S = h.rs.cut, K = (int64_t)W * S;
+    out->steps = S;
+    out->rounds = (int32_t)h.rs.rounds;
+    out->stop_reason = stop;
+    out->splits = h.rs.splits;
+    out->overflow_groups = h.rs.overflow;
+    out->second_gather_rounds = h.rs.second_gather;
+    out->required_slot_capacity = K;
+    if (K > slot_capacity)
+        return set_error(ODB_E_CAPACITY, "plan needs %lld slots, capacity is %lld", (long long)K,
+                         (long long)slot_capacity);
+    out->max_step_samples = h.rs.step_max;
+    out->emitted_samples = h.info.emitted;
+    out->leftover_samples = n - h.info.emitted;
+    out->real_tokens = h.info.real_tokens;
+    out->padded_elems = h.info.padded_elems;
+    out->missing_ids = h.info.missing_ids;
+    out->duplicate_ids = h.info.duplicate_ids;
+    out->bad_views = h.info.bad_views;
+    out->pad_fraction = h.info.pad_fraction;
+    if (h.st.err & kErrLength)
+        return set_error(ODB_E_INVALID_DATA, "sample %lld has a length outside [1, 2^31) or a negative token offset",
+                         (long long)h.st.first_bad_len);
+    if (h.st.err & kErrSortedLen)
+        return set_error(ODB_E_INVALID_DATA,
+                         "stage-1 arrays do not describe this window (sorted length of sample %lld is not its CSR "
+                         "length)", (long long)h.st.first_bad_csr);
+    if (h.st.err & kErrIdentity)
+        return set_error(ODB_E_INVALID_DATA, "identity map holds a value outside [0, num_identities)");
+    if (h.st.err & kErrInternal) return set_error(ODB_E_INTERNAL, "internal inconsistency in the aligned plan");
+    if (out->bad_views != 0)
+        return set_error(ODB_E_COVERAGE, "%lld sampler views are not emitted (or left over) exactly once",
+                         (long long)out->bad_views);
+    return ODB_OK;
+}
+
 struct RoundBuffers {
     const int32_t* ids;
     const int32_t* len;
@@ -1838,36 +2179,9 @@ extern "C" int odb_align_groups(const odb_window_t* w, int64_t budget, const odb
                              "stage-1 arrays do not describe this window (first inconsistent position %lld)",
                              (long long)h.st.first_bad);
         if (!h.rs.overflowed) {
-            const int64_t S = h.rs.cut, K = (int64_t)W * S;
-            h_info->steps = S;
-            h_info->rounds = 1;
-            h_info->stop_reason = nonjoin && h.rs.quota_hit ? ODB_STOP_QUOTA : ODB_STOP_DRAINED;
-            h_info->splits = h.rs.splits;
-            h_info->second_gather_rounds = h.rs.second_gather;
-            h_info->required_slot_capacity = K;
-            if (K > slot_capacity)
-                return set_error(ODB_E_CAPACITY, "plan needs %lld slots, capacity is %lld", (long long)K,
-                                 (long long)slot_capacity);
-            h_info->max_step_samples = h.rs.step_max;
-            h_info->emitted_samples = h.info.emitted;
-            h_info->leftover_samples = n - h.info.emitted;
-            h_info->real_tokens = h.info.real_tokens;
-            h_info->padded_elems = h.info.padded_elems;
-            h_info->missing_ids = h.info.missing_ids;
-            h_info->duplicate_ids = h.info.duplicate_ids;
-            h_info->pad_fraction = h.info.pad_fraction;
-            if (h.st.err & kErrLength)
-                return set_error(ODB_E_INVALID_DATA,
-                                 "sample %lld has a length outside [1, 2^31) or a negative token offset",
-                                 (long long)h.st.first_bad_len);
-            if (h.st.err & kErrSortedLen)
-                return set_error(ODB_E_INVALID_DATA,
-                                 "stage-1 arrays do not describe this window (sorted length of sample %lld is not its "
-                                 "CSR length)", (long long)h.st.first_bad_csr);
-            if (h.st.err & kErrIdentity)
-                return set_error(ODB_E_INVALID_DATA, "identity map holds a value outside [0, num_identities)");
-            if (h.st.err & kErrInternal) return set_error(ODB_E_INTERNAL, "internal inconsistency in the aligned plan");
-            return ODB_OK;
+            h.rs.rounds = 1;
+            return finish_short(h, W, n, slot_capacity, nonjoin && h.rs.quota_hit ? ODB_STOP_QUOTA : ODB_STOP_DRAINED,
+                                h_info);
         }
         // some rank overflows: start over, round by round
         ODB_TRY(upload_small(w, L, d_ws, cap, s));
@@ -1877,6 +2191,78 @@ extern "C" int odb_align_groups(const odb_window_t* w, int64_t budget, const odb
                        d_gbase, st, d_rs, d_info);
     ODB_LAUNCHED();
     if (n > 0) {
+        hipLaunchKernelGGL(round0_check_kernel, dim3(gridn), dim3(kBlock), 0, s, d_off, (const RankState*)d_ranks, W,
+                           n, d_order, d_sorted_len, d_group_index, gstart, st);
+        ODB_LAUNCHED();
+    }
+
+    // ---- rounds of short ranks
+    if (n > 0 && !nonjoin && max_nr <= kRankBlockMax && chain_fits(budget, max_nr)) {
+        ShortArgs a{};
+        a.W = W;
+        a.has_cap = cap ? 1 : 0;
+        a.cap = d_cap;
+        a.off = d_off;
+        a.ranks = d_ranks;
+        a.rs = d_rs;
+        a.st = st;
+        a.dst = d_emit_order;
+        a.dst_len = row_len;
+        a.srows = srows;
+        a.smax = smax;
+        a.stok = stok;
+        a.sadj = sadj;
+        a.sroff = ws_at<int64_t>(d_ws, L.row_ts);
+        OneArgs tl{};   // what tiles_kernel reads
+        tl.W = W;
+        tl.slot_capacity = slot_capacity;
+        tl.lo = const_cast<int64_t*>(d_off);
+        tl.part = ws_at<I64Pair>(d_ws, L.cs);
+        tl.rs = d_rs;
+        tl.info = d_info;
+        tl.st = st;
+        const unsigned ranges = grid_for(n, 64, kMaxRanges);
+        const int32_t *ids = d_order, *len = d_sorted_len, *gix = d_group_index;
+        int f = 0;
+        HostState h;
+        bool redo = false;
+        // join mode emits every view, so the identities count over all of them
+        if (w->d_identity) ODB_TRY(count_identities(w, L, d_ws, d_order, n, nullptr, 0, s));
+        for (int64_t more = kShortChunk;; more *= 2) {
+            for (int64_t k = 0; k < more; ++k) {
+                hipLaunchKernelGGL(short_round_kernel, dim3(W), dim3(kShortThreads), 0, s, a, ids, len, gix, bids[f],
+                                   blen[f]);
+                ODB_LAUNCHED();
+                ODB_TRY(group_short_ranks(W, budget, max_nr, d_off, blen[f], wgidx, d_ranks, st, s));
+                ids = bids[f];
+                len = blen[f];
+                gix = wgidx;
+                f ^= 1;
+            }
+            // the final plan, if these rounds were enough
+            hipLaunchKernelGGL(short_slots_kernel, dim3(ranges), dim3(kBlock), 0, s, a, tl.part, slot_capacity, d_slot_rows,
+                               d_slot_maxlen, d_slot_row_off, d_slot_tokens, d_slot_tokens_approx);
+            ODB_LAUNCHED();
+            hipLaunchKernelGGL(tiles_kernel, dim3(ranges), dim3(kBlock), 0, s, tl, (const int32_t*)d_slot_rows,
+                               (const int32_t*)d_slot_maxlen, d_slot_row_off, d_slot_tile_off, d_leftover_off);
+            ODB_LAUNCHED();
+            hipLaunchKernelGGL(short_rows_kernel, dim3(W), dim3(kShortThreads), 0, s, a, w->d_token_offsets,
+                               d_row_token_start, w->d_identity ? 0 : 1, d_info);
+            ODB_LAUNCHED();
+            ODB_TRY(read_state(L, d_ws, 0, &h, s));
+            if (h.st.err & (kErrOrder | kErrGroupIndex))
+                return set_error(ODB_E_INVALID_DATA,
+                                 "stage-1 arrays do not describe this window (first inconsistent position %lld)",
+                                 (long long)h.st.first_bad);
+            redo = h.rs.irregular != 0;
+            if (redo || !h.rs.overflowed) break;
+            if (h.rs.rounds > n) return set_error(ODB_E_INTERNAL, "alignment does not end");
+        }
+        if (!redo) return finish_short(h, W, n, slot_capacity, ODB_STOP_DRAINED, h_info);
+        ODB_TRY(upload_small(w, L, d_ws, cap, s, true));
+        hipLaunchKernelGGL(round0_ranks_kernel, dim3(1), dim3(kBlock), 0, s, d_off, d_groups_per_rank, W, d_ranks,
+                           d_gbase, st, d_rs, d_info);
+        ODB_LAUNCHED();
         hipLaunchKernelGGL(round0_check_kernel, dim3(gridn), dim3(kBlock), 0, s, d_off, (const RankState*)d_ranks, W,
                            n, d_order, d_sorted_len, d_group_index, gstart, st);
         ODB_LAUNCHED();

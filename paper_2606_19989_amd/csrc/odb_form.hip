@@ -495,13 +495,6 @@ constexpr int kRankThreads = 1024;
 constexpr int kRankWaves = kRankThreads / kWave;
 constexpr int kRankItems = 4;                     // lengths a thread loads at once in the first pass
 constexpr int kRankGroup = 4;                     // rounds of a pass whose items are loaded together
-// Samples of the largest rank grouped this way.  A block's pass over its rank is bound by
-// the issue rate of its one compute unit (every round of 1024 items costs each of its 16
-// waves a few hundred instructions: ~2.7 us per round on MI355X), so larger ranks go to the
-// multi-block path, whose launches and one synchronisation cost less than a block's
-// rounds from about this size on.
-constexpr int64_t kRankBlockMax = 16384;
-
 // Exclusive scan of v over the first 256 threads of a kRankThreads block (4 waves), every
 // thread of the block taking part in the barriers; *total receives the sum.
 __device__ __forceinline__ uint32_t scan256(uint32_t v, uint32_t* total) {
@@ -835,7 +828,8 @@ struct RunTable {
 };
 
 // kIndex: write the group indices here (short ranks); otherwise leave the run table.
-// sq = floor(sqrt(budget)); by_step: at most kRunCap - 2 steps are possible for this budget
+// ranks (or null: whole ranks): an alignment round's buffers; with kIndex the next round's,
+// whose count becomes current here.  sq = floor(sqrt(budget)); by_step: at most kRunCap - 2 steps are possible for this budget
 // and length range (otherwise the rank holds at most kRunCap samples).
 template <bool kIndex>
 __global__ void __launch_bounds__(kChainThreads) chain_kernel(const int64_t* __restrict__ off, RankState* ranks,
@@ -848,8 +842,9 @@ __global__ void __launch_bounds__(kChainThreads) chain_kernel(const int64_t* __r
     __shared__ int32_t s_len[kChainThreads];
     const int r = blockIdx.x;
     const int64_t base = off[r];
-    const int cnt = (int)(ranks ? ranks[r].cnt : off[r + 1] - base);
+    const int cnt = (int)(ranks ? (kIndex ? ranks[r].next_cnt : ranks[r].cnt) : off[r + 1] - base);
     const int t = threadIdx.x;
+    if (kIndex && ranks && t == 0) ranks[r].cnt = cnt;
     if (cnt <= 1) {   // no position >= 1, no run: position 0 (if any) is the only group start
         if (t == 0) {
             if (kIndex && cnt == 1) gidx[base] = 0;
@@ -1205,6 +1200,17 @@ enum ChainBy { kChainByStep, kChainBySample, kChainJump };
 static ChainBy chain_by(int64_t budget, int64_t max_cnt, int64_t len_range) {
     if (2 * (isqrt(budget) + 1) <= kRunCap || (len_range > 0 && len_range + 4 <= kRunCap)) return kChainByStep;
     return max_cnt <= kRunCap ? kChainBySample : kChainJump;
+}
+
+bool chain_fits(int64_t budget, int64_t max_cnt) { return chain_by(budget, max_cnt, 0) != kChainJump; }
+
+int group_short_ranks(int W, int64_t budget, int64_t max_cnt, const int64_t* d_rank_off, const int32_t* d_slen,
+                      int32_t* d_gidx, RankState* d_ranks, DevStatus* st, hipStream_t s) {
+    hipLaunchKernelGGL(chain_kernel<true>, dim3(W), dim3(kChainThreads), 0, s, d_rank_off, d_ranks, d_slen, budget,
+                       isqrt(budget), chain_by(budget, max_cnt, 0) == kChainByStep ? 1 : 0, d_gidx, (int32_t*)nullptr,
+                       RunTable{}, (const int64_t*)nullptr, st);
+    ODB_LAUNCHED();
+    return ODB_OK;
 }
 
 // Mark scan, group index of every position, global group starts, G_r.

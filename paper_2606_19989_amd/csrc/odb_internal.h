@@ -100,6 +100,8 @@ struct RoundState {
     int64_t leftover_total;  // samples back in buffers after this round
     int64_t second_gather;   // rounds in which some active rank had G_r != T (all rounds)
     int64_t overflowed;      // a one-round alignment met a rank that overflows
+    int64_t irregular;       // stage-1 groups the short ranks' rounds cannot take
+    int64_t rounds;          // rounds run (short ranks)
 };
 
 // Final summary assembled on the device (mirrors odb_plan_info_t's counters).
@@ -459,6 +461,19 @@ int device_excl_scan(Load load, Store store, int64_t n, Out* partials, hipStream
 // len_range = max_len - min_len + 1 of the sequences if known (0 otherwise); it only
 // selects between the two equivalent ways of finding the chain (see odb_form.hip).
 // tiles_ready: workspace tile_first already holds the sort tiles of d_rank_off.
+// One alignment round's grouping of short ranks (at most kRankBlockMax samples, and steps
+// that chain_fits): rank r's buffer of d_ranks[r].next_cnt lengths at its own positions; sets
+// cnt, G and every live position's group index.  One launch, one block per rank.
+// Samples of the largest rank grouped this way.  A block's pass over its rank is bound by
+// the issue rate of its one compute unit (every round of 1024 items costs each of its 16
+// waves a few hundred instructions: ~2.7 us per round on MI355X), so larger ranks go to the
+// multi-block path, whose launches and one synchronisation cost less than a block's
+// rounds from about this size on.
+constexpr int64_t kRankBlockMax = 16384;
+bool chain_fits(int64_t budget, int64_t max_cnt);
+int group_short_ranks(int W, int64_t budget, int64_t max_cnt, const int64_t* d_rank_off, const int32_t* d_slen,
+                      int32_t* d_gidx, RankState* d_ranks, DevStatus* st, hipStream_t s);
+
 int group_sequences(const Layout& L, void* ws, int W, int64_t n, int64_t budget,
                     const int64_t* d_rank_off, int64_t max_cnt, int64_t len_range, bool tiles_ready,
                     const int32_t* d_slen, int32_t* d_gidx, int32_t* d_groups_out,

@@ -639,3 +639,119 @@ def test_one_round_windows(idx):
     compare_plan(w, pipe, ref)
     compare_loss_weights(pipe, ref)
     compare_collate_full(w, outs, ref, pad_id=idx)
+
+
+def short_round_windows():
+    """Join windows of short ranks that take several rounds: rank sizes at the edges of the
+    kernels (1, 1,023 .. 1,025, 16,383 and 16,384 positions; 16,385 takes the general path),
+    rounds past the first chunk, the last group kept and returned, ranks that end early, a
+    rank without capacity, an identity map, and steps listed from the budget or the samples."""
+    rng = np.random.default_rng(92)
+    U = lambda lo, hi, n: rng.integers(lo, hi, size=n)
+    win = synth.window_from_ranks
+    out = []
+    for n in (1, 2, 1023, 1024, 1025, 16383, 16384, 16385):
+        out.append(win(f"ranks_{n}", [U(10, 900, n), U(10, 900, max(1, n // 3))], 9000,
+                       capacity=np.array([max(1, n // 90), 3 + n // 50])))
+    out.append(win("one_slot", [U(10, 300, 700), U(10, 300, 650)], 2000, capacity=np.array([1, 0])))
+    out.append(win("many_ranks", [U(10, 900, 300 + 5 * r) for r in range(67)], 4096,
+                   capacity=np.arange(67) % 5 * 9))
+    out.append(win("empty_and_small", [U(10, 900, 900), U(1, 2, 0), U(10, 900, 40), U(10, 900, 1)], 4096,
+                   capacity=np.array([11, 4, 0, 2])))
+    # equal lengths: the last group is one short of, equal to and one past a full one
+    for n in (1 + 8 * 12 - 1, 1 + 8 * 12, 1 + 8 * 12 + 1, 9, 10):
+        out.append(win(f"equal_{n}", [np.full(n, 100), U(50, 150, n + 5)], 800, capacity=np.array([4, 0])))
+    out.append(win("tail_kept", [np.concatenate([U(400, 500, 60), U(10, 20, 90)]) for _ in range(3)], 1000,
+                   capacity=np.array([7, 9, 0])))
+    out.append(win("no_capacity", [U(500, 900, 900), U(10, 20, 5), U(100, 200, 300)], 1000))
+    ident = np.concatenate([rng.permutation(1990), np.arange(10)]).astype(np.int64)
+    out.append(win("identities", [U(10, 400, 500) for _ in range(4)], 2048, capacity=np.array([9, 0, 30, 12]),
+                   identity=ident, num_identities=1990))
+    out.append(win("by_sample", [U(1, 20000, 3000), U(1, 20000, 3500)], 1 << 40, capacity=np.array([1, 1])))
+    out.append(win("general_steps", [U(1, 20000, 9000), U(1, 20000, 3500)], 1 << 40, capacity=np.array([1, 1])))
+    return out
+
+
+@pytest.mark.parametrize("idx", range(len(short_round_windows())))
+def test_short_rank_rounds(idx):
+    w = short_round_windows()[idx]
+    log(f"short ranks: {w.name}")
+    ref = oracle.plan_window(w)
+    pipe, outs = run_gpu(w, pad_id=idx)
+    compare_plan(w, pipe, ref)
+    compare_loss_weights(pipe, ref)
+    compare_collate_full(w, outs, ref, pad_id=idx)
+
+
+def _align_reference(lens, groups, caps, budget):
+    """Algorithm 1 over given first-round groups (lists of group sizes per rank, formation order
+    over samples sorted by length desc, id asc): per rank the steps' (rows, longest, tokens)."""
+    buf, steps = [], [[] for _ in lens]
+    for r, l in enumerate(lens):
+        o = np.lexsort((np.arange(len(l)), -l))
+        buf.append((list(l[o]), np.cumsum([0] + list(groups[r]))[:-1].tolist() if len(l) else []))
+    while any(b for b, _ in buf):
+        T = max(len(g) for _, g in buf)
+        T = max(1, min([T] + [len(b) for b, _ in buf if b] + [c for c, (b, _) in zip(caps, buf) if c > 0 and b]))
+        nxt = []
+        for r, (b, g) in enumerate(buf):
+            parts = [b[x:y] for x, y in zip(g, g[1:] + [len(b)])]
+            back = []
+            if b and len(parts) < T:
+                k, split = T - len(parts), []
+                for p in parts:
+                    while k and len(p) > 1:
+                        split.append(p[:1])
+                        p, k = p[1:], k - 1
+                    split.append(p)
+                parts = split
+            elif len(parts) > T:
+                keep = set(sorted(range(len(parts)), key=lambda i: (-len(parts[i]), -i))[:T])
+                back = [x for i, p in enumerate(parts) if i not in keep for x in p]
+                parts = [p for i, p in enumerate(parts) if i in keep]
+            for j in range(T):
+                p = parts[T - 1 - j] if parts else []
+                steps[r].append((len(p), p[0] if p else 0, sum(p)))
+            g2, p = [], 0
+            while p < len(back):
+                g2.append(p)
+                p += 1 if p == 0 else max(budget // int(back[p - 1]), 1)
+            nxt.append((back, g2))
+        buf = nxt
+    return np.array(steps)
+
+
+@pytest.mark.parametrize("sizes", ["uneven", "falling", "fixed"])
+@pytest.mark.parametrize("capped", [False, True])
+def test_align_takes_any_consistent_groups(sizes, capped):
+    """Group indices that odb_form_groups would not write (sizes that go up and down, or fall)
+    are accepted as long as they step by 0 or 1, with and without overflow."""
+    import torch
+    import paper_2606_19989_amd as odb
+
+    rng = np.random.default_rng(93)
+    lens = [rng.integers(1, 500, size=n) for n in (700, 655)]
+    groups = []
+    for l in lens:
+        left, s = len(l), []
+        while left:
+            c = {"uneven": int(rng.integers(1, 30)), "falling": max(1, 40 - len(s)), "fixed": 7}[sizes]
+            s.append(min(c, left))
+            left -= s[-1]
+        groups.append(s)
+    caps = np.array([9, 14]) if capped else None
+    w = synth.window_from_ranks("custom_groups", lens, 4000, capacity=caps)
+    tok_off, toks, _ = synth.device_tensors(w, "cuda")
+    win_ = odb.DeviceWindow(w.rank_off, tok_off, toks)
+    pipe = odb.Pipeline(win_, w.budget, capacity=caps)
+    pipe.form()
+    gidx = np.concatenate([np.repeat(np.arange(len(s)), s) for s in groups]).astype(np.int32)
+    pipe.group_index.copy_(torch.from_numpy(gidx))
+    pipe.groups_per_rank.copy_(torch.tensor([len(s) for s in groups], dtype=torch.int32))
+    info = pipe.align()
+    ref = _align_reference(lens, groups, [0, 0] if caps is None else caps, w.budget)
+    K = 2 * ref.shape[1]
+    assert info["steps"] == ref.shape[1] and info["emitted_samples"] == w.n and info["bad_views"] == 0
+    assert np.array_equal(pipe.slot_rows[:K].cpu().numpy(), ref[:, :, 0].reshape(-1))
+    assert np.array_equal(pipe.slot_maxlen[:K].cpu().numpy(), ref[:, :, 1].reshape(-1))
+    assert np.array_equal(pipe.slot_tokens[:K].cpu().numpy(), ref[:, :, 2].reshape(-1))
