@@ -20,8 +20,9 @@
  *   - Pointers named d_* are device pointers (HIP global memory on the current device);
  *     all other pointers are host pointers.  The caller owns every buffer; the library
  *     allocates no device memory (scratch comes from the caller's workspace), keeps no
- *     pointer after returning and holds no state except a thread-local error message and
- *     the fixed per-device scratch array of odb_collate_static.
+ *     pointer after returning and holds no state except a thread-local error message, 64 KB of
+ *     pinned host memory per calling thread (results are read back through it; freed when
+ *     the thread ends) and the fixed per-device scratch array of odb_collate_static.
  *   - `stream` is a hipStream_t (NULL = the legacy default stream).  Work is enqueued
  *     on it in order.  odb_align_groups synchronises `stream` because its output sizes
  *     are data dependent; odb_form_groups does so only on its multi-block path (ranks of
@@ -456,7 +457,7 @@ size_t odb_stream_workspace_size(const odb_window_t* w, int32_t depth, int64_t s
  *   d_left_off       [W+1] out
  *   h_trace          [max_rounds] host out, or NULL: one record per round
  * Rounds up to the first one that overflows (G_r > T for some rank) are run together; the
- * call synchronises `stream` once for them (twice in non-join mode).  From a round that
+ * call synchronises `stream` once for them.  From a round that
  * overflows on, and from the start when a positive slot_capacity is smaller than a rank's
  * largest buffer, rounds are enqueued in chunks, each as long as a lower bound on the rounds
  * left (from the sampler cursors, the rates and, non-join, the quota; at least 8 after the

@@ -1118,8 +1118,7 @@ int finish_coverage(const odb_window_t* w, const Layout& L, void* ws, const int3
     hipLaunchKernelGGL(clear_view_counters_kernel, dim3(1), dim3(64), 0, s, info, w->d_identity ? 0 : 1);
     ODB_LAUNCHED();
     ODB_TRY(run_coverage_exact(w, L, ws, emitted, ne, left, nl, s));
-    ODB_TRY_HIP(hipMemcpyAsync(hi, info, sizeof(*hi), hipMemcpyDeviceToHost, s));
-    ODB_TRY_HIP(hipStreamSynchronize(s));
+    ODB_TRY(read_device(hi, info, sizeof(*hi), s));
     return ODB_OK;
 }
 
@@ -2456,11 +2455,10 @@ extern "C" int odb_check_coverage(const odb_window_t* w, const int32_t* d_emitte
                        ws_at<DevInfo>(d_ws, L.info));
     ODB_LAUNCHED();
     ODB_TRY(run_coverage(w, L, d_ws, d_emitted, num_emitted, d_leftover, num_leftover, s));
-    DevInfo hi;
-    DevStatus hs;
-    ODB_TRY_HIP(hipMemcpyAsync(&hi, ws_at<DevInfo>(d_ws, L.info), sizeof(hi), hipMemcpyDeviceToHost, s));
-    ODB_TRY_HIP(hipMemcpyAsync(&hs, ws_at<DevStatus>(d_ws, L.status), sizeof(hs), hipMemcpyDeviceToHost, s));
-    ODB_TRY_HIP(hipStreamSynchronize(s));
+    HostState h;
+    ODB_TRY(read_state(L, d_ws, 0, &h, s));
+    DevInfo& hi = h.info;
+    const DevStatus& hs = h.st;
     ODB_TRY(finish_coverage(w, L, d_ws, d_emitted, num_emitted, d_leftover, num_leftover, &hi, s));
     h_info->bad_views = hi.bad_views;
     h_info->missing_ids = hi.missing_ids;

@@ -718,8 +718,7 @@ extern "C" int odb_collate_status(void* d_ws, size_t ws_bytes, void* stream) {
     hipStream_t s = static_cast<hipStream_t>(stream);
     DevStatus* st = static_cast<DevStatus*>(d_ws);  // the status word sits at offset 0
     int32_t v = 0;
-    ODB_TRY_HIP(hipMemcpyAsync(&v, &st->collate_err, sizeof(v), hipMemcpyDeviceToHost, s));
-    ODB_TRY_HIP(hipStreamSynchronize(s));
+    ODB_TRY(read_device(&v, &st->collate_err, sizeof(v), s));
     hipLaunchKernelGGL(clear_collate_status_kernel, dim3(1), dim3(64), 0, s, st);
     ODB_LAUNCHED();
     if (v) return set_error(ODB_E_INVALID_DATA, "collate met an inconsistent plan");

@@ -188,11 +188,33 @@ int upload_small(const odb_window_t* w, const Layout& L, void* ws, const int64_t
     return ODB_OK;
 }
 
+namespace {
+struct ReadPage {
+    void* p = nullptr;
+    ~ReadPage() {
+        if (p) (void)hipHostFree(p);
+    }
+};
+thread_local ReadPage g_page;
+}  // namespace
+
+int read_device(void* dst, const void* src, size_t bytes, hipStream_t s) {
+    if (bytes <= kReadBytes && !g_page.p &&
+        hipHostMalloc(&g_page.p, kReadBytes, hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();   // no pinned memory: read into pageable memory
+        g_page.p = nullptr;
+    }
+    void* to = bytes <= kReadBytes && g_page.p ? g_page.p : dst;
+    ODB_TRY_HIP(hipMemcpyAsync(to, src, bytes, hipMemcpyDeviceToHost, s));
+    ODB_TRY_HIP(hipStreamSynchronize(s));
+    if (to != dst) memcpy(dst, to, bytes);
+    return ODB_OK;
+}
+
 int read_state(const Layout& L, void* ws, int W, HostState* h, hipStream_t s) {
     const size_t bytes = L.ranks + sizeof(RankState) * (size_t)W - L.status;
     h->buf.resize(bytes);
-    ODB_TRY_HIP(hipMemcpyAsync(h->buf.data(), ws_at<char>(ws, L.status), bytes, hipMemcpyDeviceToHost, s));
-    ODB_TRY_HIP(hipStreamSynchronize(s));
+    ODB_TRY(read_device(h->buf.data(), ws_at<char>(ws, L.status), bytes, s));
     const char* b = h->buf.data();
     memcpy(&h->st, b, sizeof(DevStatus));
     memcpy(&h->rs, b + (L.round - L.status), sizeof(RoundState));

@@ -1335,8 +1335,7 @@ extern "C" int odb_form_groups(const odb_window_t* w, int64_t budget, int32_t* d
                        w->d_token_offsets, n, len, st);
     ODB_LAUNCHED();
     DevStatus hs;
-    ODB_TRY_HIP(hipMemcpyAsync(&hs, st, sizeof(DevStatus), hipMemcpyDeviceToHost, s));
-    ODB_TRY_HIP(hipStreamSynchronize(s));
+    ODB_TRY(read_device(&hs, st, sizeof(DevStatus), s));
     if (hs.err & kErrLength)
         return set_error(ODB_E_INVALID_DATA,
                          "sample %lld has a length outside [1, 2^31) or a negative token offset",

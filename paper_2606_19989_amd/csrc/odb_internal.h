@@ -152,6 +152,14 @@ int upload_small(const odb_window_t* w, const Layout& L, void* d_ws, const int64
 int store_values(const int64_t* src, int64_t count, int64_t* dst, DevStatus* st, hipStream_t s,
                  RoundState* rs = nullptr, DevInfo* info = nullptr);
 
+// Reads `bytes` device bytes to `dst` and synchronises the stream.  Small reads (kReadBytes)
+// go through a page of pinned memory that the calling thread keeps until it ends: a copy to
+// pageable memory followed by the synchronisation takes 24 us behind an empty kernel, to
+// pinned memory 14 us (11 us without a copy).  Every call that reads synchronises before it
+// returns, so a thread never has two reads in flight.
+constexpr size_t kReadBytes = 64 * 1024;
+int read_device(void* dst, const void* src, size_t bytes, hipStream_t s);
+
 // Host copy of the status word, round state, summary and per-rank state, read with one
 // device-to-host copy (the workspace keeps them next to each other) and one
 // synchronisation of the stream.

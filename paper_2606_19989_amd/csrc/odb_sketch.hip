@@ -160,8 +160,7 @@ extern "C" int odb_length_sketch(const odb_window_t* w, const int32_t* d_ids, in
         ODB_LAUNCHED();
     }
     DevSketch h;
-    ODB_TRY_HIP(hipMemcpyAsync(&h, d, sizeof(h), hipMemcpyDeviceToHost, s));
-    ODB_TRY_HIP(hipStreamSynchronize(s));
+    ODB_TRY(read_device(&h, d, sizeof(h), s));
     if (h.err & kSketchBadId) return set_error(ODB_E_INVALID_DATA, "a sketch id lies outside the window");
     if (h.err & kSketchBadLength) return set_error(ODB_E_INVALID_DATA, "a sketched sample has length < 1 or >= 2^31");
     h_out->samples = h.n;

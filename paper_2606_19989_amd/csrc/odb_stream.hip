@@ -2111,8 +2111,7 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
         // the state and, next to it, the targets
         const size_t bytes = SL.bulk_T - SL.bulk_st + 4 * (h_trace ? bs.E : 0);
         std::vector<char> back(bytes);
-        ODB_TRY_HIP(hipMemcpyAsync(back.data(), b.st, bytes, hipMemcpyDeviceToHost, s));
-        ODB_TRY_HIP(hipStreamSynchronize(s));
+        ODB_TRY(read_device(back.data(), b.st, bytes, s));
         memcpy(&hb, back.data(), sizeof(hb));
         if (hb.err & kSErrInternal) return set_error(ODB_E_INTERNAL, "streaming round state inconsistent");
         // bad data: the sequential rounds report what the iteration meets
