@@ -957,7 +957,7 @@ constexpr int64_t kBulkBlocks = int64_t(1) << 22;   // rank-rounds of one launch
 
 struct BulkState {
     int64_t steps;        // S: aligned steps, after a quota cut
-    int64_t emitted;      // views emitted in the last round, after a quota cut
+    int64_t emitted;      // views emitted, after a quota cut
     int64_t splits;
     int64_t changed;      // rounds in which some rank had G_r != T
     int64_t fail;         // first round with an overflow (rounds formed if none)
@@ -966,6 +966,8 @@ struct BulkState {
     unsigned long long real_tokens;
     unsigned long long bad_views;
     int64_t padded;
+    int64_t missing_ids;
+    int64_t duplicate_ids;
     int32_t err;
     int32_t pad;
 };
@@ -987,7 +989,10 @@ struct BulkArgs {
     int32_t* G;                 // [W * E] group counts, rank-major
     int32_t* gs;                // [W * q] group starts, rank r's round e from r * q + e * n_r on
     int64_t* tile;              // [W * E] padded elements of the rank's slots of the round
-    int64_t* stepsum;           // [D] samples per step of the round the quota cuts
+    // non-join: [W + 1] first emitted row of every rank; null in join mode (rank r's q rows
+    // from r * q on)
+    int64_t* lo;
+    int64_t quota;              // non-join: INT64_MAX if the quota is not reached in these rounds
     // per view, rank r's stream from r * q on
     int32_t* views;
     int32_t* ids;
@@ -1037,7 +1042,6 @@ __global__ void bulk_init_kernel(BulkArgs b, DevStatus* st) {
         st->min_len = 0xFFFFFFFFu;
         st->max_len = 0;
     }
-    for (int64_t i = t; i < b.D; i += blockDim.x) b.stepsum[i] = 0;
     for (int64_t i = t; i < b.E; i += blockDim.x) {
         b.T[i] = 0;
         b.sum[i] = 0;
@@ -1299,6 +1303,106 @@ __global__ void __launch_bounds__(1024) bulk_targets_kernel(BulkArgs b) {
     }
 }
 
+// Where a split leaves its pieces: positions [0, X) are singletons, [X, end of group j*) is one
+// group and later groups are unchanged; j* is the first group with start(j* + 1) - (j* + 1) >=
+// T - G (the surplus of groups 0 .. j* is their samples less their number).  X = -1: no split.
+struct BulkSplit {
+    int js, X;
+};
+
+__device__ __forceinline__ BulkSplit bulk_split(const int32_t* __restrict__ gs, int G, int T) {
+    const int k = T - G;
+    if (k <= 0) return BulkSplit{0, -1};
+    int lo = -1, hi = G - 1;   // surplus(lo) < k <= surplus(hi) = n - G (no rank holds fewer than T views)
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (gs[mid + 1] - (mid + 1) >= k) hi = mid; else lo = mid;
+    }
+    return BulkSplit{hi, k + hi};
+}
+
+// Positions [*a0, *a1) of adjusted group t of a buffer of n > 0 views in G groups.
+__device__ __forceinline__ void bulk_group(const int32_t* gs, int G, int n, BulkSplit sp, int t, int* a0, int* a1) {
+    if (t < sp.X) {
+        *a0 = t;
+        *a1 = t + 1;
+        return;
+    }
+    const int g = sp.X >= 0 ? sp.js + (t - sp.X) : t;
+    *a0 = t == sp.X ? sp.X : gs[g];
+    *a1 = g + 1 < G ? gs[g + 1] : n;
+}
+
+// Non-join: the steps of the last round up to the one that reaches the quota, and from them
+// every rank's emitted rows (lo: their running sum over the ranks) and left-over views.  One
+// block; dynamic LDS: a BulkSplit per rank.
+__global__ void __launch_bounds__(kST) bulk_cut_kernel(BulkArgs b, int64_t before, int64_t* __restrict__ left_off) {
+    extern __shared__ unsigned long long s_dyn[];
+    BulkSplit* s_sp = reinterpret_cast<BulkSplit*>(s_dyn);
+    if (b.st->err || b.st->fail < b.E) return;
+    const int64_t e = b.E - 1;
+    const int T = b.T[e];
+    for (int r = threadIdx.x; r < b.W; r += kST) {
+        int64_t c, n;
+        bulk_range(b, r, e, &c, &n);
+        s_sp[r] = n > 0 ? bulk_split(b.gs + (int64_t)r * b.q + c, b.G[(int64_t)r * b.E + e], T) : BulkSplit{0, -1};
+    }
+    __shared__ int s_cut;
+    if (threadIdx.x == 0) s_cut = T;
+    __syncthreads();
+    int64_t carry = before;
+    for (int j0 = 0; j0 < T && carry < b.quota; j0 += kST) {   // uniform
+        const int j = j0 + threadIdx.x;
+        int64_t v = 0;
+        if (j < T) {
+#pragma unroll 4
+            for (int r = 0; r < b.W; ++r) {
+                int64_t c, n;
+                bulk_range(b, r, e, &c, &n);
+                if (n == 0) continue;
+                int a0, a1;
+                bulk_group(b.gs + (int64_t)r * b.q + c, b.G[(int64_t)r * b.E + e], (int)n, s_sp[r], T - 1 - j, &a0, &a1);
+                v += a1 - a0;
+            }
+        }
+        int64_t tot;
+        const int64_t ex = carry + sblock_excl<kST>(v, &tot);
+        if (j < T && ex < b.quota && ex + v >= b.quota) s_cut = j + 1;
+        carry += tot;
+    }
+    __syncthreads();
+    const int cut = s_cut;
+    int64_t rows = 0, left = 0;
+    for (int r0 = 0; r0 < b.W; r0 += kST) {
+        const int r = r0 + threadIdx.x;
+        int64_t out = 0, stay = 0;
+        if (r < b.W) {
+            int64_t c, n;
+            bulk_range(b, r, e, &c, &n);
+            int a0 = 0, a1;
+            if (n > 0 && cut < T)
+                bulk_group(b.gs + (int64_t)r * b.q + c, b.G[(int64_t)r * b.E + e], (int)n, s_sp[r], T - cut, &a0, &a1);
+            out = c + n - a0;
+            stay = b.q - out;
+        }
+        int64_t to, ts;
+        const int64_t xo = sblock_excl<kST>(out, &to), xs = sblock_excl<kST>(stay, &ts);
+        if (r < b.W) {
+            b.lo[r] = rows + xo;
+            left_off[r] = left + xs;
+        }
+        rows += to;
+        left += ts;
+    }
+    if (threadIdx.x == 0) {
+        b.lo[b.W] = rows;
+        left_off[b.W] = left;
+        b.st->cut = cut;
+        b.st->emitted = rows;
+        b.st->steps = b.base[e] + cut;
+    }
+}
+
 // Where the slots go: the staging (rank r's step x at r * scap + x) or, with `fin` set, the
 // window plan layout (r * S + x) with row offsets and, within the rank-round, tile offsets.
 struct BulkSlots {
@@ -1309,7 +1413,6 @@ struct BulkSlots {
     int64_t* row_off;     // fin
     int64_t* tile_off;    // fin
     int fin;
-    int64_t cut_round;    // the round whose step sizes are wanted (a quota cut), or -1
 };
 
 // Slots of rank r in round e: the groups are split (Algorithm 1) to T_e; a group's tokens
@@ -1320,8 +1423,7 @@ __global__ void __launch_bounds__(NT) bulk_slots_kernel(BulkArgs b, BulkSlots o)
 #pragma clang fp contract(off)
     constexpr int P = NT * KPT;
     __shared__ int64_t s_tok[P + 1];   // tokens of the first i rows of the emission order
-    __shared__ int32_t s_gs[P + 1];
-    __shared__ int64_t s_X, s_js;
+    __shared__ int32_t s_gs[P];
     __shared__ int s_go;
     int64_t e;
     int r;
@@ -1339,25 +1441,24 @@ __global__ void __launch_bounds__(NT) bulk_slots_kernel(BulkArgs b, BulkSlots o)
     const int T = b.T[e], G = b.G[(int64_t)r * b.E + e];
     const int64_t base = b.base[e];
     const int64_t in = (int64_t)r * b.q + c0;
+    const int64_t row0 = (b.lo ? b.lo[r] : (int64_t)r * b.q) + c0;   // rows of the rank's rounds before
     const int64_t dst = o.fin ? (int64_t)r * S + base : (int64_t)r * b.scap + base;
-    const int64_t room = o.fin ? T : b.scap - base;   // staged steps: those below the capacity
+    // slots to write: all, those kept by a quota cut, or the steps below the staging's capacity
+    const int64_t room = !o.fin ? b.scap - base : b.lo && e + 1 == b.E ? b.st->cut : T;
+    const int m = (int)(room < T ? (room > 0 ? room : 0) : T);
     if (n == 0) {
-        for (int j = tid; j < T && j < room; j += NT) {
+        for (int j = tid; j < m; j += NT) {
             o.rows[dst + j] = 0;
             o.maxlen[dst + j] = 0;
             o.tokens[dst + j] = 0;
             if (o.approx) o.approx[dst + j] = 0.0;
             if (o.fin) {
-                o.row_off[dst + j] = in;
+                o.row_off[dst + j] = row0;
                 o.tile_off[dst + j] = 0;
             }
         }
         if (tid == 0) b.tile[(int64_t)r * b.E + e] = 0;
         return;
-    }
-    if (tid == 0) {
-        s_X = 0;
-        s_js = -1;
     }
     // prefix sums of the rows' lengths; a thread takes KPT consecutive rows
     {
@@ -1368,7 +1469,7 @@ __global__ void __launch_bounds__(NT) bulk_slots_kernel(BulkArgs b, BulkSlots o)
             v[c] = y < n ? b.len[in + y] : 0;
             sum += v[c];
         }
-        for (int g = tid; g <= G; g += NT) s_gs[g] = g < G ? b.gs[in + g] : n;
+        for (int g = tid; g < G; g += NT) s_gs[g] = b.gs[in + g];
         int64_t tot;
         int64_t ex = sblock_excl<NT>(sum, &tot);
 #pragma unroll
@@ -1379,95 +1480,33 @@ __global__ void __launch_bounds__(NT) bulk_slots_kernel(BulkArgs b, BulkSlots o)
         if (tid == 0) s_tok[P] = tot;
     }
     __syncthreads();
-    int64_t X = 0, js = 0;
-    if (G < T) {
-        // positions [0, X) become singletons, [X, end of group j*) stays one group, later
-        // groups are unchanged; j* is the first group whose cumulative surplus reaches T - G
-        const int64_t need = T - G;
-        int64_t carry = 0;
-        for (int b0 = 0; b0 < G; b0 += NT) {
-            const int g = b0 + tid;
-            const int64_t v = g < G ? (int64_t)(s_gs[g + 1] - s_gs[g]) - 1 : 0;
-            int64_t tot;
-            const int64_t ex = carry + sblock_excl<NT>(v, &tot);
-            if (g < G && ex < need && ex + v >= need) {
-                s_js = g;
-                s_X = s_gs[g] + (need - ex);
-            }
-            carry += tot;
-        }
-        __syncthreads();
-        X = s_X;
-        js = s_js;
-        if (js < 0 || X + 1 + (G - 1 - js) != T) {   // the group sizes do not add up to the buffer
-            if (tid == 0) atomicOr(&b.st->err, kSErrInternal);
-            return;
-        }
-    }
+    const BulkSplit sp = bulk_split(s_gs, G, T);   // every thread the same search, in LDS
     const double mean = (double)s_tok[P] / (double)n;
     int64_t carry = 0;
-    for (int j0 = 0; j0 < T; j0 += NT) {
-        const int j = j0 + tid;   // step of the round; adjusted group t = T - 1 - j
+    for (int j0 = 0; j0 < m; j0 += NT) {
+        const int j = j0 + tid;   // step of the round; adjusted group T - 1 - j
         int64_t cells = 0;
         int a0 = 0, a1 = 0, mlen = 0;
-        if (j < T) {
-            const int t = T - 1 - j;
-            if (t < X) {
-                a0 = t;
-                a1 = t + 1;
-            } else {
-                const int g = (int)(js + (t - X));
-                a0 = t == X ? (int)X : s_gs[g];
-                a1 = s_gs[g + 1];
-            }
+        if (j < m) {
+            bulk_group(s_gs, G, n, sp, T - 1 - j, &a0, &a1);
             mlen = b.len[in + (n - 1 - a0)];
             cells = (int64_t)(a1 - a0) * mlen;
         }
         int64_t tot = 0, ex = 0;
         if (o.fin) ex = carry + sblock_excl<NT>(cells, &tot);
         carry += tot;
-        if (j < T && j < room) {
+        if (j < m) {
             o.rows[dst + j] = a1 - a0;
             o.maxlen[dst + j] = mlen;
             o.tokens[dst + j] = s_tok[n - a0] - s_tok[n - a1];
             if (o.approx) o.approx[dst + j] = (double)(a1 - a0) * mean;
             if (o.fin) {
-                o.row_off[dst + j] = in + (n - a1);
+                o.row_off[dst + j] = row0 + (n - a1);
                 o.tile_off[dst + j] = ex;
             }
         }
-        if (j < T && e == o.cut_round)
-            atomicAdd((unsigned long long*)&b.stepsum[j], (unsigned long long)(a1 - a0));
     }
     if (o.fin && tid == 0) b.tile[(int64_t)r * b.E + e] = carry;
-}
-
-// A sample quota reached in the last round: the steps up to the one that reaches it are kept.
-__global__ void __launch_bounds__(kST) bulk_cut_kernel(BulkArgs b, int64_t before, int64_t quota) {
-    if (b.st->fail < b.E) return;
-    const int64_t e = b.E - 1, T = b.T[e];
-    __shared__ int64_t s_cut;
-    if (threadIdx.x == 0) s_cut = T;
-    __syncthreads();
-    int64_t carry = 0;
-    for (int64_t j0 = 0; j0 < T; j0 += kST) {
-        const int64_t j = j0 + threadIdx.x;
-        const int64_t v = j < T ? b.stepsum[j] : 0;
-        int64_t tot;
-        const int64_t ex = before + carry + sblock_excl<kST>(v, &tot);
-        if (j < T && ex < quota && ex + v >= quota) s_cut = j + 1;
-        carry += tot;
-    }
-    __syncthreads();
-    const int64_t cut = s_cut;
-    int64_t kept = 0;
-    for (int64_t j = threadIdx.x; j < cut; j += kST) kept += b.stepsum[j];
-    kept = sblock_sum<kST>(kept);
-    if (threadIdx.x == 0) {
-        b.st->cut = cut;
-        b.st->emitted = kept;
-        b.st->steps = b.base[e] + cut;
-    }
 }
 
 // Samples of every step over the ranks (rank stride `stride`): the largest, and the slots'
@@ -1518,35 +1557,102 @@ __global__ void __launch_bounds__(kWave) bulk_tiles_kernel(BulkArgs b, int64_t* 
     int r;
     if (blockIdx.x == 0) {
         const int64_t K = (int64_t)b.W * S, total = b.tile[(int64_t)b.W * b.E];
-        for (int64_t i = threadIdx.x; i <= b.W; i += kWave) left_off[i] = 0;
+        if (!b.lo)
+            for (int64_t i = threadIdx.x; i <= b.W; i += kWave) left_off[i] = 0;
         if (threadIdx.x == 0) {
             tile_off[K] = total;
-            row_off[K] = (int64_t)b.W * b.q;
+            row_off[K] = b.lo ? b.lo[b.W] : (int64_t)b.W * b.q;
             b.st->padded = total;
         }
     }
     if (!bulk_block(b, b.E, &e, &r)) return;
     const int64_t add = b.tile[(int64_t)r * b.E + e], at = (int64_t)r * S + b.base[e];
-    const int T = b.T[e];
+    const int T = b.lo && e + 1 == b.E ? (int)b.st->cut : b.T[e];
     for (int j = threadIdx.x; j < T; j += kWave) tile_off[at + j] += add;
 }
 
-// Rank r's emitted views moved to their place among the ranks' (a quota cut or a stop leaves
-// gaps between the ranks' streams): blockIdx.x is the rank, blockIdx.y a slice of its stream.
-__global__ void __launch_bounds__(256) bulk_emit_out_kernel(BulkArgs b, int64_t S, const int64_t* row_off,
+// Non-join.  Rank r's emitted views moved to their place among the ranks' (the stop leaves gaps
+// between the ranks' streams); blockIdx.x is the rank, blockIdx.y a slice of its stream.  The
+// left-over views in increasing view index: of the last round's buffer those past the cut, put
+// in order by one bit each (slice 0), then the views never fetched.
+__global__ void __launch_bounds__(256) bulk_emit_out_kernel(BulkArgs b, const int64_t* __restrict__ left_off,
                                                             int32_t* emit_views, int32_t* emit_order, int64_t* row_ts,
-                                                            int32_t* row_len) {
+                                                            int32_t* row_len, int32_t* __restrict__ left) {
+    if (b.st->err || b.st->fail < b.E || b.st->steps > b.scap) return;
     const int r = blockIdx.x;
-    const int64_t lo = row_off[(int64_t)r * S], hi = row_off[(int64_t)(r + 1) * S];
+    const int64_t lo = b.lo[r], rows = b.lo[r + 1] - lo, l0 = left_off[r];
     const int64_t in = (int64_t)r * b.q;
-    const int64_t stride = (int64_t)gridDim.y * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.y * blockDim.x + threadIdx.x; i < hi - lo; i += stride) {
+    const int64_t stride = (int64_t)gridDim.y * blockDim.x, i0 = (int64_t)blockIdx.y * blockDim.x + threadIdx.x;
+    for (int64_t i = i0; i < rows; i += stride) {
         emit_views[lo + i] = b.views[in + i];
         emit_order[lo + i] = b.ids[in + i];
         if (row_ts) {
             row_ts[lo + i] = b.ts[in + i];
             row_len[lo + i] = b.len[in + i];
         }
+    }
+    int64_t c, n;
+    bulk_range(b, r, b.E - 1, &c, &n);
+    const int64_t cutoff = c + n - rows;   // views of the last buffer that stay
+    for (int64_t i = c + n + i0; i < b.q; i += stride) left[l0 + cutoff + (i - c - n)] = (int32_t)(i * b.W + r);
+    if (blockIdx.y != 0 || cutoff == 0) return;
+    __shared__ uint32_t s_bit[kMaxDepth / 32];
+    for (int i = threadIdx.x; i < kMaxDepth / 32; i += 256) s_bit[i] = 0;
+    __syncthreads();
+    for (int64_t y = rows + threadIdx.x; y < c + n; y += 256) {
+        const int v = (int)((int64_t)b.views[in + y] / b.W - c);
+        atomicOr(&s_bit[v >> 5], 1u << (v & 31));
+    }
+    __syncthreads();
+    // kMaxDepth / 32 <= 256 words, one per thread
+    const uint32_t w = threadIdx.x < kMaxDepth / 32 ? s_bit[threadIdx.x] : 0u;
+    uint32_t tot;
+    uint32_t at = sblock_excl<256>((uint32_t)__popc(w), &tot);
+    for (uint32_t m = w; m; m &= m - 1) {
+        const int64_t i = c + threadIdx.x * 32 + (__ffs((int)m) - 1);
+        left[l0 + at++] = (int32_t)(i * b.W + r);
+    }
+}
+
+// Non-join: identities with no emitted view and emitted views beyond the first.  perm is a
+// permutation, so identity perm[m] is carried by the views m, m + N, ... below M = q W: only
+// the first M - N of them (fewer than W) by more than one.  A wave takes one of these at a time
+// and looks its views up in the last round's rows; every other identity has one view, so
+// their counts follow from the number of emitted views.  One block.
+__global__ void __launch_bounds__(1024) bulk_identities_kernel(BulkArgs b) {
+    if (b.st->err || b.st->fail < b.E || b.st->steps > b.scap) return;
+    const int64_t M = b.q * b.W;
+    const int64_t shared = M - b.N < b.N ? M - b.N : b.N;
+    const int lane = threadIdx.x & (kWave - 1);
+    int64_t seen = 0, miss = 0, dup = 0;   // equal in all lanes of a wave
+    for (int64_t m = threadIdx.x / kWave; m < shared; m += 1024 / kWave) {
+        int64_t k = 0;
+        for (int64_t v = m; v < M; v += b.N) {
+            const int r = (int)(v % b.W);
+            const int64_t i = v / b.W;
+            int64_t c, n;
+            bulk_range(b, r, b.E - 1, &c, &n);
+            const int64_t rows = b.lo[r + 1] - b.lo[r];
+            bool out = i < c;
+            if (!out && i < c + n) {
+                bool hit = false;
+                for (int64_t y = c + lane; y < rows; y += kWave) hit |= b.views[(int64_t)r * b.q + y] == (int32_t)v;
+                out = __ballot(hit) != 0;
+            }
+            k += out ? 1 : 0;
+        }
+        seen += k;
+        miss += k == 0;
+        dup += k > 0 ? k - 1 : 0;
+    }
+    if (lane != 0) seen = miss = dup = 0;
+    seen = sblock_sum<1024>(seen);
+    miss = sblock_sum<1024>(miss);
+    dup = sblock_sum<1024>(dup);
+    if (threadIdx.x == 0) {
+        const int64_t single = b.N - shared;
+        b.st->missing_ids = miss + single - (b.st->emitted - seen);
+        b.st->duplicate_ids = dup;
     }
 }
 
@@ -1707,6 +1813,8 @@ struct StreamTotals {
     unsigned long long bad_views;
     unsigned long long missing_ids;
     unsigned long long duplicate_ids;
+    int64_t padded;
+    int64_t left;
 };
 
 // Real tokens over the slots, and the identity counts.  perm is a permutation of [0, N),
@@ -1761,6 +1869,15 @@ __global__ void fill_i32_kernel(int32_t* p, int64_t n) {
 
 __global__ void clear_totals_kernel(StreamTotals* t) {
     if (threadIdx.x == 0) *t = StreamTotals{};
+}
+
+// The totals that the scans leave behind, and the end of the left-over offsets.
+__global__ void stream_close_kernel(StreamTotals* t, const int64_t* padded, const int64_t* left, int64_t* left_end) {
+    if (threadIdx.x == 0) {
+        t->padded = *padded;
+        t->left = left ? *left : 0;
+        *left_end = t->left;
+    }
 }
 
 struct StreamLayout {
@@ -1905,7 +2022,8 @@ BulkSchedule bulk_schedule(const StreamArgs& a, const odb_stream_params_t* p) {
         b.stop = ODB_STOP_RANK_FINISHED;
         b.stop_round = 1;
     }
-    b.use = b.rounds <= a.max_rounds && b.E <= kBulkBlocks / a.W;
+    // (bulk_cut_kernel keeps eight bytes a rank in LDS)
+    b.use = b.rounds <= a.max_rounds && b.E <= kBulkBlocks / a.W && a.W <= 8192;
     return b;
 }
 
@@ -2053,7 +2171,8 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
         // free here: only a collate without row records writes them
         b.gs = ws_at<int32_t>(d_ws, L.row_len);
         b.tile = ws_at<int64_t>(d_ws, L.row_ts);
-        b.stepsum = a.stepsum;
+        b.lo = join ? nullptr : ws_at<int64_t>(d_ws, L.gbase);
+        b.quota = bs.stop == ODB_STOP_QUOTA ? a.quota : INT64_MAX;
         b.views = join ? d_emit_views : a.evw;
         b.ids = join ? d_emit_order : const_cast<int32_t*>(a.vid);
         b.ts = join && d_row_token_start ? d_row_token_start : const_cast<int64_t*>(a.vts);
@@ -2069,10 +2188,9 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
         ODB_LAUNCHED();
         const dim3 form_grid((unsigned)bulk_grid(W, bs.E + bs.stop_round)), grid((unsigned)bulk_grid(W, bs.E));
         const BulkSlots staged{ws_at<int32_t>(d_ws, SL.srows), ws_at<int32_t>(d_ws, SL.smax), ws_at<int64_t>(d_ws, SL.stok),
-                               ws_at<double>(d_ws, SL.sadj), nullptr, nullptr, 0,
-                               bs.stop == ODB_STOP_QUOTA ? bs.E - 1 : -1};
+                               ws_at<double>(d_ws, SL.sadj), nullptr, nullptr, 0};
         const BulkSlots final_slots{d_slot_rows, d_slot_maxlen, d_slot_tokens, d_slot_tokens_approx, d_slot_row_off,
-                                    d_slot_tile_off, 1, -1};
+                                    d_slot_tile_off, 1};
         const int64_t n_max = std::min(q, *std::max_element(bs.n0.begin(), bs.n0.end()));
         auto slots = [&](const BulkSlots& o) {
             if (n_max <= 256) hipLaunchKernelGGL((bulk_slots_kernel<256, 1>), grid, dim3(256), 0, s, b, o);
@@ -2089,25 +2207,30 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
         ODB_LAUNCHED();
         hipLaunchKernelGGL(bulk_targets_kernel, dim3(1), dim3(1024), 0, s, b);
         ODB_LAUNCHED();
-        slots(join ? final_slots : staged);
+        if (!join) {
+            hipLaunchKernelGGL(bulk_cut_kernel, dim3(1), dim3(kST), 8 * (size_t)W, s, b, bs.emitted_before(bs.E - 1),
+                               d_left_off);
+            ODB_LAUNCHED();
+        }
+        slots(final_slots);
         ODB_LAUNCHED();
         const unsigned step_grid = grid_for(std::max<int64_t>(1, std::min(scap, bs.E * n_max)), kWave, gcap * 4);
-        if (join) {
-            ODB_TRY((device_excl_scan<int64_t>(BulkTileLoad{b.tile, (int64_t)W * bs.E}, StoreS{b.tile}, (int64_t)W * bs.E + 1,
-                                               ws_at<int64_t>(d_ws, SL.partials), s)));
-            hipLaunchKernelGGL(bulk_tiles_kernel, grid, dim3(kWave), 0, s, b, d_slot_tile_off, d_slot_row_off, d_left_off);
-            ODB_LAUNCHED();
-            hipLaunchKernelGGL(bulk_steps_kernel, dim3(step_grid), dim3(kWave), 0, s, b, (const int32_t*)d_slot_rows,
-                               (const int64_t*)d_slot_tokens, (int64_t)0, scap);
-        } else {
-            if (bs.stop == ODB_STOP_QUOTA) {
-                hipLaunchKernelGGL(bulk_cut_kernel, dim3(1), dim3(kST), 0, s, b, bs.emitted_before(bs.E - 1), a.quota);
-                ODB_LAUNCHED();
-            }
-            hipLaunchKernelGGL(bulk_steps_kernel, dim3(step_grid), dim3(kWave), 0, s, b, (const int32_t*)staged.rows,
-                               (const int64_t*)staged.tokens, scap, scap);
-        }
+        ODB_TRY((device_excl_scan<int64_t>(BulkTileLoad{b.tile, (int64_t)W * bs.E}, StoreS{b.tile}, (int64_t)W * bs.E + 1,
+                                           ws_at<int64_t>(d_ws, SL.partials), s)));
+        hipLaunchKernelGGL(bulk_tiles_kernel, grid, dim3(kWave), 0, s, b, d_slot_tile_off, d_slot_row_off, d_left_off);
         ODB_LAUNCHED();
+        hipLaunchKernelGGL(bulk_steps_kernel, dim3(step_grid), dim3(kWave), 0, s, b, (const int32_t*)d_slot_rows,
+                           (const int64_t*)d_slot_tokens, (int64_t)0, scap);
+        ODB_LAUNCHED();
+        if (!join) {
+            // slices of about 4,096 views, so that short streams take few blocks
+            hipLaunchKernelGGL(bulk_emit_out_kernel, dim3(W, grid_for(q, 4096, 64)), dim3(256), 0, s, b,
+                               (const int64_t*)d_left_off, d_emit_views, d_emit_order, d_row_token_start, d_row_len,
+                               d_left_views);
+            ODB_LAUNCHED();
+            hipLaunchKernelGGL(bulk_identities_kernel, dim3(1), dim3(1024), 0, s, b);
+            ODB_LAUNCHED();
+        }
         // the state and, next to it, the targets
         const size_t bytes = SL.bulk_T - SL.bulk_st + 4 * (h_trace ? bs.E : 0);
         std::vector<char> back(bytes);
@@ -2123,7 +2246,7 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
         if (fail == bs.E) {
             bulk_done = true;
             hg.steps = hb.steps;
-            hg.emitted = bs.stop == ODB_STOP_QUOTA ? bs.emitted_before(bs.E - 1) + hb.emitted : bs.emitted_before(bs.E);
+            hg.emitted = join ? M : hb.emitted;
             hg.rounds = bs.rounds;
             hg.emit_rounds = bs.E;
             hg.skip_rounds = bs.last_round + 1 - bs.E;
@@ -2145,12 +2268,12 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
                 hipLaunchKernelGGL(copy_i32_kernel, dim3(grid_for(M, 256, gcap)), dim3(256), 0, s,
                                    (const int32_t*)d_emit_views, a.evw, M);
                 ODB_LAUNCHED();
-                slots(staged);
-                ODB_LAUNCHED();
-                hipLaunchKernelGGL(bulk_steps_kernel, dim3(step_grid), dim3(kWave), 0, s, b, (const int32_t*)staged.rows,
-                                   (const int64_t*)staged.tokens, scap, scap);
-                ODB_LAUNCHED();
             }
+            slots(staged);
+            ODB_LAUNCHED();
+            hipLaunchKernelGGL(bulk_steps_kernel, dim3(step_grid), dim3(kWave), 0, s, b, (const int32_t*)staged.rows,
+                               (const int64_t*)staged.tokens, scap, scap);
+            ODB_LAUNCHED();
         }
     }
 
@@ -2203,9 +2326,12 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
             }
             hipLaunchKernelGGL(stream_book_kernel, dim3(1), dim3(kST), 0, s, a, k0 + cnt - 1);
             ODB_LAUNCHED();
-            ODB_TRY_HIP(hipMemcpyAsync(&hg, a.g, sizeof(hg), hipMemcpyDeviceToHost, s));
-            ODB_TRY_HIP(hipMemcpyAsync(hr.data(), a.ranks, sizeof(RankStream) * W, hipMemcpyDeviceToHost, s));
-            ODB_TRY_HIP(hipStreamSynchronize(s));
+            // the summary and, next to it, the committed states
+            const size_t bytes = SL.ranks - SL.g + sizeof(RankStream) * W;
+            std::vector<char> back(bytes);
+            ODB_TRY(read_device(back.data(), a.g, bytes, s));
+            memcpy(&hg, back.data(), sizeof(hg));
+            memcpy(hr.data(), back.data() + (SL.ranks - SL.g), sizeof(RankStream) * W);
             if (hg.done) break;
             k0 += cnt;
         }
@@ -2248,11 +2374,10 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
             odb_stream_round_t& t = h_trace[bs.round_of(e)];
             t.kind = 0;
             t.target = targets[e];
-            t.emitted = (e + 1 < bs.E ? bs.emitted_before(e + 1) : bulk_done ? hg.emitted : bs.emitted_before(e + 1)) -
-                        bs.emitted_before(e);
+            t.emitted = (bulk_done && e + 1 == bs.E ? hg.emitted : bs.emitted_before(e + 1)) - bs.emitted_before(e);
         }
         if (bulk_done && bs.rounds > bs.last_round + 1) h_trace[bs.rounds - 1].kind = 2;
-        for (int64_t i = bulk_done ? hg.rounds : j0; i < hg.rounds; ++i) {
+        for (int64_t i = j0; i < hg.rounds && !bulk_done; ++i) {
             h_trace[i].kind = hrec[i].kind;
             h_trace[i].target = hrec[i].kind == 0 ? hrec[i].target : 0;
             h_trace[i].emitted = hrec[i].kind == 0 ? hrec[i].emitted : 0;
@@ -2262,13 +2387,16 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
             h_trace[i].phi = phi;
         }
     };
-    if (bulk_done && join) {
-        // everything is in place: every view emitted once, each identity by its M / N views
+    if (bulk_done) {   // everything is in place
         h_info->real_tokens = (int64_t)hb.real_tokens;
         h_info->padded_elems = hb.padded;
         h_info->pad_fraction = hb.padded > 0 ? 1.0 - (double)hb.real_tokens / (double)hb.padded : 0.0;
+        h_info->undelivered_views = fetched - hg.emitted;
+        h_info->pending_views = M - fetched;
         h_info->bad_views = (int64_t)hb.bad_views;
-        h_info->duplicate_ids = M - N;
+        // join mode emits every view, and an identity has M / N of them
+        h_info->missing_ids = join ? 0 : hb.missing_ids;
+        h_info->duplicate_ids = join ? M - N : hb.duplicate_ids;
         fill_trace();
         if (hb.bad_views != 0)
             return set_error(ODB_E_INTERNAL, "streaming plan does not account for every view exactly once");
@@ -2296,11 +2424,7 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
     }
     hipLaunchKernelGGL(clear_totals_kernel, dim3(1), dim3(64), 0, s, tot);
     ODB_LAUNCHED();
-    if (K > 0 && bulk_done) {
-        hipLaunchKernelGGL(bulk_emit_out_kernel, dim3(W, 64), dim3(256), 0, s, b, S, (const int64_t*)d_slot_row_off,
-                           d_emit_views, d_emit_order, d_row_token_start, d_row_len);
-        ODB_LAUNCHED();
-    } else if (K > 0) {
+    if (K > 0) {
         hipLaunchKernelGGL(stream_emit_out_kernel, dim3(W, 64), dim3(256), 0, s, a, S, (const int64_t*)d_slot_row_off,
                            d_emit_views, d_emit_order, d_row_token_start, d_row_len);
         ODB_LAUNCHED();
@@ -2321,24 +2445,18 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
     hipLaunchKernelGGL(stream_totals_kernel, dim3(grid_for(std::max<int64_t>(std::max(K, N), 1), 256, gcap)),
                        dim3(256), 0, s, a, K, (const int64_t*)d_slot_tokens, (const uint32_t*)vbits, tot);
     ODB_LAUNCHED();
+    hipLaunchKernelGGL(stream_close_kernel, dim3(1), dim3(64), 0, s, tot, (const int64_t*)d_slot_tile_off + K,
+                       M > 0 ? (const int64_t*)partials + (M + kScanTile - 1) / kScanTile : nullptr, d_left_off + W);
+    ODB_LAUNCHED();
     StreamTotals ht{};
-    int64_t padded = 0, nleft = 0;
-    ODB_TRY_HIP(hipMemcpyAsync(&ht, tot, sizeof(ht), hipMemcpyDeviceToHost, s));
-    ODB_TRY_HIP(hipMemcpyAsync(&padded, d_slot_tile_off + K, 8, hipMemcpyDeviceToHost, s));
-    if (!bulk_done)
-        ODB_TRY_HIP(hipMemcpyAsync(hr.data(), a.ranks, sizeof(RankStream) * W, hipMemcpyDeviceToHost, s));
-    if (M > 0) ODB_TRY_HIP(hipMemcpyAsync(&nleft, partials + (M + kScanTile - 1) / kScanTile, 8,
-                                          hipMemcpyDeviceToHost, s));
-    if (h_trace && !bulk_done && hg.rounds > 0) {
+    ODB_TRY(read_device(&ht, tot, sizeof(ht), s));
+    ODB_TRY(read_device(hr.data(), a.ranks, sizeof(RankStream) * W, s));
+    if (h_trace && hg.rounds > 0) {
         hrec.resize(hg.rounds);
-        ODB_TRY_HIP(hipMemcpyAsync(hrec.data(), a.rec, sizeof(StreamRec) * hg.rounds, hipMemcpyDeviceToHost, s));
+        ODB_TRY(read_device(hrec.data(), a.rec, sizeof(StreamRec) * hg.rounds, s));
     }
-    ODB_TRY_HIP(hipStreamSynchronize(s));
-    // the left-over offsets end with the total; the scan left off[W] unset
-    ODB_TRY_HIP(hipMemcpyAsync(d_left_off + W, &nleft, 8, hipMemcpyHostToDevice, s));
-    ODB_TRY_HIP(hipStreamSynchronize(s));
-    if (!bulk_done)
-        for (int r = 0; r < W; ++r) fetched += hr[r].cursor;
+    const int64_t padded = ht.padded, nleft = ht.left;
+    for (int r = 0; r < W; ++r) fetched += hr[r].cursor;
     h_info->real_tokens = (int64_t)ht.real_tokens;
     h_info->padded_elems = padded;
     h_info->pad_fraction = padded > 0 ? 1.0 - (double)ht.real_tokens / (double)padded : 0.0;
