@@ -162,16 +162,12 @@ __device__ __forceinline__ SortTile sort_tile(const int64_t* __restrict__ off,
     return t;
 }
 
-// Digit-indexed LDS tables (a row holds 256 digit values): for one wave's access, digits d
-// and d + 32 fall in the same bank, so the lanes' accesses by digit conflict when distinct
-// digits of a wave share a bank (the first histogram pass, over near-uniform low length
-// bits, spends about one conflict cycle per conflict-free LDS cycle).  Splitting each such
-// access into four (or eight) masked steps by the digit's high bits, so that a step's
-// digits never share a bank, removed every conflict but made the passes slower (measured
-// on 16.7 M samples: 44.4 instead of 38.0 us for a histogram pass, 107.6 instead of 89.8
-// us for a scatter pass): the steps cost more issue than the conflicts stall.  The
-// accesses are therefore made once, and kept few: one LDS add per distinct digit of a
-// wave, one slot read per item.
+// Digit counts of every tile.  kHistCopies copies of the table, lane l counting in copy
+// l mod kHistCopies with a plain LDS add: equal digits of a wave (the high digit of
+// skewed lengths) then meet in groups of at most 8 lanes.  Finding the lanes of equal digit
+// first (a ballot per digit bit) for one add per distinct digit took 38 instead of 20 us on
+// 16.7 M samples.
+constexpr int kHistCopies = 8;
 
 template <bool kFirst>
 __global__ void __launch_bounds__(kBlock) radix_hist_kernel(const int64_t* __restrict__ off,
@@ -182,46 +178,89 @@ __global__ void __launch_bounds__(kBlock) radix_hist_kernel(const int64_t* __res
     const SortTile b = sort_tile(off, tile_first, W, blockIdx.x);
     const int radix = 1 << dbits;
     const uint32_t mask = (uint32_t)radix - 1;
-    // one count table per wave: each distinct digit of a wave has one leader lane, the only
-    // writer of its entry, which adds the digit's count (an LDS add without return: no wait
-    // on a read)
-    constexpr int kWaves = kBlock / kWave;
-    __shared__ uint32_t h[kWaves][256];
-    const int w = threadIdx.x / kWave;
-    for (int i = threadIdx.x; i < kWaves * 256; i += kBlock) (&h[0][0])[i] = 0;
-    __syncthreads();
+    __shared__ uint32_t h[256 * kHistCopies];
+    uint32_t key[kSortItems];
+#pragma unroll
     for (int it = 0; it < kSortItems; ++it) {
         const int li = it * kBlock + threadIdx.x;
-        const bool valid = li < b.count;
-        const int64_t p = b.start + li;
-        uint32_t key = 0;
-        if (valid) key = kFirst ? maxl - (uint32_t)len_in[p] : keys_in[p];
-        const uint32_t d = (key >> shift) & mask;
-        const uint64_t peers = match_digit(d, valid, dbits);
-        const bool lead = valid && lanes_below(peers) == 0;
-        const uint32_t c = (uint32_t)__popcll(peers);
-        if (lead) atomicAdd(&h[w][d], c);
+        const int64_t p = b.start + (li < b.count ? li : 0);
+        key[it] = kFirst ? maxl - (uint32_t)len_in[p] : keys_in[p];
     }
+    for (int i = threadIdx.x; i < radix * kHistCopies; i += kBlock) h[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < kSortItems; ++it)
+        if (it * kBlock + (int)threadIdx.x < b.count)
+            atomicAdd(&h[((key[it] >> shift) & mask) * kHistCopies + (threadIdx.x & (kHistCopies - 1))], 1u);
     __syncthreads();
     const int64_t col = (int64_t)b.first << dbits;
     for (int d = threadIdx.x; d < radix; d += kBlock) {
         uint32_t sum = 0;
 #pragma unroll
-        for (int k = 0; k < kWaves; ++k) sum += h[k][d];
+        for (int k = 0; k < kHistCopies; ++k) sum += h[d * kHistCopies + k];
         counts[col + (int64_t)d * b.seg_tiles + b.j] = sum;
     }
 }
 
-// Scatter one tile.  Items are taken in position order (round `it` covers positions
-// it*256 .. it*256+255 of the tile, wave w its w-th quarter), so the slot of an item among
-// equal digits is: the digit's first slot after earlier rounds (s_run), plus the items of
-// earlier waves this round (both folded into s_pre by one thread per digit), plus lower
-// lanes with the same digit (ballot match).  That keeps the sort stable.  The items are first
-// placed in LDS in digit order (the tile's local digit offsets come from the scanned
-// counts: consecutive entries differ by one tile's count of one digit), then written out
-// in that order, so each digit's run of the tile goes to consecutive addresses: a round
-// holds about two items per digit, and writing those straight from registers cost 4.6 B
-// of HBM writes per byte written.
+// Exclusive scan of one rank's digit counts (digit-major, its tiles in order) from the rank's
+// first position on: one block per rank, 16 consecutive counts a thread.  The ranks' scans are
+// independent because a rank's counts add up to its samples; ranks of many tiles take the
+// general scan (three launches, ~20 us) instead.
+constexpr int kRankScanThreads = 1024;
+constexpr int kRankScanItems = 16;
+constexpr int64_t kRankScanMax = 4ll * kRankScanThreads * kRankScanItems;   // about 4 us per 16,384 counts
+
+__global__ void __launch_bounds__(kRankScanThreads) rank_scan_kernel(const int64_t* __restrict__ off,
+                                                                     const int64_t* __restrict__ tile_first, int dbits,
+                                                                     uint32_t* __restrict__ counts) {
+    const int r = blockIdx.x, t = threadIdx.x;
+    const int64_t first = tile_first[r] << dbits, m = (tile_first[r + 1] << dbits) - first;
+    __shared__ uint32_t s_w[kRankScanThreads / kWave];
+    uint32_t carry = (uint32_t)off[r];
+    for (int64_t i0 = 0; i0 < m; i0 += (int64_t)kRankScanThreads * kRankScanItems) {
+        // vectors of 4: every rank's counts start at, and number, a multiple of 2^dbits >= 4
+        uint4 v[kRankScanItems / 4];
+        uint32_t sum = 0;
+        uint32_t* c = counts + first + i0 + (int64_t)t * kRankScanItems;
+#pragma unroll
+        for (int k = 0; k < kRankScanItems / 4; ++k) {
+            const bool on = i0 + (int64_t)t * kRankScanItems + 4 * k < m;
+            v[k] = on ? reinterpret_cast<const uint4*>(c)[k] : make_uint4(0, 0, 0, 0);
+            sum += v[k].x + v[k].y + v[k].z + v[k].w;
+        }
+        const uint32_t inc = wave_scan_dpp<OpAdd>(sum);
+        if ((t & (kWave - 1)) == kWave - 1) s_w[t / kWave] = inc;
+        __syncthreads();
+        uint32_t at = carry + inc - sum;
+#pragma unroll
+        for (int k = 0; k < kRankScanThreads / kWave; ++k) {
+            at += k < t / kWave ? s_w[k] : 0u;
+            carry += s_w[k];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kRankScanItems / 4; ++k) {
+            const uint4 x = v[k];
+            uint4 o;
+            o.x = at;
+            o.y = o.x + x.x;
+            o.z = o.y + x.y;
+            o.w = o.z + x.z;
+            at = o.w + x.w;
+            if (i0 + (int64_t)t * kRankScanItems + 4 * k < m) reinterpret_cast<uint4*>(c)[k] = o;
+        }
+    }
+}
+
+// Scatter one tile, stably.  A wave takes a quarter of the tile, its items in position order,
+// and keeps its running count of each digit in LDS: an item's rank among the wave's equal
+// digits is that count plus the lower lanes holding the digit (ballot match).  One scan
+// over digits and waves then gives every wave's first slot for every digit; the items are placed
+// in LDS in that order and written out from it, so each digit's run of the tile goes to
+// consecutive addresses (written straight from registers, about two items per digit and
+// round, they cost 4.6 B of HBM writes per byte).  The count, slot table and placement done round
+// by round, two block barriers each, took 90 and 82 instead of 78 and 59 us for the two passes over
+// 16.7 M samples (the low digit spreads a tile over twice the runs).
 template <bool kFirst, bool kLast>
 __global__ void __launch_bounds__(kBlock) radix_scatter_kernel(
     const int64_t* __restrict__ off, const int64_t* __restrict__ tile_first, int W,
@@ -233,87 +272,78 @@ __global__ void __launch_bounds__(kBlock) radix_scatter_kernel(
     const int radix = 1 << dbits;
     const uint32_t mask = (uint32_t)radix - 1;
     constexpr int kWaves = kBlock / kWave;
-    __shared__ uint32_t s_base[256];   // global position of the tile's first item of digit d
-    __shared__ uint32_t s_local[256];  // local position of the same item within the tile
-    __shared__ uint32_t s_run[256];    // local slot of the next item of digit d
-    __shared__ uint32_t s_w[kWaves][256];    // this round: items of digit d in wave k
-    __shared__ uint32_t s_pre[kWaves][256];  // this round: local slot of wave k's first item of digit d
+    __shared__ uint32_t s_shift[256];         // global position of the digit's first item less its local one
+    __shared__ uint32_t s_cnt[kWaves][256];   // items of a digit in a wave, then the wave's first local slot
     __shared__ uint32_t s_key[kSortTile];
     __shared__ int32_t s_val[kSortTile];
-    const int64_t col = (int64_t)b.first << dbits;
-    for (int d = threadIdx.x; d < 256; d += kBlock) {
-        uint32_t base = 0, cnt = 0;
-        if (d < radix) {
-            const int64_t i = col + (int64_t)d * b.seg_tiles + b.j;
-            base = offs[i];
-            cnt = offs[i + 1] - base;
-        }
-        s_base[d] = base;
-        s_local[d] = cnt;
-        s_run[d] = 0;
+    const int w = threadIdx.x / kWave;
+    const int p0 = w * (kSortTile / kWaves) + (threadIdx.x & (kWave - 1));   // item it: p0 + it * 64
+    uint32_t key[kSortItems];
+    int32_t val[kSortItems];
 #pragma unroll
-        for (int k = 0; k < kWaves; ++k) s_w[k][d] = 0;
+    for (int it = 0; it < kSortItems; ++it) {
+        const int li = p0 + it * kWave;
+        const int64_t p = b.start + (li < b.count ? li : 0);
+        key[it] = kFirst ? maxl - (uint32_t)len_in[p] : keys_in[p];
+        val[it] = kFirst ? (int32_t)p : vals_in[p];
+    }
+    const int64_t col = (int64_t)b.first << dbits;
+    uint32_t base = 0;
+    if ((int)threadIdx.x < radix) base = offs[col + (int64_t)threadIdx.x * b.seg_tiles + b.j];
+#pragma unroll
+    for (int k = 0; k < kWaves; ++k) s_cnt[k][threadIdx.x] = 0;
+    __syncthreads();
+    uint32_t at[kSortItems];
+#pragma unroll
+    for (int it = 0; it < kSortItems; ++it) {
+        const bool valid = p0 + it * kWave < b.count;
+        const uint32_t d = (key[it] >> shift) & mask;
+        const uint64_t peers = match_digit(d, valid, dbits);
+        const uint32_t below = lanes_below(peers);
+        // every lane reads the count before the digit's first lane adds to it: LDS operations of
+        // one wave complete in order (the fences keep the compiler to it)
+        at[it] = s_cnt[w][d] + below;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (valid && below == 0) s_cnt[w][d] += (uint32_t)__popcll(peers);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
     __syncthreads();
     {
-        // exclusive scan of the tile's digit counts (256 entries, one per thread)
-        uint32_t tot;
-        const uint32_t ex = block_excl_sum(s_local[threadIdx.x], &tot);
-        __syncthreads();
-        s_local[threadIdx.x] = ex;
-        s_run[threadIdx.x] = ex;
-    }
-    __syncthreads();
-    const int w = threadIdx.x / kWave;
-    for (int it = 0; it < kSortItems; ++it) {
-        const int li = it * kBlock + threadIdx.x;
-        const bool valid = li < b.count;
-        const int64_t p = b.start + li;
-        uint32_t key = 0;
-        int32_t val = 0;
-        if (valid) {
-            key = kFirst ? maxl - (uint32_t)len_in[p] : keys_in[p];
-            val = kFirst ? (int32_t)p : vals_in[p];
-        }
-        const uint32_t d = (key >> shift) & mask;
-        const uint64_t peers = match_digit(d, valid, dbits);
-        const uint32_t below = lanes_below(peers);
-        const bool lead = valid && below == 0;
-        const uint32_t c = (uint32_t)__popcll(peers);
-        // the wave's count of each digit (leaders), then one thread per digit turns the
-        // waves' counts into each wave's first slot, and each item reads its wave's slot
-        // for its digit
-        if (lead) s_w[w][d] = c;
-        __syncthreads();
-        for (int dd = threadIdx.x; dd < radix; dd += kBlock) {
-            uint32_t at = s_run[dd];
+        uint32_t c[kWaves], sum = 0, tot;
 #pragma unroll
-            for (int k = 0; k < kWaves; ++k) {
-                const uint32_t v = s_w[k][dd];
-                s_pre[k][dd] = at;
-                s_w[k][dd] = 0;
-                at += v;
-            }
-            s_run[dd] = at;
+        for (int k = 0; k < kWaves; ++k) {
+            c[k] = s_cnt[k][threadIdx.x];
+            sum += c[k];
         }
-        __syncthreads();
-        uint32_t q = 0;
-        if (valid) q = s_pre[w][d] + below;
-        if (valid) {
-            s_key[q] = key;
-            s_val[q] = val;
+        uint32_t ex = block_excl_sum(sum, &tot);
+        s_shift[threadIdx.x] = base - ex;
+#pragma unroll
+        for (int k = 0; k < kWaves; ++k) {
+            s_cnt[k][threadIdx.x] = ex;
+            ex += c[k];
         }
     }
     __syncthreads();
-    for (int q = threadIdx.x; q < b.count; q += kBlock) {
-        const uint32_t key = s_key[q];
-        const uint32_t d = (key >> shift) & mask;
-        const uint32_t pos = s_base[d] + (uint32_t)q - s_local[d];
+#pragma unroll
+    for (int it = 0; it < kSortItems; ++it) {
+        if (p0 + it * kWave < b.count) {
+            const uint32_t q = s_cnt[w][(key[it] >> shift) & mask] + at[it];
+            s_key[q] = key[it];
+            s_val[q] = val[it];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < kSortItems; ++it) {
+        const int q = it * kBlock + threadIdx.x;
+        if (q >= b.count) break;
+        const uint32_t k = s_key[q];
+        const uint32_t pos = s_shift[(k >> shift) & mask] + (uint32_t)q;
         vals_out[pos] = s_val[q];
         if (kLast)
-            slen_out[pos] = (int32_t)(maxl - key);
+            slen_out[pos] = (int32_t)(maxl - k);
         else
-            keys_out[pos] = key;
+            keys_out[pos] = k;
     }
 }
 
@@ -435,7 +465,7 @@ __global__ void init_jump_flags(DevStatus* st) {
 
 struct CountLoad {
     const uint32_t* c;
-    int64_t n;  // entries; the scan runs over n + 1 so that entry n holds the total
+    int64_t n;
     __device__ uint32_t operator()(int64_t i) const { return i < n ? c[i] : 0u; }
 };
 struct CountStore {
@@ -1374,8 +1404,14 @@ extern "C" int odb_form_groups(const odb_window_t* w, int64_t budget, int32_t* d
                                    (const int64_t*)d_tile_first, W, kin, (const int32_t*)len, maxl, shift, dbits,
                                    counts);
             ODB_LAUNCHED();
-            ODB_TRY((device_excl_scan<uint32_t>(CountLoad{counts, NB << dbits}, CountStore{counts}, (NB << dbits) + 1,
-                                                ws_at<uint32_t>(d_ws, L.partials), s)));
+            if (dbits >= 2 && ((max_cnt + kSortTile - 1) / kSortTile << dbits) <= kRankScanMax) {
+                hipLaunchKernelGGL(rank_scan_kernel, dim3(W), dim3(kRankScanThreads), 0, s, d_off,
+                                   (const int64_t*)d_tile_first, dbits, counts);
+                ODB_LAUNCHED();
+            } else {
+                ODB_TRY((device_excl_scan<uint32_t>(CountLoad{counts, NB << dbits}, CountStore{counts}, NB << dbits,
+                                                    ws_at<uint32_t>(d_ws, L.partials), s)));
+            }
 #define ODB_SCATTER(F, La)                                                                                  \
     hipLaunchKernelGGL((radix_scatter_kernel<F, La>), dim3((unsigned)NB), dim3(kBlock), 0, s,               \
                        d_off, (const int64_t*)d_tile_first, W, kin, (const int32_t*)len, vin, maxl, shift,  \
