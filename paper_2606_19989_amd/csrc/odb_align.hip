@@ -1160,7 +1160,7 @@ struct OneArgs {
     const int32_t* groups;     // [W] G_r
     int32_t* gs;               // [n] rank-local start of group g of rank r at off[r] + g
     int64_t* gpre;             // [n] tokens before that start within its tile of the rank
-    int64_t* tpre;             // [W * per_rank] tokens of the rank before each of its tiles
+    int64_t* tpre;             // [W * per_rank] tokens of each of the rank's tiles, or before it
     int per_rank;              // tiles (kRowTile positions) of the largest rank
     int64_t* lo;               // [W + 1] first row of every rank (the rank offsets in join mode)
     int64_t* steps;            // [max n_r] samples per step (sample quota only)
@@ -1339,6 +1339,10 @@ __global__ void __launch_bounds__(kBlock) rows_kernel(OneArgs a, int xcd) {
         }
     }
 }
+
+// Ranks of at most this many tiles leave tpre as the tiles' own tokens: a slot sums the few it
+// needs, which saves the launch that turns them into prefixes.
+constexpr int kTilesSummed = 16;
 
 // One block per rank: the tokens of the rank's tiles become the tokens before each tile.
 __global__ void __launch_bounds__(kBlock) rank_tiles_kernel(OneArgs a) {
@@ -1550,9 +1554,18 @@ __global__ void __launch_bounds__(kBlock) slots_kernel(OneArgs a, int32_t* __res
             ml = a.slen[base + a0];
             const int64_t* tp = a.tpre + (int64_t)r * a.per_rank;
             if (g >= 0) {
-                const int64_t end = a1 < cnt ? tp[a1 / kRowTile] + a.gpre[base + g + 1]
-                                             : a.tok_off[base + cnt] - a.tok_off[base];
-                sum = end - (tp[a0 / kRowTile] + a.gpre[base + g]);
+                if (a1 < cnt)
+                    sum = a.gpre[base + g + 1] - a.gpre[base + g];
+                else
+                    sum = a.tok_off[base + cnt] - a.tok_off[base] - a.gpre[base + g];
+                const int x0 = (int)(a0 / kRowTile), x1 = a1 < cnt ? (int)(a1 / kRowTile) : 0;
+                if (a.per_rank > kTilesSummed) {
+                    sum += (a1 < cnt ? tp[x1] : 0) - tp[x0];
+                } else if (a1 < cnt) {
+                    for (int i = x0; i < x1; ++i) sum += tp[i];
+                } else {
+                    for (int i = 0; i < x0; ++i) sum -= tp[i];
+                }
             } else if (a1 - a0 == 1) {
                 sum = ml;
             } else {
@@ -2150,8 +2163,10 @@ extern "C" int odb_align_groups(const odb_window_t* w, int64_t budget, const odb
         const unsigned ranges = grid_for(n, 64, kMaxRanges);
         hipLaunchKernelGGL(rows_kernel, dim3((unsigned)row_blocks), dim3(kBlock), 0, s, a, xcd);
         ODB_LAUNCHED();
-        hipLaunchKernelGGL(rank_tiles_kernel, dim3(W), dim3(kBlock), 0, s, a);
-        ODB_LAUNCHED();
+        if (per_rank > kTilesSummed) {
+            hipLaunchKernelGGL(rank_tiles_kernel, dim3(W), dim3(kBlock), 0, s, a);
+            ODB_LAUNCHED();
+        }
         if (nonjoin) {
             hipLaunchKernelGGL(cut_steps_kernel, dim3(grid_for(max_nr, kWave, kMaxRanges)), dim3(kBlock), 0, s, a);
             ODB_LAUNCHED();

@@ -131,14 +131,6 @@ int check_workspace(const odb_window_t* w, void* d_ws, size_t ws_bytes, Layout* 
     return ODB_OK;
 }
 
-// Small host arrays reach the device as kernel arguments, kValuesPerLaunch values per
-// launch: no host-to-device copy (which, from pageable memory, may wait for the stream)
-// and nothing a graph capture could not record.
-constexpr int kValuesPerLaunch = 128;
-struct Values {
-    int64_t v[kValuesPerLaunch];
-};
-
 // Stores values [first, first + count) of an array; the first launch of a call also
 // resets the status word.  The collate's error word is left alone: odb_collate clears it
 // when it starts and odb_collate_status when it has read it, so a plan call made on the

@@ -516,276 +516,7 @@ __global__ void groups_kernel(const int32_t* __restrict__ incl, const int64_t* _
     }
 }
 
-// ---- one block per rank
-// When every rank holds at most kRankBlockMax samples, each rank is grouped by one
-// 1024-thread block in two launches, with no host synchronisation: rank_sort_kernel (lengths, validity, stable LSD
-// radix sort on byte digits of the length) and chain_kernel (the group chain over the
-// runs of equal batch size, and the group index of every position in closed form).
-constexpr int kRankThreads = 1024;
-constexpr int kRankWaves = kRankThreads / kWave;
-constexpr int kRankItems = 4;                     // lengths a thread loads at once in the first pass
-constexpr int kRankGroup = 4;                     // rounds of a pass whose items are loaded together
-// Exclusive scan of v over the first 256 threads of a kRankThreads block (4 waves), every
-// thread of the block taking part in the barriers; *total receives the sum.
-__device__ __forceinline__ uint32_t scan256(uint32_t v, uint32_t* total) {
-    __shared__ uint32_t s_w[4];
-    const int t = threadIdx.x;
-    uint32_t inc = 0;
-    if (t < 256) {
-        inc = wave_scan_dpp<OpAdd>(v);
-        if ((t & (kWave - 1)) == kWave - 1) s_w[t / kWave] = inc;
-    }
-    __syncthreads();
-    uint32_t pre = 0, tot = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint32_t x = s_w[i];
-        pre += (t < 256 && i < t / kWave) ? x : 0u;
-        tot += x;
-    }
-    __syncthreads();
-    *total = tot;
-    return pre + inc - v;
-}
-
-// Per-wave digit counts: for each distinct digit of the wave's valid lanes, the lowest such
-// lane adds the number of lanes holding it to row w of `tbl` (one writer per address).
-__device__ __forceinline__ void count_digits(uint32_t (*tbl)[256], int w, uint32_t d, bool valid) {
-    const uint64_t peers = match_digit(d, valid, 8);
-    const bool lead = valid && lanes_below(peers) == 0;
-    const uint32_t c = (uint32_t)__popcll(peers);
-    if (lead) atomicAdd(&tbl[w][d], c);
-}
-
-// One stable scatter pass of rank_sort_kernel over digit bits [shift, shift + 8): round i
-// places items i*1024 .. i*1024+1023 of the pass's input (keys sk, ids sv; the first
-// pass's ids are the positions themselves).  A round's rank of an item among equal digits
-// is: items of that digit placed in earlier rounds (s_run), in lower waves of this round
-// (s_cnt prefix) and in lower lanes of its wave (ballot match).  The two barriers of a
-// round order LDS only: nothing in the block reads the round's global stores before the
-// pass ends.  Loads run a group of kRankGroup rounds ahead, into the register set (A or B)
-// of the group after next, at clamped positions (unconditional loads: a load under a branch
-// makes the compiler wait for it where the paths join).
-template <bool kFirst>
-__device__ __forceinline__ void scatter_pass(const int32_t* __restrict__ sk, const int32_t* __restrict__ sv,
-                                             int32_t* __restrict__ dk, int32_t* __restrict__ dv, int64_t base,
-                                             int cnt, int rounds, int shift, uint32_t (*s_cnt)[256],
-                                             uint32_t (*s_pre)[256], uint32_t* s_run) {
-    const int t = threadIdx.x, w = t / kWave;
-    auto load_group = [&](int g, uint32_t (&kk)[kRankGroup], int32_t (&vv)[kRankGroup]) {
-#pragma unroll
-        for (int j = 0; j < kRankGroup; ++j) {
-            const int q = (g * kRankGroup + j) * kRankThreads + t;
-            const int qc = q < cnt ? q : cnt - 1;
-            kk[j] = (uint32_t)sk[base + qc];
-            vv[j] = kFirst ? (int32_t)(base + q) : sv[base + qc];
-        }
-    };
-    auto place_group = [&](int g, const uint32_t (&kk)[kRankGroup], const int32_t (&vv)[kRankGroup]) {
-#pragma unroll
-        for (int j = 0; j < kRankGroup; ++j) {
-            const int i = g * kRankGroup + j;
-            if (i >= rounds) break;   // uniform
-            const int q = i * kRankThreads + t;
-            const bool valid = q < cnt;
-            const uint32_t key = kk[j];
-            const uint32_t d = (key >> shift) & 255u;
-            const uint64_t peers = match_digit(d, valid, 8);
-            const uint32_t below = lanes_below(peers);
-            const bool lead = valid && below == 0;
-            const uint32_t c_lead = (uint32_t)__popcll(peers);
-            if (lead) s_cnt[w][d] = c_lead;
-            lds_barrier();
-            if (t < 256) {
-                // s_pre: where this round's first item of digit t from each wave goes
-                // (s_run holds the bucket's start plus the items placed so far)
-                uint32_t run = s_run[t];
-#pragma unroll
-                for (int k2 = 0; k2 < kRankWaves; ++k2) {
-                    const uint32_t c = s_cnt[k2][t];
-                    s_pre[k2][t] = run;
-                    run += c;
-                    s_cnt[k2][t] = 0;
-                }
-                s_run[t] = run;
-            }
-            lds_barrier();
-            uint32_t at = 0;
-            if (valid) at = s_pre[w][d];
-            if (valid) {
-                dk[base + at + below] = (int32_t)key;
-                dv[base + at + below] = vv[j];
-            }
-        }
-    };
-    const int groups = (rounds + kRankGroup - 1) / kRankGroup;
-    uint32_t ka_[kRankGroup], kb_[kRankGroup];
-    int32_t va_[kRankGroup], vb_[kRankGroup];
-    load_group(0, ka_, va_);
-    for (int g = 0; g < groups; g += 2) {
-        load_group(g + 1, kb_, vb_);
-        place_group(g, ka_, va_);
-        if (g + 1 >= groups) break;   // uniform
-        load_group(g + 2, ka_, va_);
-        place_group(g + 1, kb_, vb_);
-    }
-}
-
-// Sorts rank r's samples by (length desc, id asc): writes len (every sample's length,
-// invalid ones as 1), order and sorted_len.  Digits are the bytes of the length, low to
-// high; a digit whose value is the same for every sample of the rank is skipped; each pass
-// places the buckets from the highest digit value down and keeps the order within a
-// bucket, so the result is by length descending, ties in sample-id order.
-__global__ void __launch_bounds__(kRankThreads) rank_sort_kernel(
-    const int64_t* __restrict__ tok_off, const int64_t* __restrict__ off, int32_t* __restrict__ len,
-    int32_t* __restrict__ ka, int32_t* __restrict__ va, int32_t* __restrict__ kb, int32_t* __restrict__ vb,
-    int32_t* __restrict__ order, int32_t* __restrict__ slen, DevStatus* st) {
-    __shared__ uint32_t s_cnt[kRankWaves][256];   // first pass: digit-0 counts; passes: counts of a round
-    __shared__ uint32_t s_pre[kRankWaves][256];   // first pass: digit-1 counts; passes: prefixes of a round
-    __shared__ uint32_t s_hist[4][256];
-    __shared__ uint32_t s_run[256];
-    __shared__ uint32_t s_max;
-    __shared__ unsigned long long s_bad;
-    __shared__ int s_active[4];
-    const int r = blockIdx.x;
-    const int64_t base = off[r];
-    const int cnt = (int)(off[r + 1] - base);
-    if (cnt <= 0) return;
-    const int t = threadIdx.x, w = t / kWave;
-    for (int i = t; i < kRankWaves * 256; i += kRankThreads) {
-        (&s_cnt[0][0])[i] = 0;
-        (&s_pre[0][0])[i] = 0;
-    }
-    if (t == 0) {
-        s_max = 0;
-        s_bad = ~0ull;
-    }
-    __syncthreads();
-
-    // lengths, validity, histograms of digits 0 and 1
-    uint32_t lmax = 0;
-    unsigned long long bad = ~0ull;
-    for (int q0 = 0; q0 < cnt; q0 += kRankThreads * kRankItems) {
-        int64_t a[kRankItems], b[kRankItems];
-#pragma unroll
-        for (int j = 0; j < kRankItems; ++j) {
-            const int q = q0 + j * kRankThreads + t;
-            const int qc = q < cnt ? q : cnt - 1;
-            a[j] = tok_off[base + qc];
-            b[j] = tok_off[base + qc + 1];
-        }
-#pragma unroll
-        for (int j = 0; j < kRankItems; ++j) {
-            const int q = q0 + j * kRankThreads + t;
-            const bool valid = q < cnt;
-            uint32_t l = 0;
-            if (valid) {
-                int64_t ll = b[j] - a[j];
-                if (ll < 1 || ll > INT_MAX || a[j] < 0) {
-                    const unsigned long long id = (unsigned long long)(base + q);
-                    bad = id < bad ? id : bad;
-                    ll = 1;
-                }
-                l = (uint32_t)ll;
-                len[base + q] = (int32_t)l;
-                lmax = l > lmax ? l : lmax;
-            }
-            count_digits(s_cnt, w, l & 255u, valid);
-            count_digits(s_pre, w, (l >> 8) & 255u, valid);
-        }
-    }
-    lmax = wave_scan_dpp<OpMax>(lmax);
-    if ((t & (kWave - 1)) == kWave - 1) atomicMax(&s_max, lmax);
-    if (bad != ~0ull) atomicMin(&s_bad, bad);
-    __syncthreads();
-    if (t < 512) {
-        const int d = t & 255;
-        uint32_t (*tbl)[256] = t < 256 ? s_cnt : s_pre;
-        uint32_t sum = 0;
-#pragma unroll
-        for (int k = 0; k < kRankWaves; ++k) {
-            sum += tbl[k][d];
-            tbl[k][d] = 0;
-        }
-        s_hist[t / 256][d] = sum;
-    }
-    if (t == 0 && s_bad != ~0ull) {
-        atomicOr(&st->err, kErrLength);
-        atomicMin((unsigned long long*)&st->first_bad, s_bad);
-    }
-    __syncthreads();
-    const uint32_t maxl = s_max;
-    if (maxl >= (1u << 16)) {
-        // lengths of 2^16 or more: histograms of digits 2 and 3
-        for (int q0 = 0; q0 < cnt; q0 += kRankThreads) {
-            const int q = q0 + t;
-            const bool valid = q < cnt;
-            const uint32_t l = valid ? (uint32_t)len[base + q] : 0u;
-            count_digits(s_cnt, w, (l >> 16) & 255u, valid);
-            count_digits(s_pre, w, l >> 24, valid);
-        }
-        __syncthreads();
-        if (t < 512) {
-            const int d = t & 255;
-            uint32_t (*tbl)[256] = t < 256 ? s_cnt : s_pre;
-            uint32_t sum = 0;
-#pragma unroll
-            for (int k = 0; k < kRankWaves; ++k) {
-                sum += tbl[k][d];
-                tbl[k][d] = 0;
-            }
-            s_hist[2 + t / 256][d] = sum;
-        }
-    } else if (t < 512) {
-        s_hist[2 + t / 256][t & 255] = (t & 255) == 0 ? (uint32_t)cnt : 0u;
-    }
-    __syncthreads();
-    // a digit takes part if more than one of its values occurs
-    if (t < 4 * kWave) {
-        const int k = t / kWave, lane = t & (kWave - 1);
-        int nz = 0;
-        for (int d = lane; d < 256; d += kWave) nz += s_hist[k][d] != 0;
-        nz = wave_sum(nz);
-        if (lane == 0) s_active[k] = nz > 1;
-    }
-    __syncthreads();
-    int passes = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) passes += s_active[k];
-
-    if (passes == 0) {   // every length equal: formation order is id order
-        for (int q = t; q < cnt; q += kRankThreads) {
-            order[base + q] = (int32_t)(base + q);
-            slen[base + q] = len[base + q];
-        }
-        return;
-    }
-    int pass = 0;
-    const int rounds = (cnt + kRankThreads - 1) / kRankThreads;
-    for (int k = 0; k < 4; ++k) {
-        if (!s_active[k]) continue;
-        const bool first = pass == 0, last = pass == passes - 1;
-        const int32_t* sk = first ? len : ((pass & 1) ? ka : kb);
-        const int32_t* sv = (pass & 1) ? va : vb;
-        int32_t* dk = last ? slen : ((pass & 1) ? kb : ka);
-        int32_t* dv = last ? order : ((pass & 1) ? vb : va);
-        // bucket of digit value d starts after every higher value's samples
-        {
-            uint32_t tot;
-            const uint32_t v = t < 256 ? s_hist[k][255 - t] : 0u;
-            const uint32_t ex = scan256(v, &tot);
-            if (t < 256) s_run[255 - t] = ex;
-        }
-        __syncthreads();
-        if (first)
-            scatter_pass<true>(sk, sk, dk, dv, base, cnt, rounds, 8 * k, s_cnt, s_pre, s_run);
-        else
-            scatter_pass<false>(sk, sv, dk, dv, base, cnt, rounds, 8 * k, s_cnt, s_pre, s_run);
-        __syncthreads();
-        ++pass;
-    }
-}
-
+// ---- the chain of one rank
 // Batch size B(l) (Eq. 1), clipped to 2^31 - 1 (any larger step leaves the rank).
 __device__ __forceinline__ uint32_t step_of(int32_t l, int64_t budget) {
     const int64_t b = batch_size(budget, l);
@@ -797,16 +528,15 @@ __device__ __forceinline__ uint32_t step_of(int32_t l, int64_t budget) {
 // eight lengths at a time, at clamped positions, so the loads of a batch are in flight
 // together; equal neighbouring lengths skip the divisions.
 template <typename F>
-__device__ __forceinline__ void chunk_run_starts(const int32_t* __restrict__ slen, int64_t base, int lo, int hi,
-                                                 int64_t budget, F f) {
-    int32_t lp = lo >= 2 ? slen[base + lo - 2] : 0;
+__device__ __forceinline__ void chunk_run_starts(const int32_t* len, int lo, int hi, int64_t budget, F f) {
+    int32_t lp = lo >= 2 ? len[lo - 2] : 0;
     uint32_t bp = lo >= 2 ? step_of(lp, budget) : 0u;
     for (int q0 = lo; q0 < hi; q0 += 8) {
         int32_t l8[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int qq = q0 + j < hi ? q0 + j : hi - 1;
-            l8[j] = slen[base + qq - 1];
+            l8[j] = len[qq - 1];
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -857,24 +587,25 @@ struct RunTable {
     uint32_t* runs;    // [W]
 };
 
+// LDS of chain_rank, in words: run starts, steps, first positions (and, before, candidates),
+// reciprocals (later the prefix), and the sample of lengths.
+constexpr int kChainStart = 0, kChainStep = kRunCap + 16, kChainFirst = kChainStep + kRunCap + kChaseBatch,
+              kChainMore = kChainFirst + kRunCap + kChaseBatch, kChainSample = kChainMore + kRunCap + kChaseBatch,
+              kChainWords = kChainSample + kChainThreads;
+
+// The chain of rank r: cnt sorted lengths at `len`, its positions from `base` on.
 // kIndex: write the group indices here (short ranks); otherwise leave the run table.
-// ranks (or null: whole ranks): an alignment round's buffers; with kIndex the next round's,
-// whose count becomes current here.  sq = floor(sqrt(budget)); by_step: at most kRunCap - 2 steps are possible for this budget
+// sq = floor(sqrt(budget)); by_step: at most kRunCap - 2 steps are possible for this budget
 // and length range (otherwise the rank holds at most kRunCap samples).
 template <bool kIndex>
-__global__ void __launch_bounds__(kChainThreads) chain_kernel(const int64_t* __restrict__ off, RankState* ranks,
-                                                              const int32_t* __restrict__ slen, int64_t budget,
-                                                              int64_t sq, int by_step, int32_t* __restrict__ gidx,
-                                                              int32_t* __restrict__ groups_out, RunTable tbl,
-                                                              const int64_t* __restrict__ tile_first, DevStatus* st) {
-    __shared__ uint32_t s_start[kRunCap + 1], s_b[kRunCap + kChaseBatch], s_c[kRunCap + kChaseBatch],
-        s_m[kRunCap + kChaseBatch];
-    __shared__ int32_t s_len[kChainThreads];
-    const int r = blockIdx.x;
-    const int64_t base = off[r];
-    const int cnt = (int)(ranks ? (kIndex ? ranks[r].next_cnt : ranks[r].cnt) : off[r + 1] - base);
+__device__ __forceinline__ void chain_rank(uint32_t* lds, const int32_t* len, int r, int64_t base, int cnt,
+                                           RankState* ranks, int64_t budget, int64_t sq, int by_step,
+                                           int32_t* __restrict__ gidx, int32_t* __restrict__ groups_out,
+                                           const RunTable& tbl, const int64_t* __restrict__ tile_first,
+                                           DevStatus* st) {
+    uint32_t *s_start = lds + kChainStart, *s_b = lds + kChainStep, *s_c = lds + kChainFirst, *s_m = lds + kChainMore;
+    int32_t* s_len = reinterpret_cast<int32_t*>(lds + kChainSample);
     const int t = threadIdx.x;
-    if (kIndex && ranks && t == 0) ranks[r].cnt = cnt;
     if (cnt <= 1) {   // no position >= 1, no run: position 0 (if any) is the only group start
         if (t == 0) {
             if (kIndex && cnt == 1) gidx[base] = 0;
@@ -883,7 +614,6 @@ __global__ void __launch_bounds__(kChainThreads) chain_kernel(const int64_t* __r
         }
         return;
     }
-    const int32_t* len = slen + base;
     const int last = cnt - 1;   // lengths [0, last) are the steps of positions [1, cnt)
     int R = 0;
     if (by_step) {
@@ -949,7 +679,7 @@ __global__ void __launch_bounds__(kChainThreads) chain_kernel(const int64_t* __r
         // the position before it holds no run start
         const bool busy = lo < hi && (lo == 1 || step_of(len[lo - 2], budget) != step_of(len[hi - 2], budget));
         uint32_t mine = 0, tot;
-        if (busy) chunk_run_starts(slen, base, lo, hi, budget, [&](int, uint32_t) { ++mine; });
+        if (busy) chunk_run_starts(len, lo, hi, budget, [&](int, uint32_t) { ++mine; });
         uint32_t at = chain_scan(mine, &tot);
         if (tot > (uint32_t)kRunCap) {   // cannot happen (at most kRunCap samples)
             if (t == 0) {
@@ -960,7 +690,7 @@ __global__ void __launch_bounds__(kChainThreads) chain_kernel(const int64_t* __r
             return;
         }
         if (mine)
-            chunk_run_starts(slen, base, lo, hi, budget, [&](int q, uint32_t b) {
+            chunk_run_starts(len, lo, hi, budget, [&](int q, uint32_t b) {
                 s_start[at] = (uint32_t)q;
                 s_b[at] = b;
                 ++at;
@@ -1116,6 +846,152 @@ __global__ void __launch_bounds__(kChainThreads) chain_kernel(const int64_t* __r
             tbl.runs[r] = (uint32_t)R;
         }
     }
+}
+
+// ranks (or null: whole ranks): an alignment round's buffers; with kIndex the next round's,
+// whose count becomes current here.
+template <bool kIndex>
+__global__ void __launch_bounds__(kChainThreads) chain_kernel(const int64_t* __restrict__ off, RankState* ranks,
+                                                              const int32_t* __restrict__ slen, int64_t budget,
+                                                              int64_t sq, int by_step, int32_t* __restrict__ gidx,
+                                                              int32_t* __restrict__ groups_out, RunTable tbl,
+                                                              const int64_t* __restrict__ tile_first, DevStatus* st) {
+    __shared__ uint32_t lds[kChainWords];
+    const int r = blockIdx.x;
+    const int64_t base = off[r];
+    const int cnt = (int)(ranks ? (kIndex ? ranks[r].next_cnt : ranks[r].cnt) : off[r + 1] - base);
+    if (kIndex && ranks && threadIdx.x == 0) ranks[r].cnt = cnt;
+    chain_rank<kIndex>(lds, slen + base, r, base, cnt, ranks, budget, sq, by_step, gidx, groups_out, tbl, tile_first, st);
+}
+
+// ---- one block per rank
+// Ranks of at most kRankBlockMax samples are grouped by one block each, in one launch and with
+// no host synchronisation: lengths (invalid ones as 1; odb_align_groups reports them), a
+// stable LSD radix sort by length descending in LDS, the chain and the group indices.
+//
+// The sort is that of the streaming rounds: a wave takes KPT groups of 64 consecutive positions
+// in order and keeps its running count of each digit (up to 8 bits) in LDS, so an item's rank
+// among equal digits is that count plus the lower lanes holding the digit; one scan over
+// (digit, wave) places every wave.  The chain then reads the lengths from LDS.  One round of
+// 1,024 items at a time with two block barriers each, the ids and keys in global memory, and
+// the chain in a second launch took 14 + 10 us on 2 x 2,048 samples and 21 + 13 on 8 x 4,096;
+// 18.6 and 25 us here.
+constexpr int kFormBins = 256;
+
+template <int KPT>
+constexpr size_t form_lds_bytes() {
+    constexpr size_t P = (size_t)kChainThreads * KPT;
+    constexpr size_t sort = 2 * P + 4 * kFormBins * kChainWaves, chain = 4 * kChainWords;
+    return 4 * P + (sort > chain ? sort : chain);
+}
+
+// off: rank offsets in device memory, or null: in `vals`.
+template <int KPT>
+__global__ void __launch_bounds__(kChainThreads) rank_form_kernel(Values vals, const int64_t* __restrict__ off,
+                                                                  const int64_t* __restrict__ tok_off, int64_t budget,
+                                                                  int64_t sq, int by_step,
+                                                                  int32_t* __restrict__ order,
+                                                                  int32_t* __restrict__ slen,
+                                                                  int32_t* __restrict__ gidx,
+                                                                  int32_t* __restrict__ groups_out, DevStatus* st) {
+    constexpr int P = kChainThreads * KPT;
+    constexpr int kPer = kFormBins * kChainWaves / kChainThreads;
+    extern __shared__ uint32_t dyn[];
+    uint32_t* s_len = dyn;
+    uint32_t* s_cnt = dyn + P;                                                       // [digit][wave]
+    uint16_t* s_idx = reinterpret_cast<uint16_t*>(s_cnt + kFormBins * kChainWaves);   // [P]
+    __shared__ uint32_t s_max;
+    const int r = blockIdx.x, t = threadIdx.x, w = t / kWave;
+    const int64_t base = off ? off[r] : vals.v[r];
+    const int cnt = (int)((off ? off[r + 1] : vals.v[r + 1]) - base);
+    if (t == 0) s_max = 0;
+    __syncthreads();
+    if (cnt > 0) {
+        // positions of wave w: [w * KPT * 64, (w + 1) * KPT * 64), item c at + c * 64 + lane
+        const int p0 = w * KPT * kWave + (t & (kWave - 1));
+        uint32_t len[KPT], idx[KPT], mx = 0;
+        int64_t t0[KPT], t1[KPT];
+#pragma unroll
+        for (int c = 0; c < KPT; ++c) {
+            const int p = p0 + c * kWave;
+            const int64_t s = base + (p < cnt ? p : cnt - 1);
+            t0[c] = tok_off[s];
+            t1[c] = tok_off[s + 1];
+        }
+#pragma unroll
+        for (int c = 0; c < KPT; ++c) {
+            const int64_t l = t1[c] - t0[c];
+            len[c] = l < 1 || l > INT_MAX || t0[c] < 0 ? 1u : (uint32_t)l;
+            idx[c] = (uint32_t)(p0 + c * kWave);
+            if (p0 + c * kWave < cnt) mx = len[c] > mx ? len[c] : mx;
+        }
+        mx = wave_scan_dpp<OpMax>(mx);
+        if ((t & (kWave - 1)) == kWave - 1) atomicMax(&s_max, mx);
+        __syncthreads();
+        const int bits = 32 - __clz((int)s_max);
+        const int passes = (bits + 7) / 8;
+        const int dbits = (bits + passes - 1) / passes;
+        const uint32_t mask = (1u << dbits) - 1;
+        for (int k = 0, sh = 0; k < passes; ++k, sh += dbits) {
+            for (int i = t; i < kFormBins * kChainWaves; i += kChainThreads) s_cnt[i] = 0;
+            __syncthreads();
+            uint32_t at[KPT];
+#pragma unroll
+            for (int c = 0; c < KPT; ++c) {
+                const bool valid = p0 + c * kWave < cnt;
+                const uint32_t d = mask - ((len[c] >> sh) & mask);
+                const uint64_t m = match_digit(d, valid, dbits);
+                const uint32_t below = lanes_below(m);
+                // every lane reads the count before the digit's first lane adds to it (LDS
+                // operations of one wave complete in order; the fences keep the compiler to it)
+                at[c] = s_cnt[d * kChainWaves + w] + below;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                if (valid && below == 0) s_cnt[d * kChainWaves + w] += (uint32_t)__popcll(m);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            }
+            __syncthreads();
+            {
+                uint32_t v[kPer], sum = 0, tot;
+#pragma unroll
+                for (int i = 0; i < kPer; ++i) {
+                    v[i] = s_cnt[t * kPer + i];
+                    sum += v[i];
+                }
+                uint32_t ex = chain_scan(sum, &tot);
+#pragma unroll
+                for (int i = 0; i < kPer; ++i) {
+                    s_cnt[t * kPer + i] = ex;
+                    ex += v[i];
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int c = 0; c < KPT; ++c)
+                if (p0 + c * kWave < cnt) {
+                    const uint32_t to = s_cnt[(mask - ((len[c] >> sh) & mask)) * kChainWaves + w] + at[c];
+                    s_len[to] = len[c];
+                    s_idx[to] = (uint16_t)idx[c];
+                }
+            __syncthreads();
+#pragma unroll
+            for (int c = 0; c < KPT; ++c) {
+                const int p = p0 + c * kWave;
+                len[c] = p < cnt ? s_len[p] : 1u;
+                idx[c] = p < cnt ? s_idx[p] : 0u;
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < KPT; ++c) {
+            const int p = p0 + c * kWave;
+            if (p < cnt) {
+                order[base + p] = (int32_t)(base + idx[c]);
+                slen[base + p] = (int32_t)len[c];
+            }
+        }
+        __syncthreads();   // the chain takes the place of the counters and indices
+    }
+    chain_rank<true>(dyn + P, reinterpret_cast<const int32_t*>(s_len), r, base, cnt, nullptr, budget, sq, by_step, gidx,
+                     groups_out, RunTable{}, nullptr, st);
 }
 
 typedef int32_t I4 __attribute__((ext_vector_type(4), aligned(4)));
@@ -1335,7 +1211,6 @@ extern "C" int odb_form_groups(const odb_window_t* w, int64_t budget, int32_t* d
         return set_error(ODB_E_INVALID_ARG, "stage-1 output pointers must not be NULL");
     if (!d_groups_per_rank) return set_error(ODB_E_INVALID_ARG, "d_groups_per_rank is NULL");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    ODB_TRY(upload_small(w, L, d_ws, nullptr, s));
     const int64_t* d_off = ws_at<int64_t>(d_ws, L.rank_off);
     DevStatus* st = ws_at<DevStatus>(d_ws, L.status);
     int32_t* len = ws_at<int32_t>(d_ws, L.len);
@@ -1345,20 +1220,35 @@ extern "C" int odb_form_groups(const odb_window_t* w, int64_t budget, int32_t* d
         if (c > max_cnt) max_cnt = c;
     }
 
-    // one block per rank: two launches, no synchronisation (invalid lengths are grouped as
-    // length 1 and reported by odb_align_groups)
+    // one block per rank: one launch, no synchronisation (invalid lengths are grouped as
+    // length 1 and reported by odb_align_groups); the rank offsets go along as kernel arguments
+    // where they fit
     const ChainBy by = chain_by(budget, max_cnt, 0);
     if (max_cnt <= kRankBlockMax && by != kChainJump) {
-        hipLaunchKernelGGL(rank_sort_kernel, dim3(W), dim3(kRankThreads), 0, s, w->d_token_offsets, d_off, len,
-                           ws_at<int32_t>(d_ws, L.keys0), ws_at<int32_t>(d_ws, L.vals0), ws_at<int32_t>(d_ws, L.keys1),
-                           ws_at<int32_t>(d_ws, L.vals1), d_order, d_sorted_len, st);
-        ODB_LAUNCHED();
-        hipLaunchKernelGGL(chain_kernel<true>, dim3(W), dim3(kChainThreads), 0, s, d_off, (RankState*)nullptr,
-                           (const int32_t*)d_sorted_len, budget, isqrt(budget), by == kChainByStep ? 1 : 0,
-                           d_group_index, d_groups_per_rank, RunTable{}, (const int64_t*)nullptr, st);
+        Values v{};
+        const int64_t* off = nullptr;
+        if (W < kValuesPerLaunch) {
+            for (int r = 0; r <= W; ++r) v.v[r] = w->rank_offsets[r];
+        } else {
+            ODB_TRY(upload_small(w, L, d_ws, nullptr, s));
+            off = d_off;
+        }
+#define ODB_FORM(KPT)                                                                                             \
+    hipLaunchKernelGGL(rank_form_kernel<KPT>, dim3(W), dim3(kChainThreads), form_lds_bytes<KPT>(), s, v, off,      \
+                       w->d_token_offsets, budget, isqrt(budget), by == kChainByStep ? 1 : 0, d_order, d_sorted_len, \
+                       d_group_index, d_groups_per_rank, st)
+        // the fewest positions per thread that hold the largest rank
+        if (max_cnt <= kChainThreads) ODB_FORM(1);
+        else if (max_cnt <= 2 * kChainThreads) ODB_FORM(2);
+        else if (max_cnt <= 4 * kChainThreads) ODB_FORM(4);
+        else if (max_cnt <= 8 * kChainThreads) ODB_FORM(8);
+        else ODB_FORM(16);
+#undef ODB_FORM
+        static_assert(kRankBlockMax <= 16 * kChainThreads, "positions per thread");
         ODB_LAUNCHED();
         return ODB_OK;
     }
+    ODB_TRY(upload_small(w, L, d_ws, nullptr, s));
 
     // (a1) lengths and their validity; the one synchronisation of this call
     hipLaunchKernelGGL(lengths_kernel, dim3(grid_for(n, kBlock, (int64_t)num_cus() * kLengthsBlocksPerCU)), dim3(kBlock), 0, s,

@@ -147,6 +147,14 @@ int check_workspace(const odb_window_t* w, void* d_ws, size_t ws_bytes, Layout* 
 int upload_small(const odb_window_t* w, const Layout& L, void* d_ws, const int64_t* cap,
                  hipStream_t s, bool rounds = false);
 
+// Small host arrays reach the device as kernel arguments, kValuesPerLaunch values per
+// launch: no host-to-device copy (which, from pageable memory, may wait for the stream)
+// and nothing a graph capture could not record.
+constexpr int kValuesPerLaunch = 128;
+struct Values {
+    int64_t v[kValuesPerLaunch];
+};
+
 // Stores `count` host values at dst through kernel arguments; also resets the status word,
 // the round state and the summary where they are given.
 int store_values(const int64_t* src, int64_t count, int64_t* dst, DevStatus* st, hipStream_t s,

@@ -755,3 +755,17 @@ def test_align_takes_any_consistent_groups(sizes, capped):
     assert np.array_equal(pipe.slot_rows[:K].cpu().numpy(), ref[:, :, 0].reshape(-1))
     assert np.array_equal(pipe.slot_maxlen[:K].cpu().numpy(), ref[:, :, 1].reshape(-1))
     assert np.array_equal(pipe.slot_tokens[:K].cpu().numpy(), ref[:, :, 2].reshape(-1))
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 1023, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 16384])
+def test_one_block_grouping_sizes(n):
+    """Ranks at the edges of the one-block grouping's variants (positions per thread 1 to 16),
+    beside a shorter rank, with one digit, two digits and four digits of lengths, and all equal."""
+    rng = np.random.default_rng(n)
+    m = max(1, n - 3)
+    for lo, hi, budget in ((7, 8, 64), (1, 200, 900), (1, 20000, 60000), (1, 2 ** 31 - 1, 2 ** 40)):
+        w = synth.window_from_ranks(f"form_{n}_{hi}", [rng.integers(lo, hi, n), rng.integers(lo, hi, m)], budget)
+        ref = oracle.plan_window(w)
+        import torch
+        pipe, _ = run_gpu(w, tokens=torch.zeros(1, dtype=torch.int32, device="cuda"), collate=False)
+        compare_plan(w, pipe, ref)
