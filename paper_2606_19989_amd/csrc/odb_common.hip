@@ -52,10 +52,11 @@ bool make_layout(const odb_window_t* w, Layout* L) {
     const int64_t W = w->num_ranks;
     const int64_t n = w->num_samples;
     const int64_t nid = w->d_identity ? w->num_identities : n;
-    int64_t nb = 0, max_nr = 0;
+    int64_t nb = 0, nb2 = 0, max_nr = 0;
     for (int64_t r = 0; r < W; ++r) {
         int64_t nr = w->rank_offsets[r + 1] - w->rank_offsets[r];
         nb += (nr + kSortTile - 1) / kSortTile;
+        nb2 += (nr + 2 * kSortTile - 1) / (2 * kSortTile);
         if (nr > max_nr) max_nr = nr;
     }
     const int64_t n1 = n + 1;
@@ -115,7 +116,8 @@ bool make_layout(const odb_window_t* w, Layout* L) {
     L->row_ts = take(8 * (n1 + W));
     L->row_len = take(4 * (n1 + W));
     L->total = o;
-    L->num_sort_blocks = nb;
+    L->num_sort_blocks[0] = nb;
+    L->num_sort_blocks[1] = nb2;
     L->partials_len = partials;
     return true;
 }

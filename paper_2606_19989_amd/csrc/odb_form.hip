@@ -120,16 +120,16 @@ __global__ void rank_counts_kernel(const int64_t* __restrict__ off, int W, RankS
     }
 }
 
-// First radix tile of every rank: tile_first[r] = sum_{r' < r} ceil(n_r' / kSortTile).
+// First radix tile of every rank: tile_first[r] = sum_{r' < r} ceil(n_r' / tile).
 // Tiles never straddle ranks.  One block.
-__global__ void __launch_bounds__(kBlock) sort_tiles_kernel(const int64_t* __restrict__ off, int W,
+__global__ void __launch_bounds__(kBlock) sort_tiles_kernel(const int64_t* __restrict__ off, int W, int tile,
                                                             int64_t* __restrict__ tile_first) {
     __shared__ int64_t carry;
     if (threadIdx.x == 0) carry = 0;
     __syncthreads();
     for (int b = 0; b < W; b += kBlock) {
         const int r = b + threadIdx.x;
-        const int64_t v = r < W ? (off[r + 1] - off[r] + kSortTile - 1) / kSortTile : 0;
+        const int64_t v = r < W ? (off[r + 1] - off[r] + tile - 1) / tile : 0;
         int64_t tot;
         const int64_t ex = block_excl_sum(v, &tot);
         const int64_t c = carry;
@@ -143,12 +143,13 @@ __global__ void __launch_bounds__(kBlock) sort_tiles_kernel(const int64_t* __res
 
 struct SortTile {
     int64_t start;       // first position
-    int32_t count;       // keys in this tile (<= kSortTile)
+    int32_t count;       // keys in this tile
     int32_t seg_tiles;   // tiles of this tile's rank
     int64_t first;       // global index of the rank's first tile
     int32_t j;           // index of this tile within its rank
 };
 
+template <int kTile>
 __device__ __forceinline__ SortTile sort_tile(const int64_t* __restrict__ off,
                                               const int64_t* __restrict__ tile_first, int W, int64_t b) {
     const int r = rank_of(tile_first, W, b);
@@ -156,11 +157,17 @@ __device__ __forceinline__ SortTile sort_tile(const int64_t* __restrict__ off,
     t.first = tile_first[r];
     t.j = (int32_t)(b - t.first);
     t.seg_tiles = (int32_t)(tile_first[r + 1] - t.first);
-    t.start = off[r] + (int64_t)t.j * kSortTile;
+    t.start = off[r] + (int64_t)t.j * kTile;
     const int64_t left = off[r + 1] - t.start;
-    t.count = (int32_t)(left < kSortTile ? left : kSortTile);
+    t.count = (int32_t)(left < kTile ? left : kTile);
     return t;
 }
+
+// Keys per thread of a tile: 16 where that still leaves every compute unit four tiles and more,
+// else 8.  Longer tiles write longer runs per digit (64 x 262,144 samples: the low-digit
+// scatter 78 -> 61 us, the plan 566 -> 543), shorter ones spread a smaller window further
+// (16 x 65,536: 204 us against 199).
+inline int sort_items(int64_t n) { return n >= (int64_t)4 << 20 ? 2 * kSortItems : kSortItems; }
 
 // Digit counts of every tile.  kHistCopies copies of the table, lane l counting in copy
 // l mod kHistCopies with a plain LDS add: equal digits of a wave (the high digit of
@@ -169,19 +176,19 @@ __device__ __forceinline__ SortTile sort_tile(const int64_t* __restrict__ off,
 // 16.7 M samples.
 constexpr int kHistCopies = 8;
 
-template <bool kFirst>
+template <int kItems, bool kFirst>
 __global__ void __launch_bounds__(kBlock) radix_hist_kernel(const int64_t* __restrict__ off,
                                                             const int64_t* __restrict__ tile_first, int W,
                                                             const uint32_t* __restrict__ keys_in,
                                                             const int32_t* __restrict__ len_in, uint32_t maxl,
                                                             int shift, int dbits, uint32_t* __restrict__ counts) {
-    const SortTile b = sort_tile(off, tile_first, W, blockIdx.x);
+    const SortTile b = sort_tile<kBlock * kItems>(off, tile_first, W, blockIdx.x);
     const int radix = 1 << dbits;
     const uint32_t mask = (uint32_t)radix - 1;
     __shared__ uint32_t h[256 * kHistCopies];
-    uint32_t key[kSortItems];
+    uint32_t key[kItems];
 #pragma unroll
-    for (int it = 0; it < kSortItems; ++it) {
+    for (int it = 0; it < kItems; ++it) {
         const int li = it * kBlock + threadIdx.x;
         const int64_t p = b.start + (li < b.count ? li : 0);
         key[it] = kFirst ? maxl - (uint32_t)len_in[p] : keys_in[p];
@@ -189,7 +196,7 @@ __global__ void __launch_bounds__(kBlock) radix_hist_kernel(const int64_t* __res
     for (int i = threadIdx.x; i < radix * kHistCopies; i += kBlock) h[i] = 0;
     __syncthreads();
 #pragma unroll
-    for (int it = 0; it < kSortItems; ++it)
+    for (int it = 0; it < kItems; ++it)
         if (it * kBlock + (int)threadIdx.x < b.count)
             atomicAdd(&h[((key[it] >> shift) & mask) * kHistCopies + (threadIdx.x & (kHistCopies - 1))], 1u);
     __syncthreads();
@@ -261,27 +268,27 @@ __global__ void __launch_bounds__(kRankScanThreads) rank_scan_kernel(const int64
 // round, they cost 4.6 B of HBM writes per byte).  The count, slot table and placement done round
 // by round, two block barriers each, took 90 and 82 instead of 78 and 59 us for the two passes over
 // 16.7 M samples (the low digit spreads a tile over twice the runs).
-template <bool kFirst, bool kLast>
+template <int kItems, bool kFirst, bool kLast>
 __global__ void __launch_bounds__(kBlock) radix_scatter_kernel(
     const int64_t* __restrict__ off, const int64_t* __restrict__ tile_first, int W,
     const uint32_t* __restrict__ keys_in,
     const int32_t* __restrict__ len_in, const int32_t* __restrict__ vals_in, uint32_t maxl, int shift,
     int dbits, const uint32_t* __restrict__ offs, uint32_t* __restrict__ keys_out,
     int32_t* __restrict__ vals_out, int32_t* __restrict__ slen_out) {
-    const SortTile b = sort_tile(off, tile_first, W, blockIdx.x);
+    const SortTile b = sort_tile<kBlock * kItems>(off, tile_first, W, blockIdx.x);
     const int radix = 1 << dbits;
     const uint32_t mask = (uint32_t)radix - 1;
-    constexpr int kWaves = kBlock / kWave;
+    constexpr int kWaves = kBlock / kWave, kTile = kBlock * kItems;
     __shared__ uint32_t s_shift[256];         // global position of the digit's first item less its local one
     __shared__ uint32_t s_cnt[kWaves][256];   // items of a digit in a wave, then the wave's first local slot
-    __shared__ uint32_t s_key[kSortTile];
-    __shared__ int32_t s_val[kSortTile];
+    __shared__ uint32_t s_key[kTile];
+    __shared__ int32_t s_val[kTile];
     const int w = threadIdx.x / kWave;
-    const int p0 = w * (kSortTile / kWaves) + (threadIdx.x & (kWave - 1));   // item it: p0 + it * 64
-    uint32_t key[kSortItems];
-    int32_t val[kSortItems];
+    const int p0 = w * (kTile / kWaves) + (threadIdx.x & (kWave - 1));   // item it: p0 + it * 64
+    uint32_t key[kItems];
+    int32_t val[kItems];
 #pragma unroll
-    for (int it = 0; it < kSortItems; ++it) {
+    for (int it = 0; it < kItems; ++it) {
         const int li = p0 + it * kWave;
         const int64_t p = b.start + (li < b.count ? li : 0);
         key[it] = kFirst ? maxl - (uint32_t)len_in[p] : keys_in[p];
@@ -293,9 +300,9 @@ __global__ void __launch_bounds__(kBlock) radix_scatter_kernel(
 #pragma unroll
     for (int k = 0; k < kWaves; ++k) s_cnt[k][threadIdx.x] = 0;
     __syncthreads();
-    uint32_t at[kSortItems];
+    uint32_t at[kItems];
 #pragma unroll
-    for (int it = 0; it < kSortItems; ++it) {
+    for (int it = 0; it < kItems; ++it) {
         const bool valid = p0 + it * kWave < b.count;
         const uint32_t d = (key[it] >> shift) & mask;
         const uint64_t peers = match_digit(d, valid, dbits);
@@ -325,7 +332,7 @@ __global__ void __launch_bounds__(kBlock) radix_scatter_kernel(
     }
     __syncthreads();
 #pragma unroll
-    for (int it = 0; it < kSortItems; ++it) {
+    for (int it = 0; it < kItems; ++it) {
         if (p0 + it * kWave < b.count) {
             const uint32_t q = s_cnt[w][(key[it] >> shift) & mask] + at[it];
             s_key[q] = key[it];
@@ -334,7 +341,7 @@ __global__ void __launch_bounds__(kBlock) radix_scatter_kernel(
     }
     __syncthreads();
 #pragma unroll
-    for (int it = 0; it < kSortItems; ++it) {
+    for (int it = 0; it < kItems; ++it) {
         const int q = it * kBlock + threadIdx.x;
         if (q >= b.count) break;
         const uint32_t k = s_key[q];
@@ -601,7 +608,7 @@ template <bool kIndex>
 __device__ __forceinline__ void chain_rank(uint32_t* lds, const int32_t* len, int r, int64_t base, int cnt,
                                            RankState* ranks, int64_t budget, int64_t sq, int by_step,
                                            int32_t* __restrict__ gidx, int32_t* __restrict__ groups_out,
-                                           const RunTable& tbl, const int64_t* __restrict__ tile_first,
+                                           const RunTable& tbl, const int64_t* __restrict__ tile_first, int tile,
                                            DevStatus* st) {
     uint32_t *s_start = lds + kChainStart, *s_b = lds + kChainStep, *s_c = lds + kChainFirst, *s_m = lds + kChainMore;
     int32_t* s_len = reinterpret_cast<int32_t*>(lds + kChainSample);
@@ -838,7 +845,7 @@ __device__ __forceinline__ void chain_rank(uint32_t* lds, const int32_t* len, in
         }
         const int64_t t0 = tile_first[r], t1 = tile_first[r + 1];
         for (int64_t j = t0 + t; j < t1; j += kChainThreads) {
-            const int64_t q = (j - t0) * kSortTile;
+            const int64_t q = (j - t0) * tile;
             if (q < cnt) tbl.tile[j] = (uint32_t)(q > 0 ? run_of((uint32_t)q) : 0);
         }
         if (t == 0) {
@@ -855,13 +862,15 @@ __global__ void __launch_bounds__(kChainThreads) chain_kernel(const int64_t* __r
                                                               const int32_t* __restrict__ slen, int64_t budget,
                                                               int64_t sq, int by_step, int32_t* __restrict__ gidx,
                                                               int32_t* __restrict__ groups_out, RunTable tbl,
-                                                              const int64_t* __restrict__ tile_first, DevStatus* st) {
+                                                              const int64_t* __restrict__ tile_first, int tile,
+                                                              DevStatus* st) {
     __shared__ uint32_t lds[kChainWords];
     const int r = blockIdx.x;
     const int64_t base = off[r];
     const int cnt = (int)(ranks ? (kIndex ? ranks[r].next_cnt : ranks[r].cnt) : off[r + 1] - base);
     if (kIndex && ranks && threadIdx.x == 0) ranks[r].cnt = cnt;
-    chain_rank<kIndex>(lds, slen + base, r, base, cnt, ranks, budget, sq, by_step, gidx, groups_out, tbl, tile_first, st);
+    chain_rank<kIndex>(lds, slen + base, r, base, cnt, ranks, budget, sq, by_step, gidx, groups_out, tbl, tile_first,
+                       tile, st);
 }
 
 // ---- one block per rank
@@ -991,28 +1000,29 @@ __global__ void __launch_bounds__(kChainThreads) rank_form_kernel(Values vals, c
         __syncthreads();   // the chain takes the place of the counters and indices
     }
     chain_rank<true>(dyn + P, reinterpret_cast<const int32_t*>(s_len), r, base, cnt, nullptr, budget, sq, by_step, gidx,
-                     groups_out, RunTable{}, nullptr, st);
+                     groups_out, RunTable{}, nullptr, 0, st);
 }
 
 typedef int32_t I4 __attribute__((ext_vector_type(4), aligned(4)));
 
 // Group index of every live position, and with `gstart` the global position of every group
-// start at its global group id, from the run table.  One block per sort tile, eight
+// start at its global group id, from the run table.  One block per sort tile, kItems
 // consecutive positions per thread: one search (between the runs of the tile's first
 // positions) and one division, then a step along the run.
+template <int kItems>
 __global__ void __launch_bounds__(kBlock) chain_index_kernel(const int64_t* __restrict__ off,
                                                              const int64_t* __restrict__ tile_first, int W,
                                                              const RankState* __restrict__ ranks, RunTable tbl,
                                                              int32_t* __restrict__ gidx, int32_t* __restrict__ gstart) {
-    static_assert(kSortTile == kBlock * 8, "eight positions per thread");
+    constexpr int kTile = kBlock * kItems;
     const int64_t b = blockIdx.x;
     const int r = rank_of(tile_first, W, b);
     const int64_t base = off[r];
     const int64_t cnt = ranks ? ranks[r].cnt : off[r + 1] - base;
-    const int64_t tile0 = (b - tile_first[r]) * kSortTile;
-    const int64_t q0 = tile0 + (int64_t)threadIdx.x * 8;
+    const int64_t tile0 = (b - tile_first[r]) * kTile;
+    const int64_t q0 = tile0 + (int64_t)threadIdx.x * kItems;
     if (q0 >= cnt) return;
-    const int m = cnt - q0 < 8 ? (int)(cnt - q0) : 8;
+    const int m = cnt - q0 < kItems ? (int)(cnt - q0) : kItems;
     // the run of position max(q0, 1), between the runs of this tile's and the next tile's first
     // positions
     const int32_t* start = tbl.start + base;
@@ -1037,17 +1047,17 @@ __global__ void __launch_bounds__(kBlock) chain_index_kernel(const int64_t* __re
     };
     if (cnt > 1) {
         a = (int)tbl.tile[b];
-        int z = tile0 + kSortTile < cnt ? (int)tbl.tile[b + 1] + 1 : (int)tbl.runs[r];
+        int z = tile0 + kTile < cnt ? (int)tbl.tile[b + 1] + 1 : (int)tbl.runs[r];
         while (z - a > 1) {
             const int mid = (a + z) >> 1;
             if ((uint32_t)start[mid] <= q) a = mid; else z = mid;
         }
         enter(q);
     }
-    int32_t out[8];
+    int32_t out[kItems];
     uint32_t heads = 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < kItems; ++i) {
         const uint32_t x = (uint32_t)q0 + i;
         if (x == 0) {   // position 0: the first group, of one
             out[i] = 0;
@@ -1071,18 +1081,18 @@ __global__ void __launch_bounds__(kBlock) chain_index_kernel(const int64_t* __re
         heads |= head && i < m ? 1u << i : 0u;
     }
     int32_t* o = gidx + base + q0;
-    if (m == 8) {
-        *reinterpret_cast<I4*>(o) = I4{out[0], out[1], out[2], out[3]};
-        *reinterpret_cast<I4*>(o + 4) = I4{out[4], out[5], out[6], out[7]};
+    if (m == kItems) {
+#pragma unroll
+        for (int i = 0; i < kItems; i += 4) *reinterpret_cast<I4*>(o + i) = I4{out[i], out[i + 1], out[i + 2], out[i + 3]};
     } else {
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < kItems; ++i)
             if (i < m) o[i] = out[i];
     }
     if (gstart) {
         const int64_t gb = ranks[r].gbase;
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < kItems; ++i)
             if ((heads >> i) & 1) gstart[gb + out[i]] = (int32_t)(base + q0 + i);
     }
 }
@@ -1114,7 +1124,7 @@ int group_short_ranks(int W, int64_t budget, int64_t max_cnt, const int64_t* d_r
                       int32_t* d_gidx, RankState* d_ranks, DevStatus* st, hipStream_t s) {
     hipLaunchKernelGGL(chain_kernel<true>, dim3(W), dim3(kChainThreads), 0, s, d_rank_off, d_ranks, d_slen, budget,
                        isqrt(budget), chain_by(budget, max_cnt, 0) == kChainByStep ? 1 : 0, d_gidx, (int32_t*)nullptr,
-                       RunTable{}, (const int64_t*)nullptr, st);
+                       RunTable{}, (const int64_t*)nullptr, 0, st);
     ODB_LAUNCHED();
     return ODB_OK;
 }
@@ -1148,24 +1158,26 @@ int group_sequences(const Layout& L, void* ws, int W, int64_t n, int64_t budget,
     const unsigned grid = grid_for(n + 1, kBlock, (int64_t)num_cus() * kPlanBlocksPerCU);
     const ChainBy by = chain_by(budget, max_cnt, len_range);
     if (by != kChainJump) {
+        const int items = sort_items(n);
         int64_t* d_tile_first = ws_at<int64_t>(ws, L.tile_first);
         if (!tiles_ready) {
-            hipLaunchKernelGGL(sort_tiles_kernel, dim3(1), dim3(kBlock), 0, s, d_off, W, d_tile_first);
+            hipLaunchKernelGGL(sort_tiles_kernel, dim3(1), dim3(kBlock), 0, s, d_off, W, (int)kBlock * items, d_tile_first);
             ODB_LAUNCHED();
         }
         const RunTable tbl{j0, j1, ws_at<int32_t>(ws, L.gsize), incl, ws_at<uint32_t>(ws, L.counts),
                            ws_at<uint32_t>(ws, L.rank_runs)};
         hipLaunchKernelGGL(chain_kernel<false>, dim3(W), dim3(kChainThreads), 0, s, d_off, d_ranks, d_slen, budget,
                            isqrt(budget), by == kChainByStep ? 1 : 0, (int32_t*)nullptr, d_groups_out, tbl,
-                           (const int64_t*)d_tile_first, st);
+                           (const int64_t*)d_tile_first, (int)kBlock * items, st);
         ODB_LAUNCHED();
         if (d_ranks) {   // the next round of an alignment numbers its groups over all ranks
             hipLaunchKernelGGL(rank_groups_kernel, dim3(1), dim3(kBlock), 0, s, d_ranks, W, ws_at<int64_t>(ws, L.gbase));
             ODB_LAUNCHED();
         }
-        const unsigned tiles = (unsigned)L.num_sort_blocks;
+        const unsigned tiles = (unsigned)L.num_sort_blocks[items > kSortItems];
         if (tiles > 0) {
-            hipLaunchKernelGGL(chain_index_kernel, dim3(tiles), dim3(kBlock), 0, s, d_off, (const int64_t*)d_tile_first,
+            const auto kernel = items > kSortItems ? chain_index_kernel<2 * kSortItems> : chain_index_kernel<kSortItems>;
+            hipLaunchKernelGGL(kernel, dim3(tiles), dim3(kBlock), 0, s, d_off, (const int64_t*)d_tile_first,
                                W, (const RankState*)d_ranks, tbl, d_gidx,
                                d_ranks ? ws_at<int32_t>(ws, L.gstart) : (int32_t*)nullptr);
             ODB_LAUNCHED();
@@ -1271,9 +1283,11 @@ extern "C" int odb_form_groups(const odb_window_t* w, int64_t budget, int32_t* d
         ODB_LAUNCHED();
     } else {
         const int dbits = (bits + passes - 1) / passes;
-        const int64_t NB = L.num_sort_blocks;
+        const int items = sort_items(n);
+        const bool longer = items > kSortItems;
+        const int64_t NB = L.num_sort_blocks[longer];
         int64_t* d_tile_first = ws_at<int64_t>(d_ws, L.tile_first);
-        hipLaunchKernelGGL(sort_tiles_kernel, dim3(1), dim3(kBlock), 0, s, d_off, W, d_tile_first);
+        hipLaunchKernelGGL(sort_tiles_kernel, dim3(1), dim3(kBlock), 0, s, d_off, W, (int)kBlock * items, d_tile_first);
         ODB_LAUNCHED();
         uint32_t* counts = ws_at<uint32_t>(d_ws, L.counts);
         uint32_t* keys[2] = {ws_at<uint32_t>(d_ws, L.keys0), ws_at<uint32_t>(d_ws, L.keys1)};
@@ -1285,16 +1299,12 @@ extern "C" int odb_form_groups(const odb_window_t* w, int64_t budget, int32_t* d
             const int32_t* vin = first ? nullptr : vals[(pass - 1) & 1];
             uint32_t* kout = last ? nullptr : keys[pass & 1];
             int32_t* vout = last ? d_order : vals[pass & 1];
-            if (first)
-                hipLaunchKernelGGL(radix_hist_kernel<true>, dim3((unsigned)NB), dim3(kBlock), 0, s, d_off,
-                                   (const int64_t*)d_tile_first, W, kin, (const int32_t*)len, maxl, shift, dbits,
-                                   counts);
-            else
-                hipLaunchKernelGGL(radix_hist_kernel<false>, dim3((unsigned)NB), dim3(kBlock), 0, s, d_off,
-                                   (const int64_t*)d_tile_first, W, kin, (const int32_t*)len, maxl, shift, dbits,
-                                   counts);
+            const auto hist = first ? (longer ? radix_hist_kernel<2 * kSortItems, true> : radix_hist_kernel<kSortItems, true>)
+                                    : (longer ? radix_hist_kernel<2 * kSortItems, false> : radix_hist_kernel<kSortItems, false>);
+            hipLaunchKernelGGL(hist, dim3((unsigned)NB), dim3(kBlock), 0, s, d_off, (const int64_t*)d_tile_first, W, kin,
+                               (const int32_t*)len, maxl, shift, dbits, counts);
             ODB_LAUNCHED();
-            if (dbits >= 2 && ((max_cnt + kSortTile - 1) / kSortTile << dbits) <= kRankScanMax) {
+            if (dbits >= 2 && ((max_cnt + kBlock * items - 1) / (kBlock * items) << dbits) <= kRankScanMax) {
                 hipLaunchKernelGGL(rank_scan_kernel, dim3(W), dim3(kRankScanThreads), 0, s, d_off,
                                    (const int64_t*)d_tile_first, dbits, counts);
                 ODB_LAUNCHED();
@@ -1302,10 +1312,12 @@ extern "C" int odb_form_groups(const odb_window_t* w, int64_t budget, int32_t* d
                 ODB_TRY((device_excl_scan<uint32_t>(CountLoad{counts, NB << dbits}, CountStore{counts}, NB << dbits,
                                                     ws_at<uint32_t>(d_ws, L.partials), s)));
             }
-#define ODB_SCATTER(F, La)                                                                                  \
-    hipLaunchKernelGGL((radix_scatter_kernel<F, La>), dim3((unsigned)NB), dim3(kBlock), 0, s,               \
-                       d_off, (const int64_t*)d_tile_first, W, kin, (const int32_t*)len, vin, maxl, shift,  \
-                       dbits, (const uint32_t*)counts, kout, vout, d_sorted_len)
+#define ODB_SCATTER(F, La)                                                                                    \
+    do {                                                                                                      \
+        const auto scatter = longer ? radix_scatter_kernel<2 * kSortItems, F, La> : radix_scatter_kernel<kSortItems, F, La>; \
+        hipLaunchKernelGGL(scatter, dim3((unsigned)NB), dim3(kBlock), 0, s, d_off, (const int64_t*)d_tile_first, W,          \
+                           kin, (const int32_t*)len, vin, maxl, shift, dbits, (const uint32_t*)counts, kout, vout, d_sorted_len); \
+    } while (0)
             if (first && last) ODB_SCATTER(true, true);
             else if (first) ODB_SCATTER(true, false);
             else if (last) ODB_SCATTER(false, true);

@@ -127,7 +127,7 @@ struct Layout {
     size_t buf_ids0, buf_ids1, buf_len0, buf_len1, gidx, stage, stage_len, cover, row_ts, row_len;
     size_t info, sketch;
     size_t total;
-    int64_t num_sort_blocks;
+    int64_t num_sort_blocks[2];   // radix tiles of kSortItems and of twice as many keys per thread
     int64_t partials_len;
 };
 

@@ -769,3 +769,16 @@ def test_one_block_grouping_sizes(n):
         import torch
         pipe, _ = run_gpu(w, tokens=torch.zeros(1, dtype=torch.int32, device="cuda"), collate=False)
         compare_plan(w, pipe, ref)
+
+
+@pytest.mark.parametrize("per_rank", [(1 << 22) // 3 + 1, (1 << 22) // 3])
+def test_sort_tile_lengths(per_rank):
+    """Windows just at and just below 4 Mi samples: the longer and the shorter radix tile, ragged
+    against both, with a one-sample and an empty rank between."""
+    import torch
+    rng = np.random.default_rng(95)
+    sizes = [per_rank, 0, per_rank - 1, 1, per_rank + 1]
+    w = synth.window_from_ranks("sort_tiles", [rng.integers(1, 5000, n) for n in sizes], 1 << 20)
+    ref = oracle.plan_window(w)
+    pipe, _ = run_gpu(w, tokens=torch.zeros(1, dtype=torch.int32, device="cuda"), collate=False)
+    compare_plan(w, pipe, ref)
