@@ -947,7 +947,10 @@ __global__ void __launch_bounds__(kST) stream_book_kernel(StreamArgs a, int64_t 
 // chain of latencies that leaves three quarters of the chip idle: 64 ranks x 262,144 views
 // in 257 rounds took 5.45 ms of round launches (21 us each) and 0.65 ms for the view table;
 // formed together they take 0.39 ms (the form, bound by its 16.7 M random reads of the CSR
-// offsets) and 0.06 ms (the slots).
+// offsets) and 0.06 ms (the slots).  A short stream is bound by the number of launches:
+// 2 ranks x 4,091 views take five and 43 us with the read-back and the loss weights (70 us
+// in twelve, with the cut, the tile scan, the sums over the steps and the identity counts in
+// launches of their own).
 //
 // A rank's emitted views of a round are its whole buffer, shortest first: the reverse of
 // formation order, whatever the split.  So the form writes identities, views and row
@@ -966,8 +969,8 @@ struct BulkState {
     unsigned long long real_tokens;
     unsigned long long bad_views;
     int64_t padded;
-    int64_t missing_ids;
-    int64_t duplicate_ids;
+    unsigned long long missing_ids;     // summed modulo 2^64
+    unsigned long long duplicate_ids;
     int32_t err;
     int32_t pad;
 };
@@ -1250,58 +1253,7 @@ __global__ void __launch_bounds__(NT) bulk_form_kernel(BulkArgs b) {
     for (int g = tid; g < G; g += NT) b.gs[out + g] = s_gs[g];
 }
 
-// Targets and running step counts of all rounds, and the first round that would overflow.
-// One block, one thread per round.
-__global__ void __launch_bounds__(1024) bulk_targets_kernel(BulkArgs b) {
-    __shared__ int32_t s_fail;
-    int64_t steps = 0, splits = 0, changed = 0;
-    for (int64_t e0 = 0; e0 < b.E; e0 += 1024) {
-        if (threadIdx.x == 0) s_fail = 1024;
-        __syncthreads();
-        const int64_t e = e0 + threadIdx.x;
-        int64_t T = 0, more = 0;   // target, and the splits it takes
-        if (e < b.E) {
-            const int64_t mx = b.T[e];
-            int64_t c, held, ready = b.W;   // fewest views held by a rank that is not finished
-            bulk_range(b, 0, e, &c, &held);
-            if (b.sched) {
-                held = LLONG_MAX;
-                ready = 0;
-                for (int r = 0; r < b.W; ++r) {
-                    int64_t n;
-                    bulk_range(b, r, e, &c, &n);
-                    ready += n > 0;
-                    held = n > 0 && n < held ? n : held;
-                }
-            }
-            T = mx > 1 ? mx : 1;
-            more = T * ready - (int64_t)b.sum[e];
-            if (mx > held) atomicMin(&s_fail, (int32_t)threadIdx.x);
-        }
-        __syncthreads();
-        const int32_t fail = s_fail;
-        const bool live = e < b.E && (int32_t)threadIdx.x < fail;
-        if (!live) T = more = 0;
-        int64_t tot;
-        const int64_t ex = sblock_excl<1024>(T, &tot);
-        if (live) {
-            b.T[e] = (int32_t)T;
-            b.base[e] = steps + ex;
-        }
-        steps += tot;
-        splits += sblock_sum<1024>(more);
-        changed += sblock_sum<1024>((int64_t)(more != 0));
-        if (fail < 1024 || e0 + 1024 >= b.E) {
-            if (threadIdx.x == 0) {
-                b.st->steps = steps;
-                b.st->splits = splits;
-                b.st->changed = changed;
-                b.st->fail = fail < 1024 ? e0 + fail : b.E;
-            }
-            return;
-        }
-    }
-}
+constexpr int kTargetThreads = 1024;
 
 // Where a split leaves its pieces: positions [0, X) are singletons, [X, end of group j*) is one
 // group and later groups are unchanged; j* is the first group with start(j* + 1) - (j* + 1) >=
@@ -1334,15 +1286,13 @@ __device__ __forceinline__ void bulk_group(const int32_t* gs, int G, int n, Bulk
 }
 
 // Non-join: the steps of the last round up to the one that reaches the quota, and from them
-// every rank's emitted rows (lo: their running sum over the ranks) and left-over views.  One
-// block; dynamic LDS: a BulkSplit per rank.
-__global__ void __launch_bounds__(kST) bulk_cut_kernel(BulkArgs b, int64_t before, int64_t* __restrict__ left_off) {
-    extern __shared__ unsigned long long s_dyn[];
-    BulkSplit* s_sp = reinterpret_cast<BulkSplit*>(s_dyn);
-    if (b.st->err || b.st->fail < b.E) return;
+// every rank's emitted rows (lo: their running sum over the ranks) and left-over views.
+// T, base: target of the last round and the steps before it; s_sp: LDS, a BulkSplit per rank.
+// Called by a whole block of kTargetThreads.
+__device__ void bulk_cut(const BulkArgs& b, BulkSplit* s_sp, int T, int64_t base, int64_t before,
+                         int64_t* __restrict__ left_off) {
     const int64_t e = b.E - 1;
-    const int T = b.T[e];
-    for (int r = threadIdx.x; r < b.W; r += kST) {
+    for (int r = threadIdx.x; r < b.W; r += kTargetThreads) {
         int64_t c, n;
         bulk_range(b, r, e, &c, &n);
         s_sp[r] = n > 0 ? bulk_split(b.gs + (int64_t)r * b.q + c, b.G[(int64_t)r * b.E + e], T) : BulkSplit{0, -1};
@@ -1351,7 +1301,7 @@ __global__ void __launch_bounds__(kST) bulk_cut_kernel(BulkArgs b, int64_t befor
     if (threadIdx.x == 0) s_cut = T;
     __syncthreads();
     int64_t carry = before;
-    for (int j0 = 0; j0 < T && carry < b.quota; j0 += kST) {   // uniform
+    for (int j0 = 0; j0 < T && carry < b.quota; j0 += kTargetThreads) {   // uniform
         const int j = j0 + threadIdx.x;
         int64_t v = 0;
         if (j < T) {
@@ -1366,14 +1316,14 @@ __global__ void __launch_bounds__(kST) bulk_cut_kernel(BulkArgs b, int64_t befor
             }
         }
         int64_t tot;
-        const int64_t ex = carry + sblock_excl<kST>(v, &tot);
+        const int64_t ex = carry + sblock_excl<kTargetThreads>(v, &tot);
         if (j < T && ex < b.quota && ex + v >= b.quota) s_cut = j + 1;
         carry += tot;
     }
     __syncthreads();
     const int cut = s_cut;
     int64_t rows = 0, left = 0;
-    for (int r0 = 0; r0 < b.W; r0 += kST) {
+    for (int r0 = 0; r0 < b.W; r0 += kTargetThreads) {
         const int r = r0 + threadIdx.x;
         int64_t out = 0, stay = 0;
         if (r < b.W) {
@@ -1386,7 +1336,7 @@ __global__ void __launch_bounds__(kST) bulk_cut_kernel(BulkArgs b, int64_t befor
             stay = b.q - out;
         }
         int64_t to, ts;
-        const int64_t xo = sblock_excl<kST>(out, &to), xs = sblock_excl<kST>(stay, &ts);
+        const int64_t xo = sblock_excl<kTargetThreads>(out, &to), xs = sblock_excl<kTargetThreads>(stay, &ts);
         if (r < b.W) {
             b.lo[r] = rows + xo;
             left_off[r] = left + xs;
@@ -1399,7 +1349,72 @@ __global__ void __launch_bounds__(kST) bulk_cut_kernel(BulkArgs b, int64_t befor
         left_off[b.W] = left;
         b.st->cut = cut;
         b.st->emitted = rows;
-        b.st->steps = b.base[e] + cut;
+        b.st->steps = base + cut;
+    }
+}
+
+// Targets and running step counts of all rounds, and the first round that would overflow.
+// One block, one thread per round; in non-join mode the same block goes on to the cut (dynamic
+// LDS: a BulkSplit per rank).
+__global__ void __launch_bounds__(kTargetThreads) bulk_targets_kernel(BulkArgs b, int64_t before,
+                                                                      int64_t* __restrict__ left_off) {
+    extern __shared__ unsigned long long s_dyn[];
+    __shared__ int64_t s_T, s_base;   // of the last round
+    __shared__ int32_t s_fail;
+    int64_t steps = 0, splits = 0, changed = 0;
+    for (int64_t e0 = 0; e0 < b.E; e0 += kTargetThreads) {
+        if (threadIdx.x == 0) s_fail = kTargetThreads;
+        __syncthreads();
+        const int64_t e = e0 + threadIdx.x;
+        int64_t T = 0, more = 0;   // target, and the splits it takes
+        if (e < b.E) {
+            const int64_t mx = b.T[e];
+            int64_t c, held, ready = b.W;   // fewest views held by a rank that is not finished
+            bulk_range(b, 0, e, &c, &held);
+            if (b.sched) {
+                held = LLONG_MAX;
+                ready = 0;
+                for (int r = 0; r < b.W; ++r) {
+                    int64_t n;
+                    bulk_range(b, r, e, &c, &n);
+                    ready += n > 0;
+                    held = n > 0 && n < held ? n : held;
+                }
+            }
+            T = mx > 1 ? mx : 1;
+            more = T * ready - (int64_t)b.sum[e];
+            if (mx > held) atomicMin(&s_fail, (int32_t)threadIdx.x);
+        }
+        __syncthreads();
+        const int32_t fail = s_fail;
+        const bool live = e < b.E && (int32_t)threadIdx.x < fail;
+        if (!live) T = more = 0;
+        int64_t tot;
+        const int64_t ex = sblock_excl<kTargetThreads>(T, &tot);
+        if (live) {
+            b.T[e] = (int32_t)T;
+            b.base[e] = steps + ex;
+            if (e + 1 == b.E) {
+                s_T = T;
+                s_base = steps + ex;
+            }
+        }
+        steps += tot;
+        splits += sblock_sum<kTargetThreads>(more);
+        changed += sblock_sum<kTargetThreads>((int64_t)(more != 0));
+        if (fail < kTargetThreads || e0 + kTargetThreads >= b.E) {
+            if (threadIdx.x == 0) {
+                b.st->steps = steps;
+                b.st->splits = splits;
+                b.st->changed = changed;
+                b.st->fail = fail < kTargetThreads ? e0 + fail : b.E;
+            }
+            if (b.lo && fail == kTargetThreads && !b.st->err) {   // uniform
+                __syncthreads();
+                bulk_cut(b, reinterpret_cast<BulkSplit*>(s_dyn), (int)s_T, s_base, before, left_off);
+            }
+            return;
+        }
     }
 }
 
@@ -1510,20 +1525,12 @@ __global__ void __launch_bounds__(NT) bulk_slots_kernel(BulkArgs b, BulkSlots o)
 }
 
 // Samples of every step over the ranks (rank stride `stride`): the largest, and the slots'
-// real tokens.  One thread per step; blocks of one wave, so that a thousand steps already
-// spread over the chip.
-__global__ void __launch_bounds__(kWave) bulk_steps_kernel(BulkArgs b, const int32_t* __restrict__ rows,
-                                                           const int64_t* __restrict__ tokens, int64_t stride,
-                                                           int64_t most) {
-    if (b.st->err) return;
-    int64_t S = b.st->steps;
-    if (stride == 0) {   // the plan layout
-        if (b.st->fail < b.E || S > b.scap) return;
-        stride = S;
-    }
-    S = S < most ? S : most;
+// real tokens, over steps block * 64 + lane, every blocks * 64.
+__device__ __forceinline__ void bulk_steps(const BulkArgs& b, const int32_t* __restrict__ rows,
+                                           const int64_t* __restrict__ tokens, int64_t stride, int64_t S,
+                                           int64_t block, int64_t blocks) {
     unsigned long long mx = 0, real = 0;
-    for (int64_t j = (int64_t)blockIdx.x * kWave + threadIdx.x; j < S; j += (int64_t)gridDim.x * kWave) {
+    for (int64_t j = block * kWave + threadIdx.x; j < S; j += blocks * kWave) {
         unsigned long long n = 0;
 #pragma unroll 8
         for (int r = 0; r < b.W; ++r) {
@@ -1540,6 +1547,14 @@ __global__ void __launch_bounds__(kWave) bulk_steps_kernel(BulkArgs b, const int
     }
 }
 
+// The steps staged before a round that overflows.
+__global__ void __launch_bounds__(kWave) bulk_staged_steps_kernel(BulkArgs b, const int32_t* __restrict__ rows,
+                                                                  const int64_t* __restrict__ tokens) {
+    if (b.st->err) return;
+    const int64_t S = b.st->steps < b.scap ? b.st->steps : b.scap;
+    bulk_steps(b, rows, tokens, b.scap, S, blockIdx.x, gridDim.x);
+}
+
 struct BulkTileLoad {
     const int64_t* v;
     int64_t n;   // the scan runs over n + 1 entries: entry n receives the total
@@ -1547,16 +1562,34 @@ struct BulkTileLoad {
 };
 
 // Tile offsets of rank r's slots of round e: the rank-round's first tile added to the offsets
-// within it.  Block 0 also closes the offset arrays.
-__global__ void __launch_bounds__(kWave) bulk_tiles_kernel(BulkArgs b, int64_t* __restrict__ tile_off,
+// within it.  Up to kTilesSummed rank-rounds a block adds up the ones before its own itself
+// (`scanned` 0); more are scanned before, in three launches: the whole plan of 512, 1,024,
+// 2,048 and 4,096 rank-rounds of 16 views measures 47, 50, 59 and 81 us summed, and 50, 52, 57
+// and 72 us scanned.  Block 0 also closes the offset arrays; the blocks past `tiles` sum the
+// steps.  Blocks of one wave, so that a thousand steps already spread over the chip.
+constexpr int64_t kTilesSummed = 1024;
+
+__global__ void __launch_bounds__(kWave) bulk_tiles_kernel(BulkArgs b, unsigned tiles, int scanned,
+                                                           const int32_t* __restrict__ rows,
+                                                           const int64_t* __restrict__ tokens,
+                                                           int64_t* __restrict__ tile_off,
                                                            int64_t* __restrict__ row_off,
                                                            int64_t* __restrict__ left_off) {
     const int64_t S = b.st->steps;
     if (b.st->err || b.st->fail < b.E || S > b.scap) return;
-    int64_t e;
-    int r;
+    if (blockIdx.x >= tiles) {
+        bulk_steps(b, rows, tokens, S, S, blockIdx.x - tiles, gridDim.x - tiles);
+        return;
+    }
+    const int64_t all = (int64_t)b.W * b.E;
+    auto before = [&](int64_t i) {   // padded elements of the rank-rounds before the i-th
+        if (scanned) return b.tile[i];
+        int64_t v = 0;
+        for (int64_t x = threadIdx.x; x < i; x += kWave) v += b.tile[x];
+        return wave_last(wave_scan_dpp<OpAdd>(v));
+    };
     if (blockIdx.x == 0) {
-        const int64_t K = (int64_t)b.W * S, total = b.tile[(int64_t)b.W * b.E];
+        const int64_t K = (int64_t)b.W * S, total = before(all);
         if (!b.lo)
             for (int64_t i = threadIdx.x; i <= b.W; i += kWave) left_off[i] = 0;
         if (threadIdx.x == 0) {
@@ -1565,10 +1598,46 @@ __global__ void __launch_bounds__(kWave) bulk_tiles_kernel(BulkArgs b, int64_t* 
             b.st->padded = total;
         }
     }
+    int64_t e;
+    int r;
     if (!bulk_block(b, b.E, &e, &r)) return;
-    const int64_t add = b.tile[(int64_t)r * b.E + e], at = (int64_t)r * S + b.base[e];
+    const int64_t add = before((int64_t)r * b.E + e), at = (int64_t)r * S + b.base[e];
     const int T = b.lo && e + 1 == b.E ? (int)b.st->cut : b.T[e];
     for (int j = threadIdx.x; j < T; j += kWave) tile_off[at + j] += add;
+}
+
+// Non-join: identities with no emitted view and emitted views beyond the first.  perm is a
+// permutation, so identity perm[m] is carried by the views m, m + N, ... below M = q W: only
+// the first M - N of them (fewer than W) by more than one.  A wave takes one of these and looks
+// its views up in the last round's rows; every other identity has one view, so their counts
+// follow from the number of emitted views.
+__device__ __forceinline__ void bulk_identities(const BulkArgs& b, int64_t wave, int64_t waves) {
+    const int64_t M = b.q * b.W;
+    const int64_t shared = M - b.N < b.N ? M - b.N : b.N;
+    const int lane = threadIdx.x & (kWave - 1);
+    for (int64_t m = wave; m < shared; m += waves) {
+        unsigned long long k = 0;   // equal in all lanes
+        for (int64_t v = m; v < M; v += b.N) {
+            const int r = (int)(v % b.W);
+            const int64_t i = v / b.W;
+            int64_t c, n;
+            bulk_range(b, r, b.E - 1, &c, &n);
+            const int64_t rows = b.lo[r + 1] - b.lo[r];
+            bool out = i < c;
+            if (!out && i < c + n) {
+                bool hit = false;
+                for (int64_t y = c + lane; y < rows; y += kWave) hit |= b.views[(int64_t)r * b.q + y] == (int32_t)v;
+                out = __ballot(hit) != 0;
+            }
+            k += out ? 1 : 0;
+        }
+        if (lane == 0) {
+            atomicAdd(&b.st->missing_ids, k + (k == 0 ? 1 : 0));
+            if (k > 1) atomicAdd(&b.st->duplicate_ids, k - 1);
+        }
+    }
+    if (wave == 0 && lane == 0)   // the identities of one view
+        atomicAdd(&b.st->missing_ids, (unsigned long long)(b.N - shared - b.st->emitted));
 }
 
 // Non-join.  Rank r's emitted views moved to their place among the ranks' (the stop leaves gaps
@@ -1580,9 +1649,15 @@ __global__ void __launch_bounds__(256) bulk_emit_out_kernel(BulkArgs b, const in
                                                             int32_t* row_len, int32_t* __restrict__ left) {
     if (b.st->err || b.st->fail < b.E || b.st->steps > b.scap) return;
     const int r = blockIdx.x;
+    const unsigned slices = gridDim.y - 1;
+    if (blockIdx.y == slices) {   // one row of blocks more, for the identities
+        const int waves = 256 / kWave;
+        bulk_identities(b, (int64_t)r * waves + threadIdx.x / kWave, (int64_t)b.W * waves);
+        return;
+    }
     const int64_t lo = b.lo[r], rows = b.lo[r + 1] - lo, l0 = left_off[r];
     const int64_t in = (int64_t)r * b.q;
-    const int64_t stride = (int64_t)gridDim.y * blockDim.x, i0 = (int64_t)blockIdx.y * blockDim.x + threadIdx.x;
+    const int64_t stride = (int64_t)slices * blockDim.x, i0 = (int64_t)blockIdx.y * blockDim.x + threadIdx.x;
     for (int64_t i = i0; i < rows; i += stride) {
         emit_views[lo + i] = b.views[in + i];
         emit_order[lo + i] = b.ids[in + i];
@@ -1611,48 +1686,6 @@ __global__ void __launch_bounds__(256) bulk_emit_out_kernel(BulkArgs b, const in
     for (uint32_t m = w; m; m &= m - 1) {
         const int64_t i = c + threadIdx.x * 32 + (__ffs((int)m) - 1);
         left[l0 + at++] = (int32_t)(i * b.W + r);
-    }
-}
-
-// Non-join: identities with no emitted view and emitted views beyond the first.  perm is a
-// permutation, so identity perm[m] is carried by the views m, m + N, ... below M = q W: only
-// the first M - N of them (fewer than W) by more than one.  A wave takes one of these at a time
-// and looks its views up in the last round's rows; every other identity has one view, so
-// their counts follow from the number of emitted views.  One block.
-__global__ void __launch_bounds__(1024) bulk_identities_kernel(BulkArgs b) {
-    if (b.st->err || b.st->fail < b.E || b.st->steps > b.scap) return;
-    const int64_t M = b.q * b.W;
-    const int64_t shared = M - b.N < b.N ? M - b.N : b.N;
-    const int lane = threadIdx.x & (kWave - 1);
-    int64_t seen = 0, miss = 0, dup = 0;   // equal in all lanes of a wave
-    for (int64_t m = threadIdx.x / kWave; m < shared; m += 1024 / kWave) {
-        int64_t k = 0;
-        for (int64_t v = m; v < M; v += b.N) {
-            const int r = (int)(v % b.W);
-            const int64_t i = v / b.W;
-            int64_t c, n;
-            bulk_range(b, r, b.E - 1, &c, &n);
-            const int64_t rows = b.lo[r + 1] - b.lo[r];
-            bool out = i < c;
-            if (!out && i < c + n) {
-                bool hit = false;
-                for (int64_t y = c + lane; y < rows; y += kWave) hit |= b.views[(int64_t)r * b.q + y] == (int32_t)v;
-                out = __ballot(hit) != 0;
-            }
-            k += out ? 1 : 0;
-        }
-        seen += k;
-        miss += k == 0;
-        dup += k > 0 ? k - 1 : 0;
-    }
-    if (lane != 0) seen = miss = dup = 0;
-    seen = sblock_sum<1024>(seen);
-    miss = sblock_sum<1024>(miss);
-    dup = sblock_sum<1024>(dup);
-    if (threadIdx.x == 0) {
-        const int64_t single = b.N - shared;
-        b.st->missing_ids = miss + single - (b.st->emitted - seen);
-        b.st->duplicate_ids = dup;
     }
 }
 
@@ -2205,30 +2238,26 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
         else hipLaunchKernelGGL((bulk_form_kernel<512, 8>), form_grid, dim3(512), 0, s, b);
         static_assert(kMaxDepth <= 512 * 8, "views per rank-round");
         ODB_LAUNCHED();
-        hipLaunchKernelGGL(bulk_targets_kernel, dim3(1), dim3(1024), 0, s, b);
+        hipLaunchKernelGGL(bulk_targets_kernel, dim3(1), dim3(kTargetThreads), join ? 0 : 8 * (size_t)W, s, b,
+                           join ? 0 : bs.emitted_before(bs.E - 1), d_left_off);
         ODB_LAUNCHED();
-        if (!join) {
-            hipLaunchKernelGGL(bulk_cut_kernel, dim3(1), dim3(kST), 8 * (size_t)W, s, b, bs.emitted_before(bs.E - 1),
-                               d_left_off);
-            ODB_LAUNCHED();
-        }
         slots(final_slots);
         ODB_LAUNCHED();
-        const unsigned step_grid = grid_for(std::max<int64_t>(1, std::min(scap, bs.E * n_max)), kWave, gcap * 4);
-        ODB_TRY((device_excl_scan<int64_t>(BulkTileLoad{b.tile, (int64_t)W * bs.E}, StoreS{b.tile}, (int64_t)W * bs.E + 1,
-                                           ws_at<int64_t>(d_ws, SL.partials), s)));
-        hipLaunchKernelGGL(bulk_tiles_kernel, grid, dim3(kWave), 0, s, b, d_slot_tile_off, d_slot_row_off, d_left_off);
-        ODB_LAUNCHED();
-        hipLaunchKernelGGL(bulk_steps_kernel, dim3(step_grid), dim3(kWave), 0, s, b, (const int32_t*)d_slot_rows,
-                           (const int64_t*)d_slot_tokens, (int64_t)0, scap);
+        const int64_t rank_rounds = (int64_t)W * bs.E;
+        const int scanned = rank_rounds > kTilesSummed ? 1 : 0;
+        if (scanned)
+            ODB_TRY((device_excl_scan<int64_t>(BulkTileLoad{b.tile, rank_rounds}, StoreS{b.tile}, rank_rounds + 1,
+                                               ws_at<int64_t>(d_ws, SL.partials), s)));
+        const unsigned step_grid = grid_for(std::max<int64_t>(1, std::min(scap, bs.E * n_max)), kWave, gcap);
+        hipLaunchKernelGGL(bulk_tiles_kernel, dim3(grid.x + step_grid), dim3(kWave), 0, s, b, grid.x, scanned,
+                           (const int32_t*)d_slot_rows, (const int64_t*)d_slot_tokens, d_slot_tile_off, d_slot_row_off,
+                           d_left_off);
         ODB_LAUNCHED();
         if (!join) {
             // slices of about 4,096 views, so that short streams take few blocks
-            hipLaunchKernelGGL(bulk_emit_out_kernel, dim3(W, grid_for(q, 4096, 64)), dim3(256), 0, s, b,
+            hipLaunchKernelGGL(bulk_emit_out_kernel, dim3(W, grid_for(q, 4096, 64) + 1), dim3(256), 0, s, b,
                                (const int64_t*)d_left_off, d_emit_views, d_emit_order, d_row_token_start, d_row_len,
                                d_left_views);
-            ODB_LAUNCHED();
-            hipLaunchKernelGGL(bulk_identities_kernel, dim3(1), dim3(1024), 0, s, b);
             ODB_LAUNCHED();
         }
         // the state and, next to it, the targets
@@ -2271,8 +2300,8 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
             }
             slots(staged);
             ODB_LAUNCHED();
-            hipLaunchKernelGGL(bulk_steps_kernel, dim3(step_grid), dim3(kWave), 0, s, b, (const int32_t*)staged.rows,
-                               (const int64_t*)staged.tokens, scap, scap);
+            hipLaunchKernelGGL(bulk_staged_steps_kernel, dim3(step_grid), dim3(kWave), 0, s, b, (const int32_t*)staged.rows,
+                               (const int64_t*)staged.tokens);
             ODB_LAUNCHED();
         }
     }
@@ -2395,8 +2424,8 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
         h_info->pending_views = M - fetched;
         h_info->bad_views = (int64_t)hb.bad_views;
         // join mode emits every view, and an identity has M / N of them
-        h_info->missing_ids = join ? 0 : hb.missing_ids;
-        h_info->duplicate_ids = join ? M - N : hb.duplicate_ids;
+        h_info->missing_ids = join ? 0 : (int64_t)hb.missing_ids;
+        h_info->duplicate_ids = join ? M - N : (int64_t)hb.duplicate_ids;
         fill_trace();
         if (hb.bad_views != 0)
             return set_error(ODB_E_INTERNAL, "streaming plan does not account for every view exactly once");

@@ -366,7 +366,7 @@ def test_stream_budget_int64_max():
 
 def together_cases():
     """Rounds formed together: buffer sizes at the edges of the block variants (256, 512, 1024
-    and 4096 views), 64 rounds and more (dealt to the XCDs), a capacity that never binds, and
+    and 4096 views), 64 rounds and more (dealt to the XCDs), tile offsets scanned ahead, a capacity that never binds, and
     the ways such a run ends: drained, in a round that overflows (the rest goes round by
     round), at a quota inside and at the end of a round, and at the first finished rank."""
     rng = np.random.default_rng(83)
@@ -375,6 +375,10 @@ def together_cases():
         out.append((f"buffer_{buf}", rng.integers(1, 5000, 3 * 2 * buf + 5), 2, 16384, buf, buf, [buf, buf], {}))
     out.append(("rounds_64", rng.integers(1, 700, 64 * 3 * 40), 3, 4000, 40, 40, [40] * 3, {}))
     out.append(("rounds_65_long", rng.integers(1, 2 ** 31 - 1, 65 * 40 - 3), 1, 2 ** 40, 40, 64, [64], {}))
+    # more than 1,024 rounds, and rank-rounds, drained and cut in the last round
+    many = rng.integers(1, 700, 2 * 2 * 1100 - 1)
+    out.append(("rounds_1100", many, 2, 1400, 2, 2, [2] * 2, {}))
+    out.append(("rounds_1100_quota", many, 2, 1400, 2, 2, [2] * 2, dict(mode="nonjoin", quota=4398)))
     out.append(("wide_digits", rng.integers(2 ** 16, 2 ** 24, 2000), 2, 2 ** 25, 300, 300, [300] * 2, {}))
     out.append(("free_capacity", rng.integers(1, 900, 3000), 3, 6000, 128, 128, [128] * 3,
                 dict(cap=np.array([128, 0, 500]))))
@@ -386,6 +390,10 @@ def together_cases():
                     dict(mode="nonjoin", quota=quota)))
     for quota in (1, 600, 601, 1799, 1800, 3000):
         out.append((f"quota_{quota}", rng.integers(1, 2000, 3000), 3, 6000, 200, 200, [200] * 3,
+                    dict(mode="nonjoin", quota=quota)))
+    # identities carried by two views, both, one or none of them emitted
+    for quota in (1700, 2900, 2998):
+        out.append((f"shared_{quota}", rng.integers(1, 2000, 2998), 3, 6000, 200, 200, [200] * 3,
                     dict(mode="nonjoin", quota=quota)))
     # the stop round still fetches: one rank ready (its views count as fetched), one not
     out.append(("finished", rng.integers(900, 1000, 3 * 400), 3, 1000, 50, 200, [50, 100, 200],
