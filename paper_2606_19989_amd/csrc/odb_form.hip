@@ -164,9 +164,9 @@ __device__ __forceinline__ SortTile sort_tile(const int64_t* __restrict__ off,
 }
 
 // Keys per thread of a tile: 16 where that still leaves every compute unit four tiles and more,
-// else 8.  Longer tiles write longer runs per digit (64 x 262,144 samples: the low-digit
-// scatter 78 -> 61 us, the plan 566 -> 543), shorter ones spread a smaller window further
-// (16 x 65,536: 204 us against 199).
+// else 8.  Longer tiles write longer runs per digit (64 x 262,144 samples: the plan 566 -> 543 us
+// with a key and a position per item, 497 -> 491 with both in a word), shorter ones spread a
+// smaller window further (16 x 65,536: 204 us against 199).
 inline int sort_items(int64_t n) { return n >= (int64_t)4 << 20 ? 2 * kSortItems : kSortItems; }
 
 // Digit counts of every tile.  kHistCopies copies of the table, lane l counting in copy
@@ -267,12 +267,18 @@ __global__ void __launch_bounds__(kRankScanThreads) rank_scan_kernel(const int64
 // consecutive addresses (written straight from registers, about two items per digit and
 // round, they cost 4.6 B of HBM writes per byte).  The count, slot table and placement done round
 // by round, two block barriers each, took 90 and 82 instead of 78 and 59 us for the two passes over
-// 16.7 M samples (the low digit spreads a tile over twice the runs).
-template <int kItems, bool kFirst, bool kLast>
+// 16.7 M samples, a key and a position each in tiles of 2,048 (the low digit spreads a tile over
+// twice the runs).
+//
+// Where a key and a position within its rank fit one 32-bit word (kPacked: the position in the
+// low `ibits` bits, and `shift` counts from the word's), the passes move that word instead of a
+// key and a position: half the bytes between two passes and half the LDS (64 x 262,144 samples:
+// the two passes 62 and 62 -> 46 and 48 us).
+template <int kItems, bool kPacked, bool kFirst, bool kLast>
 __global__ void __launch_bounds__(kBlock) radix_scatter_kernel(
     const int64_t* __restrict__ off, const int64_t* __restrict__ tile_first, int W,
     const uint32_t* __restrict__ keys_in,
-    const int32_t* __restrict__ len_in, const int32_t* __restrict__ vals_in, uint32_t maxl, int shift,
+    const int32_t* __restrict__ len_in, const int32_t* __restrict__ vals_in, uint32_t maxl, int ibits, int shift,
     int dbits, const uint32_t* __restrict__ offs, uint32_t* __restrict__ keys_out,
     int32_t* __restrict__ vals_out, int32_t* __restrict__ slen_out) {
     const SortTile b = sort_tile<kBlock * kItems>(off, tile_first, W, blockIdx.x);
@@ -282,7 +288,8 @@ __global__ void __launch_bounds__(kBlock) radix_scatter_kernel(
     __shared__ uint32_t s_shift[256];         // global position of the digit's first item less its local one
     __shared__ uint32_t s_cnt[kWaves][256];   // items of a digit in a wave, then the wave's first local slot
     __shared__ uint32_t s_key[kTile];
-    __shared__ int32_t s_val[kTile];
+    __shared__ int32_t s_val[kPacked ? 1 : kTile];
+    const int64_t rank0 = b.start - (int64_t)b.j * kTile;   // the rank's first position
     const int w = threadIdx.x / kWave;
     const int p0 = w * (kTile / kWaves) + (threadIdx.x & (kWave - 1));   // item it: p0 + it * 64
     uint32_t key[kItems];
@@ -292,7 +299,8 @@ __global__ void __launch_bounds__(kBlock) radix_scatter_kernel(
         const int li = p0 + it * kWave;
         const int64_t p = b.start + (li < b.count ? li : 0);
         key[it] = kFirst ? maxl - (uint32_t)len_in[p] : keys_in[p];
-        val[it] = kFirst ? (int32_t)p : vals_in[p];
+        if (kPacked && kFirst) key[it] = key[it] << ibits | (uint32_t)(p - rank0);
+        if (!kPacked) val[it] = kFirst ? (int32_t)p : vals_in[p];
     }
     const int64_t col = (int64_t)b.first << dbits;
     uint32_t base = 0;
@@ -336,7 +344,7 @@ __global__ void __launch_bounds__(kBlock) radix_scatter_kernel(
         if (p0 + it * kWave < b.count) {
             const uint32_t q = s_cnt[w][(key[it] >> shift) & mask] + at[it];
             s_key[q] = key[it];
-            s_val[q] = val[it];
+            if (!kPacked) s_val[q] = val[it];
         }
     }
     __syncthreads();
@@ -346,9 +354,12 @@ __global__ void __launch_bounds__(kBlock) radix_scatter_kernel(
         if (q >= b.count) break;
         const uint32_t k = s_key[q];
         const uint32_t pos = s_shift[(k >> shift) & mask] + (uint32_t)q;
-        vals_out[pos] = s_val[q];
+        if (!kPacked)
+            vals_out[pos] = s_val[q];
+        else if (kLast)
+            vals_out[pos] = (int32_t)(rank0 + (k & ((1u << ibits) - 1)));
         if (kLast)
-            slen_out[pos] = (int32_t)(maxl - k);
+            slen_out[pos] = (int32_t)(maxl - (kPacked ? k >> ibits : k));
         else
             keys_out[pos] = k;
     }
@@ -1292,8 +1303,11 @@ extern "C" int odb_form_groups(const odb_window_t* w, int64_t budget, int32_t* d
         uint32_t* counts = ws_at<uint32_t>(d_ws, L.counts);
         uint32_t* keys[2] = {ws_at<uint32_t>(d_ws, L.keys0), ws_at<uint32_t>(d_ws, L.keys1)};
         int32_t* vals[2] = {ws_at<int32_t>(d_ws, L.vals0), ws_at<int32_t>(d_ws, L.vals1)};
+        int ibits = 0;   // bits of a position within a rank
+        while ((int64_t(1) << ibits) < max_cnt) ++ibits;
+        const bool packed = bits + ibits <= 32;
         for (int pass = 0; pass < passes; ++pass) {
-            const int shift = pass * dbits;
+            const int shift = pass * dbits + (packed ? ibits : 0);
             const bool first = pass == 0, last = pass == passes - 1;
             const uint32_t* kin = first ? nullptr : keys[(pass - 1) & 1];
             const int32_t* vin = first ? nullptr : vals[(pass - 1) & 1];
@@ -1302,7 +1316,7 @@ extern "C" int odb_form_groups(const odb_window_t* w, int64_t budget, int32_t* d
             const auto hist = first ? (longer ? radix_hist_kernel<2 * kSortItems, true> : radix_hist_kernel<kSortItems, true>)
                                     : (longer ? radix_hist_kernel<2 * kSortItems, false> : radix_hist_kernel<kSortItems, false>);
             hipLaunchKernelGGL(hist, dim3((unsigned)NB), dim3(kBlock), 0, s, d_off, (const int64_t*)d_tile_first, W, kin,
-                               (const int32_t*)len, maxl, shift, dbits, counts);
+                               (const int32_t*)len, maxl, first ? 0 : shift, dbits, counts);
             ODB_LAUNCHED();
             if (dbits >= 2 && ((max_cnt + kBlock * items - 1) / (kBlock * items) << dbits) <= kRankScanMax) {
                 hipLaunchKernelGGL(rank_scan_kernel, dim3(W), dim3(kRankScanThreads), 0, s, d_off,
@@ -1312,16 +1326,19 @@ extern "C" int odb_form_groups(const odb_window_t* w, int64_t budget, int32_t* d
                 ODB_TRY((device_excl_scan<uint32_t>(CountLoad{counts, NB << dbits}, CountStore{counts}, NB << dbits,
                                                     ws_at<uint32_t>(d_ws, L.partials), s)));
             }
-#define ODB_SCATTER(F, La)                                                                                    \
+#define ODB_SCATTER(P, F, La)                                                                                 \
     do {                                                                                                      \
-        const auto scatter = longer ? radix_scatter_kernel<2 * kSortItems, F, La> : radix_scatter_kernel<kSortItems, F, La>; \
-        hipLaunchKernelGGL(scatter, dim3((unsigned)NB), dim3(kBlock), 0, s, d_off, (const int64_t*)d_tile_first, W,          \
-                           kin, (const int32_t*)len, vin, maxl, shift, dbits, (const uint32_t*)counts, kout, vout, d_sorted_len); \
+        const auto scatter = longer ? radix_scatter_kernel<2 * kSortItems, P, F, La> : radix_scatter_kernel<kSortItems, P, F, La>; \
+        hipLaunchKernelGGL(scatter, dim3((unsigned)NB), dim3(kBlock), 0, s, d_off, (const int64_t*)d_tile_first, W,                \
+                           kin, (const int32_t*)len, vin, maxl, ibits, shift, dbits, (const uint32_t*)counts, kout, vout,          \
+                           d_sorted_len);                                                                     \
     } while (0)
-            if (first && last) ODB_SCATTER(true, true);
-            else if (first) ODB_SCATTER(true, false);
-            else if (last) ODB_SCATTER(false, true);
-            else ODB_SCATTER(false, false);
+#define ODB_SCATTER_PASS(F, La) do { if (packed) ODB_SCATTER(true, F, La); else ODB_SCATTER(false, F, La); } while (0)
+            if (first && last) ODB_SCATTER_PASS(true, true);
+            else if (first) ODB_SCATTER_PASS(true, false);
+            else if (last) ODB_SCATTER_PASS(false, true);
+            else ODB_SCATTER_PASS(false, false);
+#undef ODB_SCATTER_PASS
 #undef ODB_SCATTER
             ODB_LAUNCHED();
         }

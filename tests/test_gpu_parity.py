@@ -771,6 +771,22 @@ def test_one_block_grouping_sizes(n):
         compare_plan(w, pipe, ref)
 
 
+@pytest.mark.parametrize("span", [256, 257, 1 << 17, (1 << 17) + 1])
+@pytest.mark.parametrize("per_rank", [1 << 15, (1 << 15) + 1])
+def test_sort_word_widths(per_rank, span):
+    """Key and position in exactly 32 bits (15 + 17) and in one more, in one, two and three passes;
+    both ends of the range of lengths occur, at the last positions of a rank, too."""
+    import torch
+    rng = np.random.default_rng(96)
+    lens = [rng.integers(1, span + 1, n) for n in (per_rank, 17, per_rank - 5)]
+    lens[0][-2:] = 1, span
+    lens[0][:2] = 1, span
+    w = synth.window_from_ranks("sort_words", lens, 1 << 20)
+    ref = oracle.plan_window(w)
+    pipe, _ = run_gpu(w, tokens=torch.zeros(1, dtype=torch.int32, device="cuda"), collate=False)
+    compare_plan(w, pipe, ref)
+
+
 @pytest.mark.parametrize("per_rank", [(1 << 22) // 3 + 1, (1 << 22) // 3])
 def test_sort_tile_lengths(per_rank):
     """Windows just at and just below 4 Mi samples: the longer and the shorter radix tile, ragged
