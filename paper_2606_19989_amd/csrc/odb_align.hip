@@ -1730,7 +1730,6 @@ struct ShortArgs {
 };
 
 constexpr int kShortThreads = 1024;
-constexpr int kShortItems = (int)(kRankBlockMax / kShortThreads);   // positions per thread
 
 template <typename T, typename Op>
 __device__ __forceinline__ T short_reduce(T v, Op op) {
@@ -1754,7 +1753,7 @@ __global__ void __launch_bounds__(kShortThreads) short_round_kernel(ShortArgs a,
 #pragma clang fp contract(off)
     __shared__ int32_t s_len[kRankBlockMax];
     __shared__ uint16_t s_gs[kRankBlockMax + 2];
-    __shared__ int64_t s_pre[kShortThreads];   // tokens before position t * kShortItems
+    __shared__ int64_t s_pre[kShortThreads];   // tokens before position t << sh
     __shared__ int64_t s_w[kShortThreads / kWave];
     if (stage1_bad(a.st)) return;
     const int t = threadIdx.x, r = blockIdx.x;
@@ -1816,12 +1815,16 @@ __global__ void __launch_bounds__(kShortThreads) short_round_kernel(ShortArgs a,
     }
     if (t == 0) s_gs[G] = (uint16_t)cnt;
     __syncthreads();
-    // tokens before every kShortItems-th position
+    // tokens before every (1 << sh)-th position, the fewest a thread that cover the buffer: 16 each
+    // left all but a few waves of a small buffer idle, their reads 16 words apart on 4 LDS banks
+    // (8 x 4,096 samples: 12.8 us a round, now 11.9)
+    int sh = 0;
+    while (kShortThreads << sh < cnt) ++sh;
     int64_t tok;
     {
         int64_t v = 0;
-#pragma unroll
-        for (int i = 0; i < kShortItems; ++i) v += t * kShortItems + i < cnt ? s_len[t * kShortItems + i] : 0;
+        const int q0 = t << sh, q1 = q0 + (1 << sh) < cnt ? q0 + (1 << sh) : cnt;
+        for (int q = q0; q < q1; ++q) v += s_len[q];
         const int64_t inc = wave_scan_dpp<OpAdd>(v);
         if ((t & (kWave - 1)) == kWave - 1) s_w[t / kWave] = inc;
         // sizes must not decrease up to the last group but one
@@ -1841,10 +1844,10 @@ __global__ void __launch_bounds__(kShortThreads) short_round_kernel(ShortArgs a,
     }
     __syncthreads();
     auto tokens_before = [&](int p) {
-        const int c = p / kShortItems;
+        const int c = p >> sh;
         if (c >= kShortThreads) return tok;
         int64_t v = s_pre[c];
-        for (int q = c * kShortItems; q < p; ++q) v += s_len[q];
+        for (int q = c << sh; q < p; ++q) v += s_len[q];
         return v;
     };
     // what is emitted: positions [A, B)
