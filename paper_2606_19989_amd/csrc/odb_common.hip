@@ -190,15 +190,64 @@ struct ReadPage {
     }
 };
 thread_local ReadPage g_page;
-}  // namespace
 
-int read_device(void* dst, const void* src, size_t bytes, hipStream_t s) {
-    if (bytes <= kReadBytes && !g_page.p &&
-        hipHostMalloc(&g_page.p, kReadBytes, hipHostMallocPortable) != hipSuccess) {
-        (void)hipGetLastError();   // no pinned memory: read into pageable memory
+// Events of the calling thread, one per device it read from with read_begin.
+constexpr int kReadDevices = 64;
+struct ReadEvents {
+    hipEvent_t e[kReadDevices] = {};
+    hipEvent_t last = nullptr;   // of the read begun
+    ~ReadEvents() {
+        for (hipEvent_t x : e)
+            if (x) (void)hipEventDestroy(x);
+    }
+};
+thread_local ReadEvents g_events;
+
+// The thread's pinned page, or null if there is no pinned memory.
+void* read_page() {
+    if (!g_page.p && hipHostMalloc(&g_page.p, kReadBytes, hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();
         g_page.p = nullptr;
     }
-    void* to = bytes <= kReadBytes && g_page.p ? g_page.p : dst;
+    return g_page.p;
+}
+
+__global__ void __launch_bounds__(256) read_page_kernel(const uint32_t* __restrict__ src, uint32_t* __restrict__ page,
+                                                        int words) {
+    for (int i = threadIdx.x; i < words; i += 256) page[i] = src[i];
+    __threadfence_system();
+}
+}  // namespace
+
+int read_begin(const void* src, size_t bytes, hipStream_t s, bool* begun) {
+    *begun = false;
+    int dev = 0;
+    if (bytes > kReadBytes || bytes % 4 || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kReadDevices ||
+        !read_page())
+        return ODB_OK;
+    hipEvent_t& e = g_events.e[dev];
+    if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+        (void)hipGetLastError();
+        e = nullptr;
+        return ODB_OK;
+    }
+    hipLaunchKernelGGL(read_page_kernel, dim3(1), dim3(256), 0, s, static_cast<const uint32_t*>(src),
+                       static_cast<uint32_t*>(g_page.p), (int)(bytes / 4));
+    ODB_LAUNCHED();
+    ODB_TRY_HIP(hipEventRecord(e, s));
+    g_events.last = e;
+    *begun = true;
+    return ODB_OK;
+}
+
+int read_end(void* dst, size_t bytes) {
+    ODB_TRY_HIP(hipEventSynchronize(g_events.last));
+    memcpy(dst, g_page.p, bytes);
+    return ODB_OK;
+}
+
+int read_device(void* dst, const void* src, size_t bytes, hipStream_t s) {
+    void* to = bytes <= kReadBytes && read_page() ? g_page.p : dst;   // no pinned memory: pageable
     ODB_TRY_HIP(hipMemcpyAsync(to, src, bytes, hipMemcpyDeviceToHost, s));
     ODB_TRY_HIP(hipStreamSynchronize(s));
     if (to != dst) memcpy(dst, to, bytes);

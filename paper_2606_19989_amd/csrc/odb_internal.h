@@ -168,6 +168,13 @@ int store_values(const int64_t* src, int64_t count, int64_t* dst, DevStatus* st,
 constexpr size_t kReadBytes = 64 * 1024;
 int read_device(void* dst, const void* src, size_t bytes, hipStream_t s);
 
+// The same in two halves, for work that is launched while the host waits: read_begin has the
+// stream write the bytes (a multiple of 4) to the page and marks that point; read_end waits for
+// the mark only.  *begun stays false, with nothing launched, if there is no page or no event.
+// No other read may come between the two.
+int read_begin(const void* src, size_t bytes, hipStream_t s, bool* begun);
+int read_end(void* dst, size_t bytes);
+
 // Host copy of the status word, round state, summary and per-rank state, read with one
 // device-to-host copy (the workspace keeps them next to each other) and one
 // synchronisation of the stream.

@@ -48,6 +48,33 @@ def _bad_offsets(kind, rng):
     return off, first
 
 
+@pytest.mark.parametrize("span", [1, 200, 20000, 1 << 30])
+def test_long_ranks_reject_bad_lengths(span):
+    """Ranks longer than one block groups: the form's first digit pass is under way when the host
+    learns of the bad length; the call fails and the workspace then serves a valid window (equal
+    lengths, one pass, two in a word, four with a position beside the key)."""
+    import torch
+    import paper_2606_19989_amd as odb
+
+    rng = np.random.default_rng(42)
+    lens = rng.integers(1, span + 1, 50000).astype(np.int64)
+    lens[:2] = 1, span
+    off = np.concatenate([[0], np.cumsum(lens)])
+    bad = off.copy()
+    bad[30000] = bad[29999] - 7
+    pipe = odb.Pipeline(_window_with_offsets(bad, 2), 1 << 20)
+    for _ in range(2):
+        with pytest.raises(odb.OdbError) as e:
+            pipe.form()
+        assert e.value.status == odb.ODB_E_INVALID_DATA, str(e.value)
+        assert "sample 29999 " in str(e.value), str(e.value)
+    pipe.win.token_offsets.copy_(torch.from_numpy(off))
+    pipe.form()
+    pipe.align()
+    w = synth.window_from_ranks("after_bad", [lens[:25000], lens[25000:]], 1 << 20)
+    compare_plan(w, pipe, oracle.plan_window(w))
+
+
 @pytest.mark.parametrize("kind", ["zero_length", "decreasing_offset", "length_2p31", "negative_offset"])
 def test_window_rejects_bad_lengths(kind):
     # l < 1, l >= 2^31 and negative token offsets are invalid data (a length the batch
