@@ -203,7 +203,13 @@ struct ReadEvents {
 };
 thread_local ReadEvents g_events;
 
-// The thread's pinned page, or null if there is no pinned memory.
+__global__ void __launch_bounds__(256) read_page_kernel(const uint32_t* __restrict__ src, uint32_t* __restrict__ page,
+                                                        int words) {
+    for (int i = threadIdx.x; i < words; i += 256) page[i] = src[i];
+    __threadfence_system();
+}
+}  // namespace
+
 void* read_page() {
     if (!g_page.p && hipHostMalloc(&g_page.p, kReadBytes, hipHostMallocPortable) != hipSuccess) {
         (void)hipGetLastError();
@@ -211,13 +217,6 @@ void* read_page() {
     }
     return g_page.p;
 }
-
-__global__ void __launch_bounds__(256) read_page_kernel(const uint32_t* __restrict__ src, uint32_t* __restrict__ page,
-                                                        int words) {
-    for (int i = threadIdx.x; i < words; i += 256) page[i] = src[i];
-    __threadfence_system();
-}
-}  // namespace
 
 int read_begin(const void* src, size_t bytes, hipStream_t s, bool* begun) {
     *begun = false;

@@ -168,6 +168,10 @@ int store_values(const int64_t* src, int64_t count, int64_t* dst, DevStatus* st,
 constexpr size_t kReadBytes = 64 * 1024;
 int read_device(void* dst, const void* src, size_t bytes, hipStream_t s);
 
+// The page itself, or null if there is no pinned memory: a kernel that is the last of its call may
+// write a result there, and the host reads it after synchronising the stream.
+void* read_page();
+
 // The same in two halves, for work that is launched while the host waits: read_begin has the
 // stream write the bytes (a multiple of 4) to the page and marks that point; read_end waits for
 // the mark only.  *begun stays false, with nothing launched, if there is no page or no event.

@@ -110,6 +110,7 @@ __global__ void __launch_bounds__(kThreads) sketch_kernel(const int64_t* __restr
         }
         if (kOne) {
             *out = DevSketch{v[0], v[1], v[2], v[3], v[4], bmn, bmx, berr, 0};
+            __threadfence_system();   // it may be host memory
             return;
         }
         if (v[0] > 0) {
@@ -144,9 +145,12 @@ extern "C" int odb_length_sketch(const odb_window_t* w, const int32_t* d_ids, in
     *h_out = odb_length_sketch_t{};
     hipStream_t s = static_cast<hipStream_t>(stream);
     DevSketch* d = ws_at<DevSketch>(d_ws, L.sketch);
+    DevSketch h;
+    // the one block writes its result to the host itself: a copy behind it costs another 1 us
+    DevSketch* page = count <= kSketchOne ? static_cast<DevSketch*>(read_page()) : nullptr;
     if (count <= kSketchOne) {
         hipLaunchKernelGGL((sketch_kernel<kSketchOneThreads, true>), dim3(1), dim3(kSketchOneThreads), 0, s,
-                           w->d_token_offsets, w->num_samples, d_ids, count, budget, d);
+                           w->d_token_offsets, w->num_samples, d_ids, count, budget, page ? page : d);
         ODB_LAUNCHED();
     } else {
         hipLaunchKernelGGL(sketch_init_kernel, dim3(1), dim3(64), 0, s, d);
@@ -155,8 +159,12 @@ extern "C" int odb_length_sketch(const odb_window_t* w, const int32_t* d_ids, in
                            dim3(kBlock), 0, s, w->d_token_offsets, w->num_samples, d_ids, count, budget, d);
         ODB_LAUNCHED();
     }
-    DevSketch h;
-    ODB_TRY(read_device(&h, d, sizeof(h), s));
+    if (page) {
+        ODB_TRY_HIP(hipStreamSynchronize(s));
+        h = *page;
+    } else {
+        ODB_TRY(read_device(&h, d, sizeof(h), s));
+    }
     if (h.err & kSketchBadId) return set_error(ODB_E_INVALID_DATA, "a sketch id lies outside the window");
     if (h.err & kSketchBadLength) return set_error(ODB_E_INVALID_DATA, "a sketched sample has length < 1 or >= 2^31");
     h_out->samples = h.n;
