@@ -1393,35 +1393,61 @@ __device__ __forceinline__ OneTarget one_target(const OneArgs& a) {
     return OneTarget{mx > 1 ? mx : 1, mx > LLONG_MAX - small};
 }
 
-// Positions [*a0, *a1) of adjusted group t of a rank with cnt > 0 samples in G groups (starts
-// gs[0 .. G)), aligned to T >= G.  Returns the formation group they are, or -1 for a piece of
-// one (a split's singletons and what is left of group j*).
-__device__ __forceinline__ int64_t one_group(const int32_t* __restrict__ gs, int64_t G, int64_t cnt, int64_t T,
-                                             int64_t t, int64_t* a0, int64_t* a1) {
+// Where a rank of G > 0 groups (starts gs[0 .. G)) aligned to T >= G is split: adjusted groups
+// [0, X) are singletons, the X-th ends with group j*; X = -1 without a split.
+struct OneSplit {
+    int64_t js, X;
+};
+
+__device__ __forceinline__ OneSplit one_split(const int32_t* __restrict__ gs, int64_t G, int64_t T) {
     const int64_t k = T - G;
-    int64_t js = 0, X = -1;
-    if (k > 0) {
-        int64_t lo = -1, hi = G - 1;   // surplus(lo) < k <= surplus(hi) = cnt - G
-        while (hi - lo > 1) {
-            const int64_t mid = (lo + hi) >> 1;
-            if ((int64_t)gs[mid + 1] - (mid + 1) >= k) hi = mid; else lo = mid;
-        }
-        js = hi;
-        X = k + js;
-        if (t < X) {
-            *a0 = t;
-            *a1 = t + 1;
-            return -1;
-        }
+    if (k <= 0) return OneSplit{0, -1};
+    int64_t lo = -1, hi = G - 1;   // surplus(lo) < k <= surplus(hi) = cnt - G
+    while (hi - lo > 1) {
+        const int64_t mid = (lo + hi) >> 1;
+        if ((int64_t)gs[mid + 1] - (mid + 1) >= k) hi = mid; else lo = mid;
     }
-    const int64_t g = k > 0 ? js + (t - X) : t;
-    *a0 = t == X ? X : (int64_t)gs[g];
+    return OneSplit{hi, k + hi};
+}
+
+// The same for a rank that a whole wave asks for: 64 places at a time, so 1,000 groups take two
+// trips to memory, not ten.
+__device__ __forceinline__ OneSplit wave_split(const int32_t* __restrict__ gs, int64_t G, int64_t T) {
+    const int64_t k = T - G;
+    if (k <= 0) return OneSplit{0, -1};
+    const int lane = threadIdx.x & (kWave - 1);
+    int64_t lo = -1, hi = G - 1;
+    while (hi - lo > 1) {
+        const int64_t w = (hi - lo + kWave) / (kWave + 1), x = lo + (lane + 1) * w;
+        const bool low = x < hi && (int64_t)gs[(x < hi ? x : lo) + 1] - (x + 1) < k;
+        const int64_t c = __popcll(__ballot(low));
+        const int64_t end = lo + (c + 1) * w;
+        lo += c * w;
+        hi = end < hi ? end : hi;
+    }
+    return OneSplit{hi, k + hi};
+}
+
+// Positions [*a0, *a1) of adjusted group t of a rank with cnt > 0 samples in G groups (starts
+// gs[0 .. G)), split at sp.  Returns the formation group they are, or -1 for a piece of one (a
+// split's singletons and what is left of group j*).
+__device__ __forceinline__ int64_t one_group(const int32_t* __restrict__ gs, int64_t G, int64_t cnt, OneSplit sp,
+                                             int64_t t, int64_t* a0, int64_t* a1) {
+    if (t < sp.X) {
+        *a0 = t;
+        *a1 = t + 1;
+        return -1;
+    }
+    const int64_t g = sp.X >= 0 ? sp.js + (t - sp.X) : t;
+    *a0 = t == sp.X ? sp.X : (int64_t)gs[g];
     *a1 = g + 1 < G ? (int64_t)gs[g + 1] : cnt;
-    return t == X ? -1 : g;
+    return t == sp.X ? -1 : g;
 }
 
 // Samples per step over the ranks, for the sample quota: a block takes 64 steps, its waves
-// every fourth rank.
+// every fourth rank.  Bound by the trips to memory of a rank's search for its split (16 x 65,536
+// samples: 12.7 us lane by lane, 7.8 by the whole wave; for the slots below, whose waves may
+// hold several ranks, it gains nothing).
 __global__ void __launch_bounds__(kBlock) cut_steps_kernel(OneArgs a) {
     if (stage1_bad(a.st)) return;
     const OneTarget tg = one_target(a);
@@ -1431,14 +1457,14 @@ __global__ void __launch_bounds__(kBlock) cut_steps_kernel(OneArgs a) {
     for (int64_t j0 = (int64_t)blockIdx.x * kWave; j0 < tg.T; j0 += (int64_t)gridDim.x * kWave) {
         const int64_t j = j0 + lane;
         int64_t n = 0;
-        if (j < tg.T) {
-            for (int r = w; r < a.W; r += kBlock / kWave) {
-                const int64_t cnt = a.off[r + 1] - a.off[r];
-                if (cnt == 0) continue;
-                int64_t a0, a1;
-                one_group(a.gs + a.off[r], a.groups[r], cnt, tg.T, tg.T - 1 - j, &a0, &a1);
-                n += a1 - a0;
-            }
+        for (int r = w; r < a.W; r += kBlock / kWave) {
+            const int64_t cnt = a.off[r + 1] - a.off[r];
+            if (cnt == 0) continue;
+            const int32_t* gs = a.gs + a.off[r];
+            const OneSplit sp = wave_split(gs, a.groups[r], tg.T);
+            int64_t a0 = 0, a1 = 0;
+            if (j < tg.T) one_group(gs, a.groups[r], cnt, sp, tg.T - 1 - j, &a0, &a1);
+            n += a1 - a0;
         }
         s_n[w][lane] = n;
         __syncthreads();
@@ -1479,7 +1505,10 @@ __global__ void __launch_bounds__(kBlock) cut_kernel(OneArgs a, int64_t* __restr
         if (r < a.W) {
             const int64_t cnt = a.off[r + 1] - a.off[r];
             int64_t q = 0, e;   // formation positions that stay
-            if (cut < tg.T && cnt > 0) one_group(a.gs + a.off[r], a.groups[r], cnt, tg.T, tg.T - cut, &q, &e);
+            if (cut < tg.T && cnt > 0) {
+                const int32_t* gs = a.gs + a.off[r];
+                one_group(gs, a.groups[r], cnt, one_split(gs, a.groups[r], tg.T), tg.T - cut, &q, &e);
+            }
             v = I64Pair{cnt - q, q};
         }
         I64Pair tot;
@@ -1550,7 +1579,8 @@ __global__ void __launch_bounds__(kBlock) slots_kernel(OneArgs a, int32_t* __res
         }
         if (on && cnt > 0) {
             const int64_t G = a.groups[r];
-            const int64_t g = one_group(a.gs + base, G, cnt, tg.T, tg.T - 1 - (k - (int64_t)r * S), &a0, &a1);
+            const OneSplit sp = one_split(a.gs + base, G, tg.T);
+            const int64_t g = one_group(a.gs + base, G, cnt, sp, tg.T - 1 - (k - (int64_t)r * S), &a0, &a1);
             ml = a.slen[base + a0];
             const int64_t* tp = a.tpre + (int64_t)r * a.per_rank;
             if (g >= 0) {

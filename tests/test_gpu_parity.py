@@ -619,6 +619,11 @@ def one_round_windows():
     # a step's end
     for q in (2, 3 * 16 + 2, 3 * 16 + 3):
         out.append(win(f"quota_even_{q}", [np.full(333, 100), np.full(333, 100)], 800, mode="nonjoin", quota=q))
+    # ranks split from 64, 66, about 2,000 and about 6,000 groups (the split is searched 64 places
+    # at a time), towards one of 7,000
+    split = [U(1000, 1001, 7000)] + [np.concatenate([U(400, 1000, g), U(1, 9, 7000 - g)]) for g in (60, 62, 2000, 6000)]
+    for q in (500, 20000):
+        out.append(win(f"quota_split_{q}", split, 1000, mode="nonjoin", quota=q))
     out.append(win("quota_overflow", [U(500, 900, 300), U(10, 20, 7)], 1000, mode="nonjoin", quota=250))
     out.append(win("quota_empty_rank", [U(10, 20, 100), U(1, 2, 0)], 100, mode="nonjoin", quota=50))
     for mode, q in (("join", 0), ("nonjoin", 900)):
