@@ -1273,6 +1273,22 @@ __device__ __forceinline__ BulkSplit bulk_split(const int32_t* __restrict__ gs, 
     return BulkSplit{hi, k + hi};
 }
 
+// The same for a buffer that a whole wave asks for, 64 places at a time.
+__device__ __forceinline__ BulkSplit bulk_wave_split(const int32_t* __restrict__ gs, int G, int T) {
+    const int k = T - G;
+    if (k <= 0) return BulkSplit{0, -1};
+    const int lane = threadIdx.x & (kWave - 1);
+    int lo = -1, hi = G - 1;
+    while (hi - lo > 1) {
+        const int w = (hi - lo + kWave) / (kWave + 1), x = lo + (lane + 1) * w;
+        const bool low = x < hi && gs[(x < hi ? x : lo) + 1] - (x + 1) < k;
+        const int c = __popcll(__ballot(low)), end = lo + (c + 1) * w;
+        lo += c * w;
+        hi = end < hi ? end : hi;
+    }
+    return BulkSplit{hi, k + hi};
+}
+
 // Positions [*a0, *a1) of adjusted group t of a buffer of n > 0 views in G groups.
 __device__ __forceinline__ void bulk_group(const int32_t* gs, int G, int n, BulkSplit sp, int t, int* a0, int* a1) {
     if (t < sp.X) {
@@ -1292,10 +1308,12 @@ __device__ __forceinline__ void bulk_group(const int32_t* gs, int G, int n, Bulk
 __device__ void bulk_cut(const BulkArgs& b, BulkSplit* s_sp, int T, int64_t base, int64_t before,
                          int64_t* __restrict__ left_off) {
     const int64_t e = b.E - 1;
-    for (int r = threadIdx.x; r < b.W; r += kTargetThreads) {
+    for (int r = threadIdx.x / kWave; r < b.W; r += kTargetThreads / kWave) {   // a wave per rank
         int64_t c, n;
         bulk_range(b, r, e, &c, &n);
-        s_sp[r] = n > 0 ? bulk_split(b.gs + (int64_t)r * b.q + c, b.G[(int64_t)r * b.E + e], T) : BulkSplit{0, -1};
+        BulkSplit sp{0, -1};
+        if (n > 0) sp = bulk_wave_split(b.gs + (int64_t)r * b.q + c, b.G[(int64_t)r * b.E + e], T);
+        if ((threadIdx.x & (kWave - 1)) == 0) s_sp[r] = sp;
     }
     __shared__ int s_cut;
     if (threadIdx.x == 0) s_cut = T;
