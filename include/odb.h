@@ -21,8 +21,9 @@
  *     all other pointers are host pointers.  The caller owns every buffer; the library
  *     allocates no device memory (scratch comes from the caller's workspace), keeps no
  *     pointer after returning and holds no state except a thread-local error message, 64 KB of
- *     pinned host memory per calling thread (results are read back through it; freed when
- *     the thread ends) and the fixed per-device scratch array of odb_collate_static.
+ *     pinned host memory per calling thread (results are read back through it) and an event
+ *     per device it planned long ranks on (both freed when the thread ends), and the fixed
+ *     per-device scratch array of odb_collate_static.
  *   - `stream` is a hipStream_t (NULL = the legacy default stream).  Work is enqueued
  *     on it in order.  odb_align_groups synchronises `stream` because its output sizes
  *     are data dependent; odb_form_groups does so only on its multi-block path (ranks of
@@ -117,9 +118,10 @@ size_t odb_workspace_size(const odb_window_t* w);
  *     its length were 1, and odb_align_groups on these outputs returns ODB_E_INVALID_DATA
  *     naming the first such sample.
  *   - otherwise a multi-block radix sort and run walk (or pointer jumping for budgets
- *     whose batch sizes may exceed the table); this path synchronises `stream` once, to
- *     size its radix passes from the window's length range, and returns
- *     ODB_E_INVALID_DATA itself for such a sample (message names the first one).
+ *     whose batch sizes may exceed the table); this path waits once for what is enqueued on
+ *     `stream` up to the window's length range, which sizes its radix passes (the first of
+ *     them runs meanwhile), and returns ODB_E_INVALID_DATA itself for such a sample (message
+ *     names the first one), with nothing left running.
  */
 int odb_form_groups(const odb_window_t* w, int64_t budget,
                     int32_t* d_order, int32_t* d_sorted_len, int32_t* d_group_index,
@@ -195,10 +197,11 @@ typedef struct odb_plan_info {
  *   d_leftover_off    [W+1] out: rank r's leftovers are [off[r], off[r+1])
  *   h_info            host out: plan summary (always filled when the plan was built)
  *
- * Synchronises `stream` once per alignment round and once at the end: twice for windows
- * that align in one round (every rank buffering the same number of samples, no capacity
- * limit, as in all of the benchmark windows), each time with one device-to-host copy.
- * Returns
+ * Synchronises `stream` once, with one device-to-host copy, for windows that align in one
+ * round (no rank buffers fewer samples than the largest group count, no slot capacity below
+ * a rank's samples, as in all of the benchmark windows).  Join windows of ranks of at most
+ * 16,384 samples that take more rounds synchronise once per chunk of 4, 8, 16, ... rounds;
+ * others once per round and once at the end.  Returns
  * ODB_E_CAPACITY (with h_info->required_slot_capacity) if slot_capacity < W * S,
  * ODB_E_INVALID_DATA if a sample's CSR length lies outside [1, 2^31) or its token offset
  * is negative (the message names the first such sample), or if the stage-1 arrays are

@@ -1,6 +1,11 @@
 // Stages 2-3 of the ODB window pipeline: Distributed Group Alignment (Eq. 3,
 // Algorithm 1, termination rules of Sec. 2.3) and identity coverage (App. C).
 //
+// Three paths, equal results: a window that aligns in one round is written from closed forms
+// (rows, slots and tiles kernels), join windows of short ranks that overflow run two launches
+// a round without waiting for the host (short_round_kernel), and what is left goes round by
+// round, as below.
+//
 // Every rank's buffer is a contiguous run of formation positions; a group is a range
 // of them.  One alignment round is:
 //   group_sizes        size of every group
@@ -1573,7 +1578,6 @@ __global__ void __launch_bounds__(kBlock) slots_kernel(OneArgs a, int32_t* __res
         bool piece = false;
         if (on) {
             r = (int)(k / S);
-            const int64_t j = k - (int64_t)r * S;
             base = a.off[r];
             cnt = a.off[r + 1] - base;
         }
@@ -1788,15 +1792,13 @@ __global__ void __launch_bounds__(kShortThreads) short_round_kernel(ShortArgs a,
     if (stage1_bad(a.st)) return;
     const int t = threadIdx.x, r = blockIdx.x;
     // Eq. 3 over the active ranks
-    int64_t maxG = 0, minC = LLONG_MAX, minS = LLONG_MAX, total = 0, active = 0;
+    int64_t maxG = 0, minC = LLONG_MAX, minS = LLONG_MAX;
     for (int q = t; q < a.W; q += kShortThreads) {
         const int64_t Gq = a.ranks[q].G, Sq = a.ranks[q].cnt;
         if (Gq <= 0) continue;
         maxG = Gq > maxG ? Gq : maxG;
         minS = Sq < minS ? Sq : minS;
         if (a.has_cap && a.cap[q] > 0 && a.cap[q] < minC) minC = a.cap[q];
-        total += Gq;
-        active += 1;
     }
     maxG = short_reduce(maxG, MaxOp{});
     minC = short_reduce(minC, MinOp{});

@@ -1,13 +1,19 @@
 // Stage 1 of the ODB window pipeline: length-aware grouping (Sec. 2.2, Eq. 1).
 //
+//   rank_form_kernel      ranks of at most 16,384 samples: everything below in one block per
+//                         rank and one launch
 //   lengths_kernel        l_i = off[i+1] - off[i], validity, window min / max length
-//   radix_hist/scatter    segmented stable LSD radix sort of every rank's samples by
+//   radix_hist, rank_scan, radix_scatter
+//                         segmented stable LSD radix sort of every rank's samples by
 //                         (length descending, id ascending): keys are max_l - l, the
 //                         segments are the ranks, and stability over the id-ordered input
 //                         gives the id tie-break
-//   links_kernel          next-group-start links from the batch-size rule
-//   jump_kernel           pointer-jumping list ranking that marks every group start
-//   gidx / groups         formation group index of every position and G_r
+//   chain_kernel          runs of equal step of every rank and the chain of group starts
+//                         through them, G_r
+//   chain_index_kernel    formation group index of every position from its run
+//   links_kernel, jump_kernel, gidx / groups
+//                         where the runs do not fit the table: next-group-start links,
+//                         pointer-jumping list ranking that marks every group start
 //
 // Grouping, restated: visiting a rank's samples longest first with threshold t (1 at
 // the start), a group closes once it holds t samples and t becomes B(l) of its last
@@ -19,8 +25,10 @@
 // Two equivalent ways to find them.  Lengths are sorted, so the step b(p) = B(l[p-1]) is
 // constant on runs of positions, and there are at most ~2 sqrt(budget) distinct values
 // of floor(budget / l): inside a run of step b the chain advances by exactly b, so one
-// thread per rank can walk the runs (in LDS) and record each run's first chain position,
-// and every position then knows whether it is a group start by one modulo.  When the
+// thread per rank can go from run to run (in LDS) with one remainder each, and every
+// position's group index follows from its run's first chain position, its step and the group
+// starts before the run.  The runs come from the budget alone: the positions where the
+// step changes are searched in the sorted lengths, so nobody reads them all.  When the
 // number of runs may exceed the LDS table, pointer jumping over the next() links marks
 // the chain in O(log G) doubling rounds instead.
 #include <climits>

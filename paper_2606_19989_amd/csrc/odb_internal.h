@@ -236,15 +236,6 @@ __device__ __forceinline__ const int64_t* stage_ranks(const int64_t* off, int W,
     return s_off;
 }
 
-// Workgroup barrier ordering LDS only: unlike __syncthreads() it does not wait for the
-// wave's outstanding global loads and stores, for loops whose barriers guard LDS tables
-// while their global stores are read by nobody in the block before a full barrier.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 template <typename T>
 __device__ __forceinline__ T wave_incl_sum(T v) {
     const int lane = threadIdx.x & (kWave - 1);
