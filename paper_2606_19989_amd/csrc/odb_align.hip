@@ -1763,7 +1763,10 @@ struct ShortArgs {
     int64_t* sroff;      // first row of the slot among the rank's
 };
 
-constexpr int kShortThreads = 1024;
+// 512 threads: 53 registers and two waves per SIMD, which fit beside the three collate waves of 88
+// there (1,024 threads took 101 registers, so that a round waited for the collate of the step
+// before).
+constexpr int kShortThreads = 512;
 
 template <typename T, typename Op>
 __device__ __forceinline__ T short_reduce(T v, Op op) {

@@ -251,9 +251,10 @@ __global__ void __launch_bounds__(kBlock) radix_hist_kernel(const int64_t* __res
 // first position on: one block per rank, 16 consecutive counts a thread.  The ranks' scans are
 // independent because a rank's counts add up to its samples; ranks of many tiles take the
 // general scan (three launches, ~20 us) instead.
-constexpr int kRankScanThreads = 1024;
+// 512 threads, not 1,024, so that a block starts beside the collate of the step before (kChainBlock).
+constexpr int kRankScanThreads = 512;
 constexpr int kRankScanItems = 16;
-constexpr int64_t kRankScanMax = 4ll * kRankScanThreads * kRankScanItems;   // about 4 us per 16,384 counts
+constexpr int64_t kRankScanMax = 8ll * kRankScanThreads * kRankScanItems;   // about 2 us per 8,192 counts
 
 __global__ void __launch_bounds__(kRankScanThreads) rank_scan_kernel(const int64_t* __restrict__ off,
                                                                      const int64_t* __restrict__ tile_first, int dbits,
@@ -507,7 +508,13 @@ __global__ void __launch_bounds__(kBlock) jump_kernel(const int32_t* __restrict_
 constexpr int kChainThreads = 1024;
 constexpr int kChainWaves = kChainThreads / kWave;
 constexpr int kRunCap = 4096;   // runs per rank
-constexpr int kChaseBatch = 8;  // runs the chase reads at once
+// chain_kernel's threads.  A plan runs beside the previous step's collate, which keeps three waves
+// of 84 vector registers on every SIMD: two more waves of a block of 512 fit there, four of a block
+// of 1,024 did not at 68, 50 or 48 registers a thread, and the plan waited until the
+// collate ended (64 x 262,144: 16 ms a chain in the two-stream schedule).
+constexpr int kChainBlock = 512;
+constexpr int kChainSamples = 1024;   // lengths of a rank sampled for the search
+constexpr int kChaseBatch = 8;        // runs the chase reads at once
 
 // One block: every rank's first global group id (exclusive sum of G_r) and the total in
 // gbase[W].
@@ -624,16 +631,17 @@ __device__ __forceinline__ void chunk_run_starts(const int32_t* len, int lo, int
     }
 }
 
-// Exclusive scan of v over the block (kChainThreads threads); *total receives the sum.
+// Exclusive scan of v over the block of NT threads; *total receives the sum.
+template <int NT>
 __device__ __forceinline__ uint32_t chain_scan(uint32_t v, uint32_t* total) {
-    __shared__ uint32_t s_w[kChainWaves];
+    __shared__ uint32_t s_w[NT / kWave];
     const int t = threadIdx.x;
     const uint32_t inc = wave_scan_dpp<OpAdd>(v);
     if ((t & (kWave - 1)) == kWave - 1) s_w[t / kWave] = inc;
     __syncthreads();
     uint32_t pre = 0, tot = 0;
 #pragma unroll
-    for (int i = 0; i < kChainWaves; ++i) {
+    for (int i = 0; i < NT / kWave; ++i) {
         const uint32_t x = s_w[i];
         pre += i < t / kWave ? x : 0u;
         tot += x;
@@ -659,13 +667,13 @@ struct RunTable {
 // reciprocals (later the prefix), and the sample of lengths.
 constexpr int kChainStart = 0, kChainStep = kRunCap + 16, kChainFirst = kChainStep + kRunCap + kChaseBatch,
               kChainMore = kChainFirst + kRunCap + kChaseBatch, kChainSample = kChainMore + kRunCap + kChaseBatch,
-              kChainWords = kChainSample + kChainThreads;
+              kChainWords = kChainSample + kChainSamples;
 
 // The chain of rank r: cnt sorted lengths at `len`, its positions from `base` on.
 // kIndex: write the group indices here (short ranks); otherwise leave the run table.
 // sq = floor(sqrt(budget)); by_step: at most kRunCap - 2 steps are possible for this budget
 // and length range (otherwise the rank holds at most kRunCap samples).
-template <bool kIndex>
+template <bool kIndex, int NT>
 __device__ __forceinline__ void chain_rank(uint32_t* lds, const int32_t* len, int r, int64_t base, int cnt,
                                            RankState* ranks, int64_t budget, int64_t sq, int by_step,
                                            int32_t* __restrict__ gidx, int32_t* __restrict__ groups_out,
@@ -686,8 +694,8 @@ __device__ __forceinline__ void chain_rank(uint32_t* lds, const int32_t* len, in
     int R = 0;
     if (by_step) {
         // the longest of every `stride` lengths
-        const int stride = (last + kChainThreads - 1) / kChainThreads;
-        s_len[t] = t * (int64_t)stride < last ? len[t * stride] : 0;
+        const int stride = (last + kChainSamples - 1) / kChainSamples;
+        for (int i = t; i < kChainSamples; i += NT) s_len[i] = i * (int64_t)stride < last ? len[i * stride] : 0;
         __syncthreads();
         const int64_t lmax = len[0], lmin = len[last - 1];
         const int64_t blo = batch_size(budget, (int32_t)lmax), bhi = batch_size(budget, (int32_t)lmin);
@@ -704,12 +712,12 @@ __device__ __forceinline__ void chain_rank(uint32_t* lds, const int32_t* len, in
             return;
         }
         // first position of every candidate step (s_c), then the runs that hold a position
-        for (int i = t; i < (int)nc; i += kChainThreads) {
+        for (int i = t; i < (int)nc; i += NT) {
             const int64_t b = i < na ? blo + i : (int64_t)step_of((int32_t)(lhi - (i - na)), budget);
             const int64_t at = i < na ? budget / b : lhi - (i - na);   // step b: lengths at most `at`
             int p = 0;
             if (i > 0) {
-                int lo = 0, hi = kChainThreads;   // first sample at or below the threshold
+                int lo = 0, hi = kChainSamples;   // first sample at or below the threshold
                 while (lo < hi) {
                     const int mid = (lo + hi) >> 1;
                     if (s_len[mid] <= at) hi = mid; else lo = mid + 1;
@@ -727,12 +735,12 @@ __device__ __forceinline__ void chain_rank(uint32_t* lds, const int32_t* len, in
             s_m[i] = (uint32_t)b;
         }
         __syncthreads();
-        for (int i0 = 0; i0 < (int)nc; i0 += kChainThreads) {
+        for (int i0 = 0; i0 < (int)nc; i0 += NT) {
             const int i = i0 + t;
             bool live = false;
             if (i < (int)nc) live = s_c[i] < (i + 1 < (int)nc ? s_c[i + 1] : (uint32_t)last);
             uint32_t tot;
-            const uint32_t ex = chain_scan(live ? 1u : 0u, &tot);
+            const uint32_t ex = chain_scan<NT>(live ? 1u : 0u, &tot);
             if (live) {
                 s_start[R + ex] = s_c[i] + 1;
                 s_b[R + ex] = s_m[i];
@@ -740,7 +748,7 @@ __device__ __forceinline__ void chain_rank(uint32_t* lds, const int32_t* len, in
             R += (int)tot;
         }
     } else {
-        const int per = (last + kChainThreads - 1) / kChainThreads;
+        const int per = (last + NT - 1) / NT;
         const int lo = 1 + t * per;
         const int hi = lo + per < cnt ? lo + per : cnt;
         // the step never decreases, so a chunk whose first and last positions have the step of
@@ -748,7 +756,7 @@ __device__ __forceinline__ void chain_rank(uint32_t* lds, const int32_t* len, in
         const bool busy = lo < hi && (lo == 1 || step_of(len[lo - 2], budget) != step_of(len[hi - 2], budget));
         uint32_t mine = 0, tot;
         if (busy) chunk_run_starts(len, lo, hi, budget, [&](int, uint32_t) { ++mine; });
-        uint32_t at = chain_scan(mine, &tot);
+        uint32_t at = chain_scan<NT>(mine, &tot);
         if (tot > (uint32_t)kRunCap) {   // cannot happen (at most kRunCap samples)
             if (t == 0) {
                 atomicOr(&st->err, kErrInternal);
@@ -779,7 +787,7 @@ __device__ __forceinline__ void chain_rank(uint32_t* lds, const int32_t* len, in
     // subtraction brings it below b, taken if it does not turn the sign (the larger unsigned
     // pattern).  Only the first run can have step 1, whose remainder is 0.
     const bool fp = cnt <= (1 << 19);
-    for (int i = t; i < R; i += kChainThreads) {
+    for (int i = t; i < R; i += NT) {
         const uint32_t b = s_b[i] < (uint32_t)cnt ? s_b[i] : (uint32_t)cnt;
         const uint32_t bp = i > 0 ? (s_b[i - 1] < (uint32_t)cnt ? s_b[i - 1] : (uint32_t)cnt) : 0u;
         // into run i: x_0 itself (cur = next(0) = 1, the second group starts at position 1), else
@@ -855,7 +863,7 @@ __device__ __forceinline__ void chain_rank(uint32_t* lds, const int32_t* len, in
     }
     __syncthreads();
     // the chain's first position in every run
-    for (int i = t; i < R; i += kChainThreads) {
+    for (int i = t; i < R; i += NT) {
         const uint32_t b = s_b[i] < (uint32_t)cnt ? s_b[i] : (uint32_t)cnt;
         const uint32_t cur = s_start[i + 1] + b - 1 - s_c[i];
         s_c[i] = cur < s_start[i + 1] ? cur : 0x7FFFFFFFu;
@@ -863,14 +871,14 @@ __device__ __forceinline__ void chain_rank(uint32_t* lds, const int32_t* len, in
     __syncthreads();
     // group starts per run and their exclusive prefix (into s_m)
     uint32_t carry = 0;
-    for (int i0 = 0; i0 < R; i0 += kChainThreads) {
+    for (int i0 = 0; i0 < R; i0 += NT) {
         const int i = i0 + t;
         uint32_t ng = 0, tot;
         if (i < R) {
             const uint32_t c = s_c[i], e = s_start[i + 1], b = s_b[i];
             ng = c < e ? (e - c + b - 1) / b : 0u;
         }
-        const uint32_t ex = chain_scan(ng, &tot);
+        const uint32_t ex = chain_scan<NT>(ng, &tot);
         if (i < R) s_m[i] = carry + ex;
         carry += tot;
     }
@@ -888,7 +896,7 @@ __device__ __forceinline__ void chain_rank(uint32_t* lds, const int32_t* len, in
         return a;
     };
     if (kIndex) {
-        for (int q = t; q < cnt; q += kChainThreads) {
+        for (int q = t; q < cnt; q += NT) {
             int32_t g = 0;
             if (q > 0) {
                 const int a = run_of((uint32_t)q);
@@ -898,14 +906,14 @@ __device__ __forceinline__ void chain_rank(uint32_t* lds, const int32_t* len, in
             gidx[base + q] = g;
         }
     } else {
-        for (int i = t; i < R; i += kChainThreads) {
+        for (int i = t; i < R; i += NT) {
             tbl.start[base + i] = (int32_t)s_start[i];
             tbl.step[base + i] = (int32_t)s_b[i];
             tbl.first[base + i] = (int32_t)s_c[i];
             tbl.before[base + i] = (int32_t)s_m[i];
         }
         const int64_t t0 = tile_first[r], t1 = tile_first[r + 1];
-        for (int64_t j = t0 + t; j < t1; j += kChainThreads) {
+        for (int64_t j = t0 + t; j < t1; j += NT) {
             const int64_t q = (j - t0) * tile;
             if (q < cnt) tbl.tile[j] = (uint32_t)(q > 0 ? run_of((uint32_t)q) : 0);
         }
@@ -919,7 +927,7 @@ __device__ __forceinline__ void chain_rank(uint32_t* lds, const int32_t* len, in
 // ranks (or null: whole ranks): an alignment round's buffers; with kIndex the next round's,
 // whose count becomes current here.
 template <bool kIndex>
-__global__ void __launch_bounds__(kChainThreads) chain_kernel(const int64_t* __restrict__ off, RankState* ranks,
+__global__ void __launch_bounds__(kChainBlock) chain_kernel(const int64_t* __restrict__ off, RankState* ranks,
                                                               const int32_t* __restrict__ slen, int64_t budget,
                                                               int64_t sq, int by_step, int32_t* __restrict__ gidx,
                                                               int32_t* __restrict__ groups_out, RunTable tbl,
@@ -930,7 +938,7 @@ __global__ void __launch_bounds__(kChainThreads) chain_kernel(const int64_t* __r
     const int64_t base = off[r];
     const int cnt = (int)(ranks ? (kIndex ? ranks[r].next_cnt : ranks[r].cnt) : off[r + 1] - base);
     if (kIndex && ranks && threadIdx.x == 0) ranks[r].cnt = cnt;
-    chain_rank<kIndex>(lds, slen + base, r, base, cnt, ranks, budget, sq, by_step, gidx, groups_out, tbl, tile_first,
+    chain_rank<kIndex, kChainBlock>(lds, slen + base, r, base, cnt, ranks, budget, sq, by_step, gidx, groups_out, tbl, tile_first,
                        tile, st);
 }
 
@@ -1037,7 +1045,7 @@ __global__ void __launch_bounds__(kChainThreads) rank_form_kernel(Values vals, c
                     v[i] = s_cnt[form_bin(d, w0 + i)];
                     sum += v[i];
                 }
-                uint32_t ex = chain_scan(sum, &tot);
+                uint32_t ex = chain_scan<kChainThreads>(sum, &tot);
 #pragma unroll
                 for (int i = 0; i < kPer; ++i) {
                     s_cnt[form_bin(d, w0 + i)] = ex;
@@ -1070,7 +1078,7 @@ __global__ void __launch_bounds__(kChainThreads) rank_form_kernel(Values vals, c
         }
         __syncthreads();   // the chain takes the place of the counters and indices
     }
-    chain_rank<true>(dyn + P, reinterpret_cast<const int32_t*>(s_len), r, base, cnt, nullptr, budget, sq, by_step, gidx,
+    chain_rank<true, kChainThreads>(dyn + P, reinterpret_cast<const int32_t*>(s_len), r, base, cnt, nullptr, budget, sq, by_step, gidx,
                      groups_out, RunTable{}, nullptr, 0, st);
 }
 
@@ -1193,7 +1201,7 @@ bool chain_fits(int64_t budget, int64_t max_cnt) { return chain_by(budget, max_c
 
 int group_short_ranks(int W, int64_t budget, int64_t max_cnt, const int64_t* d_rank_off, const int32_t* d_slen,
                       int32_t* d_gidx, RankState* d_ranks, DevStatus* st, hipStream_t s) {
-    hipLaunchKernelGGL(chain_kernel<true>, dim3(W), dim3(kChainThreads), 0, s, d_rank_off, d_ranks, d_slen, budget,
+    hipLaunchKernelGGL(chain_kernel<true>, dim3(W), dim3(kChainBlock), 0, s, d_rank_off, d_ranks, d_slen, budget,
                        isqrt(budget), chain_by(budget, max_cnt, 0) == kChainByStep ? 1 : 0, d_gidx, (int32_t*)nullptr,
                        RunTable{}, (const int64_t*)nullptr, 0, st);
     ODB_LAUNCHED();
@@ -1237,7 +1245,7 @@ int group_sequences(const Layout& L, void* ws, int W, int64_t n, int64_t budget,
         }
         const RunTable tbl{j0, j1, ws_at<int32_t>(ws, L.gsize), incl, ws_at<uint32_t>(ws, L.counts),
                            ws_at<uint32_t>(ws, L.rank_runs)};
-        hipLaunchKernelGGL(chain_kernel<false>, dim3(W), dim3(kChainThreads), 0, s, d_off, d_ranks, d_slen, budget,
+        hipLaunchKernelGGL(chain_kernel<false>, dim3(W), dim3(kChainBlock), 0, s, d_off, d_ranks, d_slen, budget,
                            isqrt(budget), by == kChainByStep ? 1 : 0, (int32_t*)nullptr, d_groups_out, tbl,
                            (const int64_t*)d_tile_first, (int)kBlock * items, st);
         ODB_LAUNCHED();

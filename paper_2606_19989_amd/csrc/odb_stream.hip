@@ -1253,7 +1253,9 @@ __global__ void __launch_bounds__(NT) bulk_form_kernel(BulkArgs b) {
     for (int g = tid; g < G; g += NT) b.gs[out + g] = s_gs[g];
 }
 
-constexpr int kTargetThreads = 1024;
+// 512 threads: the cut takes 73 registers, and a block has to fit beside the three collate waves of
+// 88 on every SIMD (1,024 threads waited for the whole collate of the step before).
+constexpr int kTargetThreads = 512;
 
 // Where a split leaves its pieces: positions [0, X) are singletons, [X, end of group j*) is one
 // group and later groups are unchanged; j* is the first group with start(j* + 1) - (j* + 1) >=
