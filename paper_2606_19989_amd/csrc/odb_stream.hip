@@ -2075,7 +2075,7 @@ BulkSchedule bulk_schedule(const StreamArgs& a, const odb_stream_params_t* p) {
         b.stop = ODB_STOP_RANK_FINISHED;
         b.stop_round = 1;
     }
-    // (bulk_cut_kernel keeps eight bytes a rank in LDS)
+    // bulk_targets_kernel keeps eight bytes a rank in LDS
     b.use = b.rounds <= a.max_rounds && b.E <= kBulkBlocks / a.W && a.W <= 8192;
     return b;
 }

@@ -398,6 +398,12 @@ def together_cases():
     # the stop round still fetches: one rank ready (its views count as fetched), one not
     out.append(("finished", rng.integers(900, 1000, 3 * 400), 3, 1000, 50, 200, [50, 100, 200],
                 dict(mode="nonjoin", quota=10 ** 6)))
+    # the most ranks formed together (64 KB of splits at the cut) and one more (round by round);
+    # schedules of more ranks than one launch's arguments hold
+    for ranks in (8192, 8193):
+        out.append((f"ranks_{ranks}", np.full(4 * ranks, 100), ranks, 100, 2, 2, [2] * ranks,
+                    dict(mode="nonjoin", quota=3 * ranks)))
+    out.append(("uneven_130", rng.integers(1, 300, 130 * 40), 130, 900, 8, 32, [4 + r % 3 for r in range(130)], {}))
     return out
 
 
