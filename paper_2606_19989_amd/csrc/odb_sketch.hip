@@ -43,8 +43,16 @@ __global__ void sketch_init_kernel(DevSketch* d) {
     }
 }
 
-constexpr int kSketchOneThreads = 1024;
-constexpr int64_t kSketchOne = 16 * kSketchOneThreads;
+constexpr int kSketchThreads = 1024;
+constexpr int64_t kSketchOne = 16 * kSketchThreads;
+// Larger sketches.  A block ends with seven atomics to the same line, ~12 ns each, one after the
+// other over all blocks, so the blocks are few and large: four samples a thread (one unrolled
+// iteration, its loads in flight together) up to one block per compute unit, then more.  us per
+// call against eight blocks of 256 threads per compute unit: 50,000 samples 35.4 / 25.6, 200,000
+// ids 84.7 / 32.4 (one sample a thread 39.8), 1,000,000 189 / 43, 2^24 206 / 72 (ids 423 / 350).
+// Up to kSketchFew samples the small blocks are still the faster ones (16,385: 24.4 / 25.6).
+constexpr int kSketchItems = 4;
+constexpr int64_t kSketchFew = 20 * kSketchThreads;
 
 // kThreads per block; kOne: the only block.
 template <int kThreads, bool kOne>
@@ -149,14 +157,19 @@ extern "C" int odb_length_sketch(const odb_window_t* w, const int32_t* d_ids, in
     // the one block writes its result to the host itself: a copy behind it costs another 1 us
     DevSketch* page = count <= kSketchOne ? static_cast<DevSketch*>(read_page()) : nullptr;
     if (count <= kSketchOne) {
-        hipLaunchKernelGGL((sketch_kernel<kSketchOneThreads, true>), dim3(1), dim3(kSketchOneThreads), 0, s,
+        hipLaunchKernelGGL((sketch_kernel<kSketchThreads, true>), dim3(1), dim3(kSketchThreads), 0, s,
                            w->d_token_offsets, w->num_samples, d_ids, count, budget, page ? page : d);
         ODB_LAUNCHED();
     } else {
         hipLaunchKernelGGL(sketch_init_kernel, dim3(1), dim3(64), 0, s, d);
         ODB_LAUNCHED();
-        hipLaunchKernelGGL((sketch_kernel<kBlock, false>), dim3(grid_for(count, kBlock, (int64_t)num_cus() * 8)),
-                           dim3(kBlock), 0, s, w->d_token_offsets, w->num_samples, d_ids, count, budget, d);
+        if (count <= kSketchFew)
+            hipLaunchKernelGGL((sketch_kernel<kBlock, false>), dim3(grid_for(count, kBlock)), dim3(kBlock), 0, s,
+                               w->d_token_offsets, w->num_samples, d_ids, count, budget, d);
+        else
+            hipLaunchKernelGGL((sketch_kernel<kSketchThreads, false>),
+                               dim3(grid_for(count, kSketchThreads * kSketchItems, (int64_t)num_cus())),
+                               dim3(kSketchThreads), 0, s, w->d_token_offsets, w->num_samples, d_ids, count, budget, d);
         ODB_LAUNCHED();
     }
     if (page) {

@@ -355,6 +355,27 @@ def test_length_sketch_whole_window_and_edge_cases():
     assert e.value.status == odb.ODB_E_INVALID_DATA
 
 
+@pytest.mark.parametrize("count", [16384, 16385, 20480, 20481, 1 << 20, (1 << 20) + 4097])
+def test_length_sketch_block_edges(count):
+    """One block, the fewest and the most small blocks, the fewest large ones, one per compute
+    unit and a grid that strides, with and without ids."""
+    import torch
+    import paper_2606_19989_amd as odb
+
+    rng = np.random.default_rng(count)
+    n = (1 << 20) + 5000
+    off = np.concatenate([[0], np.cumsum(rng.integers(1, 40000, n))]).astype(np.int64)
+    win = odb.DeviceWindow(np.array([0, n], np.int64), torch.from_numpy(off).cuda(),
+                           torch.zeros(1, dtype=torch.int32, device="cuda"), None, 0)
+    ws = torch.empty(odb.odb_workspace_size(win), dtype=torch.uint8, device="cuda")
+    log(f"sketch edge {count}")
+    ids = rng.integers(0, n, count).astype(np.int32)
+    got = odb.odb_length_sketch(win, torch.from_numpy(ids).cuda(), count, 1 << 16, ws)
+    _compare_sketch(got, oracle.length_sketch(off, ids, 1 << 16))
+    got = odb.odb_length_sketch(win, None, count, 1 << 16, ws)
+    _compare_sketch(got, oracle.length_sketch(off, np.arange(count), 1 << 16))
+
+
 def test_length_sketch_sums_past_64_bits():
     # lengths near 2^31: the sum of squares passes 2^64 (the 128-bit accumulation), at a
     # budget of 2^40 (the short-sample test 4 l < L_max in 64 bits)
