@@ -36,6 +36,7 @@
 #include <vector>
 
 #include "odb_internal.h"
+#include "odb_search.h"
 
 namespace odb {
 
@@ -694,8 +695,9 @@ __device__ __forceinline__ void chain_rank(uint32_t* lds, const int32_t* len, in
     int R = 0;
     if (by_step) {
         // the longest of every `stride` lengths
-        const int stride = (last + kChainSamples - 1) / kChainSamples;
-        for (int i = t; i < kChainSamples; i += NT) s_len[i] = i * (int64_t)stride < last ? len[i * stride] : 0;
+        const uint32_t stride = search_stride(last, kChainSamples);
+        for (uint32_t i = t; i < (uint32_t)kChainSamples; i += NT)
+            s_len[i] = i * stride < (uint32_t)last ? len[i * stride] : 0;
         __syncthreads();
         const int64_t lmax = len[0], lmin = len[last - 1];
         const int64_t blo = batch_size(budget, (int32_t)lmax), bhi = batch_size(budget, (int32_t)lmin);
@@ -715,23 +717,10 @@ __device__ __forceinline__ void chain_rank(uint32_t* lds, const int32_t* len, in
         for (int i = t; i < (int)nc; i += NT) {
             const int64_t b = i < na ? blo + i : (int64_t)step_of((int32_t)(lhi - (i - na)), budget);
             const int64_t at = i < na ? budget / b : lhi - (i - na);   // step b: lengths at most `at`
-            int p = 0;
-            if (i > 0) {
-                int lo = 0, hi = kChainSamples;   // first sample at or below the threshold
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if (s_len[mid] <= at) hi = mid; else lo = mid + 1;
-                }
-                // between sample lo - 1 (above) and sample lo
-                int a = lo > 0 ? (lo - 1) * stride + 1 : 0;
-                int z = (int64_t)lo * stride < last ? lo * stride : last;
-                while (a < z) {
-                    const int mid = (a + z) >> 1;
-                    if (len[mid] <= at) z = mid; else a = mid + 1;
-                }
-                p = a;
-            }
-            s_c[i] = (uint32_t)p;
+            const uint32_t p = i > 0 ? first_at_most([&](uint32_t k) { return s_len[k]; },
+                                                     [&](uint32_t k) { return len[k]; }, last, stride, kChainSamples, at)
+                                     : 0u;
+            s_c[i] = p;
             s_m[i] = (uint32_t)b;
         }
         __syncthreads();
