@@ -211,7 +211,10 @@ __global__ void __launch_bounds__(256) read_page_kernel(const uint32_t* __restri
 }  // namespace
 
 void* read_page() {
-    if (!g_page.p && hipHostMalloc(&g_page.p, kReadBytes, hipHostMallocPortable) != hipSuccess) {
+    // coherent, whatever HIP_HOST_COHERENT says: read_end takes what a kernel wrote as soon as an event
+    // behind it is done, without the release that the end of a stream's work brings
+    if (!g_page.p &&
+        hipHostMalloc(&g_page.p, kReadBytes, hipHostMallocPortable | hipHostMallocCoherent) != hipSuccess) {
         (void)hipGetLastError();
         g_page.p = nullptr;
     }
