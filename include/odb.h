@@ -112,7 +112,7 @@ size_t odb_workspace_size(const odb_window_t* w);
  *
  * Two paths, equal results:
  *   - every rank holds at most 16,384 samples and its distinct batch sizes fit a
- *     4,096-entry table (budget < 4,190,209, or ranks of at most 4,096 samples): one block
+ *     3,840-entry table (budget < 3,682,561, or ranks of at most 3,840 samples): one block
  *     per rank sorts and walks its samples; one kernel, asynchronous.  A sample whose
  *     length lies outside [1, 2^31), or whose token offset is negative, is grouped as if
  *     its length were 1, and odb_align_groups on these outputs returns ODB_E_INVALID_DATA

@@ -1186,6 +1186,16 @@ static ChainBy chain_by(int64_t budget, int64_t max_cnt, int64_t len_range) {
     return max_cnt <= kRunCap ? kChainBySample : kChainJump;
 }
 
+// Whether odb_form_groups takes a window by one block per rank.  The limit on the steps is narrower
+// than the chain's table: which path a call takes is seen from outside (this one leaves a bad length
+// to odb_align_groups, the other waits and reports it), so the line stays where the header has it.
+constexpr int64_t kFormSteps = 3840;
+
+static bool form_in_one_block(int64_t budget, int64_t max_cnt) {
+    return max_cnt <= kRankBlockMax && (max_cnt <= kFormSteps || 2 * (isqrt(budget) + 1) + 1 <= kFormSteps);
+}
+static_assert(kFormSteps <= kRunCap, "the one-block grouping's chain fits its table");
+
 bool chain_fits(int64_t budget, int64_t max_cnt) { return chain_by(budget, max_cnt, 0) != kChainJump; }
 
 int group_short_ranks(int W, int64_t budget, int64_t max_cnt, const int64_t* d_rank_off, const int32_t* d_slen,
@@ -1303,8 +1313,8 @@ extern "C" int odb_form_groups(const odb_window_t* w, int64_t budget, int32_t* d
     // one block per rank: one launch, no synchronisation (invalid lengths are grouped as
     // length 1 and reported by odb_align_groups); the rank offsets go along as kernel arguments
     // where they fit
-    const ChainBy by = chain_by(budget, max_cnt, 0);
-    if (max_cnt <= kRankBlockMax && by != kChainJump) {
+    if (form_in_one_block(budget, max_cnt)) {
+        const ChainBy by = chain_by(budget, max_cnt, 0);
         Values v{};
         const int64_t* off = nullptr;
         if (W < kValuesPerLaunch) {

@@ -75,6 +75,38 @@ def test_long_ranks_reject_bad_lengths(span):
     compare_plan(w, pipe, oracle.plan_window(w))
 
 
+@pytest.mark.parametrize("budget,longest,by_form", [
+    (3682560, 5000, False), (3682561, 5000, True), (4194303, 5000, True), (4194304, 5000, True),
+    (1 << 40, 3840, False), (1 << 40, 3841, True), (1 << 40, 4096, True), (1 << 40, 4097, True)])
+def test_which_call_reports_a_bad_length(budget, longest, by_form):
+    """Where the one-block grouping ends (batch sizes of 3,840 table entries, ranks of 3,840 samples):
+    up to there odb_align_groups reports a bad length, beyond it odb_form_groups itself; the plans
+    on both sides equal the oracle's."""
+    import torch
+    import paper_2606_19989_amd as odb
+
+    rng = np.random.default_rng(44)
+    lens = rng.integers(1, 3000, longest + 100).astype(np.int64)
+    off = np.concatenate([[0], np.cumsum(lens)])
+    bad = off.copy()
+    bad[78:] -= lens[77]                          # sample 77 has length 0
+    toks = torch.zeros(64, dtype=torch.int32, device="cuda")
+    rank_off = np.array([0, longest, longest + 100])
+    pipe = odb.Pipeline(odb.DeviceWindow(rank_off, torch.from_numpy(bad).cuda(), toks), budget)
+    with pytest.raises(odb.OdbError) as e:
+        pipe.form()
+        assert not by_form, "odb_form_groups took the bad length"
+        pipe.align()
+    assert e.value.status == odb.ODB_E_INVALID_DATA and "sample 77 " in str(e.value), str(e.value)
+    if not by_form:
+        pipe.form()
+    pipe.win.token_offsets.copy_(torch.from_numpy(off))
+    pipe.form()
+    pipe.align()
+    w = synth.window_from_ranks("after_bad", [lens[:longest], lens[longest:]], budget)
+    compare_plan(w, pipe, oracle.plan_window(w))
+
+
 @pytest.mark.parametrize("kind", ["zero_length", "decreasing_offset", "length_2p31", "negative_offset"])
 def test_window_rejects_bad_lengths(kind):
     # l < 1, l >= 2^31 and negative token offsets are invalid data (a length the batch
