@@ -2038,6 +2038,33 @@ __global__ void __launch_bounds__(kShortThreads) short_rows_kernel(ShortArgs a, 
 // capacities take two to six rounds as a rule, and a launch past the last one returns at once.
 constexpr int64_t kShortChunk = 4;
 
+// Samples per step over the ranks of the staged slots.
+__global__ void __launch_bounds__(kBlock) short_steps_kernel(ShortArgs a, int64_t* __restrict__ steps) {
+    const int64_t S = a.rs->cut, stride = (int64_t)gridDim.x * kBlock;
+    for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < S; j += stride) {
+        int64_t n = 0;
+        for (int r = 0; r < a.W; ++r)
+            if (j < a.ranks[r].slots) n += a.srows[a.off[r] + j];
+        steps[j] = n;
+    }
+}
+
+// The largest step from the samples per step.  One block.
+__global__ void __launch_bounds__(kBlock) step_max_kernel(const int64_t* __restrict__ steps, RoundState* rs) {
+    int64_t mx = 0;
+    for (int64_t j = threadIdx.x; j < rs->cut; j += kBlock) mx = steps[j] > mx ? steps[j] : mx;
+    mx = block_reduce(mx, MaxOp{});
+    if (threadIdx.x == 0) rs->step_max = mx;
+}
+
+// A plan that does not fit the slot arrays has no slots to take its largest step from, and reports it all
+// the same: from the samples per step, in the workspace.
+int step_max_without_slots(const int64_t* steps, RoundState* d_rs, RoundState* rs, hipStream_t s) {
+    hipLaunchKernelGGL(step_max_kernel, dim3(1), dim3(kBlock), 0, s, steps, d_rs);
+    ODB_LAUNCHED();
+    return read_device(rs, d_rs, sizeof(*rs), s);
+}
+
 // The plan summary of a device-side alignment, and what it reports.
 int finish_short(const HostState& h, int W, int64_t n, int64_t slot_capacity, int stop, odb_plan_info_t* out) {
     const int64_t S = h.rs.cut, K = (int64_t)W * S;
@@ -2047,11 +2074,11 @@ int finish_short(const HostState& h, int W, int64_t n, int64_t slot_capacity, in
     out->splits = h.rs.splits;
     out->overflow_groups = h.rs.overflow;
     out->second_gather_rounds = h.rs.second_gather;
+    out->max_step_samples = h.rs.step_max;
     out->required_slot_capacity = K;
     if (K > slot_capacity)
         return set_error(ODB_E_CAPACITY, "plan needs %lld slots, capacity is %lld", (long long)K,
                          (long long)slot_capacity);
-    out->max_step_samples = h.rs.step_max;
     out->emitted_samples = h.info.emitted;
     out->leftover_samples = n - h.info.emitted;
     out->real_tokens = h.info.real_tokens;
@@ -2231,6 +2258,13 @@ extern "C" int odb_align_groups(const odb_window_t* w, int64_t budget, const odb
                              "stage-1 arrays do not describe this window (first inconsistent position %lld)",
                              (long long)h.st.first_bad);
         if (!h.rs.overflowed) {
+            if ((int64_t)W * h.rs.cut > slot_capacity) {
+                if (!nonjoin) {   // else the cut has counted them
+                    hipLaunchKernelGGL(cut_steps_kernel, dim3(grid_for(max_nr, kWave, kMaxRanges)), dim3(kBlock), 0, s, a);
+                    ODB_LAUNCHED();
+                }
+                ODB_TRY(step_max_without_slots(steps, d_rs, &h.rs, s));
+            }
             h.rs.rounds = 1;
             return finish_short(h, W, n, slot_capacity, nonjoin && h.rs.quota_hit ? ODB_STOP_QUOTA : ODB_STOP_DRAINED,
                                 h_info);
@@ -2309,6 +2343,11 @@ extern "C" int odb_align_groups(const odb_window_t* w, int64_t budget, const odb
             redo = h.rs.irregular != 0;
             if (redo || !h.rs.overflowed) break;
             if (h.rs.rounds > n) return set_error(ODB_E_INTERNAL, "alignment does not end");
+        }
+        if (!redo && (int64_t)W * h.rs.cut > slot_capacity) {
+            hipLaunchKernelGGL(short_steps_kernel, dim3(grid_for(h.rs.cut, kBlock, gcap)), dim3(kBlock), 0, s, a, steps);
+            ODB_LAUNCHED();
+            ODB_TRY(step_max_without_slots(steps, d_rs, &h.rs, s));
         }
         if (!redo) return finish_short(h, W, n, slot_capacity, ODB_STOP_DRAINED, h_info);
         ODB_TRY(upload_small(w, L, d_ws, cap, s, true));

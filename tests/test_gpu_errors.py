@@ -182,6 +182,49 @@ def test_align_reports_capacity_and_pipeline_retries(mode):
         compare_loss_weights(pipe, ref)
 
 
+def capacity_windows():
+    """One window per path of the alignment: one round (ranks on both sides of 16 tiles, join and with
+    quotas inside and past the window), rounds of short ranks, and round by round."""
+    rng = np.random.default_rng(45)
+    U = lambda n: rng.integers(1, 3000, size=n)
+    win = synth.window_from_ranks
+    return [
+        win("one_round", [U(900), U(1025), U(700)], 12000),
+        win("one_round_long", [U(20000), U(30), U(18000)], 1 << 22),
+        win("one_round_quota", [U(900), U(1025), U(700)], 12000, mode="nonjoin", quota=1111),
+        win("one_round_quota_all", [U(900), U(1025), U(700)], 12000, mode="nonjoin", quota=1 << 40),
+        win("short_rounds", [U(900), U(1025), U(700)], 12000, capacity=np.array([40, 0, 33])),
+        win("rounds", [U(17000), U(1025), U(700)], 12000, capacity=np.array([400, 0, 330])),
+        win("rounds_quota", [U(900), U(1025), U(7)], 12000, mode="nonjoin", quota=100),
+    ]
+
+
+@pytest.mark.parametrize("idx", range(len(capacity_windows())))
+def test_capacity_error_fills_the_summary(idx):
+    """A plan that needs more slots than there are still reports what it is: steps, rounds, stop reason,
+    splits, overflow and the largest step, whichever way it was aligned."""
+    import torch
+    import paper_2606_19989_amd as odb
+
+    w = capacity_windows()[idx]
+    ref = oracle.plan_window(w)
+    log(f"capacity summary: {w.name}, rounds {ref.info['rounds']}")
+    toks = torch.zeros(1, dtype=torch.int32, device="cuda")
+    dwin = odb.DeviceWindow(w.rank_off, torch.from_numpy(w.tok_off).cuda(), toks)
+    for cap in (1, w.W * ref.steps - 1):
+        pipe = odb.Pipeline(dwin, w.budget, mode=w.mode, quota=w.quota, capacity=w.capacity, slot_capacity=cap)
+        pipe.form()
+        st, info = odb.odb_align_groups(dwin, w.budget, pipe.mode, pipe.quota, w.capacity, pipe.order, pipe.sorted_len,
+                                        pipe.group_index, pipe.groups_per_rank, cap, pipe.emit_order, pipe.slot_rows,
+                                        pipe.slot_maxlen, pipe.slot_row_off, pipe.slot_tile_off, pipe.slot_tokens,
+                                        pipe.leftover, pipe.leftover_off, pipe.ws, raise_on_capacity=False)
+        assert st == odb.ODB_E_CAPACITY
+        assert info["required_slot_capacity"] == w.W * ref.steps
+        for f in ("steps", "rounds", "stop_reason", "splits", "overflow_groups", "second_gather_rounds",
+                  "max_step_samples"):
+            assert info[f] == ref.info[f], (f, info[f], ref.info[f])
+
+
 def test_collate_status_survives_plan_calls():
     # a collate error stays readable after grouping and alignment calls on the same
     # workspace; reading it clears it; a fresh workspace full of ones reports no error
