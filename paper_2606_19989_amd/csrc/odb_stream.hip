@@ -1303,6 +1303,34 @@ __device__ __forceinline__ void bulk_group(const int32_t* gs, int G, int n, Bulk
     *a1 = g + 1 < G ? gs[g + 1] : n;
 }
 
+// The splits of all ranks' buffers of round e towards its target T, a wave per rank (s_sp: LDS), by a
+// whole block of NT threads that synchronises before it reads them.
+template <int NT>
+__device__ __forceinline__ void bulk_round_splits(const BulkArgs& b, BulkSplit* s_sp, int64_t e, int T) {
+    for (int r = threadIdx.x / kWave; r < b.W; r += NT / kWave) {
+        int64_t c, n;
+        bulk_range(b, r, e, &c, &n);
+        BulkSplit sp{0, -1};
+        if (n > 0) sp = bulk_wave_split(b.gs + (int64_t)r * b.q + c, b.G[(int64_t)r * b.E + e], T);
+        if ((threadIdx.x & (kWave - 1)) == 0) s_sp[r] = sp;
+    }
+}
+
+// Samples of step j of that round over the ranks.
+__device__ __forceinline__ int64_t bulk_step_rows(const BulkArgs& b, const BulkSplit* s_sp, int64_t e, int T, int j) {
+    int64_t v = 0;
+#pragma unroll 4
+    for (int r = 0; r < b.W; ++r) {
+        int64_t c, n;
+        bulk_range(b, r, e, &c, &n);
+        if (n == 0) continue;
+        int a0, a1;
+        bulk_group(b.gs + (int64_t)r * b.q + c, b.G[(int64_t)r * b.E + e], (int)n, s_sp[r], T - 1 - j, &a0, &a1);
+        v += a1 - a0;
+    }
+    return v;
+}
+
 // Non-join: the steps of the last round up to the one that reaches the quota, and from them
 // every rank's emitted rows (lo: their running sum over the ranks) and left-over views.
 // T, base: target of the last round and the steps before it; s_sp: LDS, a BulkSplit per rank.
@@ -1310,31 +1338,14 @@ __device__ __forceinline__ void bulk_group(const int32_t* gs, int G, int n, Bulk
 __device__ void bulk_cut(const BulkArgs& b, BulkSplit* s_sp, int T, int64_t base, int64_t before,
                          int64_t* __restrict__ left_off) {
     const int64_t e = b.E - 1;
-    for (int r = threadIdx.x / kWave; r < b.W; r += kTargetThreads / kWave) {   // a wave per rank
-        int64_t c, n;
-        bulk_range(b, r, e, &c, &n);
-        BulkSplit sp{0, -1};
-        if (n > 0) sp = bulk_wave_split(b.gs + (int64_t)r * b.q + c, b.G[(int64_t)r * b.E + e], T);
-        if ((threadIdx.x & (kWave - 1)) == 0) s_sp[r] = sp;
-    }
+    bulk_round_splits<kTargetThreads>(b, s_sp, e, T);
     __shared__ int s_cut;
     if (threadIdx.x == 0) s_cut = T;
     __syncthreads();
     int64_t carry = before;
     for (int j0 = 0; j0 < T && carry < b.quota; j0 += kTargetThreads) {   // uniform
         const int j = j0 + threadIdx.x;
-        int64_t v = 0;
-        if (j < T) {
-#pragma unroll 4
-            for (int r = 0; r < b.W; ++r) {
-                int64_t c, n;
-                bulk_range(b, r, e, &c, &n);
-                if (n == 0) continue;
-                int a0, a1;
-                bulk_group(b.gs + (int64_t)r * b.q + c, b.G[(int64_t)r * b.E + e], (int)n, s_sp[r], T - 1 - j, &a0, &a1);
-                v += a1 - a0;
-            }
-        }
+        const int64_t v = j < T ? bulk_step_rows(b, s_sp, e, T, j) : 0;
         int64_t tot;
         const int64_t ex = carry + sblock_excl<kTargetThreads>(v, &tot);
         if (j < T && ex < b.quota && ex + v >= b.quota) s_cut = j + 1;
@@ -1567,12 +1578,32 @@ __device__ __forceinline__ void bulk_steps(const BulkArgs& b, const int32_t* __r
     }
 }
 
-// The steps staged before a round that overflows.
+// The steps staged before a round that overflows (all of them: S <= scap).
 __global__ void __launch_bounds__(kWave) bulk_staged_steps_kernel(BulkArgs b, const int32_t* __restrict__ rows,
                                                                   const int64_t* __restrict__ tokens) {
     if (b.st->err) return;
-    const int64_t S = b.st->steps < b.scap ? b.st->steps : b.scap;
-    bulk_steps(b, rows, tokens, b.scap, S, blockIdx.x, gridDim.x);
+    bulk_steps(b, rows, tokens, b.scap, b.st->steps, blockIdx.x, gridDim.x);
+}
+
+// The largest step of the first `rounds` rounds from their groups, where the slots do not fit and are not
+// there to sum.  A block per round, a BulkSplit per rank in dynamic LDS.
+__global__ void __launch_bounds__(kTargetThreads) bulk_step_max_kernel(BulkArgs b, int64_t rounds) {
+    extern __shared__ unsigned long long s_dyn[];
+    BulkSplit* s_sp = reinterpret_cast<BulkSplit*>(s_dyn);
+    if (b.st->err) return;
+    int64_t mx = 0;
+    for (int64_t e = blockIdx.x; e < rounds; e += gridDim.x) {
+        const int T = b.T[e], kept = b.lo && e + 1 == b.E ? (int)b.st->cut : T;
+        __syncthreads();
+        bulk_round_splits<kTargetThreads>(b, s_sp, e, T);
+        __syncthreads();
+        for (int j = threadIdx.x; j < kept; j += kTargetThreads) {
+            const int64_t n = bulk_step_rows(b, s_sp, e, T, j);
+            mx = n > mx ? n : mx;
+        }
+    }
+    mx = sblock_max<kTargetThreads>(mx);
+    if (threadIdx.x == 0 && mx) atomicMax(&b.st->max_step, (unsigned long long)mx);
 }
 
 struct BulkTileLoad {
@@ -2251,6 +2282,10 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
             else if (n_max <= 1024) hipLaunchKernelGGL((bulk_slots_kernel<256, 4>), grid, dim3(256), 0, s, b, o);
             else hipLaunchKernelGGL((bulk_slots_kernel<512, 8>), grid, dim3(512), 0, s, b, o);
         };
+        auto step_max = [&](int64_t rounds) {
+            hipLaunchKernelGGL(bulk_step_max_kernel, dim3(grid_for(rounds, 1, gcap)), dim3(kTargetThreads), 8 * (size_t)W, s,
+                               b, rounds);
+        };
         // a buffer of n views takes the smallest block and slots per thread that hold it
         if (n_max <= 256) hipLaunchKernelGGL((bulk_form_kernel<256, 1>), form_grid, dim3(256), 0, s, b);
         else if (n_max <= 512) hipLaunchKernelGGL((bulk_form_kernel<256, 2>), form_grid, dim3(256), 0, s, b);
@@ -2294,6 +2329,11 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
         }
         if (fail == bs.E) {
             bulk_done = true;
+            if (hb.steps > scap) {   // no slots were written, but the summary has the largest step all the same
+                step_max(bs.E);
+                ODB_LAUNCHED();
+                ODB_TRY(read_device(&hb, b.st, sizeof(hb), s));
+            }
             hg.steps = hb.steps;
             hg.emitted = join ? M : hb.emitted;
             hg.rounds = bs.rounds;
@@ -2320,8 +2360,11 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
             }
             slots(staged);
             ODB_LAUNCHED();
-            hipLaunchKernelGGL(bulk_staged_steps_kernel, dim3(step_grid), dim3(kWave), 0, s, b, (const int32_t*)staged.rows,
-                               (const int64_t*)staged.tokens);
+            if (hb.steps <= scap)
+                hipLaunchKernelGGL(bulk_staged_steps_kernel, dim3(step_grid), dim3(kWave), 0, s, b,
+                                   (const int32_t*)staged.rows, (const int64_t*)staged.tokens);
+            else
+                step_max(fail);
             ODB_LAUNCHED();
         }
     }

@@ -416,6 +416,45 @@ def test_stream_rounds_together(idx):
              tokens=None if small else _one_token(), **kw)
 
 
+def capacity_cases():
+    """Iterations drained and cut at a quota, formed together, with a round that overflows after some of
+    them, and round by round from the start."""
+    rng = np.random.default_rng(84)
+    L = rng.integers(1, 900, 3 * 1003)
+    return [
+        ("drained", L, 3, 3000, 100, 100, [100] * 3, {}),
+        ("drained_many_ranks", rng.integers(1, 900, 130 * 70), 130, 3000, 16, 16, [16] * 130, {}),
+        ("cut", L, 3, 3000, 100, 100, [100] * 3, dict(mode="nonjoin", quota=1234)),
+        ("uneven_cut", L, 3, 3000, 100, 300, [100, 129, 250], dict(mode="nonjoin", quota=1234)),
+        ("resume", L, 3, 3000, 100, 300, [100, 129, 250], {}),
+        ("resume_cut", L, 3, 3000, 100, 300, [100, 129, 250], dict(mode="nonjoin", quota=3000)),
+        ("rounds", L, 3, 3000, 100, 300, [100, 129, 250], dict(cap=np.array([9, 0, 8]))),
+    ]
+
+
+@pytest.mark.parametrize("idx", range(len(capacity_cases())))
+def test_stream_capacity_error_fills_the_summary(idx):
+    """An iteration that needs more slots than there are reports the same summary, the largest step
+    among it, whether its rounds were formed together or not."""
+    import paper_2606_19989_amd as odb
+
+    name, lens, W, budget, buf, depth, rate, kw = capacity_cases()[idx]
+    perm = np.random.default_rng(85).permutation(len(lens)).astype(np.int32)
+    rate = np.asarray(rate, dtype=np.int32)
+    mode, quota, cap = kw.get("mode", "join"), kw.get("quota", 0), kw.get("cap")
+    ref = oracle.stream(offsets(lens), perm, W, budget, quota=quota, buffer_size=buf, depth=depth, rate=rate, capacity=cap,
+                        mode=oracle.MODE_NONJOIN if mode == "nonjoin" else oracle.MODE_JOIN)
+    log(f"stream capacity summary {name}: steps {ref.steps}, overflow {ref.sinfo['overflow_groups']}")
+    for steps in (1, ref.steps // 2, ref.steps - 1):
+        sp = _stream_pipeline(lens, perm, W, budget, buf, depth, rate, mode=mode, quota=quota, capacity=cap,
+                              slot_capacity=W * steps)
+        st, info = sp._call(None)
+        assert st == odb.ODB_E_CAPACITY and info["required_slot_capacity"] == W * ref.steps
+        for f in ("steps", "rounds", "emit_rounds", "skip_rounds", "stop_reason", "views", "emitted_views", "splits",
+                  "overflow_groups", "second_gather_rounds", "max_outstanding", "max_step_samples"):
+            assert info[f] == ref.sinfo[f], (steps, f, info[f], ref.sinfo[f])
+
+
 def _one_token():
     import torch
     return torch.zeros(1, dtype=torch.int32, device="cuda")
