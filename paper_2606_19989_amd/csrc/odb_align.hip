@@ -1167,6 +1167,7 @@ struct OneArgs {
     int64_t* gpre;             // [n] tokens before that start within its tile of the rank
     int64_t* tpre;             // [W * per_rank] tokens of each of the rank's tiles, or before it
     int per_rank;              // tiles (kRowTile positions) of the largest rank
+    int64_t min_nr;            // samples of the smallest rank that has any
     int64_t* lo;               // [W + 1] first row of every rank (the rank offsets in join mode)
     int64_t* steps;            // [max n_r] samples per step (sample quota only)
     I64Pair* part;             // [gridDim.x] (padded elements, real tokens) per range of slots
@@ -1211,13 +1212,16 @@ __global__ void __launch_bounds__(kBlock) rows_kernel(OneArgs a, int xcd) {
         tile = b % a.per_rank;
     }
     if (b == 0) {   // ranks without samples have no block of their own
-        for (int k = threadIdx.x; k < a.W; k += kBlock)
+        for (int k = threadIdx.x; k < a.W; k += kBlock) {
             if (!groups_ok(a.groups[k], a.off[k + 1] - a.off[k])) atomicOr(&a.st->err, kErrGroupIndex);
+            if (a.groups[k] > a.min_nr) a.rs->overflowed = 1;
+        }
     }
     if (r >= a.W) return;
     const int64_t base = a.off[r], nr = a.off[r + 1] - base;
     if (tile * kRowTile >= nr) return;
     const int64_t q0 = tile * kRowTile + (int64_t)threadIdx.x * kRowItems;
+    if (a.groups[r] > a.min_nr) return;   // this rank overflows: the window goes round by round
     const int64_t G = groups_ok(a.groups[r], nr) ? a.groups[r] : 0;
     const int64_t p0 = base + q0;
     const int m = nr - q0 < kRowItems ? (int)(nr - q0) : kRowItems;   // live positions, <= 0 past the rank
@@ -1351,6 +1355,7 @@ constexpr int kTilesSummed = 16;
 
 // One block per rank: the tokens of the rank's tiles become the tokens before each tile.
 __global__ void __launch_bounds__(kBlock) rank_tiles_kernel(OneArgs a) {
+    if (a.rs->overflowed) return;
     const int r = blockIdx.x;
     const int64_t tiles = (a.off[r + 1] - a.off[r] + kRowTile - 1) / kRowTile;
     int64_t* t = a.tpre + (int64_t)r * a.per_rank;
@@ -1366,36 +1371,23 @@ __global__ void __launch_bounds__(kBlock) rank_tiles_kernel(OneArgs a) {
 }
 
 // The target over the active ranks, and whether a rank would overflow (Eq. 3's S+_min below
-// the largest group count).  One wave's worth of work; block-uniform.
+// the largest group count).  Block-uniform.
 struct OneTarget {
     int64_t T;
     bool overflow;
 };
 
 __device__ __forceinline__ OneTarget one_target(const OneArgs& a) {
-    int64_t mx = 0, small = 0;   // small: LLONG_MAX - the fewest samples of an active rank
-    for (int r = threadIdx.x; r < a.W; r += blockDim.x) {
-        const int64_t G = a.groups[r];
-        if (G <= 0) continue;
-        const int64_t s = LLONG_MAX - (a.off[r + 1] - a.off[r]);
-        mx = G > mx ? G : mx;
-        small = s > small ? s : small;
-    }
-    __shared__ int64_t s_mx[kBlock / kWave], s_small[kBlock / kWave];
+    int64_t mx = 0;
+    for (int r = threadIdx.x; r < a.W; r += blockDim.x) mx = a.groups[r] > mx ? a.groups[r] : mx;
+    __shared__ int64_t s_mx[kBlock / kWave];
     mx = wave_last(wave_scan_dpp<OpMax>(mx));
-    small = wave_last(wave_scan_dpp<OpMax>(small));
-    if ((threadIdx.x & (kWave - 1)) == 0) {
-        s_mx[threadIdx.x / kWave] = mx;
-        s_small[threadIdx.x / kWave] = small;
-    }
+    if ((threadIdx.x & (kWave - 1)) == 0) s_mx[threadIdx.x / kWave] = mx;
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kBlock / kWave; ++i) {
-        mx = s_mx[i] > mx ? s_mx[i] : mx;
-        small = s_small[i] > small ? s_small[i] : small;
-    }
+    for (int i = 0; i < kBlock / kWave; ++i) mx = s_mx[i] > mx ? s_mx[i] : mx;
     __syncthreads();
-    return OneTarget{mx > 1 ? mx : 1, mx > LLONG_MAX - small};
+    return OneTarget{mx > 1 ? mx : 1, mx > a.min_nr};
 }
 
 // Where a rank of G > 0 groups (starts gs[0 .. G)) aligned to T >= G is split: adjusted groups
@@ -2181,10 +2173,11 @@ extern "C" int odb_align_groups(const odb_window_t* w, int64_t budget, const odb
     const unsigned gridn = grid_for(n, kBlock, gcap);
 
     // ---- a window that aligns in one round
-    int64_t max_nr = 0, empty_ranks = 0, min_cap = LLONG_MAX;
+    int64_t max_nr = 0, min_nr = LLONG_MAX, empty_ranks = 0, min_cap = LLONG_MAX;
     for (int r = 0; r < W; ++r) {
         const int64_t nr = w->rank_offsets[r + 1] - w->rank_offsets[r];
         max_nr = std::max(max_nr, nr);
+        if (nr > 0) min_nr = std::min(min_nr, nr);
         empty_ranks += nr == 0;
         if (cap && cap[r] > 0) min_cap = std::min(min_cap, cap[r]);
     }
@@ -2215,6 +2208,7 @@ extern "C" int odb_align_groups(const odb_window_t* w, int64_t budget, const odb
         a.gpre = stok;
         a.tpre = reinterpret_cast<int64_t*>(sadj);
         a.per_rank = (int)per_rank;
+        a.min_nr = min_nr;
         a.lo = nonjoin ? d_gbase : const_cast<int64_t*>(d_off);
         a.steps = steps;
         a.part = ws_at<I64Pair>(d_ws, L.cs);
@@ -2253,11 +2247,11 @@ extern "C" int odb_align_groups(const odb_window_t* w, int64_t budget, const odb
         if (w->d_identity) ODB_TRY(count_identities(w, L, d_ws, d_order, n, nullptr, 0, s));
         HostState h;
         ODB_TRY(read_state(L, d_ws, 0, &h, s));
-        if (h.st.err & (kErrOrder | kErrGroupIndex))
-            return set_error(ODB_E_INVALID_DATA,
-                             "stage-1 arrays do not describe this window (first inconsistent position %lld)",
-                             (long long)h.st.first_bad);
         if (!h.rs.overflowed) {
+            if (h.st.err & (kErrOrder | kErrGroupIndex))
+                return set_error(ODB_E_INVALID_DATA,
+                                 "stage-1 arrays do not describe this window (first inconsistent position %lld)",
+                                 (long long)h.st.first_bad);
             if ((int64_t)W * h.rs.cut > slot_capacity) {
                 if (!nonjoin) {   // else the cut has counted them
                     hipLaunchKernelGGL(cut_steps_kernel, dim3(grid_for(max_nr, kWave, kMaxRanges)), dim3(kBlock), 0, s, a);
@@ -2269,8 +2263,8 @@ extern "C" int odb_align_groups(const odb_window_t* w, int64_t budget, const odb
             return finish_short(h, W, n, slot_capacity, nonjoin && h.rs.quota_hit ? ODB_STOP_QUOTA : ODB_STOP_DRAINED,
                                 h_info);
         }
-        // some rank overflows: start over, round by round
-        ODB_TRY(upload_small(w, L, d_ws, cap, s));
+        // some rank overflows: start over, round by round, which also checks the ranks left out here
+        if (h.st.err) ODB_TRY(upload_small(w, L, d_ws, cap, s));
     }
 
     hipLaunchKernelGGL(round0_ranks_kernel, dim3(1), dim3(kBlock), 0, s, d_off, d_groups_per_rank, W, d_ranks,

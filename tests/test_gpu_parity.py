@@ -667,6 +667,49 @@ def test_one_round_windows(idx):
     compare_collate_full(w, outs, ref, pad_id=idx)
 
 
+def overflow_windows():
+    """A rank of one sample per group beside one that holds as many samples, one fewer (the window
+    overflows and goes round by round) or one more; short ranks, and more than 16 tiles."""
+    rng = np.random.default_rng(94)
+    out = []
+    for n in (50, 17000):
+        for d in (0, -1, 1):
+            for mode, q in (("join", 0), ("nonjoin", n + n // 3)):
+                ident = np.concatenate([rng.permutation(2 * n + d - 2), [0, 1]]).astype(np.int64)
+                out.append(synth.window_from_ranks(f"groups_{n}{d:+d}_{mode}", [
+                    np.full(n, 100), rng.integers(1, 90, size=n + d)], 100, mode=mode, quota=q, identity=ident,
+                    num_identities=2 * n + d - 2))
+    return out
+
+
+@pytest.mark.parametrize("idx", range(len(overflow_windows())))
+def test_one_round_overflow_edge(idx):
+    check_full(overflow_windows()[idx])
+
+
+@pytest.mark.parametrize("mode", ["join", "nonjoin"])
+@pytest.mark.parametrize("where", ["overflowing_rank", "other_rank", "groups"])
+def test_overflow_reports_the_first_bad_position(where, mode):
+    """Stage-1 arrays that are inconsistent in two places, in a window that overflows: the first place
+    is named, whichever ranks the one-round attempt looked at."""
+    import torch
+    import paper_2606_19989_amd as odb
+
+    rng = np.random.default_rng(97)
+    w = win([rng.integers(500, 900, 3000), rng.integers(10, 20, 700)], 1000, mode=mode, quota=1500 if mode == "nonjoin" else 0)
+    pipe = _formed(w)
+    assert int(pipe.groups_per_rank[0]) > 700
+    first = {"overflowing_rank": 1200, "other_rank": 3100, "groups": 2000}[where]
+    a = pipe.group_index if where == "groups" else pipe.order
+    for p in (first, 3500):
+        a[p] = -5 if where == "groups" else 0 if p >= 3000 else w.n - 1   # a group or an id of no rank of its own
+    log(f"bad stage-1 arrays in an overflowing window: {where}, {mode}")
+    with pytest.raises(odb.OdbError) as e:
+        pipe.align()
+    assert e.value.status == odb.ODB_E_INVALID_DATA
+    assert f"first inconsistent position {first})" in str(e.value), str(e.value)
+
+
 def short_round_windows():
     """Join windows of short ranks that take several rounds: rank sizes at the edges of the
     kernels (1, 1,023 .. 1,025, 16,383 and 16,384 positions; 16,385 takes the general path),
