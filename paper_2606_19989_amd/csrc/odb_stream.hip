@@ -957,6 +957,7 @@ __global__ void __launch_bounds__(kST) stream_book_kernel(StreamArgs a, int64_t 
 // records at their place in the rank's stream (position e * n_r + n - 1 - p), which in join
 // mode is their final place.
 constexpr int64_t kBulkBlocks = int64_t(1) << 22;   // rank-rounds of one launch (2^32 threads at most)
+constexpr int64_t kBulkAtOnce = 8;                  // blocks of 256 threads a compute unit holds
 
 struct BulkState {
     int64_t steps;        // S: aligned steps, after a quota cut
@@ -972,7 +973,7 @@ struct BulkState {
     unsigned long long missing_ids;     // summed modulo 2^64
     unsigned long long duplicate_ids;
     int32_t err;
-    int32_t pad;
+    int32_t over;         // a round known to overflow while the rounds are formed (INT32_MAX: none)
 };
 
 struct BulkArgs {
@@ -980,6 +981,9 @@ struct BulkArgs {
     int64_t N, q, D, budget, scap;
     int64_t E;                  // emitting rounds
     int64_t n_all, rate_all;    // every rank's n_r and rate, or read from `sched`
+    // the smallest n_r (such a rank holds views in every emitting round) where rounds after one that
+    // overflows are left out, else INT64_MAX
+    int64_t n_slow;
     const int64_t* sched;       // [W] rate << 32 | n_r where ranks differ, or null
     int64_t bufsize;
     int stop_round;             // join 0; 1: the round after the last emitting one fetches, too
@@ -1038,6 +1042,7 @@ __global__ void bulk_init_kernel(BulkArgs b, DevStatus* st) {
     const int t = threadIdx.x;
     if (t == 0) {
         *b.st = BulkState{};
+        b.st->over = INT32_MAX;
         st->err = 0;
         st->first_bad = 0x7FFFFFFFFFFFFFFFll;
         st->first_bad_len = 0x7FFFFFFFFFFFFFFFll;
@@ -1059,6 +1064,11 @@ __global__ void bulk_init_kernel(BulkArgs b, DevStatus* st) {
 // in LDS, so an item's rank among equal digits is the wave's count so far plus the lower
 // lanes holding the digit, and one scan over (digit, wave) gives every wave's first slot.
 // LDS: counts, sorted lengths and their indices in the buffer, token starts and identities.
+//
+// Where the ranks' rates differ, a rank may form more groups than the slowest rank holds views. Nothing
+// after such a round is wanted, so the first blocks that meet one say so and the blocks of later rounds,
+// most of which have not started by then, end at once (64 x 65,536 views that overflow in their first
+// round: 172 us for all rounds, 70 us now).
 typedef int64_t Offsets __attribute__((ext_vector_type(2), aligned(8)));   // a sample's two CSR offsets in one load
 
 template <int NT, int KPT>
@@ -1072,7 +1082,7 @@ __global__ void __launch_bounds__(NT) bulk_form_kernel(BulkArgs b) {
     __shared__ int32_t s_id[P];
     __shared__ uint16_t s_idx[P], s_nxt[P], s_gs[P];
     __shared__ uint32_t s_seen[P / 32];
-    __shared__ int32_t s_G, s_err, s_rep;
+    __shared__ int32_t s_G, s_err, s_rep, s_over;
     int64_t e;
     int r;
     if (!bulk_block(b, b.E + b.stop_round, &e, &r)) return;
@@ -1100,9 +1110,9 @@ __global__ void __launch_bounds__(NT) bulk_form_kernel(BulkArgs b) {
     if (tid == 0) {
         s_err = 0;
         s_rep = 0;
+        s_over = b.n_slow < INT64_MAX ? __hip_atomic_load(&b.st->over, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : INT32_MAX;
     }
     for (int i = tid; i < P / 32; i += NT) s_seen[i] = 0;
-    __syncthreads();
     // positions of wave w: [w * KPT * 64, (w + 1) * KPT * 64), item c at + c * 64 + lane
     const int p0 = w * KPT * kWave + (tid & (kWave - 1));
     uint32_t len[KPT];
@@ -1116,6 +1126,8 @@ __global__ void __launch_bounds__(NT) bulk_form_kernel(BulkArgs b) {
             const int64_t m = (c0 + (i < n ? i : n - 1)) * b.W + r;
             id[c] = b.perm[m < b.N ? m : m % b.N];
         }
+        __syncthreads();
+        if (e > s_over) return;   // uniform
         int64_t t0[KPT], t1[KPT];
 #pragma unroll
         for (int c = 0; c < KPT; ++c) {
@@ -1246,6 +1258,8 @@ __global__ void __launch_bounds__(NT) bulk_form_kernel(BulkArgs b) {
         b.G[(int64_t)r * b.E + e] = g;
         atomicMax(&b.T[e], g);
         atomicAdd(&b.sum[e], (uint32_t)g);
+        // the slowest rank holds at most n_slow views, and T is no more
+        if (g > b.n_slow) atomicMin(&b.st->over, (int32_t)e);
         if (s_rep) atomicAdd(&b.st->bad_views, 1ull);
     }
     __syncthreads();
@@ -2241,6 +2255,10 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
         b.scap = scap;
         b.E = bs.E;
         b.n_all = bs.n0[0];
+        // equal buffers never overflow, and up to kBulkAtOnce blocks per compute unit have all started by the
+        // time one knows
+        b.n_slow = bs.uniform || W * bs.E <= kBulkAtOnce * num_cus()
+                       ? INT64_MAX : *std::min_element(bs.n0.begin(), bs.n0.end());
         b.rate_all = params->rate[0];
         b.bufsize = a.bufsize;
         b.stop_round = bs.stop_round;

@@ -416,6 +416,56 @@ def test_stream_rounds_together(idx):
              tokens=None if small else _one_token(), **kw)
 
 
+def early_overflow_cases():
+    """Iterations formed together in which a round overflows early and hundreds of rounds, most of whose
+    blocks then end at once, come after it: the first round, one a few rounds later (short samples at
+    first, so that the fast rank forms few groups), 64 rounds and more or fewer, join and quota."""
+    rng = np.random.default_rng(86)
+    out = []
+    for N, depth in ((3 * 14001, 300), (3 * 700, 300), (64 * 3000, 1024)):
+        W = 64 if N > 10 ** 5 else 3
+        rate = [depth] + [20] * (W - 1)
+        for mode, quota in (("join", 0), ("nonjoin", N // 3)):
+            out.append((f"first_{N}_{mode}", rng.integers(300, 900, N), W, 3000, rate, depth, dict(mode=mode, quota=quota)))
+    lens = rng.integers(300, 900, 3 * 14001)
+    lens[:3 * 1000] = rng.integers(1, 9, 3 * 1000)
+    out.append(("later", lens, 3, 3000, [300, 20, 20], 300, dict(identity=True)))
+    return out
+
+
+@pytest.mark.parametrize("idx", range(len(early_overflow_cases())))
+def test_stream_early_overflow(idx):
+    name, lens, W, budget, rate, depth, kw = early_overflow_cases()[idx]
+    perm = np.arange(len(lens), dtype=np.int32)
+    if not kw.pop("identity", False):
+        np.random.default_rng(87 + idx).shuffle(perm)
+    _, ref = run_case(name, lens, perm, W, budget, 20, depth, np.asarray(rate, dtype=np.int32), tokens=_one_token(),
+                      full_collate=False, **kw)
+    assert ref.sinfo["overflow_groups"] > 0
+
+
+@pytest.mark.parametrize("bad", ["perm", "length"])
+def test_stream_early_overflow_meets_bad_data(bad):
+    """Bad data in a late round of such an iteration is still met."""
+    import torch
+    import paper_2606_19989_amd as odb
+
+    rng = np.random.default_rng(88)
+    N = 3 * 14001
+    lens = rng.integers(300, 900, N)
+    perm = rng.permutation(N).astype(np.int32)
+    sp = _stream_pipeline(lens, perm, 3, 3000, 20, 300, [300, 20, 20])
+    sp.plan()
+    if bad == "perm":
+        sp.perm[N - 7] = N
+    else:
+        sp.win.token_offsets[int(perm[N - 7]) + 1] = int(sp.win.token_offsets[int(perm[N - 7])])
+    for _ in range(2):
+        with pytest.raises(odb.OdbError) as e:
+            sp.plan()
+        assert e.value.status == odb.ODB_E_INVALID_DATA
+
+
 def capacity_cases():
     """Iterations drained and cut at a quota, formed together, with a round that overflows after some of
     them, and round by round from the start."""
