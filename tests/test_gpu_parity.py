@@ -856,6 +856,20 @@ def test_sort_word_widths(per_rank, span):
     compare_plan(w, pipe, ref)
 
 
+@pytest.mark.parametrize("longest,budget", [(3000, 20000), (3, 1 << 18), (40000, 1 << 17)])
+@pytest.mark.parametrize("per_rank", [1 << 19, (1 << 19) + 1])
+def test_chain_remainder_widths(per_rank, longest, budget):
+    """The largest rank whose group chain is carried in fp32 and one sample more (integers), with
+    hundreds of runs, with steps of up to half the rank, and with few samples a group."""
+    import torch
+    rng = np.random.default_rng(98)
+    w = synth.window_from_ranks("chain_widths", [rng.integers(1, longest + 1, per_rank), rng.integers(1, longest + 1, 90)],
+                                budget)
+    ref = oracle.plan_window(w)
+    pipe, _ = run_gpu(w, tokens=torch.zeros(1, dtype=torch.int32, device="cuda"), collate=False)
+    compare_plan(w, pipe, ref)
+
+
 @pytest.mark.parametrize("per_rank", [(1 << 22) // 3 + 1, (1 << 22) // 3])
 def test_sort_tile_lengths(per_rank):
     """Windows just at and just below 4 Mi samples: the longer and the shorter radix tile, ragged
