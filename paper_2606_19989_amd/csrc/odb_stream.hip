@@ -1268,7 +1268,7 @@ __global__ void __launch_bounds__(NT) bulk_form_kernel(BulkArgs b) {
 }
 
 // 512 threads: the cut takes 73 registers, and a block has to fit beside the three collate waves of
-// 88 on every SIMD (1,024 threads waited for the whole collate of the step before).
+// 84 (88 allocated) on every SIMD (1,024 threads waited for the whole collate of the step before).
 constexpr int kTargetThreads = 512;
 
 // Where a split leaves its pieces: positions [0, X) are singletons, [X, end of group j*) is one
@@ -1484,17 +1484,12 @@ __global__ void __launch_bounds__(NT) bulk_slots_kernel(BulkArgs b, BulkSlots o)
     constexpr int P = NT * KPT;
     __shared__ int64_t s_tok[P + 1];   // tokens of the first i rows of the emission order
     __shared__ int32_t s_gs[P];
-    __shared__ int s_go;
     int64_t e;
     int r;
     if (!bulk_block(b, b.E, &e, &r)) return;
     const int tid = threadIdx.x;
     const int64_t S = b.st->steps;
-    // the error word may change while this launch runs: one thread decides for the block
-    if (tid == 0)
-        s_go = b.st->err == 0 && e < b.st->fail && !(o.fin && (b.st->fail < b.E || S > b.scap));
-    __syncthreads();
-    if (!s_go) return;
+    if (b.st->err || e >= b.st->fail || (o.fin && (b.st->fail < b.E || S > b.scap))) return;
     int64_t c0, n64;
     bulk_range(b, r, e, &c0, &n64);
     const int n = (int)n64;
@@ -2338,7 +2333,6 @@ extern "C" int odb_stream_plan(const odb_window_t* w, const int32_t* d_perm, int
         std::vector<char> back(bytes);
         ODB_TRY(read_device(back.data(), b.st, bytes, s));
         memcpy(&hb, back.data(), sizeof(hb));
-        if (hb.err & kSErrInternal) return set_error(ODB_E_INTERNAL, "streaming round state inconsistent");
         // bad data: the sequential rounds report what the iteration meets
         const int64_t fail = hb.err ? 0 : hb.fail;
         if (h_trace && fail > 0) {
