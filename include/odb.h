@@ -199,10 +199,16 @@ typedef struct odb_plan_info {
  *
  * Synchronises `stream` once, with one device-to-host copy, for windows that align in one
  * round (no rank buffers fewer samples than the largest group count, no slot capacity below
- * a rank's samples, as in all of the benchmark windows).  Join windows of ranks of at most
- * 16,384 samples that take more rounds synchronise once per chunk of 4, 8, 16, ... rounds;
- * others once per round and once at the end.  Returns
- * ODB_E_CAPACITY (with h_info->required_slot_capacity) if slot_capacity < W * S,
+ * a rank's samples, as in all of the benchmark windows).  Left out are windows of very
+ * unequal ranks (W times the largest rank more than about 32 (n + 1024 W), as one rank of
+ * 1,000,000 samples beside 63 of 10, or W more than n) and, with a sample quota, windows
+ * with an empty rank.  Join windows of ranks of at most 16,384 samples that take more
+ * rounds synchronise once per chunk of 4, 8, 16, ... rounds; others, and those left out above,
+ * once per round and once at the end.  A window without a binding slot capacity is first
+ * tried as one round, so it synchronises once more if a rank overflows; and a plan that does
+ * not fit the slot arrays once more for its largest step.  Returns
+ * ODB_E_CAPACITY (with steps, rounds, stop_reason, max_step_samples, splits, overflow_groups,
+ * second_gather_rounds and required_slot_capacity in h_info) if slot_capacity < W * S,
  * ODB_E_INVALID_DATA if a sample's CSR length lies outside [1, 2^31) or its token offset
  * is negative (the message names the first such sample), or if the stage-1 arrays are
  * inconsistent (an order that is not each
@@ -460,8 +466,8 @@ size_t odb_stream_workspace_size(const odb_window_t* w, int32_t depth, int64_t s
  *   d_left_off       [W+1] out
  *   h_trace          [max_rounds] host out, or NULL: one record per round
  * Rounds up to the first one that overflows (G_r > T for some rank) are run together; the
- * call synchronises `stream` once for them.  From a round that
- * overflows on, and from the start when a positive slot_capacity is smaller than a rank's
+ * call synchronises `stream` once for them (and once more, for the largest step, if their steps
+ * do not fit the slot arrays).  From a round that overflows on, and from the start when a positive slot_capacity is smaller than a rank's
  * largest buffer, rounds are enqueued in chunks, each as long as a lower bound on the rounds
  * left (from the sampler cursors, the rates and, non-join, the quota; at least 8 after the
  * first), with one synchronisation per chunk and at the end.  Returns ODB_E_CAPACITY if

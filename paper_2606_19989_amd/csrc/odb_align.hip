@@ -1755,8 +1755,8 @@ struct ShortArgs {
     int64_t* sroff;      // first row of the slot among the rank's
 };
 
-// 512 threads: 53 registers and two waves per SIMD, which fit beside the three collate waves of 88
-// there (1,024 threads took 101 registers, so that a round waited for the collate of the step
+// 512 threads: 53 registers and two waves per SIMD, which fit beside the three collate waves of 84
+// (88 allocated) there (1,024 threads took 101 registers, so that a round waited for the collate of the step
 // before).
 constexpr int kShortThreads = 512;
 

@@ -488,7 +488,7 @@ __global__ void __launch_bounds__(kBlock) jump_kernel(const int32_t* __restrict_
 // position is the number of group starts at or before it, minus one: g_k group starts before
 // run k (position 0 not counted), plus (q - c_k) / b_k + 1 once q >= c_k.
 //
-// One block of kChainThreads per rank:
+// One block per rank (of kChainThreads in rank_form_kernel, of kChainBlock in chain_kernel):
 //   runs    the distinct steps are known without looking at the samples: the values
 //           b = B(longest) .. sqrt(budget), and for each length l below budget / sqrt(budget)
 //           the step budget / l, at most 2 sqrt(budget) + 2 or the length range; a run starts
@@ -510,7 +510,7 @@ constexpr int kChainThreads = 1024;
 constexpr int kChainWaves = kChainThreads / kWave;
 constexpr int kRunCap = 4096;   // runs per rank
 // chain_kernel's threads.  A plan runs beside the previous step's collate, which keeps three waves
-// of 84 vector registers on every SIMD: two more waves of a block of 512 fit there, four of a block
+// of 84 vector registers (88 allocated) on every SIMD: two more waves of a block of 512 fit there, four of a block
 // of 1,024 did not at 68, 50 or 48 registers a thread, and the plan waited until the
 // collate ended (64 x 262,144: 16 ms a chain in the two-stream schedule).
 constexpr int kChainBlock = 512;

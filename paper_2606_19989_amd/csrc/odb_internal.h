@@ -479,22 +479,22 @@ int device_excl_scan(Load load, Store store, int64_t n, Out* partials, hipStream
 // len_range = max_len - min_len + 1 of the sequences if known (0 otherwise); it only
 // selects between the two equivalent ways of finding the chain (see odb_form.hip).
 // tiles_ready: workspace tile_first already holds the sort tiles of d_rank_off.
-// One alignment round's grouping of short ranks (at most kRankBlockMax samples, and steps
-// that chain_fits): rank r's buffer of d_ranks[r].next_cnt lengths at its own positions; sets
-// cnt, G and every live position's group index.  One launch, one block per rank.
-// Samples of the largest rank grouped this way.  A block's pass over its rank is bound by
-// the issue rate of its one compute unit (every round of 1024 items costs each of its 16
-// waves a few hundred instructions: ~2.7 us per round on MI355X), so larger ranks go to the
-// multi-block path, whose launches and one synchronisation cost less than a block's
-// rounds from about this size on.
-constexpr int64_t kRankBlockMax = 16384;
-bool chain_fits(int64_t budget, int64_t max_cnt);
-int group_short_ranks(int W, int64_t budget, int64_t max_cnt, const int64_t* d_rank_off, const int32_t* d_slen,
-                      int32_t* d_gidx, RankState* d_ranks, DevStatus* st, hipStream_t s);
-
 int group_sequences(const Layout& L, void* ws, int W, int64_t n, int64_t budget,
                     const int64_t* d_rank_off, int64_t max_cnt, int64_t len_range, bool tiles_ready,
                     const int32_t* d_slen, int32_t* d_gidx, int32_t* d_groups_out,
                     RankState* d_ranks, hipStream_t s);
+
+// Samples of the largest rank that one block groups or aligns: what its LDS holds of lengths and
+// 16-bit positions beside the chain's tables (135 KB), and about where the multi-block path's
+// launches and its wait come to cost no more than the one compute unit's passes (grouping of 8
+// ranks of 16,384 samples: 86 us in one block each, of 16,385 samples 95 us).
+constexpr int64_t kRankBlockMax = 16384;
+
+// One alignment round's grouping of short ranks (at most kRankBlockMax samples, and steps
+// that chain_fits): rank r's buffer of d_ranks[r].next_cnt lengths at its own positions; sets
+// cnt, G and every live position's group index.  One launch, one block per rank.
+bool chain_fits(int64_t budget, int64_t max_cnt);
+int group_short_ranks(int W, int64_t budget, int64_t max_cnt, const int64_t* d_rank_off, const int32_t* d_slen,
+                      int32_t* d_gidx, RankState* d_ranks, DevStatus* st, hipStream_t s);
 
 }  // namespace odb

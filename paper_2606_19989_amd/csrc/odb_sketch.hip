@@ -13,7 +13,7 @@
 // sample, plus 4 B per id when ids are given; one block-level reduction and seven 64-bit
 // atomics per block.  A sketch of at most kSketchOne samples is latency bound: one block of 1,024
 // threads stores its sums without atomics or a launch that clears them first (5,000 ids: 31 us
-// per call with two launches and a read into pageable memory, 24 us now).
+// per call with two launches and a read into pageable memory, 20 us now).
 #include <cmath>
 
 #include "odb_internal.h"
@@ -50,7 +50,9 @@ constexpr int64_t kSketchOne = 16 * kSketchThreads;
 // iteration, its loads in flight together) up to one block per compute unit, then more.  us per
 // call against eight blocks of 256 threads per compute unit: 50,000 samples 35.4 / 25.6, 200,000
 // ids 84.7 / 32.4 (one sample a thread 39.8), 1,000,000 189 / 43, 2^24 206 / 72 (ids 423 / 350).
-// Up to kSketchFew samples the small blocks are still the faster ones (16,385: 24.4 / 25.6).
+// Up to kSketchFew samples the small blocks are no slower (16,385: 24.4 / 25.6, about what boxes differ
+// by).  The large blocks' kernel keeps its four samples' loads and the block sums in 128 registers and
+// spills 68 of them around the block sums (276 bytes of scratch a thread); the times above include that.
 constexpr int kSketchItems = 4;
 constexpr int64_t kSketchFew = 20 * kSketchThreads;
 
