@@ -1317,10 +1317,19 @@ __device__ __forceinline__ void bulk_group(const int32_t* gs, int G, int n, Bulk
     *a1 = g + 1 < G ? gs[g + 1] : n;
 }
 
-// The splits of all ranks' buffers of round e towards its target T, a wave per rank (s_sp: LDS), by a
-// whole block of NT threads that synchronises before it reads them.
+// The splits of all ranks' buffers of round e towards its target T (s_sp: LDS), by a whole block of NT
+// threads that synchronises before it reads them.  A wave per rank takes two to three trips to memory,
+// a thread per rank about ten but NT ranks at once: from five ranks a wave on the threads are ahead.
 template <int NT>
 __device__ __forceinline__ void bulk_round_splits(const BulkArgs& b, BulkSplit* s_sp, int64_t e, int T) {
+    if (b.W > 4 * (NT / kWave)) {
+        for (int r = threadIdx.x; r < b.W; r += NT) {
+            int64_t c, n;
+            bulk_range(b, r, e, &c, &n);
+            s_sp[r] = n > 0 ? bulk_split(b.gs + (int64_t)r * b.q + c, b.G[(int64_t)r * b.E + e], T) : BulkSplit{0, -1};
+        }
+        return;
+    }
     for (int r = threadIdx.x / kWave; r < b.W; r += NT / kWave) {
         int64_t c, n;
         bulk_range(b, r, e, &c, &n);
@@ -1345,28 +1354,67 @@ __device__ __forceinline__ int64_t bulk_step_rows(const BulkArgs& b, const BulkS
     return v;
 }
 
+// Views that rank r of a round with target T keeps back if the round's first `cut` steps are emitted:
+// the start of adjusted group T - cut.
+__device__ __forceinline__ int bulk_kept_back(const int32_t* gs, BulkSplit sp, int T, int cut) {
+    const int t = T - cut;
+    if (t <= sp.X) return t;
+    return gs[sp.X >= 0 ? sp.js + (t - sp.X) : t];
+}
+
+// Ranks a thread looks at in one pass of the search for the cut.
+constexpr int kCutRanks = 8;
+
 // Non-join: the steps of the last round up to the one that reaches the quota, and from them
 // every rank's emitted rows (lo: their running sum over the ranks) and left-over views.
 // T, base: target of the last round and the steps before it; s_sp: LDS, a BulkSplit per rank.
 // Called by a whole block of kTargetThreads.
+//
+// The rows of the first c steps are the sum over the ranks of what each does not keep back, one load
+// a rank, so the cut is searched: a pass tries `tries` of the steps between the bounds at once, each
+// with the ranks spread over the remaining threads, as many as leave a thread about kCutRanks ranks
+// (every step of a round at once for 8 ranks, 8 of them for 512 and more).  Every step's rows summed
+// over all ranks by one thread each, and a wave per rank for the splits, took the plan of 64 x 4,096
+// views from 71 to 90 us, of 1,024 x 1,024 from 157 to 609 (464 round by round) and of 8,192 x 512 from
+// 0.78 to 4.2 ms (1.33); 8 ranks measure the same either way.
 __device__ void bulk_cut(const BulkArgs& b, BulkSplit* s_sp, int T, int64_t base, int64_t before,
                          int64_t* __restrict__ left_off) {
     const int64_t e = b.E - 1;
+    const int tid = threadIdx.x;
     bulk_round_splits<kTargetThreads>(b, s_sp, e, T);
-    __shared__ int s_cut;
-    if (threadIdx.x == 0) s_cut = T;
+    __shared__ int64_t s_rows[kTargetThreads];
+    int tries = kTargetThreads;
+    while (tries > 8 && (int64_t)tries * b.W > (int64_t)kTargetThreads * kCutRanks) tries >>= 1;
+    const int parts = kTargetThreads / tries;
+    // emitted(lo) < quota <= emitted(hi): the schedule ends with the round that reaches the quota
+    int lo = 0, hi = T;
+    if (b.quota == INT64_MAX) lo = T - 1;
     __syncthreads();
-    int64_t carry = before;
-    for (int j0 = 0; j0 < T && carry < b.quota; j0 += kTargetThreads) {   // uniform
-        const int j = j0 + threadIdx.x;
-        const int64_t v = j < T ? bulk_step_rows(b, s_sp, e, T, j) : 0;
-        int64_t tot;
-        const int64_t ex = carry + sblock_excl<kTargetThreads>(v, &tot);
-        if (j < T && ex < b.quota && ex + v >= b.quota) s_cut = j + 1;
-        carry += tot;
+    while (hi - lo > 1) {   // uniform
+        const int w = (hi - lo + tries) / (tries + 1);   // steps between two tries
+        const int c = lo + (tid % tries + 1) * w;
+        int64_t rows = 0;
+        if (c < hi) {
+#pragma unroll 4
+            for (int r = tid / tries; r < b.W; r += parts) {
+                int64_t at, n;
+                bulk_range(b, r, e, &at, &n);
+                if (n > 0) rows += n - bulk_kept_back(b.gs + (int64_t)r * b.q + at, s_sp[r], T, c);
+            }
+        }
+        s_rows[tid] = rows;
+        __syncthreads();
+        bool low = false;
+        if (tid < tries && c < hi) {
+            for (int i = 1; i < parts; ++i) rows += s_rows[i * tries + tid];
+            low = before + rows < b.quota;
+        }
+        const int k = __syncthreads_count(low);   // the tries below the quota are the first k
+        const int end = lo + (k + 1) * w;
+        lo += k * w;
+        hi = end < hi ? end : hi;
     }
-    __syncthreads();
-    const int cut = s_cut;
+    const int cut = hi;
     int64_t rows = 0, left = 0;
     for (int r0 = 0; r0 < b.W; r0 += kTargetThreads) {
         const int r = r0 + threadIdx.x;
@@ -1374,10 +1422,8 @@ __device__ void bulk_cut(const BulkArgs& b, BulkSplit* s_sp, int T, int64_t base
         if (r < b.W) {
             int64_t c, n;
             bulk_range(b, r, e, &c, &n);
-            int a0 = 0, a1;
-            if (n > 0 && cut < T)
-                bulk_group(b.gs + (int64_t)r * b.q + c, b.G[(int64_t)r * b.E + e], (int)n, s_sp[r], T - cut, &a0, &a1);
-            out = c + n - a0;
+            const int back = n > 0 && cut < T ? bulk_kept_back(b.gs + (int64_t)r * b.q + c, s_sp[r], T, cut) : 0;
+            out = c + n - back;
             stay = b.q - out;
         }
         int64_t to, ts;
@@ -1406,25 +1452,41 @@ __global__ void __launch_bounds__(kTargetThreads) bulk_targets_kernel(BulkArgs b
     extern __shared__ unsigned long long s_dyn[];
     __shared__ int64_t s_T, s_base;   // of the last round
     __shared__ int32_t s_fail;
+    __shared__ int32_t s_held[kTargetThreads], s_ready[kTargetThreads];
+    // rounds looked at together; where they are fewer than the threads, each has several that share
+    // the ranks (2,048 x 512 views in eight rounds, the plan with one thread a round: 704 us, 480 now)
+    int rounds = kTargetThreads;
+    while (rounds > 1 && rounds / 2 >= b.E) rounds >>= 1;
     int64_t steps = 0, splits = 0, changed = 0;
     for (int64_t e0 = 0; e0 < b.E; e0 += kTargetThreads) {
         if (threadIdx.x == 0) s_fail = kTargetThreads;
+        s_held[threadIdx.x] = INT_MAX;
+        s_ready[threadIdx.x] = 0;
         __syncthreads();
+        if (b.sched) {
+            const int k = threadIdx.x & (rounds - 1);
+            if (e0 + k < b.E) {
+                int held = INT_MAX, ready = 0;   // fewest views held by a rank that is not finished
+                for (int r = threadIdx.x / rounds; r < b.W; r += kTargetThreads / rounds) {
+                    int64_t c, n;
+                    bulk_range(b, r, e0 + k, &c, &n);
+                    ready += n > 0;
+                    held = n > 0 && n < held ? (int)n : held;
+                }
+                atomicMin(&s_held[k], held);
+                atomicAdd(&s_ready[k], ready);
+            }
+            __syncthreads();
+        }
         const int64_t e = e0 + threadIdx.x;
         int64_t T = 0, more = 0;   // target, and the splits it takes
         if (e < b.E) {
             const int64_t mx = b.T[e];
-            int64_t c, held, ready = b.W;   // fewest views held by a rank that is not finished
+            int64_t c, held, ready = b.W;
             bulk_range(b, 0, e, &c, &held);
             if (b.sched) {
-                held = LLONG_MAX;
-                ready = 0;
-                for (int r = 0; r < b.W; ++r) {
-                    int64_t n;
-                    bulk_range(b, r, e, &c, &n);
-                    ready += n > 0;
-                    held = n > 0 && n < held ? n : held;
-                }
+                held = s_held[threadIdx.x];
+                ready = s_ready[threadIdx.x];
             }
             T = mx > 1 ? mx : 1;
             more = T * ready - (int64_t)b.sum[e];

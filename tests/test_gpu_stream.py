@@ -416,6 +416,47 @@ def test_stream_rounds_together(idx):
              tokens=None if small else _one_token(), **kw)
 
 
+def cut_cases():
+    """The quota cut of rounds formed together: ranks at the edges of the split search (a wave or a
+    thread per rank, 32 and 33) and of the tries of the cut's search (512 for 8 ranks down to 8 for 512 and
+    more), a few to over a thousand steps in the last round, quotas reached by its first step, its last and in
+    between, even and uneven rates."""
+    rng = np.random.default_rng(87)
+    out = []
+    for W, n, top in ((1, 1500, 900), (3, 2000, 9000), (8, 2000, 9000), (9, 700, 900), (32, 300, 900), (33, 300, 900), (64, 200, 9000),
+                      (511, 60, 900), (513, 40, 9000), (1100, 24, 900)):
+        lens = rng.integers(1, top, 2 * n * W)
+        for rate in ([n], [n, n + n // 4]):
+            first = sum(min(2 * n, rate[r % len(rate)]) for r in range(W))   # views of the first round
+            for quota in (1, W + 1, first // 2, first - 1, first, first + 1, int(1.5 * first)):
+                out.append((f"{W}x{n}_{len(rate)}_{quota}", lens, W, 4000, n, 2 * n, [rate[r % len(rate)] for r in range(W)],
+                            quota))
+    return out
+
+
+@pytest.mark.parametrize("W", sorted({c[2] for c in cut_cases()}))
+def test_stream_quota_cut_of_rounds_together(W):
+    for name, lens, ranks, budget, buf, depth, rate, quota in cut_cases():
+        if ranks != W:
+            continue
+        perm = np.random.default_rng(W).permutation(len(lens)).astype(np.int32)
+        run_case(f"cut_{name}", lens, perm, W, budget, buf, depth, np.asarray(rate, dtype=np.int32), mode="nonjoin",
+                 quota=quota, full_collate=False, tokens=_one_token())
+
+
+@pytest.mark.parametrize("rounds", [1, 2, 3, 255, 256, 257, 511, 512, 513, 1025])
+def test_stream_uneven_rounds_together(rounds):
+    # rounds share the block's threads by powers of two, up to 512 rounds a pass; the fast ranks finish early
+    W = 5
+    lens = np.random.default_rng(88).integers(1, 40, W * rounds * 16)
+    perm = np.random.default_rng(rounds).permutation(len(lens)).astype(np.int32)
+    rate = np.asarray([16, 18, 17, 20, 16], dtype=np.int32)
+    for mode, quota in (("join", 0), ("nonjoin", len(lens))):
+        _, ref = run_case(f"uneven_{rounds}_{mode}", lens, perm, W, 200, 16, 20, rate, mode=mode, quota=quota,
+                          full_collate=False, tokens=_one_token())
+    assert mode == "join" or ref.sinfo["emit_rounds"] <= rounds
+
+
 def early_overflow_cases():
     """Iterations formed together in which a round overflows early and hundreds of rounds, most of whose
     blocks then end at once, come after it: the first round, one a few rounds later (short samples at
