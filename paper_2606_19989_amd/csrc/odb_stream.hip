@@ -981,9 +981,6 @@ struct BulkArgs {
     int64_t N, q, D, budget, scap;
     int64_t E;                  // emitting rounds
     int64_t n_all, rate_all;    // every rank's n_r and rate, or read from `sched`
-    // the smallest n_r (such a rank holds views in every emitting round) where rounds after one that
-    // overflows are left out, else INT64_MAX
-    int64_t n_slow;
     const int64_t* sched;       // [W] rate << 32 | n_r where ranks differ, or null
     int64_t bufsize;
     int stop_round;             // join 0; 1: the round after the last emitting one fetches, too
@@ -1005,6 +1002,10 @@ struct BulkArgs {
     int32_t* ids;
     int64_t* ts;
     int32_t* len;
+    // the smallest n_r (such a rank holds views in every emitting round) where rounds after one that
+    // overflows are left out, else INT64_MAX; last, because between the fields that the form loads first
+    // it cost each of its blocks a trip more (11.6 -> 12.0 us at 8 x 27,985 views, 16.2 -> 17.0 at 8 x 7,500)
+    int64_t n_slow;
 };
 
 __device__ __forceinline__ int64_t bulk_n(const BulkArgs& b, int r) {
@@ -1107,12 +1108,14 @@ __global__ void __launch_bounds__(NT) bulk_form_kernel(BulkArgs b) {
         if (tid == 0 && !check_only) b.G[(int64_t)r * b.E + e] = 0;
         return;
     }
+    const bool look = b.n_slow < INT64_MAX;   // uniform
     if (tid == 0) {
         s_err = 0;
         s_rep = 0;
-        s_over = b.n_slow < INT64_MAX ? __hip_atomic_load(&b.st->over, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : INT32_MAX;
+        if (look) s_over = __hip_atomic_load(&b.st->over, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     for (int i = tid; i < P / 32; i += NT) s_seen[i] = 0;
+    if (!look) __syncthreads();
     // positions of wave w: [w * KPT * 64, (w + 1) * KPT * 64), item c at + c * 64 + lane
     const int p0 = w * KPT * kWave + (tid & (kWave - 1));
     uint32_t len[KPT];
@@ -1126,8 +1129,10 @@ __global__ void __launch_bounds__(NT) bulk_form_kernel(BulkArgs b) {
             const int64_t m = (c0 + (i < n ? i : n - 1)) * b.W + r;
             id[c] = b.perm[m < b.N ? m : m % b.N];
         }
-        __syncthreads();
-        if (e > s_over) return;   // uniform
+        if (look) {
+            __syncthreads();
+            if (e > s_over) return;   // uniform
+        }
         int64_t t0[KPT], t1[KPT];
 #pragma unroll
         for (int c = 0; c < KPT; ++c) {
@@ -1259,7 +1264,7 @@ __global__ void __launch_bounds__(NT) bulk_form_kernel(BulkArgs b) {
         atomicMax(&b.T[e], g);
         atomicAdd(&b.sum[e], (uint32_t)g);
         // the slowest rank holds at most n_slow views, and T is no more
-        if (g > b.n_slow) atomicMin(&b.st->over, (int32_t)e);
+        if (look && g > b.n_slow) atomicMin(&b.st->over, (int32_t)e);
         if (s_rep) atomicAdd(&b.st->bad_views, 1ull);
     }
     __syncthreads();
@@ -1550,18 +1555,21 @@ __global__ void __launch_bounds__(NT) bulk_slots_kernel(BulkArgs b, BulkSlots o)
     int r;
     if (!bulk_block(b, b.E, &e, &r)) return;
     const int tid = threadIdx.x;
-    const int64_t S = b.st->steps;
-    if (b.st->err || e >= b.st->fail || (o.fin && (b.st->fail < b.E || S > b.scap))) return;
+    // all of them in one trip, ahead of the first branch (the last three may hold nothing of use)
+    const int64_t S = b.st->steps, fail = b.st->fail, cut = b.st->cut;
+    const int32_t err = b.st->err;
+    const int T = b.T[e], G = b.G[(int64_t)r * b.E + e];
+    const int64_t base = b.base[e];
+    asm volatile("" ::"v"(S), "v"(fail), "v"(cut), "v"(err), "v"(T), "v"(G), "v"(base));
+    if (err || e >= fail || (o.fin && (fail < b.E || S > b.scap))) return;
     int64_t c0, n64;
     bulk_range(b, r, e, &c0, &n64);
     const int n = (int)n64;
-    const int T = b.T[e], G = b.G[(int64_t)r * b.E + e];
-    const int64_t base = b.base[e];
     const int64_t in = (int64_t)r * b.q + c0;
     const int64_t row0 = (b.lo ? b.lo[r] : (int64_t)r * b.q) + c0;   // rows of the rank's rounds before
     const int64_t dst = o.fin ? (int64_t)r * S + base : (int64_t)r * b.scap + base;
     // slots to write: all, those kept by a quota cut, or the steps below the staging's capacity
-    const int64_t room = !o.fin ? b.scap - base : b.lo && e + 1 == b.E ? b.st->cut : T;
+    const int64_t room = !o.fin ? b.scap - base : b.lo && e + 1 == b.E ? cut : T;
     const int m = (int)(room < T ? (room > 0 ? room : 0) : T);
     if (n == 0) {
         for (int j = tid; j < m; j += NT) {
