@@ -98,6 +98,59 @@ __global__ void __launch_bounds__(kBlock) loss_weights_kernel(int W, int64_t S, 
     }
 }
 
+// Few ranks and many steps: one thread per step.  The steps alone fill the chip, a load over 64 steps is
+// as wide, and no wave waits for another or loads for ranks that are not there.  us per call, the waves
+// over the ranks / one thread per step, sample and approximate mode: 1 x 1,048,576 steps 67 / 21 and
+// 86 / 21, 4 x 100,000 21 / 17 and 24 / 17, 8 x 30,000 17.8 / 17.3 and 18.6 / 18.2, 12 x 100,000
+// 24 / 22 and 27 / 26, 16 x 100,000 24.4 / 25.0 and 28 / 30, 16 x 400,000 46 / 40 and 70 / 49,
+// 24 x 200,000 36 / 37 and 53 / 46, 32 x 200,000 40 / 45 and 63 / 56, 64 x 100,000 43 / 55 and 54 / 68;
+// below 30,000 steps equal for up to 8 ranks.  So the line lies at 32,768 steps for up to 10 ranks and
+// 16,384 more for each rank after them, up to 24; the approximate mode, whose waves wait for each other,
+// takes up to 32 ranks from 196,608 steps on.
+constexpr int kFewItems = 4;
+
+inline bool few_ranks(int W, int64_t S, int mode) {
+    if (mode == ODB_WEIGHT_TOKEN_APPROX && W <= 32 && S >= 196608) return true;
+    return W <= 24 && S >= 16384 * (int64_t)(W > 10 ? W - 8 : 2);
+}
+
+__global__ void __launch_bounds__(kBlock) loss_weights_few_kernel(int W, int64_t S, int mode,
+                                                                  const int32_t* __restrict__ rows,
+                                                                  const int64_t* __restrict__ tokens,
+                                                                  const double* __restrict__ approx,
+                                                                  double* __restrict__ weight,
+                                                                  int64_t* __restrict__ step_tokens,
+                                                                  int64_t* __restrict__ step_samples) {
+#pragma clang fp contract(off)
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < S; j += stride) {
+        int64_t t = 0, n = 0;
+        double a = 0.0;
+#pragma unroll kFewItems
+        for (int r = 0; r < W; ++r) {
+            const int64_t k = (int64_t)r * S + j;
+            t += tokens[k];
+            n += rows[k];
+            if (mode == ODB_WEIGHT_TOKEN_APPROX) a = a + approx[k];
+        }
+#pragma unroll kFewItems
+        for (int r = 0; r < W; ++r) {
+            const int64_t k = (int64_t)r * S + j;
+            double v = 0.0;
+            if (mode == ODB_WEIGHT_SAMPLE) {
+                if (n > 0) v = (double)rows[k] / (double)n;
+            } else if (mode == ODB_WEIGHT_TOKEN_APPROX) {
+                if (a > 0.0) v = approx[k] / a;
+            } else {
+                if (t > 0) v = (double)tokens[k] / (double)t;
+            }
+            weight[k] = v;
+        }
+        if (step_tokens) step_tokens[j] = t;
+        if (step_samples) step_samples[j] = n;
+    }
+}
+
 }  // namespace
 
 }  // namespace odb
@@ -118,8 +171,10 @@ extern "C" int odb_loss_weights(int32_t num_ranks, int64_t steps, int32_t mode, 
     if (mode == ODB_WEIGHT_TOKEN_APPROX && !d_slot_tokens_approx)
         return set_error(ODB_E_INVALID_ARG, "the approximate mode needs d_slot_tokens_approx");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(loss_weights_kernel, dim3(grid_for(steps, kWave, (int64_t)num_cus() * 8)), dim3(kBlock), 0,
-                       s, (int)num_ranks, steps, (int)mode, d_slot_rows, d_slot_tokens, d_slot_tokens_approx, d_weight,
+    const bool few = few_ranks(num_ranks, steps, mode);
+    hipLaunchKernelGGL(few ? loss_weights_few_kernel : loss_weights_kernel,
+                       dim3(grid_for(steps, few ? kBlock : kWave, (int64_t)num_cus() * 8)), dim3(kBlock), 0, s,
+                       (int)num_ranks, steps, (int)mode, d_slot_rows, d_slot_tokens, d_slot_tokens_approx, d_weight,
                        d_step_tokens, d_step_samples);
     ODB_LAUNCHED();
     return ODB_OK;

@@ -881,3 +881,33 @@ def test_sort_tile_lengths(per_rank):
     ref = oracle.plan_window(w)
     pipe, _ = run_gpu(w, tokens=torch.zeros(1, dtype=torch.int32, device="cuda"), collate=False)
     compare_plan(w, pipe, ref)
+
+
+@pytest.mark.parametrize("W,S", [(1, 32767), (1, 32768), (2, 40001), (3, 100003), (8, 32768), (10, 32767), (10, 32768),
+                                 (11, 49151), (11, 49152), (12, 65536), (24, 196608), (24, 262144), (25, 300001), (32, 196607), (32, 196608), (33, 200000)])
+def test_loss_weights_few_ranks(W, S):
+    # both sides of the line between one thread per step and the waves over the ranks; the reference adds
+    # the ranks in order, one fp64 operation each, as the library states
+    import torch
+    import paper_2606_19989_amd as odb
+
+    rng = np.random.default_rng(W)
+    rows = rng.integers(0, 50, (W, S)).astype(np.int32)
+    rows[:, ::97] = 0   # steps without a sample: zero weights
+    tokens = rows.astype(np.int64) * rng.integers(1, 3000, (W, S))
+    approx = rows * rng.uniform(1.0, 3000.0, (W, S))
+    d = [torch.from_numpy(x).cuda() for x in (rows, tokens, approx)]
+    a_sum = np.zeros(S)
+    for r in range(W):
+        a_sum = a_sum + approx[r]
+    t_sum, n_sum = tokens.sum(0), rows.sum(0, dtype=np.int64)
+    for mode, x, total in ((oracle.WEIGHT_SAMPLE, rows, n_sum), (oracle.WEIGHT_TOKEN_APPROX, approx, a_sum),
+                           (oracle.WEIGHT_TOKEN_EXACT, tokens, t_sum)):
+        log(f"loss weights {W} x {S}, mode {mode}")
+        wt = torch.empty(W * S, dtype=torch.float64, device="cuda")
+        st, ss = (torch.empty(S, dtype=torch.int64, device="cuda") for _ in range(2))
+        odb.odb_loss_weights(W, S, mode, *d, wt, st, ss)
+        den = total.astype(np.float64)
+        want = np.where(total > 0, x.astype(np.float64) / np.where(total > 0, den, 1.0), 0.0)
+        assert np.array_equal(wt.cpu().numpy().reshape(W, S).view(np.int64), want.view(np.int64)), mode
+        assert np.array_equal(st.cpu().numpy(), t_sum) and np.array_equal(ss.cpu().numpy(), n_sum)
