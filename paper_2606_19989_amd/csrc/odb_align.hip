@@ -1444,17 +1444,24 @@ __device__ __forceinline__ int64_t one_group(const int32_t* __restrict__ gs, int
 // Samples per step over the ranks, for the sample quota: a block takes 64 steps, its waves
 // every fourth rank.  Bound by the trips to memory of a rank's search for its split (16 x 65,536
 // samples: 12.7 us lane by lane, 7.8 by the whole wave; for the slots below, whose waves may
-// hold several ranks, it gains nothing).
+// hold several ranks, it gains nothing).  Beyond kCutSlice ranks, blockIdx.y takes a slice of them
+// and adds to the steps, cleared before: the one block of the few steps of 8,192 ranks x 100 samples went
+// through all of them, 2.2 ms (the quota plan 3.2 ms, now 0.88; 1,024 x 1,000 samples 500 and 214 us, 96 x
+// 4,000 121 and 110, 65 x 16,384 168 and 169).
+constexpr int kCutSlice = 64;
+
 __global__ void __launch_bounds__(kBlock) cut_steps_kernel(OneArgs a) {
     if (stage1_bad(a.st)) return;
     const OneTarget tg = one_target(a);
     if (tg.overflow) return;
     __shared__ int64_t s_n[kBlock / kWave][kWave];
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    const int r0 = blockIdx.y * kCutSlice;
+    const int r1 = gridDim.y > 1 && r0 + kCutSlice < a.W ? r0 + kCutSlice : a.W;
     for (int64_t j0 = (int64_t)blockIdx.x * kWave; j0 < tg.T; j0 += (int64_t)gridDim.x * kWave) {
         const int64_t j = j0 + lane;
         int64_t n = 0;
-        for (int r = w; r < a.W; r += kBlock / kWave) {
+        for (int r = r0 + w; r < r1; r += kBlock / kWave) {
             const int64_t cnt = a.off[r + 1] - a.off[r];
             if (cnt == 0) continue;
             const int32_t* gs = a.gs + a.off[r];
@@ -1468,10 +1475,27 @@ __global__ void __launch_bounds__(kBlock) cut_steps_kernel(OneArgs a) {
         if (w == 0 && j < tg.T) {
 #pragma unroll
             for (int i = 1; i < kBlock / kWave; ++i) n += s_n[i][lane];
-            a.steps[j] = n;
+            if (gridDim.y > 1)
+                atomicAdd((unsigned long long*)&a.steps[j], (unsigned long long)n);
+            else
+                a.steps[j] = n;
         }
         __syncthreads();
     }
+}
+
+int cut_steps(const OneArgs& a, int64_t max_nr, hipStream_t s) {
+    const int64_t slices = (a.W + kCutSlice - 1) / kCutSlice;
+    if (slices > 1) {   // no more steps than samples of a rank
+        hipLaunchKernelGGL(fill_i32_kernel, dim3(grid_for(2 * max_nr, kBlock, kMaxRanges)), dim3(kBlock), 0, s,
+                           reinterpret_cast<int32_t*>(a.steps), 2 * max_nr, 0);
+        ODB_LAUNCHED();
+    }
+    // at most 65,535 slices a launch; more ranks than those hold go in one
+    hipLaunchKernelGGL(cut_steps_kernel, dim3(grid_for(max_nr, kWave, kMaxRanges), slices <= 65535 ? (unsigned)slices : 1u),
+                       dim3(kBlock), 0, s, a);
+    ODB_LAUNCHED();
+    return ODB_OK;
 }
 
 // The first step at which the emitted samples reach the quota, every rank's emitted rows
@@ -2227,8 +2251,7 @@ extern "C" int odb_align_groups(const odb_window_t* w, int64_t budget, const odb
             ODB_LAUNCHED();
         }
         if (nonjoin) {
-            hipLaunchKernelGGL(cut_steps_kernel, dim3(grid_for(max_nr, kWave, kMaxRanges)), dim3(kBlock), 0, s, a);
-            ODB_LAUNCHED();
+            ODB_TRY(cut_steps(a, max_nr, s));
             hipLaunchKernelGGL(cut_kernel, dim3(1), dim3(kBlock), 0, s, a, d_leftover_off);
             ODB_LAUNCHED();
         }
@@ -2253,10 +2276,7 @@ extern "C" int odb_align_groups(const odb_window_t* w, int64_t budget, const odb
                                  "stage-1 arrays do not describe this window (first inconsistent position %lld)",
                                  (long long)h.st.first_bad);
             if ((int64_t)W * h.rs.cut > slot_capacity) {
-                if (!nonjoin) {   // else the cut has counted them
-                    hipLaunchKernelGGL(cut_steps_kernel, dim3(grid_for(max_nr, kWave, kMaxRanges)), dim3(kBlock), 0, s, a);
-                    ODB_LAUNCHED();
-                }
+                if (!nonjoin) ODB_TRY(cut_steps(a, max_nr, s));   // else the cut has counted them
                 ODB_TRY(step_max_without_slots(steps, d_rs, &h.rs, s));
             }
             h.rs.rounds = 1;

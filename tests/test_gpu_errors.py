@@ -196,6 +196,9 @@ def capacity_windows():
         win("short_rounds", [U(900), U(1025), U(700)], 12000, capacity=np.array([40, 0, 33])),
         win("rounds", [U(17000), U(1025), U(700)], 12000, capacity=np.array([400, 0, 330])),
         win("rounds_quota", [U(900), U(1025), U(7)], 12000, mode="nonjoin", quota=100),
+        # the steps summed over slices of 64 ranks
+        win("slices", [U(90) for _ in range(65)], 12000),
+        win("slices_quota", [U(60 + r % 7) for r in range(700)], 12000, mode="nonjoin", quota=20000),
     ]
 
 

@@ -911,3 +911,18 @@ def test_loss_weights_few_ranks(W, S):
         want = np.where(total > 0, x.astype(np.float64) / np.where(total > 0, den, 1.0), 0.0)
         assert np.array_equal(wt.cpu().numpy().reshape(W, S).view(np.int64), want.view(np.int64)), mode
         assert np.array_equal(st.cpu().numpy(), t_sum) and np.array_equal(ss.cpu().numpy(), n_sum)
+
+
+@pytest.mark.parametrize("W", [63, 64, 65, 128, 129, 700])
+def test_quota_cut_of_many_ranks(W):
+    # one slice of 64 ranks, several, and a last one of a single rank; of unequal size, so that most are split
+    rng = np.random.default_rng(W)
+    ranks = [rng.integers(1, 3000, 200 + r % 60) for r in range(W)]
+    n = sum(map(len, ranks))
+    for q in (1, W, n // 2, n - 1, n + 1):
+        w = win(ranks, 20000, mode="nonjoin", quota=q)
+        log(f"quota {q} of {n} over {W} ranks")
+        ref = oracle.plan_window(w)
+        pipe, _ = run_gpu(w, collate=False)
+        compare_plan(w, pipe, ref)
+        compare_loss_weights(pipe, ref)
