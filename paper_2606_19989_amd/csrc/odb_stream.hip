@@ -1344,27 +1344,25 @@ __device__ __forceinline__ void bulk_round_splits(const BulkArgs& b, BulkSplit* 
     }
 }
 
-// Samples of step j of that round over the ranks.
-__device__ __forceinline__ int64_t bulk_step_rows(const BulkArgs& b, const BulkSplit* s_sp, int64_t e, int T, int j) {
-    int64_t v = 0;
-#pragma unroll 4
-    for (int r = 0; r < b.W; ++r) {
-        int64_t c, n;
-        bulk_range(b, r, e, &c, &n);
-        if (n == 0) continue;
-        int a0, a1;
-        bulk_group(b.gs + (int64_t)r * b.q + c, b.G[(int64_t)r * b.E + e], (int)n, s_sp[r], T - 1 - j, &a0, &a1);
-        v += a1 - a0;
-    }
-    return v;
-}
-
 // Views that rank r of a round with target T keeps back if the round's first `cut` steps are emitted:
 // the start of adjusted group T - cut.
 __device__ __forceinline__ int bulk_kept_back(const int32_t* gs, BulkSplit sp, int T, int cut) {
     const int t = T - cut;
     if (t <= sp.X) return t;
     return gs[sp.X >= 0 ? sp.js + (t - sp.X) : t];
+}
+
+// Rows of the first c steps of round e (target T) over the ranks part, part + parts, ...
+__device__ __forceinline__ int64_t bulk_rows(const BulkArgs& b, const BulkSplit* s_sp, int64_t e, int T, int c,
+                                             int part, int parts) {
+    int64_t rows = 0;
+#pragma unroll 4
+    for (int r = part; r < b.W; r += parts) {
+        int64_t at, n;
+        bulk_range(b, r, e, &at, &n);
+        if (n > 0) rows += n - bulk_kept_back(b.gs + (int64_t)r * b.q + at, s_sp[r], T, c);
+    }
+    return rows;
 }
 
 // Ranks a thread looks at in one pass of the search for the cut.
@@ -1399,14 +1397,7 @@ __device__ void bulk_cut(const BulkArgs& b, BulkSplit* s_sp, int T, int64_t base
         const int w = (hi - lo + tries) / (tries + 1);   // steps between two tries
         const int c = lo + (tid % tries + 1) * w;
         int64_t rows = 0;
-        if (c < hi) {
-#pragma unroll 4
-            for (int r = tid / tries; r < b.W; r += parts) {
-                int64_t at, n;
-                bulk_range(b, r, e, &at, &n);
-                if (n > 0) rows += n - bulk_kept_back(b.gs + (int64_t)r * b.q + at, s_sp[r], T, c);
-            }
-        }
+        if (c < hi) rows = bulk_rows(b, s_sp, e, T, c, tid / tries, parts);
         s_rows[tid] = rows;
         __syncthreads();
         bool low = false;
@@ -1665,20 +1656,40 @@ __global__ void __launch_bounds__(kWave) bulk_staged_steps_kernel(BulkArgs b, co
 }
 
 // The largest step of the first `rounds` rounds from their groups, where the slots do not fit and are not
-// there to sum.  A block per round, a BulkSplit per rank in dynamic LDS.
+// there to sum.  A block per round, a BulkSplit per rank in dynamic LDS.  The rows of the first c steps
+// over all ranks for every c, as the cut takes them, with the ranks spread over the threads that the
+// steps leave; a step is what one c has more than the one before.
 __global__ void __launch_bounds__(kTargetThreads) bulk_step_max_kernel(BulkArgs b, int64_t rounds) {
     extern __shared__ unsigned long long s_dyn[];
     BulkSplit* s_sp = reinterpret_cast<BulkSplit*>(s_dyn);
+    __shared__ int64_t s_rows[kTargetThreads];
     if (b.st->err) return;
+    const int tid = threadIdx.x;
     int64_t mx = 0;
     for (int64_t e = blockIdx.x; e < rounds; e += gridDim.x) {
         const int T = b.T[e], kept = b.lo && e + 1 == b.E ? (int)b.st->cut : T;
+        int wide = 1;   // steps at a time
+        while (wide < kTargetThreads && wide < kept) wide <<= 1;
         __syncthreads();
         bulk_round_splits<kTargetThreads>(b, s_sp, e, T);
         __syncthreads();
-        for (int j = threadIdx.x; j < kept; j += kTargetThreads) {
-            const int64_t n = bulk_step_rows(b, s_sp, e, T, j);
-            mx = n > mx ? n : mx;
+        int64_t carry = 0;
+        for (int j0 = 0; j0 < kept; j0 += wide) {   // uniform
+            const int c = j0 + (tid & (wide - 1)) + 1;
+            int64_t rows = 0;
+            if (c <= kept) rows = bulk_rows(b, s_sp, e, T, c, tid / wide, kTargetThreads / wide);
+            s_rows[tid] = rows;
+            __syncthreads();
+            for (int h = kTargetThreads / 2; h >= wide; h >>= 1) {
+                if (tid < h) s_rows[tid] += s_rows[tid + h];
+                __syncthreads();
+            }
+            if (tid < wide && c <= kept) {
+                const int64_t n = s_rows[tid] - (tid > 0 ? s_rows[tid - 1] : carry);
+                mx = n > mx ? n : mx;
+            }
+            carry = s_rows[wide - 1];
+            __syncthreads();
         }
     }
     mx = sblock_max<kTargetThreads>(mx);

@@ -520,6 +520,9 @@ def capacity_cases():
         ("resume", L, 3, 3000, 100, 300, [100, 129, 250], {}),
         ("resume_cut", L, 3, 3000, 100, 300, [100, 129, 250], dict(mode="nonjoin", quota=3000)),
         ("rounds", L, 3, 3000, 100, 300, [100, 129, 250], dict(cap=np.array([9, 0, 8]))),
+        # more steps in a round than the block has threads; more ranks, and a cut
+        ("long_rounds", rng.integers(1, 9000, 3 * 4000), 3, 4000, 2000, 2000, [2000] * 3, {}),
+        ("many_ranks_cut", rng.integers(1, 900, 600 * 40), 600, 3000, 16, 16, [16] * 600, dict(mode="nonjoin", quota=15000)),
     ]
 
 
