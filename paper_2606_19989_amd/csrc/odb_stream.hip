@@ -1272,7 +1272,7 @@ __global__ void __launch_bounds__(NT) bulk_form_kernel(BulkArgs b) {
     for (int g = tid; g < G; g += NT) b.gs[out + g] = s_gs[g];
 }
 
-// 512 threads: the cut takes 73 registers, and a block has to fit beside the three collate waves of
+// 512 threads: the cut takes 78 registers, and a block has to fit beside the three collate waves of
 // 84 (88 allocated) on every SIMD (1,024 threads waited for the whole collate of the step before).
 constexpr int kTargetThreads = 512;
 
