@@ -42,10 +42,6 @@ namespace odb {
 
 namespace {
 
-__device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-
 // Lanes of this wave whose `valid` digit equals this lane's (ballot per digit bit).
 __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid, int dbits) {
     uint64_t peers = __ballot(valid);
@@ -366,7 +362,7 @@ __global__ void __launch_bounds__(kBlock) radix_scatter_kernel(
         const bool valid = p0 + it * kWave < b.count;
         const uint32_t d = (key[it] >> shift) & mask;
         const uint64_t peers = match_digit(d, valid, dbits);
-        const uint32_t below = lanes_below(peers);
+        const uint32_t below = (uint32_t)lanes_below(peers);
         // every lane reads the count before the digit's first lane adds to it: LDS operations of
         // one wave complete in order (the fences keep the compiler to it)
         at[it] = s_cnt[w][d] + below;
@@ -595,8 +591,7 @@ __global__ void groups_kernel(const int32_t* __restrict__ incl, const int64_t* _
 // ---- the chain of one rank
 // Batch size B(l) (Eq. 1), clipped to 2^31 - 1 (any larger step leaves the rank).
 __device__ __forceinline__ uint32_t step_of(int32_t l, int64_t budget) {
-    const int64_t b = batch_size(budget, l);
-    return (uint32_t)(b < INT32_MAX ? b : INT32_MAX);
+    return (uint32_t)batch_size(budget, l);
 }
 
 // Calls f(q, step) for every run start q in [lo, hi) (1 <= lo < hi <= cnt), in order: q = 1,
@@ -1015,7 +1010,7 @@ __global__ void __launch_bounds__(kChainThreads) rank_form_kernel(Values vals, c
                 const bool valid = p0 + c * kWave < cnt;
                 const uint32_t d = mask - ((len[c] >> sh) & mask);
                 const uint64_t m = match_digit(d, valid, dbits);
-                const uint32_t below = lanes_below(m);
+                const uint32_t below = (uint32_t)lanes_below(m);
                 // every lane reads the count before the digit's first lane adds to it (LDS
                 // operations of one wave complete in order; the fences keep the compiler to it)
                 at[c] = s_cnt[form_bin(d, w)] + below;
